@@ -61,8 +61,6 @@ struct tcw_ctx {
     std::string err;
     int* flag = nullptr;          // device scratch flag
     int32_t* rot_min = nullptr;   // device scratch of exact_rotate1 (the least reduction count)
-    void* claw_scratch = nullptr;
-    size_t claw_scratch_bytes = 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     void* noalloc = nullptr;        // this device's copy of the tcw_step_noalloc scratch array
     hipError_t noalloc_err = hipSuccess;
@@ -475,7 +473,6 @@ int tcw_destroy(tcw_ctx* c) {
     if (c->rot_min) (void)hipFree(c->rot_min);
     for (auto& e : c->pool) (void)hipFree(e.second);
     c->pool.clear();
-    if (c->claw_scratch) (void)hipFree(c->claw_scratch);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     delete c;
@@ -845,16 +842,7 @@ int tcw_claw_check(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, const u
     Space s;
     int rc = prepare_space(c, t, sp, s);
     if (rc) return rc;
-    const size_t need = tcw::exact_claw_scratch_bytes(t->n);
-    if (c->claw_scratch_bytes < need) {
-        if (c->claw_scratch) (void)hipFree(c->claw_scratch);
-        c->claw_scratch = nullptr;
-        c->claw_scratch_bytes = 0;
-        HIP_TRY(c, hipMalloc(&c->claw_scratch, need));
-        c->claw_scratch_bytes = need;
-    }
-    HIP_TRY(c, tcw::exact_claw_check(s.S, sp->k, u0, u1, count, c->claw_scratch, c->claw_scratch_bytes, ok, perm,
-                                     sign, c->stream));
+    HIP_TRY(c, tcw::exact_claw_check(s.S, sp->k, u0, u1, count, ok, perm, sign, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return TCW_OK;
 }
@@ -1117,22 +1105,9 @@ struct ClawWs {
     }
 };
 
-// The context's scratch for exact claw checks of n-qubit spaces, grown when too small.
-int ensure_claw_scratch(tcw_ctx* c, int n) {
-    const size_t need = tcw::exact_claw_scratch_bytes(n);
-    if (c->claw_scratch_bytes < need) {
-        if (c->claw_scratch) (void)hipFree(c->claw_scratch);
-        c->claw_scratch = nullptr;
-        c->claw_scratch_bytes = 0;
-        HIP_TRY(c, hipMalloc(&c->claw_scratch, need));
-        c->claw_scratch_bytes = need;
-    }
-    return TCW_OK;
-}
-
 // Exact check of candidate pairs (u0[i], u1[i]) on the context's stream, in the given order; the first
-// verified one fills res.  With ws and the claw scratch already large enough, it allocates nothing (so
-// it can run beside other device work).
+// verified one fills res.  With ws already large enough, it allocates nothing (so it can run beside
+// other device work).
 int check_pairs_ws(tcw_ctx* c, const Space& sp, const uint64_t* u0, const uint64_t* u1, int64_t m, tcw_result* res,
                    int* found, ClawWs& ws) {
     *found = 0;
@@ -1142,9 +1117,7 @@ int check_pairs_ws(tcw_ctx* c, const Space& sp, const uint64_t* u0, const uint64
     HIP_TRY(c, ws.reserve(m, R));
     HIP_TRY(c, hipMemcpyAsync(ws.d0, u0, m * 8, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipMemcpyAsync(ws.d1, u1, m * 8, hipMemcpyHostToDevice, c->stream));
-    if (int rc = ensure_claw_scratch(c, n)) return rc;
-    HIP_TRY(c, tcw::exact_claw_check(sp.S, sp.k, ws.d0, ws.d1, m, c->claw_scratch, c->claw_scratch_bytes, ws.ok,
-                                     ws.perm, ws.sign, c->stream));
+    HIP_TRY(c, tcw::exact_claw_check(sp.S, sp.k, ws.d0, ws.d1, m, ws.ok, ws.perm, ws.sign, c->stream));
     std::vector<int32_t> ok(m), perm(m * R);
     std::vector<int8_t> sign(m * R);
     HIP_TRY(c, hipMemcpyAsync(ok.data(), ws.ok, m * 4, hipMemcpyDeviceToHost, c->stream));
@@ -2275,7 +2248,6 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
     }
     ClawWs cws;
     HIP_TRY(c, cws.reserve(BATCH_CLAW_CAP, 1 << (2 * nmax)));
-    if (int e = ensure_claw_scratch(c, nmax)) return e;
     int rc = TCW_OK;
     for (int i = 0; i < count && !rc; ++i) {
         rc = batch_advance(c, bt[i], i, bb, t0, false);

@@ -5,8 +5,8 @@
 // rule: column q is e_q when <p, q> = 0, else (e_q + s(p, q) e_{p^q}) / sqrt2, so
 //   (M R)[:, q] = (M[:, q] + s M[:, p^q]) / sqrt2        (anticommuting q)
 //   (M R)[:, q] = (sqrt2 M[:, q]) / sqrt2, (a, b) -> (2b, a)   (commuting q)
-// and R^T flips s.  Every kernel here is single-block per matrix: these are set-up and
-// verification paths (target preparation, chunk matrices S_c, claw checks), not the walk loop.
+// and R^T flips s.  These are set-up and verification paths (target preparation, chunk matrices S_c,
+// claw checks), not the walk loop.
 #include "common.h"
 #include "internal.h"
 
@@ -342,102 +342,162 @@ __global__ void k_pack_phi(const T* a, const T* b, uint32_t* phi, int* flag) {
     phi[Q4 * R + idx] = wb;
 }
 
+// ---- rows of a matrix under right-multiplied rotations ----
+// Right multiplication acts on each row by itself (the column rule above), so a row lives in the
+// registers of a group of G = min(R, 64) lanes: lane gl holds columns gl * CPL + j.
+template <int NQ>
+struct RowGeo {
+    static constexpr int R = EGeo<NQ>::R;
+    static constexpr int G = R < 64 ? R : 64;  // lanes per row
+    static constexpr int CPL = R / G;          // columns per lane (1 or 4)
+    static constexpr int RPW = 64 / G;         // rows per wavefront
+};
+
+__device__ inline int32_t shfl_t(int32_t v, int src) { return (int32_t)shfl32((uint32_t)v, src); }
+__device__ inline int64_t shfl_t(int64_t v, int src) { return (int64_t)shfl64((uint64_t)v, src); }
+
+template <int C, int CPL, typename T>
+__device__ inline void fetch_cols(const T* v, int src, T* part) {
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) part[j] = shfl_t(v[j ^ C], src);
+}
+
+// One rotation R(p) (R(p)^T if transposed) applied to NB rows held by the lane's group, unreduced: the
+// exponent grows by one.  p is the same in every lane of the wavefront (1..4^n - 1).
+template <int NQ, int NB, typename T>
+__device__ inline void rotate_rows(T (*a)[RowGeo<NQ>::CPL], T (*b)[RowGeo<NQ>::CPL], uint32_t p, bool transposed, int gl,
+                                   int gbase) {
+    constexpr int CPL = RowGeo<NQ>::CPL;
+    bool anti[CPL], plus[CPL];
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+        const uint32_t q = (uint32_t)(gl * CPL + j);
+        anti[j] = anticommutes<NQ>(p, q) != 0;
+        plus[j] = (rotation_sign<NQ>(p, q) > 0) != transposed;
+    }
+    const int src = gbase + (gl ^ (int)(CPL == 4 ? p >> 2 : p));
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        T pa[CPL], pb[CPL];
+        if constexpr (CPL == 4) {
+            switch (p & 3) {  // uniform: the partner's register
+                case 0: fetch_cols<0, CPL>(a[i], src, pa); fetch_cols<0, CPL>(b[i], src, pb); break;
+                case 1: fetch_cols<1, CPL>(a[i], src, pa); fetch_cols<1, CPL>(b[i], src, pb); break;
+                case 2: fetch_cols<2, CPL>(a[i], src, pa); fetch_cols<2, CPL>(b[i], src, pb); break;
+                default: fetch_cols<3, CPL>(a[i], src, pa); fetch_cols<3, CPL>(b[i], src, pb); break;
+            }
+        } else {
+            fetch_cols<0, CPL>(a[i], src, pa);
+            fetch_cols<0, CPL>(b[i], src, pb);
+        }
+#pragma unroll
+        for (int j = 0; j < CPL; ++j) {
+            const T sa = plus[j] ? pa[j] : -pa[j], sb = plus[j] ? pb[j] : -pb[j];
+            const T na = anti[j] ? a[i][j] + sa : 2 * b[i][j];
+            b[i][j] = anti[j] ? b[i][j] + sb : a[i][j];
+            a[i][j] = na;
+        }
+    }
+}
+
 // Claw check of (u0, u1): V = R(p_0)...R(p_{h-1}) from the side-0 point, W = S R(q_0)^T ... from
 // the side-1 point, D = W V^T must be a signed permutation (Sec. 3, last merge case).
+//   D = S R(q_0)^T ... R(q_{h-1})^T R(p_{h-1})^T ... R(p_0)^T
+// is S under 2h rotations from the right, so no dense product is formed: one block per pair, its 16
+// wavefronts each take rows of S through the rotations in registers, unreduced, at exponent
+// E = e_S + 2h.  S has int8 entries and orthonormal rows, so e_S <= log2(3 R 127^2) and every value,
+// bounded by 2^(E/2), stays below 2^16 at n >= 3 and 2^29 at n <= 2.  A row must hold one unit entry
+// and the columns must differ; the first row that does not ends the pair.  Bound by the butterflies
+// (2 h R^2 of them).  256 pairs at n = 4, k = 7, half of them claws: 0.14 ms the whole call; the
+// dense product W V^T it replaces (R^3 64-bit products a pair, 16 blocks) took 244 ms.
+constexpr int CLAW_WAVES = 16;
 template <int NQ, typename T>
-__global__ __launch_bounds__(1024) void k_claw(const T* sa, const T* sb, const int32_t* se, int k, const uint64_t* u0,
-                                               const uint64_t* u1, int64_t count, T* scratch, int32_t* ok,
-                                               int32_t* perm, int8_t* sign) {
-    constexpr int R = EGeo<NQ>::R;
+__global__ __launch_bounds__(CLAW_WAVES * 64) void k_claw(const T* __restrict__ sa, const T* __restrict__ sb,
+                                                          const int32_t* se, int k, const uint64_t* u0,
+                                                          const uint64_t* u1, int64_t count, int32_t* ok, int32_t* perm,
+                                                          int8_t* sign) {
+    using Gm = RowGeo<NQ>;
+    constexpr int R = Gm::R, CPL = Gm::CPL;
     constexpr uint32_t XI = R - 1;
+    constexpr int NB = NQ >= 3 ? 4 : 1;  // row sets a wavefront holds at a time
     __shared__ uint16_t seq[64];
-    __shared__ uint8_t trs[64];
     __shared__ int cnt[R];
     __shared__ int rowof[R];
     __shared__ int sgn[R];
     __shared__ int bad;
-    __shared__ int oflow;
-    T* va = scratch + (size_t)blockIdx.x * 6 * R * R;
-    T* vb = va + R * R;
-    T* wa = vb + R * R;
-    T* wb = wa + R * R;
-    T* ta = wb + R * R;
-    T* tb = ta + R * R;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int gi = lane / Gm::G, gl = lane % Gm::G, gbase = gi * Gm::G;
     const int h = k / 2;
+    const int E = *se + 2 * h;
+    const T unit = (T)1 << (E / 2);
     for (int64_t pi = blockIdx.x; pi < count; pi += gridDim.x) {
         uint64_t p0 = u0[pi], p1 = u1[pi];
         if ((p0 >> 32) & 1) {
             const uint64_t x = p0; p0 = p1; p1 = x;
         }
         const bool sides_ok = (((p0 >> 32) & 1) == 0) && (((p1 >> 32) & 1) == 1);
-        // V from the identity
-        for (int idx = threadIdx.x; idx < R * R; idx += blockDim.x) {
-            va[idx] = ((idx / R) == (idx % R)) ? 1 : 0;
-            vb[idx] = 0;
-            wa[idx] = sa[idx];
-            wb[idx] = sb[idx];
-        }
-        if (threadIdx.x == 0) {
-            uint32_t x = (uint32_t)p0;
-            for (int t = 0; t < h; ++t) {
-                seq[t] = (uint16_t)(x % XI + 1);
-                trs[t] = 0;
-                x /= XI;
-            }
-            bad = sides_ok ? 0 : 1;
-            oflow = 0;
-        }
-        __syncthreads();
-        int ev = 0;
-        block_apply<NQ, T>(va, vb, ta, tb, ev, seq, trs, h, &oflow);
         if (threadIdx.x == 0) {
             uint32_t x = (uint32_t)p1;
             for (int t = 0; t < h; ++t) {
                 seq[t] = (uint16_t)(x % XI + 1);
-                trs[t] = 1;
                 x /= XI;
             }
-        }
-        __syncthreads();
-        int ew = *se;
-        block_apply<NQ, T>(wa, wb, ta, tb, ew, seq, trs, h, &oflow);
-        for (int q = threadIdx.x; q < R; q += blockDim.x) {
-            cnt[q] = 0;
-            rowof[q] = -1;
-            sgn[q] = 0;
-        }
-        __syncthreads();
-        // D_iq = sum_k W_ik V_qk with exponent E = ew + ev; a unit entry is +-sqrt2^E
-        const int E = ew + ev;
-        const int64_t unit = (int64_t)1 << (E / 2);
-        for (int idx = threadIdx.x; idx < R * R; idx += blockDim.x) {
-            const int i = idx / R, q = idx % R;
-            int64_t da = 0, db = 0;
-            for (int kk = 0; kk < R; ++kk) {
-                const int64_t xa = wa[i * R + kk], xb = wb[i * R + kk];
-                const int64_t ya = va[q * R + kk], yb = vb[q * R + kk];
-                da += xa * ya + 2 * xb * yb;
-                db += xa * yb + xb * ya;
+            x = (uint32_t)p0;
+            for (int t = 0; t < h; ++t) {
+                seq[2 * h - 1 - t] = (uint16_t)(x % XI + 1);
+                x /= XI;
             }
-            if (da != 0 || db != 0) {
-                atomicAdd(&cnt[q], 1);
-                int s = 0;
-                if (E % 2 == 0) {
-                    if (db == 0 && (da == unit || da == -unit)) s = da > 0 ? 1 : -1;
-                } else {
-                    if (da == 0 && (db == unit || db == -unit)) s = db > 0 ? 1 : -1;
+            bad = sides_ok ? 0 : 1;
+        }
+        for (int q = threadIdx.x; q < R; q += blockDim.x) cnt[q] = 0;
+        __syncthreads();
+        for (int r0 = wave * NB * Gm::RPW; r0 < R; r0 += CLAW_WAVES * NB * Gm::RPW) {
+            // one answer for the whole wavefront: the rotations below exchange lanes
+            if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)))
+                break;
+            T a[NB][CPL], b[NB][CPL];
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < CPL; ++j) {
+                    // at n = 1 the wavefront has more lane groups than the matrix has rows
+                    const int row = r0 + i * Gm::RPW + gi, at = row * R + gl * CPL + j;
+                    a[i][j] = row < R ? sa[at] : 0;
+                    b[i][j] = row < R ? sb[at] : 0;
                 }
-                if (s == 0) atomicOr(&bad, 1);
-                rowof[q] = i;
-                sgn[q] = s;
+            for (int t = 0; t < 2 * h; ++t)
+                rotate_rows<NQ, NB, T>(a, b, (uint32_t)__builtin_amdgcn_readfirstlane(seq[t]), true, gl, gbase);
+            bool row_ok = true;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                int nz = 0, col = 0, s = 0;
+#pragma unroll
+                for (int j = 0; j < CPL; ++j) {
+                    const bool here = a[i][j] != 0 || b[i][j] != 0;
+                    const uint64_t m = __ballot(here);
+                    const uint64_t mine = Gm::G == 64 ? m : (m >> gbase) & ((1ull << (Gm::G & 63)) - 1);
+                    nz += (int)__popcll(mine);
+                    if (here) {
+                        col = gl * CPL + j;
+                        const T x = E % 2 == 0 ? a[i][j] : b[i][j], y = E % 2 == 0 ? b[i][j] : a[i][j];
+                        s = y == 0 && (x == unit || x == -unit) ? (x > 0 ? 1 : -1) : 2;
+                    }
+                }
+                if (r0 + i * Gm::RPW + gi >= R) continue;
+                if (nz != 1 || s == 2) row_ok = false;
+                if (nz == 1 && s != 0 && s != 2) {  // the lane that holds the row's entry
+                    atomicAdd(&cnt[col], 1);
+                    rowof[col] = r0 + i * Gm::RPW + gi;
+                    sgn[col] = s;
+                }
             }
+            if (!row_ok) __hip_atomic_store(&bad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
         __syncthreads();
-        for (int q = threadIdx.x; q < R; q += blockDim.x) {
-            if (cnt[q] != 1) atomicOr(&bad, 1);
-        }
+        for (int q = threadIdx.x; q < R; q += blockDim.x)
+            if (cnt[q] != 1) __hip_atomic_store(&bad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __syncthreads();
-        const int good = (bad == 0 && oflow == 0) ? 1 : 0;
+        const int good = bad == 0 ? 1 : 0;
         for (int q = threadIdx.x; q < R; q += blockDim.x) {
             perm[pi * R + q] = good ? rowof[q] : -1;
             sign[pi * R + q] = (int8_t)(good ? sgn[q] : 0);
@@ -844,21 +904,13 @@ hipError_t exact_pack_phi(const ExactDev& m, uint32_t* phi, int* flag, hipStream
     return dispatch_exact(m.n, f);
 }
 
-size_t exact_claw_scratch_bytes(int n) {
-    const size_t r = (size_t)1 << (2 * n);
-    const size_t elem = n <= 2 ? 8 : 4;
-    return 16 * 6 * r * r * elem;  // 16 blocks, 6 matrices of R x R each
-}
-
-hipError_t exact_claw_check(const ExactDev& S, int k, const uint64_t* u0, const uint64_t* u1, int64_t count,
-                            void* scratch, size_t scratch_bytes, int32_t* ok, int32_t* perm, int8_t* sign,
-                            hipStream_t s) {
+hipError_t exact_claw_check(const ExactDev& S, int k, const uint64_t* u0, const uint64_t* u1, int64_t count, int32_t* ok,
+                            int32_t* perm, int8_t* sign, hipStream_t s) {
     if (count <= 0) return hipSuccess;
-    if (scratch_bytes < exact_claw_scratch_bytes(S.n)) return hipErrorInvalidValue;
     auto f = [&]<int NQ, typename T>() -> hipError_t {
-        const int blocks = (int)(count < 16 ? count : 16);
-        hipLaunchKernelGGL((k_claw<NQ, T>), dim3(blocks), dim3(1024), 0, s, (const T*)S.a, (const T*)S.b, S.e, k,
-                           u0, u1, count, (T*)scratch, ok, perm, sign);
+        const int blocks = (int)(count < 4096 ? count : 4096);
+        hipLaunchKernelGGL((k_claw<NQ, T>), dim3(blocks), dim3(CLAW_WAVES * 64), 0, s, (const T*)S.a, (const T*)S.b,
+                           S.e, k, u0, u1, count, ok, perm, sign);
         return hipGetLastError();
     };
     return dispatch_exact(S.n, f);

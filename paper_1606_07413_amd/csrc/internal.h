@@ -113,11 +113,9 @@ hipError_t exact_check_orthogonal(const ExactDev& m, int* flag_dev, hipStream_t 
 hipError_t exact_signed_perm(const ExactDev& m, int32_t* ok_dev, int32_t* perm_dev, int8_t* sign_dev, hipStream_t s);
 // int8 packing of S for the walk kernels; flag |= 2 if a value is outside [-127, 127]
 hipError_t exact_pack_phi(const ExactDev& m, uint32_t* phi_dev, int* flag_dev, hipStream_t s);
-// claw checks: for each pair (u0, u1) compute V, W exactly and D = W V^T
-hipError_t exact_claw_check(const ExactDev& S, int k, const uint64_t* u0, const uint64_t* u1, int64_t count,
-                            void* scratch, size_t scratch_bytes, int32_t* ok, int32_t* perm, int8_t* sign,
-                            hipStream_t s);
-size_t exact_claw_scratch_bytes(int n);
+// claw checks: for each pair (u0, u1) D = W V^T exactly (S's entries within int8, as exact_pack_phi checks)
+hipError_t exact_claw_check(const ExactDev& S, int k, const uint64_t* u0, const uint64_t* u1, int64_t count, int32_t* ok,
+                            int32_t* perm, int8_t* sign, hipStream_t s);
 // canonical FP32 features (n <= 3)
 hipError_t exact_features(const ExactDev& m, float* out_dev, hipStream_t s);
 // many targets from words: phi (n <= 3 int8 layout), rot_e, features; flag |= 2 / 4 / 8 on range errors
