@@ -3023,20 +3023,22 @@ extern "C" int tcw_mlp_depth_order(tcw_mlp* m, const tcw_target* t, int k_max, c
 namespace {
 
 // Hash table of every left-Clifford coset reached by <= h rotations from the identity, keyed by
-// matrix hash, value 255 - (least number of rotations); shared by the labelling and certificate calls.
+// matrix hash, value 255 - (least number of rotations), and the keys of the products with <= h_probe
+// rotations on the target's side; shared by the labelling and certificate calls.
 struct LevelTable {
     uint64_t* table = nullptr;
     uint64_t* keys = nullptr;
     uint32_t* zero_phi = nullptr;
+    void* frags = nullptr;  // the target side's keys (mitm_frags)
     int lg = 0;
     tcw::SpaceDev sp{};
     ~LevelTable() {
-        for (void* q : {(void*)table, (void*)keys, (void*)zero_phi})
+        for (void* q : {(void*)table, (void*)keys, (void*)zero_phi, frags})
             if (q) (void)hipFree(q);
     }
 };
 
-int build_level_table(tcw_ctx* c, int n, int h_levels, uint64_t seed, LevelTable& lt) {
+int build_level_table(tcw_ctx* c, int n, int h_levels, int h_probe, uint64_t seed, LevelTable& lt) {
     const int R = 1 << (2 * n);
     HIP_TRY(c, hipMalloc(&lt.zero_phi, (size_t)R * R / 2 * 4));
     HIP_TRY(c, hipMemsetAsync(lt.zero_phi, 0, (size_t)R * R / 2 * 4, c->stream));
@@ -3056,6 +3058,10 @@ int build_level_table(tcw_ctx* c, int n, int h_levels, uint64_t seed, LevelTable
         lt.sp.h = h;
         lt.sp.n_half = (uint32_t)n_half_of(n, h);
         HIP_TRY(c, tcw::mitm_levels(n, lt.sp, h, lt.table, lt.lg, c->stream));
+    }
+    if (const size_t bytes = tcw::mitm_frag_bytes(n, h_probe)) {
+        HIP_TRY(c, hipMalloc(&lt.frags, bytes));
+        HIP_TRY(c, tcw::mitm_frags(n, lt.sp, h_probe, lt.frags, c->stream));
     }
     return TCW_OK;
 }
@@ -3141,7 +3147,7 @@ extern "C" int tcw_label_batch(tcw_ctx* c, int n, int count, const uint16_t* wor
     LB_TRY(hipMalloc(&scratch, tcw::build_batch_scratch_bytes(n, blocks)));
     const int h_id = mitm_split(n, h_max, count);
     LevelTable lt;
-    if ((rc = build_level_table(c, n, h_id, seed, lt)) || (rc = clear_flag(c))) {
+    if ((rc = build_level_table(c, n, h_id, 2 * h_max - h_id, seed, lt)) || (rc = clear_flag(c))) {
         cleanup();
         return rc;
     }
@@ -3149,8 +3155,8 @@ extern "C" int tcw_label_batch(tcw_ctx* c, int n, int count, const uint16_t* wor
         const int cnt = std::min(chunk, count - first);
         LB_TRY(tcw::build_batch(n, dwords, doff + first, dk + first, cnt, scratch, blocks, phi, rot,
                                 features_dev + (size_t)first * R * R, c->flag, c->stream));
-        LB_TRY(tcw::mitm_probe(n, lt.sp, phi, rot, cnt, 2 * h_max - h_id, lt.table, lt.lg, labels_dev + first,
-                               c->stream));
+        LB_TRY(tcw::mitm_probe(n, lt.sp, phi, rot, cnt, 2 * h_max - h_id, lt.frags, lt.table, lt.lg,
+                               labels_dev + first, c->stream));
     }
     int flag = 0;
     rc = read_flag(c, &flag);
@@ -3200,11 +3206,12 @@ extern "C" int tcw_min_tcount(tcw_ctx* c, const tcw_target* t, int h_max, uint64
         return hip_fail(c, err, "rot_e upload");
     }
     const int h_id = mitm_split(n, h_max, 1);
-    if ((rc = build_level_table(c, n, h_id, seed, lt))) {
+    if ((rc = build_level_table(c, n, h_id, 2 * h_max - h_id, seed, lt))) {
         cleanup();
         return rc;
     }
-    err = tcw::mitm_probe(n, lt.sp, phi, dev_i32, 1, 2 * h_max - h_id, lt.table, lt.lg, dev_i32 + 1, c->stream);
+    err = tcw::mitm_probe(n, lt.sp, phi, dev_i32, 1, 2 * h_max - h_id, lt.frags, lt.table, lt.lg, dev_i32 + 1,
+                          c->stream);
     if (err == hipSuccess) err = hipMemcpyAsync(t_out, dev_i32 + 1, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
     if (err == hipSuccess) err = hipStreamSynchronize(c->stream);
     cleanup();

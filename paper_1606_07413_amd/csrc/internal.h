@@ -125,8 +125,12 @@ hipError_t build_batch(int n, const uint16_t* words, const int32_t* offsets, con
                        hipStream_t s);
 // meet-in-the-middle level table and probes (walk.hip)
 hipError_t mitm_levels(int n, const SpaceDev& sp, int h, uint64_t* table, int log2_table, hipStream_t s);
+// the target side's workspace (mitm_frag_bytes(n, h_max) bytes, none at n <= 2), filled once for any number
+// of mitm_probe calls with the same sp and h_max (unless it holds only a part at a time)
+size_t mitm_frag_bytes(int n, int h_max);
+hipError_t mitm_frags(int n, const SpaceDev& sp, int h_max, void* frags, hipStream_t s);
 hipError_t mitm_probe(int n, const SpaceDev& sp, const uint32_t* phi_all, const int32_t* rot_e_all, int count,
-                      int h_max, const uint64_t* table, int log2_table, int32_t* best_out, hipStream_t s);
+                      int h_max, void* frags, const uint64_t* table, int log2_table, int32_t* best_out, hipStream_t s);
 
 // ---- launchers (walk.hip) ----
 hipError_t keys_fill(int n, uint64_t seed, uint64_t* keys_dev, hipStream_t s);

@@ -23,6 +23,8 @@
 //   (NH of Black, Halevi, Krawczyk, Krovetz and Rogaway, UMAC, CRYPTO 1999, on the digest's two
 //   32-bit words: one 32 x 32 -> 64-bit product per row)
 //   f(x, b) = (floor(H * xi^h / 2^64), H mod 2)                    (reduction back to a point)
+#include <algorithm>
+
 #include "common.h"
 #include "internal.h"
 
@@ -1574,6 +1576,15 @@ __device__ inline int level_lookup(const uint64_t* table, int log2_table, uint64
     return -1;
 }
 
+// Which products of rotations a level needs.  R(p_0) R(p_1) ... with two commuting neighbours equals the
+// product with them swapped, so only p_t < p_{t+1} is kept; with two equal neighbours R(p)^2 is a
+// Clifford, so the same left coset appears two levels lower on the identity's side, and on the
+// target's side (where that Clifford moves to the far right and through the identity's half) its
+// match does.  Sorting commuting neighbours ends, so each class keeps a member: at n = 3 about 47 of
+// the 63 choices for each next rotation.
+__device__ inline bool keep_pair(uint32_t p0, uint32_t p1, bool anti) { return anti || p0 < p1; }
+
+// n <= 2: one walk group per product, as in the walk kernels.
 template <int NQ, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_mitm_levels(SpaceDev sp, int h, uint64_t* table, int log2_table) {
     using Gm = Geo<NQ>;
@@ -1601,8 +1612,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_mitm_levels(SpaceDev sp, int h, 
     }
 }
 
-// Per target (block): least i + j over side-1 products of j <= h_max rotations from U whose hash is
-// in the level table at level i; stops once j reaches the best total.  best_out = -1 if none.
+// Per target: least i + j over side-1 products of j <= h_max rotations from U whose hash is in the level
+// table at level i; stops once j reaches the best total.  blockIdx.y shares a target's products between
+// the blocks of one column; best_out starts at -1 (none), which as unsigned is above every total.
 template <int NQ, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_mitm_probe(SpaceDev sp0, const uint32_t* phi_all,
                                                            const int32_t* rot_e_all, int count, int h_max,
@@ -1610,7 +1622,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_mitm_probe(SpaceDev sp0, const u
     using Gm = Geo<NQ>;
     constexpr int NPHI = Gm::Q4 * Gm::R;
     __shared__ Lds<NQ, WAVES> L;
-    __shared__ int best;
+    __shared__ uint32_t best;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int gi = lane / Gm::G, gl = lane % Gm::G, gbase = gi * Gm::G;
     uint32_t* limbs = L.limbs[wave * Gm::WPW + gi];
@@ -1620,27 +1632,267 @@ __global__ __launch_bounds__(WAVES * 64) void k_mitm_probe(SpaceDev sp0, const u
         sp.rot_e = rot_e_all[t];
         __syncthreads();
         load_lds(L, sp);
-        if (threadIdx.x == 0) best = 1 << 20;
+        if (threadIdx.x == 0) best = ~0u;
         __syncthreads();
         uint32_t nh = 1;
         for (int j = 0; j <= h_max; ++j) {
-            if (j >= best) break;
+            if ((uint32_t)j >= best) break;
             sp.h = j;
             sp.n_half = nh;
-            for (int64_t base = (int64_t)wave * Gm::WPW; base < (int64_t)nh; base += WAVES * Gm::WPW) {
+            for (int64_t base = ((int64_t)blockIdx.y * WAVES + wave) * Gm::WPW; base < (int64_t)nh;
+                 base += (int64_t)gridDim.y * WAVES * Gm::WPW) {
                 const int64_t x = base + gi;
                 if (x >= (int64_t)nh) continue;
                 uint64_t o, H;
                 walk_step<NQ, WAVES>(sp, L, limbs, (uint64_t)x | (1ull << 32), gl, gbase, o, H);
                 if (gl == 0) {
                     const int lvl = level_lookup(table, log2_table, H == EMPTY_KEY ? (H ^ 1) : H);
-                    if (lvl >= 0) atomicMin(&best, j + lvl);
+                    if (lvl >= 0) atomicMin(&best, (uint32_t)(j + lvl));
                 }
             }
             nh *= Gm::XI;
             __syncthreads();
         }
-        if (threadIdx.x == 0) best_out[t] = best < (1 << 20) ? best : -1;
+        if (threadIdx.x == 0 && best != ~0u) atomicMin(reinterpret_cast<uint32_t*>(&best_out[t]), best);
+    }
+}
+
+// ---- n = 3: both halves by families of products that share all but their last-applied rotation ----
+// A wavefront takes one prefix (p_1, ..., p_{j-1}) and every p_0 that the pruning keeps (at most 62 of 63).
+
+// Row r = lane of the n = 3 butterflies: bit p of anti = P_p and P_r anticommute, bit p of plus = the
+// butterfly of R (side 0) adds the partner.
+__device__ inline void rot3_masks(int lane, uint64_t& anti, uint64_t& plus) {
+    anti = plus = 0;
+    for (uint32_t p = 1; p < 64; ++p) {
+        const uint32_t b = ROT3_TAB.v[p * 64 + lane];
+        anti |= (uint64_t)(b & 1) << p;
+        plus |= (uint64_t)((b >> 1) & 1) << p;
+    }
+}
+
+// one rotation of rotate1 at n = 3, p uniform
+__device__ inline uint64_t rot3(uint64_t u, uint32_t p, uint64_t anti, uint64_t plus, int lane) {
+    const uint64_t part = shfl64(u, lane ^ (int)p);
+    const uint64_t q = ((plus >> p) & 1) ? part : (2 * P61 - part);
+    const uint64_t sum = u + q;
+    const uint64_t rot = (sum >> 31) + ((sum & 0x7fffffffull) << 30);
+    return ((anti >> p) & 1) ? rot : u;
+}
+
+// p_1 .. p_{j-1} of prefix y (p[1] first), and the p_0 that may stand before them (bit p; bit 0 alone for
+// the product of no rotation).  0: the prefix is pruned.
+__device__ inline uint64_t prefix3(uint32_t y, int j, uint32_t* p) {
+    constexpr int HMAX = Geo<3>::HMAX;
+    if (j == 0) return 1;
+#pragma unroll
+    for (int t = 1; t < HMAX; ++t) {
+        p[t] = y % Geo<3>::XI + 1;
+        y /= Geo<3>::XI;
+    }
+    bool keep = true;
+#pragma unroll
+    for (int t = 1; t + 1 < HMAX; ++t)
+        if (t + 1 < j) keep = keep && keep_pair(p[t], p[t + 1], anticommutes<3>(p[t], p[t + 1]) != 0);
+    if (!keep) return 0;
+    uint64_t m = ~1ull;
+    if (j >= 2) {
+        const uint32_t lane = threadIdx.x & 63;
+        m = __ballot(lane != 0 && keep_pair(lane, p[1], anticommutes<3>(lane, p[1]) != 0));
+    }
+    return m;
+}
+
+// The keys through the prefix's rotations (side 0: R, side 1: R^T), p_{j-1} first.
+__device__ inline uint64_t prefix_keys3(uint64_t u, const uint32_t* p, int j, uint64_t anti, uint64_t plus, int lane) {
+#pragma unroll
+    for (int t = Geo<3>::HMAX - 1; t >= 1; --t)
+        if (t < j) u = rot3(u, p[t], anti, plus, lane);
+    return u;
+}
+
+// the element map of the multiset hash on a digest c in [0, p]
+__device__ inline uint64_t digest_map(uint64_t c, uint32_t ka, uint32_t kb) {
+    const uint64_t d = c ^ (P61 & (0ull - ((c >> 60) & 1)));
+    return (uint64_t)((uint32_t)d + ka) * (uint64_t)((uint32_t)(d >> 32) + kb);
+}
+
+// v summed over the lane's 16-lane row
+__device__ inline uint64_t row_sum16(uint64_t v) {
+    v += dpp64<0xB1>(v);
+    v += dpp64<0x4E>(v);
+    v += dpp64<0x124>(v);
+    v += dpp64<0x128>(v);
+    return v;
+}
+
+// Level h of the table: four products at a time, whose wave sums share their last stages (two
+// cross-half exchanges leave one product per 16-lane row), each kept by one lane; then every lane
+// finishes and stores its own product, so that the table's atomics, each a round trip to memory, run 64
+// at a time.  Bound by the butterfly, the element map and the sums (about 45 VALU instructions a
+// product) with the pruned products left out: the 16 million products of levels 0..4 take 0.84 ms,
+// against 4.85 ms with a wavefront per product and one lane at the table.
+constexpr int MITM_WAVES = 4;
+__global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_levels3(SpaceDev sp, int h, uint32_t prefixes, uint64_t* table,
+                                                                  int log2_table) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t ka = (uint32_t)sp.salt_h, kb = (uint32_t)(sp.salt_h >> 32);
+    uint64_t anti, plus;
+    rot3_masks(lane, anti, plus);
+    const uint64_t key0 = sp.keys[lane];
+    WalkDev wd{};
+    wd.table = table;
+    wd.log2_table = log2_table;
+    for (uint32_t y = uniform32(blockIdx.x * MITM_WAVES + (threadIdx.x >> 6)); y < prefixes;
+         y += gridDim.x * MITM_WAVES) {
+        uint32_t p[Geo<3>::HMAX] = {};
+        uint64_t todo = prefix3(y, h, p);
+        const int products = (int)__popcll(todo);
+        if (products == 0) continue;
+        const uint64_t u = prefix_keys3(key0, p, h, anti, plus, lane);
+        uint64_t mine = 0;
+        for (int quad = 0; todo != 0; ++quad) {
+            uint64_t acc[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t p0 = todo ? (uint32_t)__builtin_ctzll(todo) : 0u;
+                todo &= todo - 1;
+                const uint64_t v = p0 ? rot3(u, p0, anti, plus, lane) : u;
+                acc[i] = digest_map(m61_fold(v), ka, kb);
+            }
+            // rows 0..3 of 16 lanes: products 0, 1, 2, 3
+            const uint64_t sum = row_sum16(half_add16(half_add32(acc[0], acc[2]), half_add32(acc[1], acc[3])));
+            if ((lane & 15) == quad) mine = sum;
+        }
+        if (4 * (lane & 15) + (lane >> 4) < products) {
+            const uint64_t H = mix64(mine);
+            uint64_t slot = 0;
+            if (table_claim(wd, H == EMPTY_KEY ? (H ^ 1) : H, slot) != 3)
+                atomicMax(&table[2 * slot + 1], (uint64_t)(255 - h));
+        }
+    }
+}
+
+// The target-side keys u = R(p_0)^T ... R(p_{j-1})^T K as MFMA A-operand fragments, the same for every
+// target: prefix y's products in the order of their p_0, two per 16-row operand (rows 0..7 the signed
+// base-256 digits of the first, rows 8..15 of the second), K = [u | 2^31 u] in two steps: 2 KiB a pair,
+// 32 pairs a prefix (MITM_PREFIX_V4 vectors).  Lane l of a fragment holds row l % 16, columns
+// 16 (l / 16) .. + 15.
+constexpr int MITM_PREFIX_V4 = 32 * 2 * 64;
+__global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_keys3(SpaceDev sp, int j, uint32_t y0, uint32_t prefixes,
+                                                                v4i* frags) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint64_t anti, plus;
+    rot3_masks(lane, anti, plus);
+    plus = ~plus;  // R^T: the butterfly adds where R subtracts
+    for (uint32_t i = blockIdx.x; i < prefixes; i += gridDim.x) {
+        uint32_t p[Geo<3>::HMAX] = {};
+        uint64_t todo = prefix3(uniform32(y0 + i), j, p);
+        if (todo == 0) continue;
+        const uint64_t u = prefix_keys3(sp.keys[lane], p, j, anti, plus, lane);
+        uint8_t* out = reinterpret_cast<uint8_t*>(frags + (size_t)i * MITM_PREFIX_V4);
+        const int slots = ((int)__popcll(todo) + 3) / 4 * 4;  // whole quads; what no product fills repeats the prefix
+        for (int s = 0; s < slots; ++s) {
+            const uint32_t p0 = todo ? (uint32_t)__builtin_ctzll(todo) : 0u;
+            todo &= todo - 1;
+            if ((s & (MITM_WAVES - 1)) != wave) continue;
+            const uint64_t v = p0 ? rot3(u, p0, anti, plus, lane) : u;
+            uint8_t* at = out + (size_t)(s >> 1) * 2048 + ((lane >> 4) * 16 + (s & 1) * 8) * 16 + (lane & 15);
+#pragma unroll
+            for (int set = 0; set < 2; ++set) {
+                const uint64_t w = set ? (v >> 30) + ((v & 0x3fffffffull) << 31) : v;
+                const uint64_t b = w + 0x8080808080808080ull;
+#pragma unroll
+                for (int m = 0; m < N4_DIG; ++m) at[set * 1024 + m * 16] = (uint8_t)((b >> (8 * m)) ^ 0x80);
+            }
+        }
+    }
+}
+
+// Two products' hash sums from one pass of 8 MFMAs: accumulator row 4g + i of lane l (g = l / 16) is
+// digit 4 (g & 1) + i of product g >> 1 in matrix row 16 nt + l % 16.  A swap of 16-lane rows between
+// the tiles nt and nt + 2 leaves every lane all eight digits of one row: of tile nt in even g, of tile
+// nt + 2 in odd g.  With |acc| <= 128 * 128 * 127 < 2^21 the halves lo + 2^8, hi + 2^8 stay below 2^30,
+// and x = A + 2^32 B (|A|, |B| < 2^47) is p + A + (B >> 29) + (B mod 2^29) 2^32 (mod p), in (0, 2^62);
+// its product by 2^s is ((x << s) mod 2^61) + (x >> (61 - s)) < 2^62, folded once into [0, p].
+__device__ inline uint64_t pair_sum3(const v4i a0, const v4i a1, const v4i* bf, uint32_t s, uint32_t ka, uint32_t kb) {
+    v4i acc[N3_NT];
+#pragma unroll
+    for (int nt = 0; nt < N3_NT; ++nt) {
+        acc[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bf[2 * nt], v4i{0, 0, 0, 0}, 0, 0, 0);
+        acc[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bf[2 * nt + 1], acc[nt], 0, 0, 0);
+    }
+    uint64_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)(acc[i][0] + acc[i][1] * 256),
+                                                         (uint32_t)(acc[2 + i][0] + acc[2 + i][1] * 256), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(acc[i][2] + acc[i][3] * 256),
+                                                         (uint32_t)(acc[2 + i][2] + acc[2 + i][3] * 256), false, false);
+        const int64_t A = (int64_t)(int32_t)lo[0] + (int64_t)(int32_t)hi[0] * 65536;
+        const int64_t B = (int64_t)((int32_t)lo[1] + (1 << 28)) + (int64_t)(int32_t)hi[1] * 65536;
+        const uint64_t x =
+            P61 - (1ull << 60) + (uint64_t)(A + (B >> 29)) + ((uint64_t)((uint32_t)B & 0x1fffffffu) << 32);
+        const uint64_t t = ((x << s) & P61) + (x >> (61 - s));
+        sum += digest_map((t & P61) + (t >> 61), ka, kb);
+    }
+    return sum;
+}
+
+// Probes of `count` targets against the level table, products of j rotations of prefixes y0 ..
+// y0 + prefixes - 1 (frags from k_mitm_keys3).  A wavefront keeps its target's packed U as eight B
+// fragments in registers and shares the target's prefixes with the `slices` wavefronts of the same
+// target; two pairs of products fill the four 16-lane rows, as in k_mitm_levels3, and 64 lanes look up
+// at a time.  A target that an earlier level has answered is skipped, and one hit ends its level: every
+// coset of T-count <= h_id is tabled, so the first level with a hit is T - h_id (or 0) and its total T.
+// About 41 VALU instructions and four MFMAs a product; label batches read the fragments (3 MiB for
+// j <= 2) from L2.  16384 circuits against the table of T-count <= 4: 4.3 ms, one target's 142 thousand
+// products of <= 3 rotations 0.05 ms (its fragments 0.11 ms), against 34 ms and 63 ms with one block per
+// target that ran the walk step on each product.
+__global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_probe3(SpaceDev sp, const v4i* __restrict__ phi_all,
+                                                                 const int32_t* __restrict__ rot_e_all, int count,
+                                                                 int j, uint32_t y0, uint32_t prefixes, int slices,
+                                                                 const v4i* __restrict__ frags, const uint64_t* table,
+                                                                 int log2_table, int32_t* best_out) {
+    const int lane = threadIdx.x & 63;
+    const int64_t unit = uniform32(blockIdx.x * MITM_WAVES + (threadIdx.x >> 6));
+    const int t = (int)(unit / slices), slice = (int)(unit % slices);
+    if (t >= count) return;
+    uint32_t* best = reinterpret_cast<uint32_t*>(&best_out[t]);
+    if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != ~0u) return;
+    const uint32_t ka = (uint32_t)sp.salt_h, kb = (uint32_t)(sp.salt_h >> 32);
+    v4i bf[N3_NT * N3_KK];
+#pragma unroll
+    for (int i = 0; i < N3_NT * N3_KK; ++i) bf[i] = phi_all[((size_t)t * N3_NT * N3_KK + i) * 64 + lane];
+    const uint32_t s = uniform32((uint32_t)rot_e_all[t]);
+    for (uint32_t y = (uint32_t)slice; y < prefixes; y += (uint32_t)slices) {
+        uint32_t p[Geo<3>::HMAX] = {};
+        const int products = (int)__popcll(prefix3(y0 + y, j, p));
+        if (products == 0) continue;
+        const v4i* f = frags + (size_t)y * MITM_PREFIX_V4 + lane;
+        const int quads = (products + 3) / 4;
+        uint64_t mine = 0;
+        v4i nx[4] = {f[0], f[64], f[128], f[192]};
+        for (int quad = 0; quad < quads; ++quad) {
+            const v4i a[4] = {nx[0], nx[1], nx[2], nx[3]};
+            if (quad + 1 < quads) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) nx[i] = f[(quad + 1) * 256 + 64 * i];
+            }
+            const uint64_t s01 = pair_sum3(a[0], a[1], bf, s, ka, kb), s23 = pair_sum3(a[2], a[3], bf, s, ka, kb);
+            // 32-lane halves hold the two products of a pair; after the exchange row g of 16 lanes holds
+            // product 0, 2, 1, 3 of the quad
+            const uint64_t sum = row_sum16(half_add16(s01, s23));
+            if ((lane & 15) == quad) mine = sum;
+        }
+        const int g = lane >> 4, in_quad = ((g & 1) << 1) | (g >> 1);
+        int lvl = -1;
+        if (4 * (lane & 15) + in_quad < products) {
+            const uint64_t H = mix64(mine);
+            lvl = level_lookup(table, log2_table, H == EMPTY_KEY ? (H ^ 1) : H);
+        }
+        if (lvl >= 0) atomicMin(best, (uint32_t)(j + lvl));
+        if (__ballot(lvl >= 0) != 0) return;
     }
 }
 
@@ -1831,7 +2083,14 @@ namespace tcw {
 hipError_t mitm_levels(int n, const SpaceDev& sp, int h, uint64_t* table, int log2_table, hipStream_t s) {
     auto f = [&]<int NQ>() -> hipError_t {
         constexpr int W = WalkWaves<NQ>::value;
-        if constexpr (NQ <= 3) {
+        if constexpr (NQ == 3) {
+            const uint32_t prefixes = h == 0 ? 1 : sp.n_half / Geo<3>::XI;
+            uint32_t blocks = (prefixes + MITM_WAVES - 1) / MITM_WAVES;
+            if (blocks > 4096) blocks = 4096;
+            hipLaunchKernelGGL(k_mitm_levels3, dim3(blocks), dim3(MITM_WAVES * 64), 0, s, sp, h, prefixes, table,
+                               log2_table);
+            return hipGetLastError();
+        } else if constexpr (NQ <= 2) {
             int64_t blocks = ((int64_t)sp.n_half + W * Geo<NQ>::WPW - 1) / (W * Geo<NQ>::WPW);
             if (blocks > 4096) blocks = 4096;
             if (blocks < 1) blocks = 1;
@@ -1845,14 +2104,93 @@ hipError_t mitm_levels(int n, const SpaceDev& sp, int h, uint64_t* table, int lo
     return dispatch_n(n, f);
 }
 
+// At n = 3 the fragments of at most MITM_CHUNK prefixes (64 KiB each) are held at a time.
+constexpr uint32_t MITM_CHUNK = 1024;
+static uint32_t mitm_prefixes(int j) {
+    uint32_t v = 1;
+    for (int i = 1; i < j; ++i) v *= Geo<3>::XI;
+    return v;
+}
+
+size_t mitm_frag_bytes(int n, int h_max) {
+    if (n != 3) return 0;
+    size_t all = 0;
+    for (int j = 0; j <= h_max; ++j) all += mitm_prefixes(j);
+    return std::min<size_t>(all, MITM_CHUNK) * MITM_PREFIX_V4 * sizeof(v4i);
+}
+
+// The wavefronts of k_mitm_probe3 that share a target: enough for 8 wavefronts per SIMD of the chip, one
+// prefix each at least.
+static int mitm_slices(int count, uint32_t prefixes) {
+    const int64_t want = (8192 + count - 1) / count;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(want, prefixes));
+}
+
+static hipError_t mitm_keys(const SpaceDev& sp, int j, uint32_t y0, uint32_t prefixes, void* frags, hipStream_t s) {
+    hipLaunchKernelGGL(k_mitm_keys3, dim3(prefixes), dim3(MITM_WAVES * 64), 0, s, sp, j, y0, prefixes, (v4i*)frags);
+    return hipGetLastError();
+}
+
+static hipError_t mitm_probe3(const SpaceDev& sp, const uint32_t* phi_all, const int32_t* rot_e_all, int count, int j,
+                              uint32_t y0, uint32_t prefixes, const void* frags, const uint64_t* table, int log2_table,
+                              int32_t* best_out, hipStream_t s) {
+    const int slices = mitm_slices(count, prefixes);
+    const int64_t blocks = ((int64_t)count * slices + MITM_WAVES - 1) / MITM_WAVES;
+    hipLaunchKernelGGL(k_mitm_probe3, dim3((unsigned)blocks), dim3(MITM_WAVES * 64), 0, s, sp, (const v4i*)phi_all,
+                       rot_e_all, count, j, y0, prefixes, slices, (const v4i*)frags, table, log2_table, best_out);
+    return hipGetLastError();
+}
+
+hipError_t mitm_frags(int n, const SpaceDev& sp, int h_max, void* frags, hipStream_t s) {
+    if (n != 3) return hipSuccess;
+    uint32_t at = 0, all = 0;
+    for (int j = 0; j <= h_max; ++j) all += mitm_prefixes(j);
+    if (all > MITM_CHUNK) return hipSuccess;  // built chunk by chunk in mitm_probe
+    for (int j = 0; j <= h_max; ++j) {
+        const uint32_t m = mitm_prefixes(j);
+        hipError_t e = mitm_keys(sp, j, 0, m, (v4i*)frags + (size_t)at * MITM_PREFIX_V4, s);
+        if (e != hipSuccess) return e;
+        at += m;
+    }
+    return hipSuccess;
+}
+
 hipError_t mitm_probe(int n, const SpaceDev& sp, const uint32_t* phi_all, const int32_t* rot_e_all, int count,
-                      int h_max, const uint64_t* table, int log2_table, int32_t* best_out, hipStream_t s) {
+                      int h_max, void* frags, const uint64_t* table, int log2_table, int32_t* best_out, hipStream_t s) {
+    hipError_t e = fill_i32(best_out, -1, count, s);
+    if (e != hipSuccess) return e;
+    if (n == 3) {
+        uint32_t at = 0, all = 0;
+        for (int j = 0; j <= h_max; ++j) all += mitm_prefixes(j);
+        for (int j = 0; j <= h_max; ++j) {
+            const uint32_t m = mitm_prefixes(j);
+            if (all <= MITM_CHUNK) {
+                e = mitm_probe3(sp, phi_all, rot_e_all, count, j, 0, m, (v4i*)frags + (size_t)at * MITM_PREFIX_V4,
+                                table, log2_table, best_out, s);
+                if (e != hipSuccess) return e;
+                at += m;
+                continue;
+            }
+            for (uint32_t y = 0; y < m; y += MITM_CHUNK) {
+                const uint32_t c = std::min(MITM_CHUNK, m - y);
+                e = mitm_keys(sp, j, y, c, frags, s);
+                if (e == hipSuccess)
+                    e = mitm_probe3(sp, phi_all, rot_e_all, count, j, y, c, frags, table, log2_table, best_out, s);
+                if (e != hipSuccess) return e;
+            }
+        }
+        return hipSuccess;
+    }
     auto f = [&]<int NQ>() -> hipError_t {
         constexpr int W = WalkWaves<NQ>::value;
-        if constexpr (NQ <= 3) {
+        if constexpr (NQ <= 2) {
             const int blocks = count < 4096 ? count : 4096;
-            hipLaunchKernelGGL((k_mitm_probe<NQ, W>), dim3(blocks), dim3(W * 64), 0, s, sp, phi_all, rot_e_all, count,
-                               h_max, table, log2_table, best_out);
+            int64_t most = 1;  // products of the deepest level, a block's groups at a time
+            for (int i = 0; i < h_max; ++i) most *= Geo<NQ>::XI;
+            most = (most + W * Geo<NQ>::WPW - 1) / (W * Geo<NQ>::WPW);
+            const int64_t slices = std::max<int64_t>(1, std::min<int64_t>(most, 1024 / blocks));
+            hipLaunchKernelGGL((k_mitm_probe<NQ, W>), dim3(blocks, (unsigned)slices), dim3(W * 64), 0, s, sp, phi_all,
+                               rot_e_all, count, h_max, table, log2_table, best_out);
             return hipGetLastError();
         } else {
             return hipErrorInvalidValue;

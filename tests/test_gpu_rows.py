@@ -57,3 +57,36 @@ def test_claw_check_edges(ctx, n, kt, k, count):
         assert np.array_equal(sign[i], dec.sign if dec else np.zeros(r)), i
     if kt == k:
         assert ok[0] == 1 and ok[-1] == 1
+
+
+# labels and certificates whose halves take several levels: all on one side (h_max 0), one target and few
+# (the products shared between wavefronts), more than one batch of targets, n = 1 and 2
+@pytest.mark.parametrize("n,h_max,count", [(1, 3, 5), (1, 4, 300), (2, 2, 1), (2, 3, 40), (3, 0, 7), (3, 1, 1), (3, 1, 65),
+                                           (3, 2, 3), (3, 2, 1100), (3, 3, 2)])
+def test_labels_match_search(ctx, n, h_max, count):
+    import torch
+    print("labels", n, h_max, count, flush=True)
+    tws = [seeded_inputs.target_words(n, i % (2 * h_max + 3), 9000 + i) for i in range(count)]
+    feats = torch.empty((count, 16 ** n), dtype=torch.float32, device="cuda:0")
+    labels = torch.empty(count, dtype=torch.int32, device="cuda:0")
+    ctx.label_batch(n, [(t.paulis, t.clifford) for t in tws], h_max, 3, feats, labels)
+    labels = labels.cpu().tolist()
+    for i in list(range(min(count, 6))) + list(range(6, count, 97)):
+        tgt = ctx.target_from_words(n, tws[i].paulis, tws[i].clifford)
+        p = ctx.default_params(n)
+        p.k_max, p.enum_max, p.chunk_parallel = min(2 * h_max, 5), 1 << 22, 0
+        res = ctx.search(tgt, p)
+        want = res.t if res.status == 1 else -1
+        if want < 0 and 2 * h_max > 5:
+            assert labels[i] in (-1, 6, 7, 8), i      # above the depths searched here
+        else:
+            assert labels[i] == want, i
+        assert ctx.min_tcount(tgt, h_max, 17) == labels[i], i
+
+
+def test_certificate_above_six(ctx):
+    """h_max = 4: the target's products come in parts; the Toffoli's T-count is 7."""
+    v = seeded_inputs.permutation_unitary(seeded_inputs.NAMED_GATES["toffoli"])
+    tgt = ctx.target_from_unitary(3, v, 0)
+    assert ctx.min_tcount(tgt, 4) == 7
+    assert ctx.min_tcount(tgt, 3) == -1
