@@ -3122,10 +3122,9 @@ extern "C" int tcw_label_batch(tcw_ctx* c, int n, int count, const uint16_t* wor
     uint16_t* dwords = nullptr;
     int32_t *doff = nullptr, *dk = nullptr, *rot = nullptr;
     uint32_t* phi = nullptr;
-    void* scratch = nullptr;
-    const int chunk = 1024, blocks = 256;
+    const int chunk = 4096;
     auto cleanup = [&]() {
-        for (void* q : {(void*)dwords, (void*)doff, (void*)dk, (void*)rot, (void*)phi, scratch})
+        for (void* q : {(void*)dwords, (void*)doff, (void*)dk, (void*)rot, (void*)phi})
             if (q) (void)hipFree(q);
     };
 #define LB_TRY(expr)                         \
@@ -3144,7 +3143,6 @@ extern "C" int tcw_label_batch(tcw_ctx* c, int n, int count, const uint16_t* wor
     LB_TRY(hipMemcpyAsync(dk, kof, count * 4, hipMemcpyHostToDevice, c->stream));
     LB_TRY(hipMalloc(&rot, chunk * 4));
     LB_TRY(hipMalloc(&phi, (size_t)chunk * R * R / 2 * 4));
-    LB_TRY(hipMalloc(&scratch, tcw::build_batch_scratch_bytes(n, blocks)));
     const int h_id = mitm_split(n, h_max, count);
     LevelTable lt;
     if ((rc = build_level_table(c, n, h_id, 2 * h_max - h_id, seed, lt)) || (rc = clear_flag(c))) {
@@ -3153,7 +3151,7 @@ extern "C" int tcw_label_batch(tcw_ctx* c, int n, int count, const uint16_t* wor
     }
     for (int first = 0; first < count; first += chunk) {
         const int cnt = std::min(chunk, count - first);
-        LB_TRY(tcw::build_batch(n, dwords, doff + first, dk + first, cnt, scratch, blocks, phi, rot,
+        LB_TRY(tcw::build_batch(n, dwords, doff + first, dk + first, cnt, phi, rot,
                                 features_dev + (size_t)first * R * R, c->flag, c->stream));
         LB_TRY(tcw::mitm_probe(n, lt.sp, phi, rot, cnt, 2 * h_max - h_id, lt.frags, lt.table, lt.lg,
                                labels_dev + first, c->stream));

@@ -567,85 +567,266 @@ __device__ void block_features(const T* a, const T* b, int e, int32_t* rows /* R
     __syncthreads();
 }
 
+// ---- canonical features and packed targets from rows in registers (n <= 3) ----
+// A matrix is held by WPT wavefronts, NB row sets each (RowGeo: one row per lane group).
+template <int NQ>
+struct FeatGeo {
+    using Gm = RowGeo<NQ>;
+    static constexpr int R = Gm::R;
+    static constexpr int WPT = NQ == 3 ? 4 : 1;
+    static constexpr int THREADS = WPT * 64;
+    static constexpr int NB = NQ == 1 ? 1 : R / (Gm::RPW * WPT);
+    static constexpr int WORDS = 2 * R / 8;          // 8-byte words of a row's sort key
+    static constexpr int KEY = 2 * R / 8 + (NQ == 3 ? 1 : 0);  // row pitch in words (odd: lanes read a row each)
+};
+
+template <int NQ>
+struct FeatLds {
+    uint64_t key[FeatGeo<NQ>::R * FeatGeo<NQ>::KEY];
+    int32_t rank[FeatGeo<NQ>::R];
+};
+
+// The canonical features of block_features, for entries within int8.  A row's key is its integer
+// sequence (a_0, b_0, a_1, ...) as bytes v + 128, first entry in the highest byte, so rows compare as
+// unsigned 8-byte words; a row's place is the number of rows below it.  Lane i compares row i with
+// the rows j of its wavefront's share, a word at a time until every pair is decided.
 template <int NQ, typename T>
-__global__ __launch_bounds__(256) void k_features(const T* a, const T* b, const int32_t* e, float* out) {
-    constexpr int R = EGeo<NQ>::R;
-    __shared__ int32_t rows[R * 2 * R];
-    __shared__ int32_t idx[R];
-    block_features<NQ, T>(a, b, *e, rows, idx, out);
+__device__ void rows_features(T (*a)[1], T (*b)[1], int e, FeatLds<NQ>& L, float* out) {
+    using Fg = FeatGeo<NQ>;
+    using Gm = RowGeo<NQ>;
+    constexpr int R = Fg::R;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int gi = lane / Gm::G, gl = lane % Gm::G, gbase = gi * Gm::G;
+    for (int r = threadIdx.x; r < R; r += Fg::THREADS) L.rank[r] = 0;
+#pragma unroll
+    for (int i = 0; i < Fg::NB; ++i) {
+        const int row = (wave * Fg::NB + i) * Gm::RPW + gi;
+        const int32_t va = (int32_t)a[i][0], vb = (int32_t)b[i][0];
+        // the sign of va + vb sqrt2, decided exactly
+        const bool positive = (va >= 0 && vb >= 0) || (va > 0 && vb < 0 && va * va > 2 * vb * vb) ||
+                              (va < 0 && vb > 0 && 2 * vb * vb > va * va);
+        const uint64_t nz = __ballot(va != 0 || vb != 0), pos = __ballot(positive);
+        const uint64_t mine = Gm::G == 64 ? nz : (nz >> gbase) & ((1ull << (Gm::G & 63)) - 1);
+        const int first = mine ? gbase + (int)__builtin_ctzll(mine) : gbase;
+        if (!((pos >> first) & 1)) {
+            a[i][0] = -a[i][0];
+            b[i][0] = -b[i][0];
+        }
+        if (row < R) {
+            const uint32_t ka = (uint32_t)((int32_t)a[i][0] + 128), kb = (uint32_t)((int32_t)b[i][0] + 128);
+            uint8_t* at = reinterpret_cast<uint8_t*>(&L.key[row * Fg::KEY + gl / 4]) + 6 - 2 * (gl & 3);
+            *reinterpret_cast<uint16_t*>(at) = (uint16_t)((ka << 8) | (kb & 255));
+        }
+    }
+    __syncthreads();
+    if (lane < R) {
+        uint64_t own[Fg::WORDS];
+#pragma unroll
+        for (int w = 0; w < Fg::WORDS; ++w) own[w] = L.key[lane * Fg::KEY + w];
+        int below = 0;
+        for (int j = wave * (R / Fg::WPT); j < (wave + 1) * (R / Fg::WPT); ++j) {
+            bool open = lane != j, less = false;
+#pragma unroll
+            for (int w = 0; w < Fg::WORDS; ++w) {
+                const uint64_t kj = L.key[j * Fg::KEY + w];
+                less = (open && kj < own[w]) || less;
+                open = open && kj == own[w];
+                if (__ballot(open) == 0) break;
+            }
+            below += less;
+        }
+        atomicAdd(&L.rank[lane], below);
+    }
+    __syncthreads();
+    const double sqrt2 = 1.4142135623730951, sqrt1_2 = 0.7071067811865476;
+    const double scale = ldexp(1.0, -(e / 2));
+#pragma unroll
+    for (int i = 0; i < Fg::NB; ++i) {
+        const int row = (wave * Fg::NB + i) * Gm::RPW + gi;
+        if (row >= R) continue;
+        double v = __dadd_rn((double)(int32_t)a[i][0], __dmul_rn((double)(int32_t)b[i][0], sqrt2));
+        if (e & 1) v = __dmul_rn(v, sqrt1_2);
+        out[L.rank[row] * R + gl] = (float)__dmul_rn(v, scale);
+    }
+    __syncthreads();
 }
 
-// Network data: targets built exactly from their words (Clifford word then rotations), packed as
-// int8 for the walk step (n <= 3 layout) and turned into canonical features.  One block per target.
+// One target's features.  Entries beyond int8 take block_features' general sort (32-bit entries, one
+// row per thread): 72 us at n = 3 where the byte keys take 14 us.
 template <int NQ, typename T>
-__global__ __launch_bounds__(1024) void k_build_batch(const uint16_t* words, const int32_t* offsets,
-                                                      const int32_t* kof, int count, T* scratch, uint32_t* phi_out,
-                                                      int32_t* rot_e_out, float* feat_out, int* flag) {
-    constexpr int R = EGeo<NQ>::R;
-    constexpr int Q4 = R / 4;
-    __shared__ uint16_t seq[256];
+__global__ __launch_bounds__(FeatGeo<NQ>::THREADS) void k_features(const T* a, const T* b, const int32_t* e, float* out) {
+    using Fg = FeatGeo<NQ>;
+    using Gm = RowGeo<NQ>;
+    constexpr int R = Fg::R;
+    __shared__ FeatLds<NQ> L;
     __shared__ int32_t rows[R * 2 * R];
     __shared__ int32_t idx[R];
-    T* a = scratch + (size_t)blockIdx.x * 4 * R * R;
-    T* b = a + R * R;
-    T* ta = b + R * R;
-    T* tb = ta + R * R;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int gi = lane / Gm::G, gl = lane % Gm::G;
+    T ra[Fg::NB][1], rb[Fg::NB][1];
+    int wide = 0;
+#pragma unroll
+    for (int i = 0; i < Fg::NB; ++i) {
+        const int row = (wave * Fg::NB + i) * Gm::RPW + gi;
+        ra[i][0] = row < R ? a[row * R + gl] : 0;
+        rb[i][0] = row < R ? b[row * R + gl] : 0;
+        wide |= ra[i][0] > 127 || ra[i][0] < -127 || rb[i][0] > 127 || rb[i][0] < -127;
+    }
+    if (__syncthreads_or(wide))
+        block_features<NQ, T>(a, b, *e, rows, idx, out);
+    else
+        rows_features<NQ, T>(ra, rb, *e, L, out);
+}
+
+// The signed permutation of columns that R(p)^2 is: an entry in column c of a row moves to column
+// p ^ c with sign s(p, p ^ c) when P_p and P_c anticommute, and stays otherwise.
+template <int NQ>
+__device__ inline void clifford_step(uint32_t p, uint32_t& c, uint32_t& neg) {
+    if (anticommutes<NQ>(p, c)) {
+        c ^= p;
+        neg ^= rotation_sign<NQ>(p, c) < 0 ? 1u : 0u;
+    }
+}
+
+// Reduction steps that a matrix at exponent e allows, from the OR of its a and of its b entries (which
+// has the least 2-adic valuation among them): k_rotate1 has the rule.
+template <typename T>
+__device__ inline int reduction_steps(T or_a, T or_b, int e) {
+    const int ma = or_a ? 2 * (int)__builtin_ctzll((unsigned long long)or_a) : 1 << 20;
+    const int mb = or_b ? 2 * (int)__builtin_ctzll((unsigned long long)or_b) + 1 : 1 << 20;
+    const int m = ma < mb ? ma : mb;
+    return m < e ? m : e;
+}
+template <typename T>
+__device__ inline void reduce_entry(T& a, T& b, int m) {
+    const int j = m >> 1;
+    const T va = a, vb = b;
+    a = m & 1 ? vb >> j : va >> j;
+    b = m & 1 ? va >> (j + 1) : vb >> j;
+}
+
+// Unreduced rotations stay exact up to this exponent: |a|, |b sqrt2| <= 2^(e/2) <= 2^28.
+constexpr int E_FREE = 56;
+
+// Network data: targets built exactly from their words (Clifford word then rotations), packed as
+// int8 for the walk step (n <= 3 layout) and turned into canonical features.  One block per target,
+// the rows in registers throughout: the Clifford word is a signed permutation of columns, so every
+// lane follows one row's single entry through its share of the word; the rotations then act on the
+// rows, reduced once at the end (and before every rotation beyond exponent E_FREE, where the entries'
+// range is checked).  Bound by instructions (about 2,200 per wavefront): 16384 circuits of 48 Clifford
+// factors and 1 to 10 rotations at n = 3 take 0.66 ms, against 33 ms with every factor as two rotations
+// through global memory, a reduction after each.
+template <int NQ, typename T>
+__global__ __launch_bounds__(FeatGeo<NQ>::THREADS) void k_build_batch(const uint16_t* words, const int32_t* offsets,
+                                                                      const int32_t* kof, int count, uint32_t* phi_out,
+                                                                      int32_t* rot_e_out, float* feat_out, int* flag) {
+    using Fg = FeatGeo<NQ>;
+    using Gm = RowGeo<NQ>;
+    constexpr int R = Fg::R, NB = Fg::NB, WPT = Fg::WPT, Q4 = R / 4;
+    __shared__ FeatLds<NQ> L;
+    __shared__ __attribute__((aligned(16))) int8_t bytes[2][R * R];  // A, then B
+    __shared__ uint16_t part[WPT][R];  // each wavefront's share of the Clifford word: column | sign << 8
+    __shared__ T ors[2][WPT];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int gi = lane / Gm::G, gl = lane % Gm::G, gbase = gi * Gm::G;
+    const T lim = lim_of<T>();
     for (int t = blockIdx.x; t < count; t += gridDim.x) {
-        const int w0 = offsets[t], w1 = offsets[t + 1], k = kof[t];
-        const int m = w1 - w0 - k;
-        int nseq = 2 * m + k;
-        if (nseq > 256) {
+        const int w0 = offsets[t], w1 = offsets[t + 1];
+        int k = kof[t], m = w1 - w0 - k;
+        if (2 * m + k > 256) {
             if (threadIdx.x == 0) atomicOr(flag, 8);
-            nseq = 0;
+            k = m = 0;
         }
-        if (threadIdx.x == 0 && nseq > 0) {
-            int s = 0;
-            for (int j = 0; j < m; ++j) {
-                seq[s++] = words[w0 + k + j];
-                seq[s++] = words[w0 + k + j];
-            }
-            for (int j = k - 1; j >= 0; --j) seq[s++] = words[w0 + j];
-        }
-        for (int i = threadIdx.x; i < R * R; i += blockDim.x) {
-            a[i] = (i / R == i % R) ? 1 : 0;
-            b[i] = 0;
+        {
+            uint32_t c = (uint32_t)lane & (R - 1), neg = 0;
+            for (int j = m * wave / WPT; j < m * (wave + 1) / WPT; ++j)
+                clifford_step<NQ>((uint32_t)__builtin_amdgcn_readfirstlane(words[w0 + k + j]), c, neg);
+            if (lane < R) part[wave][lane] = (uint16_t)(c | (neg << 8));
         }
         __syncthreads();
+        uint32_t c = (uint32_t)lane & (R - 1), neg = 0;
+#pragma unroll
+        for (int w = 0; w < WPT; ++w) {
+            const uint32_t v = part[w][c];
+            c = v & 255u;
+            neg ^= v >> 8;
+        }
+        T a[NB][1], b[NB][1];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int row = (wave * NB + i) * Gm::RPW + gi;
+            const uint32_t v = shfl32(c | (neg << 8), row & (R - 1));
+            a[i][0] = row < R && (int)(v & 255u) == gl ? (v >> 8 ? -1 : 1) : 0;
+            b[i][0] = 0;
+        }
         int e = 0;
-        block_apply<NQ, T>(a, b, ta, tb, e, seq, nullptr, nseq, flag);
-        if constexpr (NQ == 3) {
-            // MFMA fragment layout (as k_pack_phi for n >= 3)
-            constexpr int KK = 2 * R / 64;
-            for (int i = threadIdx.x; i < 2 * Q4 * R; i += blockDim.x) {
-                const int fi = i >> 2, w = i & 3;
-                const int l = fi & 63, fk = fi >> 6;
-                const int nt = fk / KK, kk = fk % KK;
-                const int r = nt * 16 + (l & 15);
-                uint32_t word = 0;
-                for (int c = 0; c < 4; ++c) {
-                    const int qq = kk * 64 + (l >> 4) * 16 + 4 * w + c;
-                    const T v = qq < R ? a[r * R + qq] : b[r * R + qq - R];
-                    if (v > 127 || v < -127) atomicOr(flag, 2);
-                    word |= ((uint32_t)(uint8_t)(int8_t)v) << (8 * c);
-                }
-                phi_out[(size_t)t * 2 * Q4 * R + i] = word;
+        auto reduce = [&]() {
+            T oa = 0, ob = 0;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                oa |= a[i][0];
+                ob |= b[i][0];
             }
-        } else {
-            for (int i = threadIdx.x; i < Q4 * R; i += blockDim.x) {
-                const int q4 = i / R, r = i % R;
-                uint32_t wa = 0, wb = 0;
-                for (int c = 0; c < 4; ++c) {
-                    const T va = a[r * R + 4 * q4 + c], vb = b[r * R + 4 * q4 + c];
-                    if (va > 127 || va < -127 || vb > 127 || vb < -127) atomicOr(flag, 2);
-                    wa |= ((uint32_t)(uint8_t)(int8_t)va) << (8 * c);
-                    wb |= ((uint32_t)(uint8_t)(int8_t)vb) << (8 * c);
+            for (int off = 32; off >= 1; off >>= 1) {
+                oa |= shfl_t(oa, lane ^ off);
+                ob |= shfl_t(ob, lane ^ off);
+            }
+            if constexpr (WPT > 1) {
+                if (lane == 0) {
+                    ors[0][wave] = oa;
+                    ors[1][wave] = ob;
                 }
-                phi_out[(size_t)t * 2 * Q4 * R + i] = wa;
-                phi_out[(size_t)t * 2 * Q4 * R + Q4 * R + i] = wb;
+                __syncthreads();
+#pragma unroll
+                for (int w = 0; w < WPT; ++w) {
+                    oa |= ors[0][w];
+                    ob |= ors[1][w];
+                }
+                __syncthreads();
+            }
+            const int steps = reduction_steps(oa, ob, e);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) reduce_entry(a[i][0], b[i][0], steps);
+            e -= steps;
+        };
+        for (int j = k - 1; j >= 0; --j) {
+            if (e >= E_FREE) reduce();
+            rotate_rows<NQ, NB, T>(a, b, (uint32_t)__builtin_amdgcn_readfirstlane(words[w0 + j]), false, gl, gbase);
+            if (++e > E_FREE) {
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+                    if (a[i][0] > lim || a[i][0] < -lim || b[i][0] > lim || b[i][0] < -lim) atomicOr(flag, 4);
             }
         }
+        reduce();
+        bool wide = false;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int row = (wave * NB + i) * Gm::RPW + gi;
+            wide |= a[i][0] > 127 || a[i][0] < -127 || b[i][0] > 127 || b[i][0] < -127;
+            if (row < R) {
+                bytes[0][row * R + gl] = (int8_t)a[i][0];
+                bytes[1][row * R + gl] = (int8_t)b[i][0];
+            }
+        }
+        if (wide) atomicOr(flag, 2);
         if (threadIdx.x == 0) rot_e_out[t] = (int32_t)((30ll * e) % 61);
-        block_features<NQ, T>(a, b, e, rows, idx, feat_out + (size_t)t * R * R);
+        __syncthreads();
+        if constexpr (NQ == 3) {
+            // MFMA fragment layout (as k_pack_phi for n >= 3): 16 bytes of a row per lane
+            typedef int v4 __attribute__((ext_vector_type(4)));
+            v4* out = reinterpret_cast<v4*>(phi_out + (size_t)t * 2 * Q4 * R);
+            for (int x = threadIdx.x; x < 2 * R * R / 16; x += Fg::THREADS) {
+                const int l = x & 63, kk = (x >> 6) & 1, nt = x >> 7;
+                out[x] = *reinterpret_cast<const v4*>(&bytes[kk][(nt * 16 + (l & 15)) * R + (l >> 4) * 16]);
+            }
+        } else {
+            for (int x = threadIdx.x; x < 2 * Q4 * R; x += Fg::THREADS) {
+                const int q4 = (x % (Q4 * R)) / R, r = x % R;
+                phi_out[(size_t)t * 2 * Q4 * R + x] = *reinterpret_cast<const uint32_t*>(&bytes[x / (Q4 * R)][r * R + 4 * q4]);
+            }
+        }
+        rows_features<NQ, T>(a, b, e, L, feat_out + (size_t)t * R * R);
     }
 }
 
@@ -923,7 +1104,8 @@ namespace tcw {
 hipError_t exact_features(const ExactDev& m, float* out, hipStream_t s) {
     auto f = [&]<int NQ, typename T>() -> hipError_t {
         if constexpr (NQ <= 3) {
-            hipLaunchKernelGGL((k_features<NQ, T>), dim3(1), dim3(256), 0, s, (const T*)m.a, (const T*)m.b, m.e, out);
+            hipLaunchKernelGGL((k_features<NQ, T>), dim3(1), dim3(FeatGeo<NQ>::THREADS), 0, s, (const T*)m.a,
+                               (const T*)m.b, m.e, out);
             return hipGetLastError();
         } else {
             return hipErrorInvalidValue;
@@ -932,18 +1114,13 @@ hipError_t exact_features(const ExactDev& m, float* out, hipStream_t s) {
     return dispatch_exact(m.n, f);
 }
 
-size_t build_batch_scratch_bytes(int n, int blocks) {
-    const size_t r = (size_t)1 << (2 * n);
-    return (size_t)blocks * 4 * r * r * (n <= 2 ? 8 : 4);
-}
-
 hipError_t build_batch(int n, const uint16_t* words, const int32_t* offsets, const int32_t* kof, int count,
-                       void* scratch, int blocks, uint32_t* phi_out, int32_t* rot_e_out, float* feat_out, int* flag,
-                       hipStream_t s) {
+                       uint32_t* phi_out, int32_t* rot_e_out, float* feat_out, int* flag, hipStream_t s) {
     auto f = [&]<int NQ, typename T>() -> hipError_t {
         if constexpr (NQ <= 3) {
-            hipLaunchKernelGGL((k_build_batch<NQ, T>), dim3(blocks), dim3(1024), 0, s, words, offsets, kof, count,
-                               (T*)scratch, phi_out, rot_e_out, feat_out, flag);
+            const int blocks = count < 8192 ? count : 8192;
+            hipLaunchKernelGGL((k_build_batch<NQ, T>), dim3(blocks), dim3(FeatGeo<NQ>::THREADS), 0, s, words, offsets,
+                               kof, count, phi_out, rot_e_out, feat_out, flag);
             return hipGetLastError();
         } else {
             return hipErrorInvalidValue;

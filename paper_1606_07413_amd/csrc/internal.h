@@ -119,10 +119,8 @@ hipError_t exact_claw_check(const ExactDev& S, int k, const uint64_t* u0, const 
 // canonical FP32 features (n <= 3)
 hipError_t exact_features(const ExactDev& m, float* out_dev, hipStream_t s);
 // many targets from words: phi (n <= 3 int8 layout), rot_e, features; flag |= 2 / 4 / 8 on range errors
-size_t build_batch_scratch_bytes(int n, int blocks);
 hipError_t build_batch(int n, const uint16_t* words, const int32_t* offsets, const int32_t* kof, int count,
-                       void* scratch, int blocks, uint32_t* phi_out, int32_t* rot_e_out, float* feat_out, int* flag,
-                       hipStream_t s);
+                       uint32_t* phi_out, int32_t* rot_e_out, float* feat_out, int* flag, hipStream_t s);
 // meet-in-the-middle level table and probes (walk.hip)
 hipError_t mitm_levels(int n, const SpaceDev& sp, int h, uint64_t* table, int log2_table, hipStream_t s);
 // the target side's workspace (mitm_frag_bytes(n, h_max) bytes, none at n <= 2), filled once for any number

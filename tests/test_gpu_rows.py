@@ -90,3 +90,51 @@ def test_certificate_above_six(ctx):
     tgt = ctx.target_from_unitary(3, v, 0)
     assert ctx.min_tcount(tgt, 4) == 7
     assert ctx.min_tcount(tgt, 3) == -1
+
+
+def long_word(n, rotations, seed):
+    """`rotations` seeded rotations and their inverses (R(P)^8 = I, so R(P)^7 = R(P)^T), then two more: an
+    unreduced exponent far above the end's."""
+    ps = seeded_inputs.target_words(n, rotations + 2, seed).paulis
+    return [p for p in ps[:rotations]] + [p for p in reversed(ps[:rotations]) for _ in range(7)] + ps[rotations:]
+
+
+# no rotation and no Clifford word, ragged Clifford words, words past the exponent at which rows are reduced
+# on the way, more targets than blocks are started for one at a time
+@pytest.mark.parametrize("n,count", [(1, 70), (2, 70), (3, 24)])
+def test_batch_features(ctx, n, count):
+    import torch
+    from oracle import mlp as omlp
+    print("batch features", n, count, flush=True)
+    words = []
+    for i in range(count):
+        tw = seeded_inputs.target_words(n, i % 8, 300 + i, clifford_len=(0, 1, 5, 16 * n)[i % 4])
+        words.append((tw.paulis, tw.clifford))
+    words[5] = (long_word(n, 10, 7), words[5][1])
+    words[6] = ([1] * 160, [])
+    feats = torch.empty((count, 16 ** n), dtype=torch.float32, device="cuda:0")
+    labels = torch.empty(count, dtype=torch.int32, device="cuda:0")
+    ctx.label_batch(n, words, 1, 3, feats, labels)
+    feats = feats.cpu().numpy()
+    for i, (paulis, clifford) in enumerate(words):
+        want = omlp.features(zmat.target_from_words(n, paulis, clifford))
+        assert np.array_equal(feats[i].view(np.uint32), want.view(np.uint32)), i
+
+
+def test_features_beyond_int8(ctx):
+    """Entries beyond int8 (the general sort), and words too long for int8 refused by the batch."""
+    import torch
+    from oracle import mlp as omlp
+    from paper_1606_07413_amd import tcw
+    for n, k in ((1, 22), (2, 24), (3, 26)):
+        print("features beyond int8", n, k, flush=True)
+        tw = seeded_inputs.target_words(n, k, 12)
+        if n == 1:
+            tw.paulis = [1 + i % 3 for i in range(k)]     # no two neighbours alike: the exponent grows with each
+        u = zmat.target_from_words(n, tw.paulis, tw.clifford)
+        assert max(abs(int(v)) for row in u.A for v in row) > 127
+        out = torch.empty(16 ** n, dtype=torch.float32, device="cuda:0")
+        ctx.features(ctx.target_from_words(n, tw.paulis, tw.clifford), out)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), omlp.features(u).view(np.uint32))
+        with pytest.raises(tcw.TcwError):
+            ctx.label_batch(n, [(tw.paulis, tw.clifford)], 1, 3, out, torch.empty(1, dtype=torch.int32, device="cuda:0"))
