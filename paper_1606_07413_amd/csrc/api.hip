@@ -60,7 +60,7 @@ struct tcw_ctx {
     hipStream_t stream = nullptr;
     std::string err;
     int* flag = nullptr;          // device scratch flag
-    int32_t* rot_min = nullptr;   // device scratch of exact_rotate1 (the least reduction count)
+    uint64_t* ors = nullptr;      // device scratch of exact_rotate1 and exact_words
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     void* noalloc = nullptr;        // this device's copy of the tcw_step_noalloc scratch array
     hipError_t noalloc_err = hipSuccess;
@@ -282,7 +282,7 @@ int prepare_space(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, Space& o
     // S_c = U R(c)^T for odd k, U for even k
     hipError_t e = hipSuccess;
     if (sp->k % 2 == 1) {
-        e = tcw::exact_rotate1(out.S, t->U, (uint32_t)sp->chunk, 1, c->rot_min, c->flag, c->stream);
+        e = tcw::exact_rotate1(out.S, t->U, (uint32_t)sp->chunk, 1, c->ors, c->flag, c->stream);
     } else {
         const size_t bytes = (size_t)out.S.r * out.S.r * out.S.elem;
         e = hipMemcpyAsync(out.S.a, t->U.a, bytes, hipMemcpyDeviceToDevice, c->stream);
@@ -455,7 +455,7 @@ int tcw_create(tcw_ctx** out, int device, void* stream) {
     c->device = device;
     c->stream = (hipStream_t)stream;
     if (hipSetDevice(device) != hipSuccess || hipMalloc(&c->flag, sizeof(int)) != hipSuccess ||
-        hipMalloc(&c->rot_min, sizeof(int32_t)) != hipSuccess || hipEventCreate(&c->ev0) != hipSuccess ||
+        hipMalloc(&c->ors, 2 * sizeof(uint64_t)) != hipSuccess || hipEventCreate(&c->ev0) != hipSuccess ||
         hipEventCreate(&c->ev1) != hipSuccess) {
         delete c;
         return TCW_EDEVICE;
@@ -470,7 +470,7 @@ int tcw_destroy(tcw_ctx* c) {
     if (c->stopped) free_search_run(c->stopped);
     c->stopped = nullptr;
     if (c->flag) (void)hipFree(c->flag);
-    if (c->rot_min) (void)hipFree(c->rot_min);
+    if (c->ors) (void)hipFree(c->ors);
     for (auto& e : c->pool) (void)hipFree(e.second);
     c->pool.clear();
     if (c->ev0) (void)hipEventDestroy(c->ev0);
@@ -496,37 +496,41 @@ int tcw_target_from_words(tcw_ctx* c, int n, const uint16_t* paulis, int k, cons
     if (n < 1 || n > 4) return fail(c, TCW_EINVAL, "n must be in 1..4");
     if (k < 0 || m < 0 || (k > 0 && !paulis) || (m > 0 && !clifford)) return fail(c, TCW_EINVAL, "bad word arrays");
     const uint32_t xi = xi_of(n);
-    // right-multiplication sequence: C_1 C_1 C_2 C_2 ... C_m C_m P_k ... P_1
-    std::vector<uint16_t> seq;
-    seq.reserve(2 * m + k);
-    for (int j = 0; j < m; ++j) {
+    for (int j = 0; j < m; ++j)
         if (clifford[j] < 1 || clifford[j] > xi) return fail(c, TCW_EINVAL, "Clifford Pauli out of range");
-        seq.push_back(clifford[j]);
-        seq.push_back(clifford[j]);
-    }
+    std::vector<uint16_t> rot;  // as they are multiplied from the right: P_k ... P_1
+    rot.reserve(k);
     for (int j = k - 1; j >= 0; --j) {
         if (paulis[j] < 1 || paulis[j] > xi) return fail(c, TCW_EINVAL, "Pauli out of range");
-        seq.push_back(paulis[j]);
+        rot.push_back(paulis[j]);
     }
     tcw_target* t = new (std::nothrow) tcw_target();
     if (!t) return TCW_ENOMEM;
     t->ctx = c;
     t->n = n;
     hipError_t e = tcw::exact_alloc(t->U, n);
-    uint16_t* seq_dev = nullptr;
-    if (e == hipSuccess && !seq.empty()) e = hipMalloc(&seq_dev, seq.size() * sizeof(uint16_t));
-    if (e == hipSuccess && !seq.empty())
-        e = hipMemcpyAsync(seq_dev, seq.data(), seq.size() * sizeof(uint16_t), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->flag, 0, sizeof(int), c->stream);
-    if (e == hipSuccess) e = tcw::exact_build(t->U, seq_dev, nullptr, (int)seq.size(), c->flag, c->stream);
-    if (seq_dev) (void)hipFree(seq_dev);
-    if (e != hipSuccess) {
-        tcw::exact_free(t->U);
-        delete t;
-        return hip_fail(c, e, "target build");
-    }
     int flag = 0;
-    int rc = read_flag(c, &flag);
+    int rc = TCW_OK;
+    if (tcw::exact_words_fit(m, k)) {
+        // within the exact range by construction: no flag to read
+        if (e == hipSuccess) e = tcw::exact_words(t->U, clifford, m, rot.data(), k, c->ors, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    } else {
+        // the general path: C_1 C_1 C_2 C_2 ... C_m C_m P_k ... P_1, one block, reduced after each
+        std::vector<uint16_t> seq;
+        seq.reserve(2 * (size_t)m + k);
+        for (int j = 0; j < m; ++j) seq.insert(seq.end(), 2, clifford[j]);
+        seq.insert(seq.end(), rot.begin(), rot.end());
+        DevScope scope;
+        uint16_t* seq_dev = nullptr;
+        if (e == hipSuccess) e = scope.alloc(&seq_dev, seq.size() * sizeof(uint16_t));
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(seq_dev, seq.data(), seq.size() * sizeof(uint16_t), hipMemcpyHostToDevice, c->stream);
+        if (e == hipSuccess) e = hipMemsetAsync(c->flag, 0, sizeof(int), c->stream);
+        if (e == hipSuccess) e = tcw::exact_build(t->U, seq_dev, nullptr, (int)seq.size(), c->flag, c->stream);
+        if (e == hipSuccess) rc = read_flag(c, &flag);
+    }
+    if (e != hipSuccess) rc = hip_fail(c, e, "target build");
     if (rc == TCW_OK && flag) rc = fail(c, TCW_EOVERFLOW, "exact value out of range while building the target");
     if (rc) {
         tcw::exact_free(t->U);
@@ -685,6 +689,14 @@ int tcw_target_free(tcw_target* t) {
 int tcw_target_channel(tcw_ctx* c, const tcw_target* t, int32_t* a, int32_t* b, int32_t* e) {
     if (!c || !t || !a || !b || !e) return TCW_EINVAL;
     const size_t rr = (size_t)1 << (4 * t->n);
+    if (t->U.elem == 4) {
+        // held as int32: nothing to convert or to check
+        HIP_TRY(c, hipMemcpyAsync(a, t->U.a, rr * 4, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(b, t->U.b, rr * 4, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(e, t->U.e, 4, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        return TCW_OK;
+    }
     int32_t *da = nullptr, *db = nullptr;
     DevScope scope;
     HIP_TRY(c, scope.alloc(&da, rr * 4));

@@ -689,7 +689,7 @@ __device__ inline void clifford_step(uint32_t p, uint32_t& c, uint32_t& neg) {
 }
 
 // Reduction steps that a matrix at exponent e allows, from the OR of its a and of its b entries (which
-// has the least 2-adic valuation among them): k_rotate1 has the rule.
+// has the least 2-adic valuation among them): the rule stands at or_entries.
 template <typename T>
 __device__ inline int reduction_steps(T or_a, T or_b, int e) {
     const int ma = or_a ? 2 * (int)__builtin_ctzll((unsigned long long)or_a) : 1 << 20;
@@ -904,29 +904,43 @@ hipError_t exact_apply(ExactDev& dst, const ExactDev& src, const uint16_t* seq, 
 }
 
 namespace {
-// One rotation on many blocks (the chunk matrix S_c = U R(c)^T), in two passes with no work matrices.
-// Pass 1 writes (A', B') = the rotated columns of (src.A, src.B) into dst and folds into *m_min the
-// number of reduction steps each entry allows: a step (a, b) -> (b, a / 2) needs a even, so from
-// (a, b) the steps alternate the conditions 2 | a, 2 | b, 4 | a, 4 | b, ... and entry (a, b) allows
-// min(2 v2(a), 2 v2(b) + 1) of them (v2 = 2-adic valuation, unbounded for 0).  Pass 2 takes
-// m = min(*m_min, e + 1) steps in closed form, as block_apply's loop would: after 2j steps
-// (a, b) / 2^j, after 2j + 1 steps (b / 2^j, a / 2^(j + 1)).
-template <typename T>
-__device__ inline int v2_of(T v) {
-    if (v == 0) return 1 << 20;
-    return (int)__builtin_ctzll((unsigned long long)v);
+// A matrix multiplied from the right on many blocks, in two passes with no work matrices: the first leaves
+// the product unreduced and ors its a entries into ors[0] and its b entries into ors[1] (one atomic
+// per block); the second takes all reduction steps in closed form.  A step (a, b) -> (b, a / 2) needs a
+// even, so from (a, b) the steps alternate the conditions 2 | a, 2 | b, 4 | a, 4 | b, ... and entry (a, b)
+// allows min(2 v2(a), 2 v2(b) + 1) of them (v2 = 2-adic valuation, unbounded for 0, that of an OR being
+// the least of its terms'): reduction_steps.  After 2j steps an entry is (a, b) / 2^j, after 2j + 1 steps
+// (b / 2^j, a / 2^(j + 1)): reduce_entry.
+template <typename T, int WAVES>
+__device__ inline void or_entries(T oa, T ob, unsigned long long* ors) {
+    __shared__ T red[2][WAVES];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int off = 32; off >= 1; off >>= 1) {
+        oa |= shfl_t(oa, lane ^ off);
+        ob |= shfl_t(ob, lane ^ off);
+    }
+    if (lane == 0) {
+        red[0][wave] = oa;
+        red[1][wave] = ob;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        T v = 0;
+        for (int w = 0; w < WAVES; ++w) v |= red[threadIdx.x][w];
+        if (v) atomicOr(&ors[threadIdx.x], (unsigned long long)v);
+    }
 }
 
+constexpr int ROT1_THREADS = 1024;
 template <int NQ, typename T>
-__global__ __launch_bounds__(256) void k_rotate1(T* a, T* b, const T* sa, const T* sb, uint32_t p, int transposed,
-                                                int* flag, int32_t* m_min) {
+__global__ __launch_bounds__(ROT1_THREADS) void k_rotate1(T* a, T* b, const T* sa, const T* sb, uint32_t p,
+                                                         int transposed, int* flag, unsigned long long* ors) {
     constexpr int R = EGeo<NQ>::R;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    int m = 1 << 30;
+    T va = 0, vb = 0;
     if (idx < R * R) {
         const uint32_t q = idx & (R - 1);
         const int row = idx - (int)q;
-        T va, vb;
         if (anticommutes<NQ>(p, q)) {
             int sg = rotation_sign<NQ>(p, q);
             if (transposed) sg = -sg;
@@ -941,36 +955,72 @@ __global__ __launch_bounds__(256) void k_rotate1(T* a, T* b, const T* sa, const 
         if (va > lim || va < -lim || vb > lim || vb < -lim) atomicOr(flag, 4);
         a[idx] = va;
         b[idx] = vb;
-        const int ma = 2 * v2_of(va), mb = 2 * v2_of(vb) + 1;
-        m = ma < mb ? ma : mb;
     }
-    // the wavefront's least, then one atomic per wavefront
-    for (int off = 32; off >= 1; off >>= 1) {
-        const int o = __shfl_xor(m, off);
-        m = o < m ? o : m;
-    }
-    if ((threadIdx.x & 63) == 0 && m < (1 << 30)) atomicMin(m_min, m);
+    or_entries<T, ROT1_THREADS / 64>(va, vb, ors);
 }
 
+// (a, b) at exponent *se (0 if null) + grown, reduced in place; *e_io = the exponent left.
 template <int NQ, typename T>
-__global__ __launch_bounds__(256) void k_rotate1_reduce(T* a, T* b, int32_t* e_io, const int32_t* se,
-                                                       const int32_t* m_min) {
+__global__ __launch_bounds__(256) void k_reduce(T* a, T* b, int32_t* e_io, const int32_t* se, int grown,
+                                               const unsigned long long* ors) {
     constexpr int R = EGeo<NQ>::R;
-    const int e1 = *se + 1;
-    const int m = *m_min < e1 ? *m_min : e1;
+    const int e1 = (se ? *se : 0) + grown;
+    const int m = reduction_steps((T)ors[0], (T)ors[1], e1);
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx < R * R && m > 0) {
-        const T va = a[idx], vb = b[idx];
-        const int j = m >> 1;
-        if (m & 1) {
-            a[idx] = vb / ((T)1 << j);
-            b[idx] = va / ((T)1 << (j + 1));
-        } else {
-            a[idx] = va / ((T)1 << j);
-            b[idx] = vb / ((T)1 << j);
-        }
-    }
+    if (idx < R * R && m > 0) reduce_entry(a[idx], b[idx], m);
     if (idx == 0) *e_io = e1 - m;
+}
+
+// A target from its words (m Clifford factors, then its rotations, as they are multiplied from the right):
+// every wavefront takes rows of the product through the words in registers, as k_build_batch does, but
+// one row set each, so that the rows of one target fill up to 64 blocks.  At most E_FREE rotations, so
+// nothing leaves the exact range.  Bound by the chain of the Clifford word and by launches: at n = 4, 64
+// factors and 7 rotations, building a target and reading it back takes 97 us, against 6.5 ms with every
+// factor as two rotations on one block, a reduction after each (k_apply, which words with more rotations
+// still take).
+constexpr int WORDS_MAX = 1024;
+struct Words {
+    uint16_t w[WORDS_MAX];
+};
+constexpr int WORDS_WAVES = 4;
+template <int NQ, typename T>
+__global__ __launch_bounds__(WORDS_WAVES * 64) void k_words(Words words, int m, int k, T* a, T* b,
+                                                            unsigned long long* ors) {
+    using Gm = RowGeo<NQ>;
+    constexpr int R = Gm::R, CPL = Gm::CPL;
+    const int lane = threadIdx.x & 63;
+    const int gi = lane / Gm::G, gl = lane % Gm::G, gbase = gi * Gm::G;
+    const int row = (int)(blockIdx.x * WORDS_WAVES + (threadIdx.x >> 6)) * Gm::RPW + gi;
+    uint32_t c = (uint32_t)row & (R - 1), neg = 0;
+    for (int base = 0; base < m; base += 64) {
+        const int n = m - base < 64 ? m - base : 64;
+        const int mine = lane < n ? words.w[base + lane] : 0;
+        for (int j = 0; j < n; ++j) clifford_step<NQ>((uint32_t)__builtin_amdgcn_readlane(mine, j), c, neg);
+    }
+    T ra[1][CPL], rb[1][CPL];
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+        ra[0][j] = row < R && (int)c == gl * CPL + j ? (neg ? -1 : 1) : 0;
+        rb[0][j] = 0;
+    }
+    const int mine = lane < k ? words.w[m + lane] : 0;
+    for (int j = 0; j < k; ++j)
+        rotate_rows<NQ, 1, T>(ra, rb, (uint32_t)__builtin_amdgcn_readlane(mine, j), false, gl, gbase);
+    T oa = 0, ob = 0;
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+        if (row < R) {
+            a[row * R + gl * CPL + j] = ra[0][j];
+            b[row * R + gl * CPL + j] = rb[0][j];
+        }
+        oa |= ra[0][j];
+        ob |= rb[0][j];
+    }
+    or_entries<T, WORDS_WAVES>(oa, ob, ors);
+}
+
+__global__ void k_clear_ors(unsigned long long* ors) {
+    if (threadIdx.x < 2) ors[threadIdx.x] = 0;
 }
 
 __global__ void k_seq_one(uint16_t* seq, uint8_t* tr, uint16_t p, uint8_t t) {
@@ -984,18 +1034,17 @@ __global__ void k_fill_i32(int* dst, int v, int count) {
 }
 }  // namespace
 
-hipError_t exact_rotate1(ExactDev& dst, const ExactDev& src, uint32_t p, int transposed, int32_t* m_tmp, int* flag,
+hipError_t exact_rotate1(ExactDev& dst, const ExactDev& src, uint32_t p, int transposed, uint64_t* ors, int* flag,
                          hipStream_t s) {
     if (dst.a == src.a || dst.b == src.b) return hipErrorInvalidValue;
-    hipError_t err = fill_i32(m_tmp, 1 << 30, 1, s);
-    if (err != hipSuccess) return err;
+    unsigned long long* o = reinterpret_cast<unsigned long long*>(ors);
+    hipLaunchKernelGGL(k_clear_ors, dim3(1), dim3(64), 0, s, o);
     auto f = [&]<int NQ, typename T>() -> hipError_t {
         constexpr int R = EGeo<NQ>::R;
-        const int blocks = (R * R + 255) / 256;
-        hipLaunchKernelGGL((k_rotate1<NQ, T>), dim3(blocks), dim3(256), 0, s, (T*)dst.a, (T*)dst.b, (const T*)src.a,
-                           (const T*)src.b, p, transposed, flag, m_tmp);
-        hipLaunchKernelGGL((k_rotate1_reduce<NQ, T>), dim3(blocks), dim3(256), 0, s, (T*)dst.a, (T*)dst.b, dst.e,
-                           src.e, m_tmp);
+        hipLaunchKernelGGL((k_rotate1<NQ, T>), dim3((R * R + ROT1_THREADS - 1) / ROT1_THREADS), dim3(ROT1_THREADS), 0, s,
+                           (T*)dst.a, (T*)dst.b, (const T*)src.a, (const T*)src.b, p, transposed, flag, o);
+        hipLaunchKernelGGL((k_reduce<NQ, T>), dim3((R * R + 255) / 256), dim3(256), 0, s, (T*)dst.a, (T*)dst.b, dst.e,
+                           src.e, 1, o);
         return hipGetLastError();
     };
     return dispatch_exact(dst.n, f);
@@ -1009,6 +1058,27 @@ hipError_t exact_seq_one(uint16_t* seq, uint8_t* tr, uint16_t p, uint8_t transpo
 hipError_t fill_i32(int* dst, int v, int count, hipStream_t s) {
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, dst, v, count);
     return hipGetLastError();
+}
+
+bool exact_words_fit(int m, int k) { return k <= E_FREE && m + k <= WORDS_MAX; }
+
+hipError_t exact_words(ExactDev& dst, const uint16_t* clifford, int m, const uint16_t* rotations, int k, uint64_t* ors,
+                       hipStream_t s) {
+    if (!exact_words_fit(m, k)) return hipErrorInvalidValue;
+    Words w;
+    for (int j = 0; j < m; ++j) w.w[j] = clifford[j];
+    for (int j = 0; j < k; ++j) w.w[m + j] = rotations[j];
+    unsigned long long* o = reinterpret_cast<unsigned long long*>(ors);
+    hipLaunchKernelGGL(k_clear_ors, dim3(1), dim3(64), 0, s, o);
+    auto f = [&]<int NQ, typename T>() -> hipError_t {
+        constexpr int R = EGeo<NQ>::R, rows = RowGeo<NQ>::RPW * WORDS_WAVES;
+        hipLaunchKernelGGL((k_words<NQ, T>), dim3((R + rows - 1) / rows), dim3(WORDS_WAVES * 64), 0, s, w, m, k,
+                           (T*)dst.a, (T*)dst.b, o);
+        hipLaunchKernelGGL((k_reduce<NQ, T>), dim3((R * R + 255) / 256), dim3(256), 0, s, (T*)dst.a, (T*)dst.b, dst.e,
+                           (const int32_t*)nullptr, k, o);
+        return hipGetLastError();
+    };
+    return dispatch_exact(dst.n, f);
 }
 
 hipError_t exact_build(ExactDev& m, const uint16_t* seq, const uint8_t* tr, int nseq, int* flag, hipStream_t s) {

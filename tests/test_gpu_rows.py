@@ -138,3 +138,23 @@ def test_features_beyond_int8(ctx):
         assert np.array_equal(out.cpu().numpy().view(np.uint32), omlp.features(u).view(np.uint32))
         with pytest.raises(tcw.TcwError):
             ctx.label_batch(n, [(tw.paulis, tw.clifford)], 1, 3, out, torch.empty(1, dtype=torch.int32, device="cuda:0"))
+
+
+# no words at all; a Clifford word only, past one wavefront's worth of words; the most rotations that the
+# rows take unreduced (56) and more; words that grow and come back (82 rotations)
+@pytest.mark.parametrize("n,k,m", [(1, 0, 0), (2, 0, 0), (3, 0, 0), (4, 0, 0), (1, 9, 130), (2, 0, 65), (3, 3, 64),
+                                   (3, 0, 200), (4, 9, 3), (1, 56, 2), (1, 57, 2), (2, 56, 5), (2, 57, 5), (3, 56, 1),
+                                   (1, -1, 3), (2, -1, 3), (3, -1, 3)])
+def test_target_words_edges(ctx, n, k, m):
+    from paper_1606_07413_amd import tcw
+    print("target words", n, k, m, flush=True)
+    paulis = long_word(n, 10, 9) if k < 0 else seeded_inputs.target_words(n, k, 71).paulis
+    clifford = seeded_inputs.random_clifford_word(n, 5, length=m)
+    u = zmat.target_from_words(n, paulis, clifford)
+    a, b, e = ctx.target_from_words(n, paulis, clifford).channel()
+    assert e == u.e
+    assert np.array_equal(a, np.array(u.A, dtype=np.int64)) and np.array_equal(b, np.array(u.B, dtype=np.int64))
+    if k == 56 and n == 3:
+        with pytest.raises(tcw.TcwError) as err:     # beyond int32 on the way
+            ctx.target_from_words(n, seeded_inputs.target_words(n, 90, 71).paulis, clifford)
+        assert err.value.code == tcw.TCW_EOVERFLOW
