@@ -31,15 +31,18 @@ struct TunedCfg {
 namespace tcw {
 // n = 4: rotated key vectors (SpaceDev::rkeys, rkeys2), shared by the spaces of one search seed.
 struct RotKeys {
+    uint64_t* keys = nullptr;  // the keys K that they start from
     uint64_t* t1 = nullptr;  // 1 MiB
     uint64_t* t2 = nullptr;  // 256 MiB, or null when the allocation failed
     ~RotKeys() {
+        if (keys) (void)hipFree(keys);
         if (t1) (void)hipFree(t1);
         if (t2) (void)hipFree(t2);
     }
 };
 }  // namespace tcw
 
+constexpr size_t PINNED_BYTES = 4096;
 constexpr size_t ROT_KEYS_KEEP = 32;  // seeds whose n = 4 rotated keys (257 MiB each) a context keeps
 
 struct SearchRun;
@@ -60,7 +63,8 @@ struct tcw_ctx {
     hipStream_t stream = nullptr;
     std::string err;
     int* flag = nullptr;          // device scratch flag
-    uint64_t* ors = nullptr;      // device scratch of exact_rotate1 and exact_words
+    uint64_t* ors = nullptr;      // device scratch of exact_words
+    int32_t* pinned = nullptr;    // PINNED_BYTES of pinned host memory for small results
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     void* noalloc = nullptr;        // this device's copy of the tcw_step_noalloc scratch array
     hipError_t noalloc_err = hipSuccess;
@@ -191,40 +195,30 @@ void space_salts(tcw::SpaceDev& dev, uint64_t seed, uint32_t version, int k, int
     dev.salt_s = tcw::sm64(tcw::sm64(seed, 4), ctxi);
 }
 
-// A prepared search space: S_c on the device (exact and int8-packed), keys, salts.
+// A prepared search space: S_c on the device (int8-packed), keys, salts, and the target it is made from
+// (borrowed, for the exact claw check).
 struct Space {
     tcw_ctx* ctx = nullptr;
     int n = 0, k = 0, chunk = 0, delta = 0;
     uint64_t seed = 0;
     uint32_t version = 0;
-    ExactDev S;
-    int32_t e_s = 0;
-    uint32_t* phi = nullptr;
-    uint64_t* keys = nullptr;
+    ExactDev U;
+    uint8_t* mem = nullptr;            // the packing, the keys, two words of scratch, made
+    int32_t* made = nullptr;           // SpaceJob::out
     std::shared_ptr<tcw::RotKeys> rk;  // n = 4: rotated keys (SpaceDev::rkeys, rkeys2)
     SpaceDev dev{};
-    bool pooled = false;  // a batch member's space: buffers from and back to the context's pool
+    bool pooled = false;  // a batch member's space: memory from and back to the context's pool
 
-    size_t mat_bytes() const { return (size_t)S.r * S.r * S.elem; }
-    size_t phi_bytes() const { return (size_t)S.r * S.r / 2 * sizeof(uint32_t) + 16; }
-    size_t key_bytes() const { return (size_t)S.r * sizeof(uint64_t); }
+    static size_t phi_bytes(int n) { return (size_t)2 << (8 * n / 2); }
+    static size_t key_bytes(int n) { return (size_t)8 << (2 * n); }
+    static size_t mem_bytes(int n) { return phi_bytes(n) + key_bytes(n) + 2 * 8 + 2 * 4; }
 
     void release() {
-        if (pooled && ctx) {
-            pool_put(ctx, S.a, mat_bytes());
-            pool_put(ctx, S.b, mat_bytes());
-            pool_put(ctx, S.e, sizeof(int32_t));
-            pool_put(ctx, phi, phi_bytes());
-            pool_put(ctx, keys, key_bytes());
-            S.a = S.b = nullptr;
-            S.e = nullptr;
-        } else {
-            tcw::exact_free(S);
-            if (phi) (void)hipFree(phi);
-            if (keys) (void)hipFree(keys);
-        }
-        phi = nullptr;
-        keys = nullptr;
+        if (mem && pooled && ctx)
+            pool_put(ctx, mem, mem_bytes(n));
+        else if (mem)
+            (void)hipFree(mem);
+        mem = nullptr;
     }
 
     ~Space() { release(); }
@@ -232,6 +226,20 @@ struct Space {
     void set_version(uint32_t v) {
         version = v;
         space_salts(dev, seed, v, k, chunk);
+    }
+
+    tcw::SpaceJob job() const {
+        tcw::SpaceJob j{};
+        j.a = U.a;
+        j.b = U.b;
+        j.e = U.e;
+        j.seed = seed;
+        j.phi = reinterpret_cast<uint32_t*>(mem);
+        j.keys = reinterpret_cast<uint64_t*>(mem + phi_bytes(n));
+        j.ors = reinterpret_cast<unsigned long long*>(mem + phi_bytes(n) + key_bytes(n));
+        j.out = made;
+        j.c = (uint32_t)chunk;
+        return j;
     }
 };
 
@@ -249,92 +257,104 @@ int check_space(tcw_ctx* c, int n, const tcw_space* sp) {
     return TCW_OK;
 }
 
-int prepare_space(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, Space& out) {
+// n = 4: the rotated keys of a search seed.  The keys depend on the seed only: one set per seed, cached in
+// the context.
+int rotated_keys(tcw_ctx* c, uint64_t seed, std::shared_ptr<tcw::RotKeys>& out) {
+    auto it = c->rot_keys.find(seed);
+    if (it == c->rot_keys.end()) {
+        while (c->rot_keys.size() >= ROT_KEYS_KEEP) {
+            auto victim = c->rot_keys.end();
+            for (auto e = c->rot_keys.begin(); e != c->rot_keys.end(); ++e) {
+                const bool unused = e->second.rk.use_count() == 1;
+                if (unused && (victim == c->rot_keys.end() || e->second.last < victim->second.last)) victim = e;
+            }
+            if (victim == c->rot_keys.end()) break;  // every cached table is in use
+            c->rot_keys.erase(victim);
+        }
+        auto rk = std::make_shared<tcw::RotKeys>();
+        HIP_TRY(c, hipMalloc(&rk->keys, 256 * sizeof(uint64_t)));
+        HIP_TRY(c, tcw::keys_fill(4, seed, rk->keys, c->stream));
+        HIP_TRY(c, hipMalloc(&rk->t1, (size_t)2 * 256 * 256 * sizeof(uint64_t)));
+        HIP_TRY(c, tcw::rot_keys_fill(rk->keys, rk->t1, c->stream));
+        if (hipMalloc(&rk->t2, (size_t)2 * 256 * 256 * 256 * sizeof(uint64_t)) == hipSuccess) {
+            HIP_TRY(c, tcw::rot_keys2_fill(rk->t1, rk->t2, c->stream));
+        } else {
+            rk->t2 = nullptr;  // without the 256 MiB table the step applies one more rotation
+            (void)hipGetLastError();
+        }
+        it = c->rot_keys.emplace(seed, tcw_ctx::RotEntry{rk, 0}).first;
+    }
+    it->second.last = ++c->rot_clock;
+    out = it->second.rk;
+    return TCW_OK;
+}
+
+// Everything of a space but what the device makes of it (made: where that goes, or null for the space's
+// own memory): memory, keys shared by the seed, descriptors.  A Space set up before for the same qubit
+// count keeps its memory (a batch member's next chunk).
+int setup_space(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, Space& out, int32_t* made) {
     int rc = check_space(c, t->n, sp);
     if (rc) return rc;
     const int n = t->n;
-    const int R = 1 << (2 * n);
+    if (out.mem == nullptr || out.n != n) {
+        out.release();
+        out.ctx = c;
+        out.n = n;
+        if (out.pooled)
+            HIP_TRY(c, pool_alloc(c, reinterpret_cast<void**>(&out.mem), Space::mem_bytes(n)));
+        else
+            HIP_TRY(c, hipMalloc(&out.mem, Space::mem_bytes(n)));
+    }
     out.ctx = c;
-    out.n = n;
     out.k = sp->k;
     out.chunk = sp->chunk;
     out.delta = sp->delta;
     out.seed = sp->seed;
-    // a Space prepared before for the same qubit count keeps its buffers (a batch member's next chunk)
-    if (out.S.a == nullptr || out.S.n != n || !out.phi || !out.keys) {
-        out.release();
-        if (out.pooled) {
-            out.S.n = n;
-            out.S.r = R;
-            out.S.elem = n <= 2 ? 8 : 4;
-            HIP_TRY(c, pool_alloc(c, &out.S.a, out.mat_bytes()));
-            HIP_TRY(c, pool_alloc(c, &out.S.b, out.mat_bytes()));
-            HIP_TRY(c, pool_alloc(c, reinterpret_cast<void**>(&out.S.e), sizeof(int32_t)));
-            HIP_TRY(c, pool_alloc(c, reinterpret_cast<void**>(&out.phi), out.phi_bytes()));
-            HIP_TRY(c, pool_alloc(c, reinterpret_cast<void**>(&out.keys), out.key_bytes()));
-        } else {
-            HIP_TRY(c, tcw::exact_alloc(out.S, n));
-            HIP_TRY(c, hipMalloc(&out.phi, (size_t)R * R / 2 * sizeof(uint32_t) + 16));
-            HIP_TRY(c, hipMalloc(&out.keys, (size_t)R * sizeof(uint64_t)));
-        }
-    }
-    if ((rc = clear_flag(c))) return rc;
-    // S_c = U R(c)^T for odd k, U for even k
-    hipError_t e = hipSuccess;
-    if (sp->k % 2 == 1) {
-        e = tcw::exact_rotate1(out.S, t->U, (uint32_t)sp->chunk, 1, c->ors, c->flag, c->stream);
-    } else {
-        const size_t bytes = (size_t)out.S.r * out.S.r * out.S.elem;
-        e = hipMemcpyAsync(out.S.a, t->U.a, bytes, hipMemcpyDeviceToDevice, c->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(out.S.b, t->U.b, bytes, hipMemcpyDeviceToDevice, c->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(out.S.e, t->U.e, sizeof(int32_t), hipMemcpyDeviceToDevice, c->stream);
-    }
-    if (e != hipSuccess) return hip_fail(c, e, "chunk matrix");
-    HIP_TRY(c, tcw::exact_pack_phi(out.S, out.phi, c->flag, c->stream));
-    HIP_TRY(c, tcw::keys_fill(n, sp->seed, out.keys, c->stream));
-    if (n == 4) {
-        // the keys depend on the seed only: one set of rotated keys per seed, cached in the context
-        auto it = c->rot_keys.find(sp->seed);
-        if (it == c->rot_keys.end()) {
-            while (c->rot_keys.size() >= ROT_KEYS_KEEP) {
-                auto victim = c->rot_keys.end();
-                for (auto e = c->rot_keys.begin(); e != c->rot_keys.end(); ++e) {
-                    const bool unused = e->second.rk.use_count() == 1;
-                    if (unused && (victim == c->rot_keys.end() || e->second.last < victim->second.last)) victim = e;
-                }
-                if (victim == c->rot_keys.end()) break;  // every cached table is in use
-                c->rot_keys.erase(victim);
-            }
-            auto rk = std::make_shared<tcw::RotKeys>();
-            HIP_TRY(c, hipMalloc(&rk->t1, (size_t)2 * 256 * 256 * sizeof(uint64_t)));
-            HIP_TRY(c, tcw::rot_keys_fill(out.keys, rk->t1, c->stream));
-            if (hipMalloc(&rk->t2, (size_t)2 * 256 * 256 * 256 * sizeof(uint64_t)) == hipSuccess) {
-                HIP_TRY(c, tcw::rot_keys2_fill(rk->t1, rk->t2, c->stream));
-            } else {
-                rk->t2 = nullptr;  // without the 256 MiB table the step applies one more rotation
-                (void)hipGetLastError();
-            }
-            it = c->rot_keys.emplace(sp->seed, tcw_ctx::RotEntry{rk, 0}).first;
-        }
-        it->second.last = ++c->rot_clock;
-        out.rk = it->second.rk;
-    }
-    HIP_TRY(c, hipMemcpyAsync(&out.e_s, out.S.e, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
-    int flag = 0;
-    if ((rc = read_flag(c, &flag))) return rc;
-    if (flag & 4) return fail(c, TCW_EOVERFLOW, "exact value out of range while forming S_c");
-    if (flag & 2) return fail(c, TCW_EOVERFLOW, "S_c entry outside int8 range (exponent too large)");
+    out.U = t->U;
+    out.made = made ? made : reinterpret_cast<int32_t*>(out.mem + Space::mem_bytes(n) - 2 * 4);
+    if (n == 4 && (rc = rotated_keys(c, sp->seed, out.rk))) return rc;
+    const tcw::SpaceJob j = out.job();
     const int h = sp->k / 2;
     out.dev.n_half = (uint32_t)n_half_of(n, h);
     out.dev.h = h;
     out.dev.delta = sp->delta;
-    out.dev.rot_e = (int32_t)((30ll * out.e_s) % 61);
-    out.dev.phi = out.phi;
-    out.dev.keys = out.keys;
+    out.dev.rot_e = 0;
+    out.dev.made = out.made;
+    out.dev.phi = j.phi;
+    out.dev.keys = j.keys;
     out.dev.rkeys = out.rk ? out.rk->t1 : nullptr;
     out.dev.rkeys2 = out.rk ? out.rk->t2 : nullptr;
     out.set_version(sp->version);
     return TCW_OK;
+}
+
+// What the device made of a space, read back: {exponent, flags}.
+int accept_space(tcw_ctx* c, Space& s, const int32_t* made) {
+    if (made[1] & 4) return fail(c, TCW_EOVERFLOW, "exact value out of range while forming S_c");
+    if (made[1] & 2) return fail(c, TCW_EOVERFLOW, "S_c entry outside int8 range (exponent too large)");
+    s.dev.rot_e = (int32_t)((30ll * made[0]) % 61);
+    s.dev.made = nullptr;
+    return TCW_OK;
+}
+
+// setup_space and the device's part, which the stream runs before what is launched next (SpaceDev::made)
+int start_space(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, Space& out) {
+    int rc = setup_space(c, t, sp, out, nullptr);
+    if (rc) return rc;
+    HIP_TRY(c, tcw::spaces_make(t->n, out.job(), nullptr, 1, c->stream));
+    return TCW_OK;
+}
+
+// waits for the stream and takes the space's answer
+int finish_space(tcw_ctx* c, Space& s) {
+    HIP_TRY(c, hipMemcpyAsync(c->pinned, s.made, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return accept_space(c, s, c->pinned);
+}
+
+int prepare_space(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, Space& out) {
+    int rc = start_space(c, t, sp, out);
+    return rc ? rc : finish_space(c, out);
 }
 
 int default_log2_table(int n) { return n <= 2 ? 12 : (n == 3 ? 20 : 26); }
@@ -374,7 +394,7 @@ struct tcw_walk {
         if (wd.table) (void)hipFree(wd.table);
         if (wd.stats) (void)hipFree(wd.stats);
         if (wd.claws) (void)hipFree(wd.claws);
-        if (wd.claw_count) (void)hipFree(wd.claw_count);
+        // claw_count is the word after the statistics
     }
 };
 
@@ -386,8 +406,7 @@ int walk_restart(tcw_walk* w) {
     w->launches = 0;
     HIP_TRY(c, tcw::launch_table_clear(w->wd.table, w->wd.log2_table, w->wd.enumerate ? tcw::ENUM_TABLE_INIT : 0,
                                        c->stream));
-    HIP_TRY(c, hipMemsetAsync(w->wd.stats, 0, tcw::ST_COUNT * sizeof(unsigned long long), c->stream));
-    HIP_TRY(c, hipMemsetAsync(w->wd.claw_count, 0, sizeof(unsigned long long), c->stream));
+    HIP_TRY(c, hipMemsetAsync(w->wd.stats, 0, (tcw::ST_COUNT + 1) * sizeof(unsigned long long), c->stream));
     HIP_TRY(c, tcw::launch_walk_init(w->space.dev, w->wd, c->stream));
     return TCW_OK;
 }
@@ -455,7 +474,8 @@ int tcw_create(tcw_ctx** out, int device, void* stream) {
     c->device = device;
     c->stream = (hipStream_t)stream;
     if (hipSetDevice(device) != hipSuccess || hipMalloc(&c->flag, sizeof(int)) != hipSuccess ||
-        hipMalloc(&c->ors, 2 * sizeof(uint64_t)) != hipSuccess || hipEventCreate(&c->ev0) != hipSuccess ||
+        hipMalloc(&c->ors, 2 * sizeof(uint64_t)) != hipSuccess ||
+        hipHostMalloc(&c->pinned, PINNED_BYTES, hipHostMallocDefault) != hipSuccess || hipEventCreate(&c->ev0) != hipSuccess ||
         hipEventCreate(&c->ev1) != hipSuccess) {
         delete c;
         return TCW_EDEVICE;
@@ -471,6 +491,7 @@ int tcw_destroy(tcw_ctx* c) {
     c->stopped = nullptr;
     if (c->flag) (void)hipFree(c->flag);
     if (c->ors) (void)hipFree(c->ors);
+    if (c->pinned) (void)hipHostFree(c->pinned);
     for (auto& e : c->pool) (void)hipFree(e.second);
     c->pool.clear();
     if (c->ev0) (void)hipEventDestroy(c->ev0);
@@ -720,11 +741,10 @@ int tcw_step(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, const uint64_
     if (!c || !t || count < 0 || (count > 0 && (!in || !out))) return TCW_EINVAL;
     if (count == 0) return check_space(c, t->n, sp);
     Space s;
-    int rc = prepare_space(c, t, sp, s);
+    int rc = start_space(c, t, sp, s);
     if (rc) return rc;
     HIP_TRY(c, tcw::launch_step(t->n, s.dev, in, out, hash, count, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    return TCW_OK;
+    return finish_space(c, s);
 }
 
 int tcw_step_noalloc(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, const uint64_t* in, uint64_t* out,
@@ -790,11 +810,10 @@ int tcw_trails(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, const uint6
     if (!c || !t || count < 0 || cap == 0 || (count > 0 && (!starts || !dp || !len))) return TCW_EINVAL;
     if (count == 0) return check_space(c, t->n, sp);
     Space s;
-    int rc = prepare_space(c, t, sp, s);
+    int rc = start_space(c, t, sp, s);
     if (rc) return rc;
     HIP_TRY(c, tcw::launch_trails(t->n, s.dev, starts, count, cap, dp, len, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    return TCW_OK;
+    return finish_space(c, s);
 }
 
 int tcw_start_points(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, int64_t w0, uint32_t j, int64_t count,
@@ -852,11 +871,10 @@ int tcw_claw_check(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, const u
     if (!c || !t || count < 0 || (count > 0 && (!u0 || !u1 || !ok || !perm || !sign))) return TCW_EINVAL;
     if (count == 0) return check_space(c, t->n, sp);
     Space s;
-    int rc = prepare_space(c, t, sp, s);
+    int rc = start_space(c, t, sp, s);
     if (rc) return rc;
-    HIP_TRY(c, tcw::exact_claw_check(s.S, sp->k, u0, u1, count, ok, perm, sign, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    return TCW_OK;
+    HIP_TRY(c, tcw::exact_claw_check(s.U, (uint32_t)sp->chunk, sp->k, s.made, u0, u1, count, ok, perm, sign, c->stream));
+    return finish_space(c, s);
 }
 
 // ---- walk sessions ----
@@ -884,9 +902,9 @@ int tcw_walk_begin(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, int64_t
     wd.claw_cap = 4096;
     hipError_t e = hipMalloc(&wd.states, (size_t)walks * sizeof(tcw::WalkState));
     if (e == hipSuccess) e = hipMalloc(&wd.table, ((size_t)1 << log2_table) * 16);
-    if (e == hipSuccess) e = hipMalloc(&wd.stats, tcw::ST_COUNT * sizeof(unsigned long long));
+    if (e == hipSuccess) e = hipMalloc(&wd.stats, (tcw::ST_COUNT + 1) * sizeof(unsigned long long));
     if (e == hipSuccess) e = hipMalloc(&wd.claws, (size_t)wd.claw_cap * 16);
-    if (e == hipSuccess) e = hipMalloc(&wd.claw_count, sizeof(unsigned long long));
+    wd.claw_count = wd.stats ? wd.stats + tcw::ST_COUNT : nullptr;
     if (e != hipSuccess) {
         delete w;
         return hip_fail(c, e, "walk session allocation");
@@ -916,11 +934,11 @@ int tcw_walk_run(tcw_walk* w, int iters) {
 int tcw_walk_stats_get(tcw_walk* w, tcw_walk_stats* out) {
     if (!w || !out) return TCW_EINVAL;
     tcw_ctx* c = w->ctx;
-    unsigned long long v[tcw::ST_COUNT];
-    unsigned long long cc = 0;
-    HIP_TRY(c, hipMemcpyAsync(v, w->wd.stats, sizeof(v), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(&cc, w->wd.claw_count, sizeof(cc), hipMemcpyDeviceToHost, c->stream));
+    const unsigned long long* v = reinterpret_cast<const unsigned long long*>(c->pinned);
+    static_assert((tcw::ST_COUNT + 1) * sizeof(*v) <= PINNED_BYTES, "the statistics fit the pinned buffer");
+    HIP_TRY(c, hipMemcpyAsync(c->pinned, w->wd.stats, (tcw::ST_COUNT + 1) * sizeof(*v), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const unsigned long long cc = v[tcw::ST_COUNT];
     out->claws_dropped = cc > w->wd.claw_cap ? (int64_t)(cc - w->wd.claw_cap) : 0;
     out->steps = (int64_t)v[tcw::ST_STEPS];
     out->dps = (int64_t)v[tcw::ST_DPS];
@@ -1129,7 +1147,8 @@ int check_pairs_ws(tcw_ctx* c, const Space& sp, const uint64_t* u0, const uint64
     HIP_TRY(c, ws.reserve(m, R));
     HIP_TRY(c, hipMemcpyAsync(ws.d0, u0, m * 8, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipMemcpyAsync(ws.d1, u1, m * 8, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, tcw::exact_claw_check(sp.S, sp.k, ws.d0, ws.d1, m, ws.ok, ws.perm, ws.sign, c->stream));
+    HIP_TRY(c, tcw::exact_claw_check(sp.U, (uint32_t)sp.chunk, sp.k, sp.made, ws.d0, ws.d1, m, ws.ok, ws.perm, ws.sign,
+                                     c->stream));
     std::vector<int32_t> ok(m), perm(m * R);
     std::vector<int8_t> sign(m * R);
     HIP_TRY(c, hipMemcpyAsync(ok.data(), ws.ok, m * 4, hipMemcpyDeviceToHost, c->stream));
@@ -2002,10 +2021,13 @@ struct BatchBuffers {
     int32_t* counts = nullptr;             // 5: items queued per qubit count
     int32_t* heads = nullptr;              // 5: queue positions (zeroed by a kernel at the start of a round)
     int32_t* restart = nullptr;            // count: slots restarted before the next round
+    int32_t* made = nullptr;               // count x 2: SpaceJob::out of each member's space
+    tcw::SpaceJob* jobs = nullptr;         // count
     std::vector<int32_t> pending;          // host: members whose restart waits for the next round
+    std::vector<int32_t> unmade;           // host: members whose space the device has to make before it
     ~BatchBuffers() {
         for (void* q : {(void*)stats, (void*)claw_count, (void*)claws, (void*)sps, (void*)wds, (void*)counts,
-                        (void*)heads, (void*)restart})
+                        (void*)heads, (void*)restart, (void*)made, (void*)jobs})
             if (q) (void)hipFree(q);
         for (auto* q : items)
             if (q) (void)hipFree(q);
@@ -2026,6 +2048,30 @@ void free_walk_buffers(tcw_ctx* c, BatchTarget& b) {
 // Queued and done for every pending member in one launch on the batch stream before the next round
 // (k_member_restart), after that round's descriptors are on the device.
 void batch_restart(BatchBuffers& bb, int slot) { bb.pending.push_back(slot); }
+
+// The spaces that members have moved to, made in one go per qubit count (a depth's chunks open together),
+// and their answers read back.
+int batch_make_spaces(tcw_ctx* c, std::vector<BatchTarget>& bt, BatchBuffers& bb) {
+    if (bb.unmade.empty()) return TCW_OK;
+    std::vector<tcw::SpaceJob> jobs;
+    jobs.reserve(bb.unmade.size());
+    int from[6] = {0, 0, 0, 0, 0, 0};  // jobs of qubit count n: from[n] .. from[n + 1] - 1
+    for (int n = 1; n <= 4; ++n) {
+        for (const int32_t i : bb.unmade)
+            if (bt[i].t->n == n) jobs.push_back(bt[i].space->job());
+        from[n + 1] = (int)jobs.size();
+    }
+    HIP_TRY(c, hipMemcpyAsync(bb.jobs, jobs.data(), jobs.size() * sizeof(tcw::SpaceJob), hipMemcpyHostToDevice, c->stream));
+    for (int n = 1; n <= 4; ++n)
+        HIP_TRY(c, tcw::spaces_make(n, tcw::SpaceJob{}, bb.jobs + from[n], from[n + 1] - from[n], c->stream));
+    std::vector<int32_t> made(2 * bt.size());
+    HIP_TRY(c, hipMemcpyAsync(made.data(), bb.made, made.size() * 4, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    for (const int32_t i : bb.unmade)
+        if (int rc = accept_space(c, *bt[i].space, &made[2 * i])) return rc;
+    bb.unmade.clear();
+    return TCW_OK;
+}
 
 // A verified decomposition of member b (in b.res).  TCW_ORDER_GIVEN then searches the depths below it
 // not yet searched, in increasing order (the first further hit is the lowest); otherwise b is done.
@@ -2135,7 +2181,8 @@ int batch_advance(tcw_ctx* c, BatchTarget& b, int slot, BatchBuffers& bb, double
             b.space->pooled = true;
         }
         tcw_space sp{b.k, b.chunk, b.p.seed, b.p.version, delta};
-        if ((rc = prepare_space(c, b.t, &sp, *b.space))) return rc;
+        if ((rc = setup_space(c, b.t, &sp, *b.space, bb.made + 2 * slot))) return rc;
+        bb.unmade.push_back(slot);
         b.res->spaces++;
         b.res->versions++;
         b.version = b.p.version;
@@ -2248,6 +2295,9 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
     HIP_TRY(c, hipMalloc(&bb.counts, 5 * 4));
     HIP_TRY(c, hipMalloc(&bb.heads, 5 * 4));
     HIP_TRY(c, hipMalloc(&bb.restart, (size_t)count * 4));
+    HIP_TRY(c, hipMalloc(&bb.made, (size_t)count * 2 * 4));
+    HIP_TRY(c, hipMalloc(&bb.jobs, (size_t)count * sizeof(tcw::SpaceJob)));
+    HIP_TRY(c, hipMemsetAsync(bb.made, 0, (size_t)count * 2 * 4, c->stream));
     HIP_TRY(c, hipMemsetAsync(bb.stats, 0, (size_t)count * tcw::ST_COUNT * 8, c->stream));
     HIP_TRY(c, hipMemsetAsync(bb.claw_count, 0, (size_t)count * 8, c->stream));
     HIP_TRY(c, hipMemsetAsync(bb.counts, 0, 5 * 4, c->stream));
@@ -2265,6 +2315,7 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
         rc = batch_advance(c, bt[i], i, bb, t0, false);
         if (bt[i].done) bt[i].res->seconds = now_s() - t0;
     }
+    if (!rc) rc = batch_make_spaces(c, bt, bb);
     if (rc) {
         (void)hipStreamSynchronize(c->stream);
         for (auto& b : bt) free_walk_buffers(c, b);
@@ -2370,6 +2421,7 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
             stop->stopped = true;
             break;
         }
+        BATCH_RC(batch_make_spaces(c, bt, bb));
         if (dirty) {
             // the queues: every walking member that is not held, in slices of its walks.  A qubit count's
             // queue holds about four items per block of its grid, shared out by walks, so an item spans
@@ -2480,17 +2532,17 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
             walk_seconds += now_s() - tl;
             if (stop && stop->launches) (*stop->launches)++;
             // enumerated members whose last point is done: read out their candidates
-            bool formed = false;
+            std::vector<int32_t> whole;
             for (int i = 0; i < count; ++i) {
                 BatchTarget& b = bt[i];
                 if (!queued[i] || !b.wd.enumerate) continue;
-                if (stats[(size_t)i * tcw::ST_COUNT + tcw::ST_STEPS] >= b.budget) {
-                    BATCH_TRY(tcw::launch_enum_pairs(b.wd, gs[0]));
-                    formed = true;
-                }
+                if (stats[(size_t)i * tcw::ST_COUNT + tcw::ST_STEPS] >= b.budget) whole.push_back(i);
             }
-            if (formed)
+            if (!whole.empty()) {
+                BATCH_TRY(hipMemcpyAsync(bb.restart, whole.data(), whole.size() * 4, hipMemcpyHostToDevice, gs[0]));
+                BATCH_TRY(tcw::launch_member_pairs(bb.wds, bb.restart, (int)whole.size(), gs[0]));
                 BATCH_TRY(hipMemcpyAsync(stats.data(), bb.stats, stats.size() * 8, hipMemcpyDeviceToHost, gs[0]));
+            }
             BATCH_TRY(hipMemcpyAsync(ccount.data(), bb.claw_count, count * 8, hipMemcpyDeviceToHost, gs[0]));
             BATCH_TRY(hipStreamSynchronize(gs[0]));
         }

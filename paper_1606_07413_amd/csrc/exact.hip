@@ -404,18 +404,20 @@ __device__ inline void rotate_rows(T (*a)[RowGeo<NQ>::CPL], T (*b)[RowGeo<NQ>::C
 // the side-1 point, D = W V^T must be a signed permutation (Sec. 3, last merge case).
 //   D = S R(q_0)^T ... R(q_{h-1})^T R(p_{h-1})^T ... R(p_0)^T
 // is S under 2h rotations from the right, so no dense product is formed: one block per pair, its 16
-// wavefronts each take rows of S through the rotations in registers, unreduced, at exponent
-// E = e_S + 2h.  S has int8 entries and orthonormal rows, so e_S <= log2(3 R 127^2) and every value,
-// bounded by 2^(E/2), stays below 2^16 at n >= 3 and 2^29 at n <= 2.  A row must hold one unit entry
+// wavefronts each take rows of U through the rotations in registers (R(c)^T of the chunk first, at odd
+// k), unreduced, at exponent E = e_U + k mod 2 + 2h.  S has int8 entries and orthonormal rows, so
+// e_S <= log2(3 R 127^2), e_U <= e_S + 1 and every value, bounded by 2^(E/2), stays below 2^17 at n >= 3
+// and 2^30 at n <= 2.  A row must hold one unit entry
 // and the columns must differ; the first row that does not ends the pair.  Bound by the butterflies
 // (2 h R^2 of them).  256 pairs at n = 4, k = 7, half of them claws: 0.14 ms the whole call; the
 // dense product W V^T it replaces (R^3 64-bit products a pair, 16 blocks) took 244 ms.
 constexpr int CLAW_WAVES = 16;
 template <int NQ, typename T>
 __global__ __launch_bounds__(CLAW_WAVES * 64) void k_claw(const T* __restrict__ sa, const T* __restrict__ sb,
-                                                          const int32_t* se, int k, const uint64_t* u0,
-                                                          const uint64_t* u1, int64_t count, int32_t* ok, int32_t* perm,
-                                                          int8_t* sign) {
+                                                          const int32_t* se, uint32_t c, int k, const int32_t* made,
+                                                          const uint64_t* u0, const uint64_t* u1, int64_t count,
+                                                          int32_t* ok, int32_t* perm, int8_t* sign) {
+    if (made[1] != 0) return;
     using Gm = RowGeo<NQ>;
     constexpr int R = Gm::R, CPL = Gm::CPL;
     constexpr uint32_t XI = R - 1;
@@ -428,7 +430,8 @@ __global__ __launch_bounds__(CLAW_WAVES * 64) void k_claw(const T* __restrict__ 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int gi = lane / Gm::G, gl = lane % Gm::G, gbase = gi * Gm::G;
     const int h = k / 2;
-    const int E = *se + 2 * h;
+    const int first = c ? 1 : 0, steps = first + 2 * h;
+    const int E = *se + steps;
     const T unit = (T)1 << (E / 2);
     for (int64_t pi = blockIdx.x; pi < count; pi += gridDim.x) {
         uint64_t p0 = u0[pi], p1 = u1[pi];
@@ -437,14 +440,15 @@ __global__ __launch_bounds__(CLAW_WAVES * 64) void k_claw(const T* __restrict__ 
         }
         const bool sides_ok = (((p0 >> 32) & 1) == 0) && (((p1 >> 32) & 1) == 1);
         if (threadIdx.x == 0) {
+            seq[0] = (uint16_t)c;
             uint32_t x = (uint32_t)p1;
             for (int t = 0; t < h; ++t) {
-                seq[t] = (uint16_t)(x % XI + 1);
+                seq[first + t] = (uint16_t)(x % XI + 1);
                 x /= XI;
             }
             x = (uint32_t)p0;
             for (int t = 0; t < h; ++t) {
-                seq[2 * h - 1 - t] = (uint16_t)(x % XI + 1);
+                seq[steps - 1 - t] = (uint16_t)(x % XI + 1);
                 x /= XI;
             }
             bad = sides_ok ? 0 : 1;
@@ -465,7 +469,7 @@ __global__ __launch_bounds__(CLAW_WAVES * 64) void k_claw(const T* __restrict__ 
                     a[i][j] = row < R ? sa[at] : 0;
                     b[i][j] = row < R ? sb[at] : 0;
                 }
-            for (int t = 0; t < 2 * h; ++t)
+            for (int t = 0; t < steps; ++t)
                 rotate_rows<NQ, NB, T>(a, b, (uint32_t)__builtin_amdgcn_readfirstlane(seq[t]), true, gl, gbase);
             bool row_ok = true;
 #pragma unroll
@@ -931,44 +935,14 @@ __device__ inline void or_entries(T oa, T ob, unsigned long long* ors) {
     }
 }
 
-constexpr int ROT1_THREADS = 1024;
+// (a, b) at exponent `grown`, reduced in place; *e_io = the exponent left.
 template <int NQ, typename T>
-__global__ __launch_bounds__(ROT1_THREADS) void k_rotate1(T* a, T* b, const T* sa, const T* sb, uint32_t p,
-                                                         int transposed, int* flag, unsigned long long* ors) {
+__global__ __launch_bounds__(256) void k_reduce(T* a, T* b, int32_t* e_io, int grown, const unsigned long long* ors) {
     constexpr int R = EGeo<NQ>::R;
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    T va = 0, vb = 0;
-    if (idx < R * R) {
-        const uint32_t q = idx & (R - 1);
-        const int row = idx - (int)q;
-        if (anticommutes<NQ>(p, q)) {
-            int sg = rotation_sign<NQ>(p, q);
-            if (transposed) sg = -sg;
-            const int j = row + (int)(q ^ p);
-            va = sg > 0 ? sa[idx] + sa[j] : sa[idx] - sa[j];
-            vb = sg > 0 ? sb[idx] + sb[j] : sb[idx] - sb[j];
-        } else {
-            va = sb[idx] * 2;
-            vb = sa[idx];
-        }
-        const T lim = lim_of<T>();
-        if (va > lim || va < -lim || vb > lim || vb < -lim) atomicOr(flag, 4);
-        a[idx] = va;
-        b[idx] = vb;
-    }
-    or_entries<T, ROT1_THREADS / 64>(va, vb, ors);
-}
-
-// (a, b) at exponent *se (0 if null) + grown, reduced in place; *e_io = the exponent left.
-template <int NQ, typename T>
-__global__ __launch_bounds__(256) void k_reduce(T* a, T* b, int32_t* e_io, const int32_t* se, int grown,
-                                               const unsigned long long* ors) {
-    constexpr int R = EGeo<NQ>::R;
-    const int e1 = (se ? *se : 0) + grown;
-    const int m = reduction_steps((T)ors[0], (T)ors[1], e1);
+    const int m = reduction_steps((T)ors[0], (T)ors[1], grown);
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx < R * R && m > 0) reduce_entry(a[idx], b[idx], m);
-    if (idx == 0) *e_io = e1 - m;
+    if (idx == 0) *e_io = grown - m;
 }
 
 // A target from its words (m Clifford factors, then its rotations, as they are multiplied from the right):
@@ -1023,6 +997,126 @@ __global__ void k_clear_ors(unsigned long long* ors) {
     if (threadIdx.x < 2) ors[threadIdx.x] = 0;
 }
 
+// ---- search spaces (SpaceJob) ----
+// Entry (row, q) of U R(c)^T, unreduced; c = 0: of U.
+template <int NQ, typename T>
+__device__ inline void chunk_entry(const T* a, const T* b, uint32_t c, int row, uint32_t q, T& va, T& vb) {
+    constexpr int R = EGeo<NQ>::R;
+    const int at = row * R + (int)q;
+    va = a[at];
+    vb = b[at];
+    if (c == 0) return;
+    if (anticommutes<NQ>(c, q)) {
+        const int j = row * R + (int)(q ^ c);
+        const bool plus = rotation_sign<NQ>(c, q) < 0;  // transposed
+        va += plus ? a[j] : -a[j];
+        vb += plus ? b[j] : -b[j];
+    } else {
+        const T x = va;
+        va = 2 * vb;
+        vb = x;
+    }
+}
+
+// The int8 packing of S_c (the layouts of k_pack_phi) and the keys, by threads i, i + stride, ... of a job.
+template <int NQ, typename T>
+__device__ void space_pack(const SpaceJob& J, T or_a, T or_b, int i, int stride) {
+    constexpr int R = EGeo<NQ>::R;
+    constexpr int Q4 = R / 4;
+    const T *a = (const T*)J.a, *b = (const T*)J.b;
+    const int e1 = *J.e + (J.c ? 1 : 0);
+    // a target is held reduced, so only a rotation's product has steps to take
+    const int m = J.c ? reduction_steps(or_a, or_b, e1) : 0;
+    int flags = 0;
+    const T lim = lim_of<T>();
+    auto entry = [&](int row, uint32_t q, bool second, T& v) {
+        T va, vb;
+        chunk_entry<NQ, T>(a, b, J.c, row, q, va, vb);
+        if (J.c && (va > lim || va < -lim || vb > lim || vb < -lim)) flags |= 4;
+        if (m > 0) reduce_entry(va, vb, m);
+        v = second ? vb : va;
+        if (v > 127 || v < -127) flags |= 2;
+    };
+    for (int idx = i; idx < 2 * Q4 * R; idx += stride) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            T v;
+            if constexpr (NQ >= 3) {
+                constexpr int KK = 2 * R / 64;
+                const int fi = idx >> 2, l = fi & 63, fk = fi >> 6;
+                const int qq = (fk % KK) * 64 + (l >> 4) * 16 + 4 * (idx & 3) + c;
+                entry((fk / KK) * 16 + (l & 15), (uint32_t)(qq & (R - 1)), qq >= R, v);
+            } else {
+                const int x = idx % (Q4 * R);
+                entry(x % R, (uint32_t)(4 * (x / R) + c), idx >= Q4 * R, v);
+            }
+            word |= ((uint32_t)(uint8_t)(int8_t)v) << (8 * c);
+        }
+        J.phi[idx] = word;
+    }
+    if (flags) atomicOr(&J.out[1], flags);
+    const uint64_t s0 = sm64(J.seed, 0);
+    for (int q = i; q < R; q += stride) {
+        uint64_t k = sm64(s0, (uint64_t)q) >> 3;
+        if (k >= P61) k -= P61;
+        J.keys[q] = k;
+    }
+    if (i == 0) J.out[0] = e1 - m;
+}
+
+// n <= 3: one block per job
+template <int NQ, typename T>
+__global__ __launch_bounds__(1024) void k_space(SpaceJob one, const SpaceJob* many) {
+    constexpr int R = EGeo<NQ>::R;
+    const SpaceJob J = many ? many[blockIdx.x] : one;
+    __shared__ unsigned long long ors[2];
+    if (threadIdx.x < 2) ors[threadIdx.x] = 0;
+    if (threadIdx.x == 0) J.out[1] = 0;
+    __syncthreads();
+    if (J.c) {
+        T oa = 0, ob = 0;
+        for (int idx = threadIdx.x; idx < R * R; idx += blockDim.x) {
+            T va, vb;
+            chunk_entry<NQ, T>((const T*)J.a, (const T*)J.b, J.c, idx / R, (uint32_t)(idx & (R - 1)), va, vb);
+            oa |= va;
+            ob |= vb;
+        }
+        if (oa) atomicOr(&ors[0], (unsigned long long)oa);
+        if (ob) atomicOr(&ors[1], (unsigned long long)ob);
+    }
+    __syncthreads();
+    space_pack<NQ, T>(J, (T)ors[0], (T)ors[1], (int)threadIdx.x, (int)blockDim.x);
+}
+
+// n = 4: 32 blocks per job in each of two passes (blockIdx.y: the job)
+constexpr int SPACE_BLOCKS = 32;
+__global__ void k_space_clear(SpaceJob one, const SpaceJob* many, int count) {
+    for (int i = threadIdx.x; i < count; i += blockDim.x) {
+        const SpaceJob J = many ? many[i] : one;
+        J.ors[0] = J.ors[1] = 0;
+        J.out[1] = 0;
+    }
+}
+__global__ __launch_bounds__(1024) void k_space_or4(SpaceJob one, const SpaceJob* many) {
+    constexpr int R = 256;
+    const SpaceJob J = many ? many[blockIdx.y] : one;
+    if (J.c == 0) return;
+    int32_t oa = 0, ob = 0;
+    for (int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x); idx < R * R; idx += SPACE_BLOCKS * (int)blockDim.x) {
+        int32_t va, vb;
+        chunk_entry<4, int32_t>((const int32_t*)J.a, (const int32_t*)J.b, J.c, idx / R, (uint32_t)(idx & (R - 1)), va, vb);
+        oa |= va;
+        ob |= vb;
+    }
+    or_entries<int32_t, 16>(oa, ob, J.ors);
+}
+__global__ __launch_bounds__(1024) void k_space_pack4(SpaceJob one, const SpaceJob* many) {
+    const SpaceJob J = many ? many[blockIdx.y] : one;
+    space_pack<4, int32_t>(J, (int32_t)J.ors[0], (int32_t)J.ors[1], (int)(blockIdx.x * blockDim.x + threadIdx.x),
+                           SPACE_BLOCKS * (int)blockDim.x);
+}
+
 __global__ void k_seq_one(uint16_t* seq, uint8_t* tr, uint16_t p, uint8_t t) {
     if (threadIdx.x == 0) {
         seq[0] = p;
@@ -1034,20 +1128,24 @@ __global__ void k_fill_i32(int* dst, int v, int count) {
 }
 }  // namespace
 
-hipError_t exact_rotate1(ExactDev& dst, const ExactDev& src, uint32_t p, int transposed, uint64_t* ors, int* flag,
-                         hipStream_t s) {
-    if (dst.a == src.a || dst.b == src.b) return hipErrorInvalidValue;
-    unsigned long long* o = reinterpret_cast<unsigned long long*>(ors);
-    hipLaunchKernelGGL(k_clear_ors, dim3(1), dim3(64), 0, s, o);
-    auto f = [&]<int NQ, typename T>() -> hipError_t {
-        constexpr int R = EGeo<NQ>::R;
-        hipLaunchKernelGGL((k_rotate1<NQ, T>), dim3((R * R + ROT1_THREADS - 1) / ROT1_THREADS), dim3(ROT1_THREADS), 0, s,
-                           (T*)dst.a, (T*)dst.b, (const T*)src.a, (const T*)src.b, p, transposed, flag, o);
-        hipLaunchKernelGGL((k_reduce<NQ, T>), dim3((R * R + 255) / 256), dim3(256), 0, s, (T*)dst.a, (T*)dst.b, dst.e,
-                           src.e, 1, o);
+hipError_t spaces_make(int n, const SpaceJob& one, const SpaceJob* many, int count, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    if (n == 4) {
+        hipLaunchKernelGGL(k_space_clear, dim3(1), dim3(many ? 256 : 64), 0, s, one, many, count);
+        if (many || one.c)
+            hipLaunchKernelGGL(k_space_or4, dim3(SPACE_BLOCKS, count), dim3(1024), 0, s, one, many);
+        hipLaunchKernelGGL(k_space_pack4, dim3(SPACE_BLOCKS, count), dim3(1024), 0, s, one, many);
         return hipGetLastError();
+    }
+    auto f = [&]<int NQ, typename T>() -> hipError_t {
+        if constexpr (NQ <= 3) {
+            hipLaunchKernelGGL((k_space<NQ, T>), dim3(count), dim3(NQ == 3 ? 1024 : 256), 0, s, one, many);
+            return hipGetLastError();
+        } else {
+            return hipErrorInvalidValue;
+        }
     };
-    return dispatch_exact(dst.n, f);
+    return dispatch_exact(n, f);
 }
 
 hipError_t exact_seq_one(uint16_t* seq, uint8_t* tr, uint16_t p, uint8_t transpose, hipStream_t s) {
@@ -1075,7 +1173,7 @@ hipError_t exact_words(ExactDev& dst, const uint16_t* clifford, int m, const uin
         hipLaunchKernelGGL((k_words<NQ, T>), dim3((R + rows - 1) / rows), dim3(WORDS_WAVES * 64), 0, s, w, m, k,
                            (T*)dst.a, (T*)dst.b, o);
         hipLaunchKernelGGL((k_reduce<NQ, T>), dim3((R * R + 255) / 256), dim3(256), 0, s, (T*)dst.a, (T*)dst.b, dst.e,
-                           (const int32_t*)nullptr, k, o);
+                           k, o);
         return hipGetLastError();
     };
     return dispatch_exact(dst.n, f);
@@ -1155,16 +1253,16 @@ hipError_t exact_pack_phi(const ExactDev& m, uint32_t* phi, int* flag, hipStream
     return dispatch_exact(m.n, f);
 }
 
-hipError_t exact_claw_check(const ExactDev& S, int k, const uint64_t* u0, const uint64_t* u1, int64_t count, int32_t* ok,
-                            int32_t* perm, int8_t* sign, hipStream_t s) {
+hipError_t exact_claw_check(const ExactDev& U, uint32_t c, int k, const int32_t* made, const uint64_t* u0,
+                            const uint64_t* u1, int64_t count, int32_t* ok, int32_t* perm, int8_t* sign, hipStream_t s) {
     if (count <= 0) return hipSuccess;
     auto f = [&]<int NQ, typename T>() -> hipError_t {
         const int blocks = (int)(count < 4096 ? count : 4096);
-        hipLaunchKernelGGL((k_claw<NQ, T>), dim3(blocks), dim3(CLAW_WAVES * 64), 0, s, (const T*)S.a, (const T*)S.b,
-                           S.e, k, u0, u1, count, ok, perm, sign);
+        hipLaunchKernelGGL((k_claw<NQ, T>), dim3(blocks), dim3(CLAW_WAVES * 64), 0, s, (const T*)U.a, (const T*)U.b,
+                           U.e, c, k, made, u0, u1, count, ok, perm, sign);
         return hipGetLastError();
     };
-    return dispatch_exact(S.n, f);
+    return dispatch_exact(U.n, f);
 }
 
 }  // namespace tcw

@@ -14,6 +14,7 @@ struct SpaceDev {
     int32_t h;          // rotations per half
     int32_t delta;      // theta = 2^-delta
     int32_t rot_e;      // (30 * e_S) mod 61: multiplication by phi(1/sqrt2)^e_S in Z/p
+    const int32_t* made;   // tcw_step, tcw_trails: SpaceJob::out, read on the device instead of rot_e (else null)
     uint64_t salt_h;    // matrix-hash salt
     uint64_t salt_d;    // distinguished-point salt
     uint64_t salt_s;    // trail-start salt
@@ -66,6 +67,22 @@ struct WalkDev {
     uint32_t claw_cap;
 };
 
+// One space to be made from a target on the device: S_c = U R(c)^T (c = 0: U itself) packed as int8 for
+// the walk step, the row-digest keys, and out = {exponent of S_c, flags}: 4 an exact value out of range,
+// 2 an entry of S_c outside int8.  S_c itself is not kept (the claw check starts from U).
+struct SpaceJob {
+    const void* a;       // U (ExactDev)
+    const void* b;
+    const int32_t* e;
+    uint64_t seed;
+    uint32_t* phi;
+    uint64_t* keys;
+    unsigned long long* ors;  // two words of scratch
+    int32_t* out;
+    uint32_t c;
+    uint32_t pad;
+};
+
 // ---- launchers (exact.hip) ----
 // Exact matrices live on the device as int32 pairs (int64 for n <= 2) with exponent e.
 struct ExactDev {
@@ -89,11 +106,9 @@ hipError_t exact_apply(ExactDev& dst, const ExactDev& src, const uint16_t* seq_d
 // synchronisation
 hipError_t exact_apply_ws(ExactDev& dst, const ExactDev& src, const uint16_t* seq, const uint8_t* tr, int nseq,
                           void* ta, void* tb, int* flag, hipStream_t s);
-// dst = src * R(p)^(T if transposed), reduced, for dst distinct from src: the result of exact_apply
-// with a one-rotation word, on many blocks and without work matrices; ors is two device uint64 of
-// scratch.  No synchronisation.
-hipError_t exact_rotate1(ExactDev& dst, const ExactDev& src, uint32_t p, int transposed, uint64_t* ors, int* flag,
-                         hipStream_t s);
+// the spaces of `count` jobs of n-qubit targets: the job `one` (host), or with many != null that device
+// array.  No synchronisation; the flags are in each job's out.
+hipError_t spaces_make(int n, const SpaceJob& one, const SpaceJob* many, int count, hipStream_t s);
 // dst = R(C_1)^2 ... R(C_m)^2 R(rotations[0]) ... R(rotations[k - 1]), reduced: the result of exact_build, for
 // words (host) that exact_words_fit: at most 56 rotations and 1024 Paulis.  No synchronisation.
 bool exact_words_fit(int m, int k);
@@ -118,9 +133,11 @@ hipError_t exact_check_orthogonal(const ExactDev& m, int* flag_dev, hipStream_t 
 hipError_t exact_signed_perm(const ExactDev& m, int32_t* ok_dev, int32_t* perm_dev, int8_t* sign_dev, hipStream_t s);
 // int8 packing of S for the walk kernels; flag |= 2 if a value is outside [-127, 127]
 hipError_t exact_pack_phi(const ExactDev& m, uint32_t* phi_dev, int* flag_dev, hipStream_t s);
-// claw checks: for each pair (u0, u1) D = W V^T exactly (S's entries within int8, as exact_pack_phi checks)
-hipError_t exact_claw_check(const ExactDev& S, int k, const uint64_t* u0, const uint64_t* u1, int64_t count, int32_t* ok,
-                            int32_t* perm, int8_t* sign, hipStream_t s);
+// claw checks: for each pair (u0, u1) D = W V^T exactly, from the target U and the chunk c (0 for even k).
+// made: the space's SpaceJob::out; nothing is written where its flags are set (the entries of S_c have to
+// be within int8).
+hipError_t exact_claw_check(const ExactDev& U, uint32_t c, int k, const int32_t* made, const uint64_t* u0,
+                            const uint64_t* u1, int64_t count, int32_t* ok, int32_t* perm, int8_t* sign, hipStream_t s);
 // canonical FP32 features (n <= 3)
 hipError_t exact_features(const ExactDev& m, float* out_dev, hipStream_t s);
 // many targets from words: phi (n <= 3 int8 layout), rot_e, features; flag |= 2 / 4 / 8 on range errors
@@ -171,6 +188,8 @@ hipError_t launch_member_restart(const SpaceDev* sps, const WalkDev* wds, const 
                                  hipStream_t s);
 // enumeration mode, after the last point: one claw candidate per key reached from both sides
 hipError_t launch_enum_pairs(const WalkDev& wd, hipStream_t s);
+// the same for batch members slots[0..count) (descriptors and slots on the device) in one launch
+hipError_t launch_member_pairs(const WalkDev* wds, const int32_t* slots, int count, hipStream_t s);
 int walk_grid_blocks(int n, int device, bool queue, int64_t walks);
 hipError_t pack_phi_i32(int n, const int32_t* a, const int32_t* b, int64_t count, uint32_t* phi_out,
                         int* flag_dev, hipStream_t s);

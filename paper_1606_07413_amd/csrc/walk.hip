@@ -798,11 +798,20 @@ struct WalkWaves {
 };
 
 // ---- parity kernels ----
+// A space that was made just before on the stream: its exponent read here, and nothing done where its
+// flags refuse it (the host reads them afterwards).
+__device__ inline bool space_ready(SpaceDev& sp) {
+    if (sp.made == nullptr) return true;
+    sp.rot_e = (int32_t)((30u * (uint32_t)sp.made[0]) % 61u);
+    return sp.made[1] == 0;
+}
+
 template <int NQ, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_step(SpaceDev sp, const uint64_t* in, uint64_t* out,
                                                      uint64_t* hash, int64_t count) {
     using Gm = Geo<NQ>;
     __shared__ Lds<NQ, WAVES> L;
+    if (!space_ready(sp)) return;
     load_lds(L, sp);
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -827,6 +836,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_trails(SpaceDev sp, const uint64
                                                        uint32_t cap, uint64_t* dp, uint32_t* len) {
     using Gm = Geo<NQ>;
     __shared__ Lds<NQ, WAVES> L;
+    if (!space_ready(sp)) return;
     load_lds(L, sp);
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1540,11 +1550,10 @@ __global__ void k_table_clear(uint64_t* table, uint64_t slots, uint64_t value) {
 
 // After an exhaustive pass (enumeration mode): every key reached from both sides gives one
 // candidate, the least x of side 0 against the least x of side 1.
-__global__ void k_enum_pairs(WalkDev wd) {
+__device__ inline void enum_pairs(const WalkDev& wd, uint64_t first, uint64_t stride) {
     const uint64_t slots = 1ull << wd.log2_table;
     unsigned long long found = 0;
-    for (uint64_t i = threadIdx.x + (uint64_t)blockIdx.x * blockDim.x; i < slots;
-         i += (uint64_t)blockDim.x * gridDim.x) {
+    for (uint64_t i = first; i < slots; i += stride) {
         if (wd.table[2 * i] == EMPTY_KEY) continue;
         const uint64_t v = wd.table[2 * i + 1];
         const uint32_t x0 = (uint32_t)v, x1 = (uint32_t)(v >> 32);
@@ -1557,6 +1566,14 @@ __global__ void k_enum_pairs(WalkDev wd) {
         }
     }
     if (found) atomicAdd(&wd.stats[ST_CLAWS], found);
+}
+__global__ void k_enum_pairs(WalkDev wd) {
+    enum_pairs(wd, threadIdx.x + (uint64_t)blockIdx.x * blockDim.x, (uint64_t)blockDim.x * gridDim.x);
+}
+// the same for batch member slots[blockIdx.x / RESTART_PER], RESTART_PER blocks each
+__global__ __launch_bounds__(256) void k_member_pairs(const WalkDev* wds, const int32_t* slots) {
+    const WalkDev wd = wds[slots[blockIdx.x / RESTART_PER]];
+    enum_pairs(wd, (uint64_t)(blockIdx.x % RESTART_PER) * blockDim.x + threadIdx.x, (uint64_t)RESTART_PER * blockDim.x);
 }
 
 // ---- meet-in-the-middle labels for the depth-order network ----
@@ -2065,6 +2082,12 @@ hipError_t launch_table_clear(uint64_t* table, int log2_table, uint64_t value, h
     uint64_t blocks = (slots + 255) / 256;
     if (blocks > 65535) blocks = 65535;
     hipLaunchKernelGGL(k_table_clear, dim3((unsigned)blocks), dim3(256), 0, s, table, slots, value);
+    return hipGetLastError();
+}
+
+hipError_t launch_member_pairs(const WalkDev* wds, const int32_t* slots, int count, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_member_pairs, dim3((unsigned)(count * RESTART_PER)), dim3(256), 0, s, wds, slots);
     return hipGetLastError();
 }
 

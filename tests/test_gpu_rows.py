@@ -158,3 +158,54 @@ def test_target_words_edges(ctx, n, k, m):
         with pytest.raises(tcw.TcwError) as err:     # beyond int32 on the way
             ctx.target_from_words(n, seeded_inputs.target_words(n, 90, 71).paulis, clifford)
         assert err.value.code == tcw.TCW_EOVERFLOW
+
+
+# a step's space made from the target: even and odd k, the smallest and the last chunk, a chunk that lowers the
+# exponent and one that raises it; and the refusal of entries beyond int8 with nothing written
+@pytest.mark.parametrize("n,k", [(1, 1), (1, 6), (2, 1), (2, 4), (2, 7), (3, 3), (3, 6), (3, 7), (4, 1), (4, 2), (4, 5)])
+def test_spaces_of_chunks(ctx, n, k):
+    import torch
+    from paper_1606_07413_amd import tcw
+    tw, u = oracle_target(n, k, 200 + n)
+    tgt = ctx.target_from_words(n, tw.paulis, tw.clifford)
+    for chunk in ([1, 4 ** n - 1, tw.paulis[0]] if k % 2 else [0]):
+        print("space", n, k, chunk, flush=True)
+        spec = owalk.make_spec(u, n, k, chunk, 5, delta=3)
+        pts = seeded_inputs.random_points(spec.n_half, 5, 8) + [0, 1 << 32, spec.n_half - 1, (1 << 32) + spec.n_half - 1]
+        pin = torch.tensor(pts, dtype=torch.int64, device="cuda:0")
+        out, hh = torch.empty_like(pin), torch.empty_like(pin)
+        ctx.step(tgt, k, chunk, 5, 3, pin, out, hh)
+        want = [owalk.f_with_hash(spec, p) for p in pts]
+        mask = (1 << 64) - 1
+        assert [int(v) & mask for v in out.cpu().tolist()] == [w[0] for w in want]
+        assert [int(v) & mask for v in hh.cpu().tolist()] == [w[1] for w in want]
+    big = ctx.target_from_words(n, [1 + (5 * i) % 3 for i in range(20)], [])
+    if n == 1:
+        pin = torch.zeros(3, dtype=torch.int64, device="cuda:0")
+        out = torch.full_like(pin, 77)
+        with pytest.raises(tcw.TcwError) as err:
+            ctx.step(big, 3, 1, 5, 3, pin, out)
+        assert err.value.code == tcw.TCW_EOVERFLOW and out.cpu().tolist() == [77] * 3
+
+
+def test_batch_opens_chunks_together(ctx):
+    """Targets of every n in one batch (their spaces are made together per qubit count), exhaustively: the answers of
+    the single searches."""
+    from paper_1606_07413_amd import tcw
+    tws = [seeded_inputs.target_words(n, k, 40 + n) for n, k in ((1, 3), (2, 3), (2, 4), (3, 3), (3, 4), (4, 2))]
+    tgts = [ctx.target_from_words(t.n, t.paulis, t.clifford) for t in tws]
+    ps = []
+    for t in tws:
+        p = ctx.default_params(t.n)
+        p.k_max, p.enum_max = t.k, 1 << 20
+        ps.append(p)
+    res, _ = ctx.search_batch(tgts, ps)
+    for t, tgt, p, r in zip(tws, tgts, ps, res):
+        for par in (0, 1, 5):
+            p.chunk_parallel = par
+            one = ctx.search(tgt, p)
+            print("batch", t.n, t.k, par, one.t, flush=True)
+            assert (one.status, one.t, one.minimal) == (1, r.t, 1) and r.status == 1
+            dec = tcw.decomposition_of(one)
+            got = osearch.Decomposition(t=dec.t, paulis_desc=dec.paulis_desc, perm=dec.perm, sign=dec.sign)
+            assert osearch.reconstruct(t.n, got).equals(zmat.target_from_words(t.n, t.paulis, t.clifford))
