@@ -59,7 +59,7 @@ struct Lds {
 // n = 4: S_c as MFMA B-operand fragments.  With K stacked as [A | B] (512 columns), fragment
 // (nt, kk) holds, for lane l, the 16 bytes S''[nt*16 + l%16][kk*64 + (l/16)*16 + 0..15] where
 // S''[r][q] = A[r][q] for q < 256 and B[r][q - 256] otherwise; one ds_read_b128 per lane per MFMA.
-// Per walk: digit rows [8][68] (signed base-256 digits of the rotated key vector, 4 columns per
+// Per wavefront: digit rows [4][68] (signed base-256 digits of the rotated key vector, 4 columns per
 // dword; the row stride of 68 dwords keeps the MFMA A-operand reads free of bank conflicts).
 constexpr int N4_NT = 16, N4_KK = 8, N4_ROW = 68;
 constexpr int N4_DIG = 8;  // signed base-256 digits of a residue below 2^62
@@ -67,8 +67,7 @@ template <int WAVES>
 struct Lds<4, WAVES> {
     v4i frag[N4_NT * N4_KK * 64];
     uint64_t K[256];
-    uint32_t limbs[WAVES][N4_DIG * N4_ROW];
-    alignas(16) uint32_t zero_row[N4_ROW];  // A-operand rows 8..15 (no digit) read this
+    alignas(16) uint32_t limbs[WAVES][4 * N4_ROW];
 };
 
 // n = 3: S_c as MFMA B-operand fragments in the same layout with KK = 2 K steps and NT = 4 tiles;
@@ -104,7 +103,6 @@ __device__ void load_lds(Lds<NQ, WAVES>& L, const SpaceDev& sp) {
     if constexpr (NQ == 4) {
         const v4i* src = reinterpret_cast<const v4i*>(sp.phi);
         for (int i = threadIdx.x; i < N4_NT * N4_KK * 64; i += blockDim.x) L.frag[i] = src[i];
-        for (int i = threadIdx.x; i < N4_ROW; i += blockDim.x) L.zero_row[i] = 0;
     } else if constexpr (NQ == 3) {
         const v4i* src = reinterpret_cast<const v4i*>(sp.phi);
         for (int i = threadIdx.x; i < N3_NT * N3_KK * 64; i += blockDim.x) L.frag[i] = src[i];
@@ -172,6 +170,49 @@ __device__ inline uint64_t half_add16(uint64_t x, uint64_t y) {
 __device__ inline int32_t half_add32_i32(int32_t x, int32_t y) {
     const auto v = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
     return (int32_t)(v[0] + v[1]);
+}
+
+// Two 16-lane rows' halves of one matrix row brought together: with x, y the same quantity of two tiles,
+// even rows of lanes get (x, x(lane + 16)), odd rows (y(lane - 16), y): the first is from the lanes that
+// hold the low digits, the second from those with the high ones.
+struct LowHigh {
+    int32_t low, high;
+};
+__device__ inline LowHigh swap_rows16(int32_t x, int32_t y) {
+    const auto v = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    return {(int32_t)v[0], (int32_t)v[1]};
+}
+
+// A row digest from its eight signed digit sums, in the halves lo = acc_0 + 2^8 acc_1, hi = acc_2 + 2^8 acc_3 of
+// the low and of the high four digits:
+//   2^s (lo.low + 2^16 hi.low + 2^32 lo.high + 2^48 hi.high)  mod p, in [0, p],
+// for |lo|, |hi| <= 257 * 512 * 128 * 127 < 2^31 - 2^23.  With A = lo.low + 2^16 hi.low and T = (A >> 32) + lo.high (within
+// int32) this is
+//   A mod 2^32 + 2^32 ((T mod 2^29) + 2^16 (hi.high mod 2^13)) + (T >> 29) + (hi.high >> 13)   (mod p),
+// and the last two are kept positive by DIGEST_BIAS, taken off lo.low first.  So 0 <= x < 2^62 - 2^47, and x 2^s is
+// ((x << s) mod 2^61) + (x >> (61 - s)) < 2^62 - 2^46, folded once.  Only 32-bit halves cross lanes and one
+// modular word is formed per row; with a residue per half that crossed lanes as 64 bits, then folded and
+// rotated, the recombination and the hash took 55 instead of 37 instructions a row.
+constexpr int32_t DIGEST_BIAS = (1 << 18) + 4;
+// x + v and x * 2^16 + v as one multiply-add each (full rate here); written as 64-bit sums they take
+// moves to widen their operands.
+__device__ inline uint64_t add_u32(uint64_t x, uint32_t v) {
+    uint64_t r;
+    asm("v_mad_u64_u32 %0, vcc, %1, 1, %2" : "=v"(r) : "v"(v), "v"(x) : "vcc");
+    return r;
+}
+__device__ inline int64_t shl16_add(int32_t x, int32_t v) {
+    int64_t r;
+    asm("v_mad_i64_i32 %0, vcc, %1, %2, %3" : "=v"(r) : "v"(x), "s"(65536), "v"((int64_t)v) : "vcc");
+    return r;
+}
+__device__ inline uint64_t digest_of(LowHigh lo, LowHigh hi, uint32_t s) {
+    const int64_t A = shl16_add(hi.low, lo.low - DIGEST_BIAS);
+    const int32_t T = (int32_t)(A >> 32) + lo.high;
+    const uint32_t top = ((uint32_t)T & 0x1fffffffu) + (((uint32_t)hi.high & 0x1fffu) << 16);
+    const uint64_t x = add_u32(((uint64_t)top << 32) | (uint32_t)A, (uint32_t)((T >> 29) + (hi.high >> 13) + DIGEST_BIAS));
+    const uint64_t t = ((x << s) & P61) + (x >> (61 - s));
+    return add_u32(t & P61, (uint32_t)(t >> 61));
 }
 
 // n <= 2: phi(S_c) u with v_dot4_i32_i8 on A, B (int8, LDS) and 7-bit limbs of u.
@@ -243,69 +284,73 @@ __device__ inline void transpose_bytes4(const uint32_t* x, uint32_t* out) {
     out[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
 }
 
+// Digit rows of u (set 0) or of 2^31 u (set 1), four columns per lane: half 0 the low four, half 1 the high
+// four, into the wavefront's 4-row buffer.  Signed base-256 digits: for v < 2^62, b = v + C0 with
+// C0 = 0x8080808080808080 stays below 2^64 and v = sum_m (byte_m(b) - 128) 256^m, each digit in [-128, 127];
+// as an int8 the digit is byte_m(b) xor 0x80.  u is lazily reduced (< 2^61 + 2^32), and so is its image
+// 2^31 u = (u >> 30) + (u mod 2^30) 2^31 (mod p).
+__device__ inline void digit_words(const uint64_t* u, int set, uint32_t* lo, uint32_t* hi) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint64_t v = set ? (u[j] >> 30) + ((u[j] & 0x3fffffffull) << 31) : u[j];
+        const uint64_t b = v + 0x8080808080808080ull;
+        lo[j] = (uint32_t)b;
+        hi[j] = (uint32_t)(b >> 32);
+    }
+}
+__device__ inline void digit_rows(uint32_t* limbs, const uint32_t* words, int lane) {
+    // 4 x 4 byte transpose: digit row m gets byte m of the lane's four values (columns 4 lane + j)
+    uint32_t dg[4];
+    transpose_bytes4(words, dg);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) limbs[m * N4_ROW + lane] = dg[m] ^ 0x80808080u;
+    wave_sync();
+}
+
 template <int WAVES>
 __device__ inline void side1_mfma(const Lds<4, WAVES>& L, uint32_t* limbs, const uint64_t* u, int lane, int rot_e,
                                   uint64_t* S) {
     const int g = lane >> 4, n16 = lane & 15;
     // A operand (16 rows x K = 512): rows 0..7 hold the digits of u on the A half of K (columns
     // q < 256) and are zero on the B half; rows 8..15 hold the digits of 2^31 u on the B half and
-    // are zero on the A half.  Both sets go through the same 8-row LDS buffer, one after the other.
-    const uint32_t* arow0 = n16 < N4_DIG ? limbs + n16 * N4_ROW : L.zero_row;
-    const uint32_t* arow1 = n16 >= N4_DIG ? limbs + (n16 - N4_DIG) * N4_ROW : L.zero_row;
+    // are zero on the A half.  Four rows at a time go through the LDS buffer.
+    const uint32_t* arow = limbs + (n16 & 3) * N4_ROW;
     v4i afr[N4_KK];
 #pragma unroll
+    for (int kk = 0; kk < N4_KK; ++kk) afr[kk] = v4i{0, 0, 0, 0};
+#pragma unroll
     for (int set = 0; set < 2; ++set) {
-        // Signed base-256 digits: for v < 2^62, b = v + C0 with C0 = 0x8080808080808080 stays below
-        // 2^64 and v = sum_m (byte_m(b) - 128) 256^m, each digit in [-128, 127]; as an int8 the digit
-        // is byte_m(b) xor 0x80.  u is lazily reduced (< 2^61 + 2^32), and so is its image
-        // 2^31 u = (u >> 30) + (u mod 2^30) 2^31 (mod p).
-        uint32_t lo[4], hi[4];
+        uint32_t words[2][4];
+        digit_words(u, set, words[0], words[1]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint64_t w = set ? (u[j] >> 30) + ((u[j] & 0x3fffffffull) << 31) : u[j];
-            const uint64_t b = w + 0x8080808080808080ull;
-            lo[j] = (uint32_t)b;
-            hi[j] = (uint32_t)(b >> 32);
+        for (int half = 0; half < 2; ++half) {
+            digit_rows(limbs, words[half], lane);
+            if ((n16 >> 2) == 2 * set + half) {
+#pragma unroll
+                for (int kq = 0; kq < 4; ++kq)
+                    afr[set * 4 + kq] = *reinterpret_cast<const v4i*>(&arow[kq * 16 + g * 4]);
+            }
+            wave_sync();
         }
-        // 4 x 4 byte transposes: digit row m gets byte m of the lane's four values (columns 4 lane + j)
-        uint32_t dg[N4_DIG];
-        transpose_bytes4(lo, dg);
-        transpose_bytes4(hi, dg + 4);
-#pragma unroll
-        for (int m = 0; m < N4_DIG; ++m) limbs[m * N4_ROW + lane] = dg[m] ^ 0x80808080u;
-        wave_sync();
-        const uint32_t* arow = set ? arow1 : arow0;
-#pragma unroll
-        for (int kq = 0; kq < 4; ++kq) afr[set * 4 + kq] = *reinterpret_cast<const v4i*>(&arow[kq * 16 + g * 4]);
-        wave_sync();
     }
     // N tiles in groups of NG: NG independent accumulation chains over the 8 K steps, then each
     // finished tile is combined at once, so only NG accumulators and 2 NG fragments (the current
     // and the next K step's) are live.
     // Accumulator row m = 4g + j of this lane is digit m % 8 of set g >> 1 (u, or 2^31 u), weight
-    // 2^(8 (m % 8)) = 2^(32 (g & 1)) 2^(8j).  Each row sums 256 products, |acc| <= 256 * 128 * 127
-    // < 2^22, so x = acc_0 + 2^8 acc_1 + 2^16 acc_2 + 2^24 acc_3 lies in (-2^45, 2^45) and the sum of
-    // two such in (-2^46, 2^46).  Its weighted residue, kept lazily in [0, 2^62): with
-    // s = 61 - 32 (g & 1),
-    //   2^(61 - s) x = (x >> s) 2^61 + (x mod 2^s) 2^(61 - s) = (x >> s) + (x mod 2^s) 2^(61 - s)  (mod p)
-    // and y = p + (x >> s) + (x mod 2^s) 2^(61 - s).  Four such values sum below 2^64.
+    // 2^(8 (m % 8)).  Each row sums 256 products, |acc| <= 256 * 128 * 127 < 2^22.
     constexpr int NG = 2;
-    const uint32_t s_g = 61 - 32 * (uint32_t)(g & 1);
-    const uint64_t m_g = (1ull << s_g) - 1;
     // Fragments of tiles 8..15 lie beyond the 64 KiB reach of a DS immediate offset: they are read
     // through a second base address (kept opaque, so it is formed once instead of per read).
     uint32_t hi_base = 8 * N4_KK * 64;
     asm("" : "+v"(hi_base));
     const v4i* frag_hi = L.frag + hi_base;
-    // Per tile, the two 32-bit halves of the raw sum: lo = acc_0 + 2^8 acc_1, hi = acc_2 + 2^8 acc_3,
-    // |lo|, |hi| <= 257 * 256 * 128 * 127 < 2^30.
     int32_t lo[N4_NT], hi[N4_NT];
-    uint64_t Q[8];
-    // tile groups in the order 0..1, 8..9, 2..3, 10..11, ...: after every second group the tile
-    // pairs (i, 8 + i) are complete and reduce at once, which keeps few halves live
+    // tile groups in the order 0..1, 8..9, 4..5, 12..13, 2..3, ...: the tiles (i, 8 + i), then (i, i + 4) of
+    // their sums, complete early, which keeps few halves live
+    constexpr int order[8] = {0, 8, 4, 12, 2, 10, 6, 14};
 #pragma unroll
     for (int gi = 0; gi < N4_NT / NG; ++gi) {
-        const int n0 = (gi & 1) * 8 + (gi >> 1) * NG;
+        const int n0 = order[gi];
         v4i acc[NG];
 #pragma unroll
         for (int i = 0; i < NG; ++i) acc[i] = v4i{0, 0, 0, 0};
@@ -336,75 +381,74 @@ __device__ inline void side1_mfma(const Lds<4, WAVES>& L, uint32_t* limbs, const
             hi[n0 + i] = acc[i][2] + acc[i][3] * 256;
         }
         // reduce-scatter over the four lane groups.  Groups g and g ^ 2 carry the same digit weights,
-        // so their halves add exactly first, still in 32 bits (|lo + lo'| < 2^31): lanes g < 2 keep
-        // tiles 0..7 plus their l^32 partner's, lanes g >= 2 keep tiles 8..15.  The raw sum
-        // x = lo + 2^16 hi (|x| < 2^47) then becomes its lazy weighted residue.
+        // so their halves add exactly first, in 32 bits (|lo + lo'| < 2^31): lanes g < 2 keep
+        // tiles 0..7 plus their l^32 partner's, lanes g >= 2 keep tiles 8..15.  Then the low and the high
+        // digits of tiles i and i + 4 meet.
         if (gi & 1) {
 #pragma unroll
             for (int i = n0 - 8; i < n0 - 8 + NG; ++i) {
-                const int64_t x =
-                    (int64_t)half_add32_i32(lo[i], lo[8 + i]) + (int64_t)half_add32_i32(hi[i], hi[8 + i]) * 65536;
-                Q[i] = P61 + (uint64_t)(x >> s_g) + (((uint64_t)x & m_g) << (61 - s_g));
+                lo[i] = half_add32_i32(lo[i], lo[8 + i]);
+                hi[i] = half_add32_i32(hi[i], hi[8 + i]);
             }
         }
-    }
-    // within each half the even groups keep Q[0..3], the odd groups Q[4..7], adding the l^16
-    // partner's: plain 64-bit sums below 2^63, one fold at the end.
+        if ((gi & 3) == 3) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) S[i] = m61_rot(m61_fold(half_add16(Q[i], Q[4 + i])), rot_e);
+            for (int i = n0 - 12; i < n0 - 12 + NG; ++i)
+                S[i] = digest_of(swap_rows16(lo[i], lo[4 + i]), swap_rows16(hi[i], hi[4 + i]), (uint32_t)rot_e);
+        }
+    }
 }
 
 // n = 4, two walks of one wavefront on side 1 together: walk w's digit rows become A-operand rows
 // 8w .. 8w + 7, each over the whole K = [u | 2^31 u] (digit m of u on the A half, digit m of 2^31 u
 // on the B half), so no A row is zero and one pass of the 128 MFMAs serves both walks.  Walk w's
-// u goes through the wavefront's 8-row digit buffer one digit set at a time; only the lanes that
-// hold rows of walk w (n16 / 8 == w) take fragments from it.
+// u goes through the wavefront's 4-row buffer half a digit set at a time; only the lanes that
+// hold those rows take fragments from it.
 __device__ inline void digits_pair(uint32_t* limbs, const uint64_t* u, int lane, int w, v4i* afr) {
     const int g = lane >> 4, n16 = lane & 15;
-    const bool mine = (n16 >> 3) == w;
-    const uint32_t* arow = limbs + (n16 & 7) * N4_ROW;
+    int quarter = n16 >> 2;
+    const uint32_t* arow = limbs + (n16 & 3) * N4_ROW;
 #pragma unroll
     for (int set = 0; set < 2; ++set) {
-        // signed base-256 digits of u (set 0) or of 2^31 u (set 1), as in side1_mfma
-        uint32_t lo[4], hi[4];
+        uint32_t words[2][4];
+        digit_words(u, set, words[0], words[1]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint64_t v = set ? (u[j] >> 30) + ((u[j] & 0x3fffffffull) << 31) : u[j];
-            const uint64_t b = v + 0x8080808080808080ull;
-            lo[j] = (uint32_t)b;
-            hi[j] = (uint32_t)(b >> 32);
+        for (int half = 0; half < 2; ++half) {
+            digit_rows(limbs, words[half], lane);
+            asm("" : "+v"(quarter));  // compared afresh: four lane masks kept for the whole launch would spill
+            if (quarter == 2 * w + half) {
+#pragma unroll
+                for (int kq = 0; kq < 4; ++kq)
+                    afr[set * 4 + kq] = *reinterpret_cast<const v4i*>(&arow[kq * 16 + g * 4]);
+            }
+            wave_sync();
         }
-        uint32_t dg[N4_DIG];
-        transpose_bytes4(lo, dg);
-        transpose_bytes4(hi, dg + 4);
-#pragma unroll
-        for (int m = 0; m < N4_DIG; ++m) limbs[m * N4_ROW + lane] = dg[m] ^ 0x80808080u;
-        wave_sync();
-        if (mine) {
-#pragma unroll
-            for (int kq = 0; kq < 4; ++kq) afr[set * 4 + kq] = *reinterpret_cast<const v4i*>(&arow[kq * 16 + g * 4]);
-        }
-        wave_sync();
     }
 }
 
-// The product of both walks on the shared A operand.  Accumulator row m = 4g + j of lane l is
-// digit 4 (g & 1) + j of walk g >> 1 summed over both digit sets: 512 products of at most
-// 128 x 127, |acc| < 2^23, so lo = acc_0 + 2^8 acc_1 and hi = acc_2 + 2^8 acc_3 stay within
-// 257 x 512 x 128 x 127 < 2^31.  Each tile's raw sum x = lo + 2^16 hi becomes its lazy weighted
-// residue (weight 2^(32 (g & 1)), as in side1_mfma); the two digit halves of a row sit in lanes l
-// and l ^ 16 and are added by one cross-row swap per tile pair (i, 8 + i).  R[i] is then, in lanes
-// of even g, row 16 i + n16 and, in lanes of odd g, row 16 (8 + i) + n16 of walk g >> 1.
+// an element of the multiset hash: the map g of a digest c in [0, p] after the sign fold.  For c in
+// [0, p]: p - c = c ^ p, and of c and p - c the smaller is the one with bit 60 clear, so
+// min(c mod p, p - c mod p) = c ^ (bit 60 of c ? p : 0) (which also sends p to 0).
+__device__ inline uint64_t digest_map(uint64_t c, uint32_t ka, uint32_t kb) {
+    const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int32_t)(c >> 32), 28, 1);
+    const uint32_t lo = (uint32_t)c ^ m, hi = (uint32_t)(c >> 32) ^ (m & 0x1fffffffu);
+    return (uint64_t)(lo + ka) * (uint64_t)(hi + kb);
+}
+
+// The product of both walks on the shared A operand, and the hash elements of its rows summed per lane.
+// Accumulator row m = 4g + j of lane l is digit 4 (g & 1) + j of walk g >> 1 summed over both digit sets:
+// 512 products of at most 128 x 127, so lo = acc_0 + 2^8 acc_1 and hi = acc_2 + 2^8 acc_3 are within
+// digest_of's bounds.  After the swap of a tile pair (i, 8 + i) a lane of even g has all digits of row
+// 16 i + n16, one of odd g those of row 16 (8 + i) + n16, of walk g >> 1.
 template <int WAVES>
-__device__ inline void side1_mfma_pair(const Lds<4, WAVES>& L, const v4i* afr, int lane, int rot_e, uint64_t* R) {
-    const int g = lane >> 4;
+__device__ inline uint64_t side1_mfma_pair(const Lds<4, WAVES>& L, const v4i* afr, int lane, uint32_t s, uint32_t ka,
+                                           uint32_t kb) {
     constexpr int NG = 2;
-    const uint32_t s_g = 61 - 32 * (uint32_t)(g & 1);
-    const uint64_t m_g = (1ull << s_g) - 1;
     uint32_t hi_base = 8 * N4_KK * 64;
     asm("" : "+v"(hi_base));
     const v4i* frag_hi = L.frag + hi_base;
-    uint64_t Q[8];
+    int32_t lo[NG], hi[NG];
+    uint64_t sum = 0;
 #pragma unroll
     for (int gi = 0; gi < N4_NT / NG; ++gi) {
         const int n0 = (gi & 1) * 8 + (gi >> 1) * NG;
@@ -431,23 +475,23 @@ __device__ inline void side1_mfma_pair(const Lds<4, WAVES>& L, const v4i* afr, i
         }
 #pragma unroll
         for (int i = 0; i < NG; ++i) {
-            const int64_t x = (int64_t)(acc[i][0] + acc[i][1] * 256) + (int64_t)(acc[i][2] + acc[i][3] * 256) * 65536;
-            const uint64_t q = P61 + (uint64_t)(x >> s_g) + (((uint64_t)x & m_g) << (61 - s_g));
-            if (gi & 1)
-                R[n0 - 8 + i] = half_add16(Q[n0 - 8 + i], q);
-            else
-                Q[n0 + i] = q;
+            const int32_t l = acc[i][0] + acc[i][1] * 256, h = acc[i][2] + acc[i][3] * 256;
+            if (gi & 1) {
+                sum += digest_map(digest_of(swap_rows16(lo[i], l), swap_rows16(hi[i], h), s), ka, kb);
+            } else {
+                lo[i] = l;
+                hi[i] = h;
+            }
         }
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) R[i] = m61_rot(m61_fold(R[i]), rot_e);
+    return sum;
 }
 
 // n = 3: phi(S_c) u on MFMA, the n = 4 scheme at R = 64 with one row per lane: A-operand rows 0..7
 // are the signed base-256 digits of u on the A half of K = 128, rows 8..15 those of 2^31 u on the
 // B half; 4 N tiles x 2 K steps.  Lane l holds accumulator rows 4g..4g+3 (g = l/16) of column l%16
 // of each tile; groups g and g ^ 2 have equal digit weights, so their raw sums add first (l^32),
-// then as lazy weighted residues within each half (l^16), leaving each lane one finished row.
+// then the low and the high digits of a row meet (l^16), leaving each lane one finished row.
 template <int WAVES>
 __device__ inline void side1_mfma3(const Lds<3, WAVES>& L, uint32_t* limbs, const uint64_t* u, int lane, int rot_e,
                                    uint64_t* S) {
@@ -468,9 +512,7 @@ __device__ inline void side1_mfma3(const Lds<3, WAVES>& L, uint32_t* limbs, cons
         afr[set] = *reinterpret_cast<const v4i*>(&arow[g * 4]);
         wave_sync();
     }
-    const uint32_t s_g = 61 - 32 * (uint32_t)(g & 1);
-    const uint64_t m_g = (1ull << s_g) - 1;
-    uint64_t P[N3_NT];
+    int32_t lo[N3_NT], hi[N3_NT];
 #pragma unroll
     for (int nt = 0; nt < N3_NT; ++nt) {
         v4i acc = v4i{0, 0, 0, 0};
@@ -478,17 +520,15 @@ __device__ inline void side1_mfma3(const Lds<3, WAVES>& L, uint32_t* limbs, cons
         for (int kk = 0; kk < N3_KK; ++kk)
             acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(afr[kk], L.frag[(nt * N3_KK + kk) * 64 + lane], acc, 0, 0, 0);
         // |acc| <= 64 * 128 * 127 < 2^20
-        const int32_t lo = acc[0] + acc[1] * 256;
-        const int32_t hi = acc[2] + acc[3] * 256;
-        P[nt] = (uint64_t)((int64_t)lo + (int64_t)hi * 65536);
+        lo[nt] = acc[0] + acc[1] * 256;
+        hi[nt] = acc[2] + acc[3] * 256;
     }
-    uint64_t Q[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int64_t x = (int64_t)half_add32(P[i], P[2 + i]);
-        Q[i] = P61 + (uint64_t)(x >> s_g) + (((uint64_t)x & m_g) << (61 - s_g));
+        lo[i] = half_add32_i32(lo[i], lo[2 + i]);
+        hi[i] = half_add32_i32(hi[i], hi[2 + i]);
     }
-    S[0] = m61_rot(m61_fold(half_add16(Q[0], Q[1])), rot_e);
+    S[0] = digest_of(swap_rows16(lo[0], lo[1]), swap_rows16(hi[0], hi[1]), (uint32_t)rot_e);
 }
 
 // n = 3: for each (p, row r) bit 0 = P_p and P_r anticommute, bit 1 = their product's phase c is 3
@@ -689,17 +729,11 @@ __device__ void walk_step(const SpaceDev& sp, const Lds<NQ, WAVES>& L, uint32_t*
         for (int j = 0; j < RPL; ++j) S[j] = m61_fold(u[j]);  // n = 4 keeps u lazily reduced
     }
 
-    // sign-normalised row digests and the multiset hash of the walk group's rows.  For c in
-    // [0, p]: p - c = c ^ p, and of c and p - c the smaller is the one with bit 60 clear, so
-    // min(c mod p, p - c mod p) = c ^ (bit 60 of c ? p : 0) (which also sends p to 0).
+    // sign-normalised row digests and the multiset hash of the walk group's rows
     uint64_t acc = 0;
     const uint32_t ka = (uint32_t)sp.salt_h, kb = (uint32_t)(sp.salt_h >> 32);
 #pragma unroll
-    for (int j = 0; j < RPL; ++j) {
-        const uint64_t c = S[j];
-        const uint64_t d = c ^ (P61 & (0ull - ((c >> 60) & 1)));
-        acc += (uint64_t)((uint32_t)d + ka) * (uint64_t)((uint32_t)(d >> 32) + kb);
-    }
+    for (int j = 0; j < RPL; ++j) acc += digest_map(S[j], ka, kb);
     if constexpr (Gm::G == 64) {
         // within each 16-lane row by DPP (quad permutes, then row rotations by 4 and 8, which add the
         // other quads' sums), then across rows by the cross-half swaps: no LDS round trip
@@ -752,16 +786,8 @@ __device__ void walk_step_pair4(const SpaceDev& sp, const Lds<4, WAVES>& L, uint
         rotate4(u, dig, h_left, 1, lane, 0);
         digits_pair(limbs, u, lane, w, afr);
     }
-    uint64_t R[8];
-    side1_mfma_pair<WAVES>(L, afr, lane, sp.rot_e, R);
-    uint64_t acc = 0;
-    const uint32_t ka = (uint32_t)sp.salt_h, kb = (uint32_t)(sp.salt_h >> 32);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const uint64_t c = R[i];
-        const uint64_t d = c ^ (P61 & (0ull - ((c >> 60) & 1)));
-        acc += (uint64_t)((uint32_t)d + ka) * (uint64_t)((uint32_t)(d >> 32) + kb);
-    }
+    uint64_t acc = side1_mfma_pair<WAVES>(L, afr, lane, (uint32_t)sp.rot_e, (uint32_t)sp.salt_h,
+                                          (uint32_t)(sp.salt_h >> 32));
     acc += dpp64<0xB1>(acc);   // quad_perm [1,0,3,2]
     acc += dpp64<0x4E>(acc);   // quad_perm [2,3,0,1]
     acc += dpp64<0x124>(acc);  // row_ror:4
@@ -791,10 +817,14 @@ __device__ inline uint64_t start_point(const SpaceDev& sp, uint64_t w, uint32_t 
     return mulhi64(g, sp.n_half) | ((g & 1) << 32);
 }
 
+// n = 4: one block per CU (S_c's fragments take 128 KiB of its LDS) of 16 wavefronts, four per SIMD.  Twelve
+// were all that fitted while a wavefront had an 8-row digit buffer and the walks' states in vector
+// registers (168 of them).  2^18 walks x 16 steps: 4.60 ms then; 4.38 with the digests of digest_of,
+// 4.06 with 16 wavefronts, 3.52 with all of walk_block_pairs.
 constexpr int WAVES_SMALL = 4;
 template <int NQ>
 struct WalkWaves {
-    static constexpr int value = NQ == 4 ? 12 : WAVES_SMALL;
+    static constexpr int value = NQ == 4 ? 16 : WAVES_SMALL;
 };
 
 // ---- parity kernels ----
@@ -1098,37 +1128,68 @@ __device__ inline void count_events(WalkCounts& c, uint32_t ev) {
     if (ev & EV_SPIN) c.spin++;
 }
 
-__device__ inline WalkState load_state(const WalkDev& wd, int64_t w, bool uniform) {
-    WalkState st = wd.states[w];
-    if (uniform) {
-        st.start = uniform64(st.start);
-        st.cur = uniform64(st.cur);
-        st.pa = uniform64(st.pa);
-        st.pb = uniform64(st.pb);
-        st.na = uniform64(st.na);
-        st.ha = uniform64(st.ha);
-        st.len = uniform32(st.len);
-        st.trail = uniform32(st.trail);
-        st.mode = uniform32(st.mode);
-        st.rem = uniform32(st.rem);
-    }
-    return st;
+// A walk in hand: what every step uses, in registers, and what only backtracking uses, which a whole
+// wavefront's walk keeps in LDS (in scalar registers the two walks of a wavefront spilled, and reading
+// spilled values back took a tenth of the step's vector instructions).
+struct Trail {
+    uint64_t start, cur;
+    uint32_t len, trail, mode;
+};
+struct Back {
+    uint64_t pa, pb, na, ha;
+    uint32_t rem;
+};
+
+template <bool WHOLE>
+__device__ inline uint64_t same64(uint64_t v) {
+    if constexpr (WHOLE) return uniform64(v);
+    return v;
+}
+
+template <bool WHOLE>
+__device__ inline void load_state(const WalkDev& wd, int64_t w, Trail& tr, Back& bk) {
+    const WalkState st = wd.states[w];
+    tr.start = same64<WHOLE>(st.start);
+    tr.cur = same64<WHOLE>(st.cur);
+    tr.len = (uint32_t)same64<WHOLE>(st.len);
+    tr.trail = (uint32_t)same64<WHOLE>(st.trail);
+    tr.mode = (uint32_t)same64<WHOLE>(st.mode);
+    bk.pa = st.pa;
+    bk.pb = st.pb;
+    bk.na = st.na;
+    bk.ha = st.ha;
+    bk.rem = st.rem;
+}
+
+__device__ inline void store_state(const WalkDev& wd, int64_t w, const Trail& tr, const Back& bk) {
+    WalkState st;
+    st.start = tr.start;
+    st.cur = tr.cur;
+    st.pa = bk.pa;
+    st.pb = bk.pb;
+    st.na = bk.na;
+    st.ha = bk.ha;
+    st.len = tr.len;
+    st.trail = tr.trail;
+    st.mode = tr.mode;
+    st.rem = bk.rem;
+    wd.states[w] = st;
 }
 
 // The point a walk evaluates f on next: its current point while walking, else the backtracking
 // point that ALIGN / LOCK advances.
-__device__ inline uint64_t step_arg(const WalkState& st) {
-    // as masks rather than a choice of field, so the states stay in registers
-    const uint64_t walk = 0ull - (uint64_t)((st.mode & 0xff) == MODE_WALK);
-    const uint64_t second = 0ull - (uint64_t)((st.mode >> 8) & 1);
-    return (st.cur & walk) | (((st.pb & second) | (st.pa & ~second)) & ~walk);
+template <bool WHOLE>
+__device__ inline uint64_t step_arg(const Trail& tr, const Back& bk) {
+    if ((tr.mode & 0xff) == MODE_WALK) return tr.cur;
+    const uint64_t second = 0ull - (uint64_t)((tr.mode >> 8) & 1);  // masks: a choice of field would go through memory
+    return same64<WHOLE>((bk.pb & second) | (bk.pa & ~second));
 }
 
 // Walk w's state after one evaluation f(arg) = (nxt, H): distinguished points into the table,
 // backtracking of two trails that met (Sec. 3, Fig. 2), claws recorded, trails restarted.  WHOLE:
 // the walk occupies the whole wavefront (its leader is lane 0).
 template <bool WHOLE>
-__device__ inline uint32_t advance_walk(const SpaceDev& sp, const WalkDev& wd, WalkState& st, int64_t w,
+__device__ inline uint32_t advance_walk(const SpaceDev& sp, const WalkDev& wd, Trail& st, Back& bk, int64_t w,
                                         uint64_t arg, uint64_t nxt, uint64_t H, bool leader, int gbase) {
     uint32_t ev = 0;
     const uint32_t mode = st.mode & 0xff;
@@ -1203,20 +1264,20 @@ __device__ inline uint32_t advance_walk(const SpaceDev& sp, const WalkDev& wd, W
                 if (ostart != st.start) {
                     // backtrack the two trails (Sec. 3, Fig. 2)
                     restart = false;
-                    st.pa = st.start;
-                    st.pb = ostart;
+                    bk.pa = st.start;
+                    bk.pb = ostart;
                     const uint32_t la = st.len, lb = olen;
                     if (la > lb) {
                         st.mode = MODE_ALIGN;
-                        st.rem = la - lb;
+                        bk.rem = la - lb;
                         st.len = lb;
                     } else if (lb > la) {
                         st.mode = MODE_ALIGN | (1u << 8);
-                        st.rem = lb - la;
+                        bk.rem = lb - la;
                         st.len = la;
                     } else {
                         st.mode = MODE_LOCK;
-                        st.rem = la;
+                        bk.rem = la;
                     }
                 }
             }
@@ -1227,45 +1288,52 @@ __device__ inline uint32_t advance_walk(const SpaceDev& sp, const WalkDev& wd, W
             st.cur = nxt;
         }
     } else if (mode == MODE_ALIGN) {
-        if (which) st.pb = nxt; else st.pa = nxt;
-        if (--st.rem == 0) {
-            if (st.pa == st.pb) {
+        const uint64_t second = 0ull - (uint64_t)which;
+        bk.pa = (bk.pa & second) | (nxt & ~second);
+        bk.pb = (nxt & second) | (bk.pb & ~second);
+        const uint32_t rem = (uint32_t)same64<WHOLE>(bk.rem) - 1;
+        bk.rem = rem;
+        if (rem == 0) {
+            if (same64<WHOLE>(bk.pa) == same64<WHOLE>(bk.pb)) {
                 ev |= EV_RH;  // one trail started on the other
                 restart = true;
             } else {
                 st.mode = MODE_LOCK;
-                st.rem = st.len;
+                bk.rem = st.len;
             }
         }
     } else {  // MODE_LOCK
         if (!which) {
-            st.na = nxt;
-            st.ha = H;
+            bk.na = nxt;
+            bk.ha = H;
             st.mode = MODE_LOCK | (1u << 8);
         } else {
-            if (st.na == nxt) {
+            const uint64_t na = same64<WHOLE>(bk.na);
+            if (na == nxt) {
                 // f(pa) = f(pb) with pa != pb: the merge
-                const uint64_t sa = (st.pa >> 32) & 1, sb = (st.pb >> 32) & 1;
+                const uint64_t sa = (same64<WHOLE>(bk.pa) >> 32) & 1, sb = (same64<WHOLE>(bk.pb) >> 32) & 1;
                 if (sa == sb) {
                     ev |= EV_SAME;
-                } else if (st.ha != H) {
+                } else if (same64<WHOLE>(bk.ha) != H) {
                     ev |= EV_RED;
                 } else {
                     ev |= EV_CLAW;
                     if (leader) {
                         const unsigned long long idx = atomicAdd(wd.claw_count, 1ull);
                         if (idx < wd.claw_cap) {
-                            wd.claws[2 * idx] = st.pa;
-                            wd.claws[2 * idx + 1] = st.pb;
+                            wd.claws[2 * idx] = bk.pa;
+                            wd.claws[2 * idx + 1] = bk.pb;
                         }
                     }
                 }
                 restart = true;
             } else {
-                st.pa = st.na;
-                st.pb = nxt;
+                const uint32_t rem = (uint32_t)same64<WHOLE>(bk.rem) - 1;
+                bk.pa = na;
+                bk.pb = nxt;
+                bk.rem = rem;
                 st.mode = MODE_LOCK;
-                if (--st.rem == 0) restart = true;  // cannot happen for two trails with one end
+                if (rem == 0) restart = true;  // cannot happen for two trails with one end
             }
         }
     }
@@ -1295,7 +1363,7 @@ template <int NQ, int WAVES>
 __device__ void walk_block_single(const SpaceDev& sp, const WalkDev& wd, int iters, Lds<NQ, WAVES>& L, int64_t block,
                                   int64_t nblocks, WalkCounts& cnt) {
     using Gm = Geo<NQ>;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = (int)uniform32(threadIdx.x >> 6);
     const int gi = lane / Gm::G, gl = lane % Gm::G, gbase = gi * Gm::G;
     const bool leader = gl == 0;
     uint32_t* limbs = L.limbs[wave * Gm::WPW + gi];
@@ -1304,23 +1372,32 @@ __device__ void walk_block_single(const SpaceDev& sp, const WalkDev& wd, int ite
     uint32_t steps = 0, active = 0, dps = 0, ins = 0;
     const int64_t stride = nblocks * WAVES * Gm::WPW;
     for (int64_t base = (block * WAVES + wave) * Gm::WPW; base < wd.walks; base += stride) {
-        const int64_t w = base + gi;
+        const int64_t w = Gm::G == 64 ? base : base + gi;
         if (w >= wd.walks) continue;
-        WalkState st = load_state(wd, w, Gm::G == 64);
+        Trail st;
+        Back bk;
+        load_state<Gm::G == 64>(wd, w, st, bk);
+        if constexpr (Gm::G == 64) {
+            bk.pa = uniform64(bk.pa);
+            bk.pb = uniform64(bk.pb);
+            bk.na = uniform64(bk.na);
+            bk.ha = uniform64(bk.ha);
+            bk.rem = uniform32(bk.rem);
+        }
         for (int it = 0; it < iters; ++it) {
             if ((st.mode & 0xff) == MODE_DONE) break;
-            const uint64_t arg = step_arg(st);
+            const uint64_t arg = step_arg<Gm::G == 64>(st, bk);
             uint64_t nxt, H;
             walk_step<NQ, WAVES>(sp, L, limbs, arg, gl, gbase, nxt, H);
             steps++;
-            const uint32_t ev = advance_walk<Gm::G == 64>(sp, wd, st, w, arg, nxt, H, leader, gbase);
+            const uint32_t ev = advance_walk<Gm::G == 64>(sp, wd, st, bk, w, arg, nxt, H, leader, gbase);
             dps += ev & EV_DP;
             ins += (ev >> 1) & 1;
             const uint32_t rare = ev & ~(uint32_t)(EV_DP | EV_INS);
             if (rare && leader) count_events(cnt, rare);
         }
         if ((st.mode & 0xff) != MODE_DONE) active++;
-        if (leader) wd.states[w] = st;
+        if (leader) store_state(wd, w, st, bk);
     }
     if (leader) {
         cnt.steps += steps;
@@ -1330,31 +1407,45 @@ __device__ void walk_block_single(const SpaceDev& sp, const WalkDev& wd, int ite
     }
 }
 
-// n = 4: each wavefront runs two walks, 2q and 2q + 1 for q = block * WAVES + wave, then every
-// nblocks * WAVES further, and gives the pair 2 iters evaluations of f (a walk without a partner
-// gets iters); cnt as in walk_block_single.  A walk whose next point is on side 0 steps alone; when both next points are on side
-// 1 the two steps share one MFMA product (walk_step_pair4).  So the pair's steps add up to 2 iters
-// while each walk's share varies with its sides: a launch's total is walks x iters as before.
+// n = 4: each wavefront runs two walks, 2q and 2q + 1, and gives the pair 2 iters evaluations of f (a walk
+// without a partner gets iters); cnt as in walk_block_single.  A walk whose next point is on side 0 steps
+// alone; when both next points are on side 1 the two steps share one MFMA product (walk_step_pair4).  So
+// the pair's steps add up to 2 iters while each walk's share varies with its sides: a launch's total is
+// walks x iters.
+// The block's pairs are q = block * WAVES + i for i < WAVES, then every nblocks * WAVES further; its
+// wavefronts take them in turn from *next (LDS, zero at the start).  With a fixed share each, the
+// wavefronts that the SIMDs prefer finished early and few were left at the end: a wavefront lived 0.78 of
+// the launch on average, now 0.98 (2^18 walks x 16 steps: 3.96 -> 3.62 ms).
 template <int WAVES>
 __device__ void walk_block_pairs(const SpaceDev& sp, const WalkDev& wd, int iters, Lds<4, WAVES>& L, int64_t block,
-                                 int64_t nblocks, WalkCounts& cnt) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                                 int64_t nblocks, WalkCounts& cnt, uint32_t* next, Back* back) {
+    // the wavefront's index made explicitly uniform, and with it the walks' numbers and states: they stay
+    // in scalar registers (as lane values they took 60 vector registers)
+    const int lane = threadIdx.x & 63, wave = (int)uniform32(threadIdx.x >> 6);
     const bool leader = lane == 0;
     uint32_t* limbs = L.limbs[wave];
+    Back &ba = back[2 * wave], &bb = back[2 * wave + 1];  // every lane writes the same values
     uint32_t steps = 0, active = 0, dps = 0, ins = 0;  // frequent events in registers, as in walk_block_single
     const int64_t pairs = (wd.walks + 1) / 2;
-    for (int64_t q = block * WAVES + wave; q < pairs; q += nblocks * WAVES) {
+    for (;;) {
+        uint32_t i = 0;
+        if (leader) i = atomicAdd(next, 1u);
+        i = uniform32(i);
+        const int64_t q = (int64_t)(i / WAVES) * nblocks * WAVES + block * WAVES + i % WAVES;
+        if (q >= pairs) break;
         const int64_t w0 = 2 * q, w1 = 2 * q + 1;
         const bool has_b = w1 < wd.walks;
-        WalkState sa = load_state(wd, w0, true);
-        WalkState sb = has_b ? load_state(wd, w1, true) : sa;
+        Trail sa, sb;
+        load_state<true>(wd, w0, sa, ba);
+        sb = sa;
+        if (has_b) load_state<true>(wd, w1, sb, bb);
         const int total = has_b ? 2 * iters : iters;
         int left = total;
         while (left > 0) {
             const bool act_a = (sa.mode & 0xff) != MODE_DONE;
             const bool act_b = has_b && (sb.mode & 0xff) != MODE_DONE;
             if (!act_a && !act_b) break;
-            const uint64_t arg_a = step_arg(sa), arg_b = step_arg(sb);
+            const uint64_t arg_a = step_arg<true>(sa, ba), arg_b = has_b ? step_arg<true>(sb, bb) : arg_a;
             const bool s1a = (arg_a >> 32) & 1, s1b = (arg_b >> 32) & 1;
             uint64_t na = 0, ha = 0, nb = 0, hb = 0;
             bool do_a, do_b;
@@ -1376,9 +1467,9 @@ __device__ void walk_block_pairs(const SpaceDev& sp, const WalkDev& wd, int iter
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 if (!(k ? do_b : do_a)) continue;
-                WalkState st = k ? sb : sa;
+                Trail st = k ? sb : sa;
                 const uint32_t ev =
-                    advance_walk<true>(sp, wd, st, k ? w1 : w0, k ? arg_b : arg_a, k ? nb : na, k ? hb : ha, leader, 0);
+                    advance_walk<true>(sp, wd, st, k ? bb : ba, k ? w1 : w0, k ? arg_b : arg_a, k ? nb : na, k ? hb : ha, leader, 0);
                 dps += ev & EV_DP;
                 ins += (ev >> 1) & 1;
                 const uint32_t rare = ev & ~(uint32_t)(EV_DP | EV_INS);
@@ -1393,8 +1484,8 @@ __device__ void walk_block_pairs(const SpaceDev& sp, const WalkDev& wd, int iter
         if ((sa.mode & 0xff) != MODE_DONE) active++;
         if (has_b && (sb.mode & 0xff) != MODE_DONE) active++;
         if (leader) {
-            wd.states[w0] = sa;
-            if (has_b) wd.states[w1] = sb;
+            store_state(wd, w0, sa, ba);
+            if (has_b) store_state(wd, w1, sb, bb);
         }
     }
     if (leader) {
@@ -1408,9 +1499,9 @@ __device__ void walk_block_pairs(const SpaceDev& sp, const WalkDev& wd, int iter
 // The walks of one slice: paired on side 1 at n = 4, one walk group at a time otherwise.
 template <int NQ, int WAVES>
 __device__ void walk_block(const SpaceDev& sp, const WalkDev& wd, int iters, Lds<NQ, WAVES>& L, int64_t block,
-                           int64_t nblocks, WalkCounts& cnt) {
+                           int64_t nblocks, WalkCounts& cnt, uint32_t* next, Back* back) {
     if constexpr (NQ == 4)
-        walk_block_pairs<WAVES>(sp, wd, iters, L, block, nblocks, cnt);
+        walk_block_pairs<WAVES>(sp, wd, iters, L, block, nblocks, cnt, next, back);
     else
         walk_block_single<NQ, WAVES>(sp, wd, iters, L, block, nblocks, cnt);
 }
@@ -1423,10 +1514,13 @@ __global__ __launch_bounds__(WAVES * 64) void k_walk(SpaceDev sp, WalkDev wd, in
     const int lane = threadIdx.x & 63;
     const bool leader = lane % Geo<NQ>::G == 0;
     WalkCounts& mine = reinterpret_cast<WalkCounts*>(s_cnt)[(threadIdx.x >> 6) * Geo<NQ>::WPW + lane / Geo<NQ>::G];
+    __shared__ uint32_t s_pair;
+    __shared__ Back s_back[NQ == 4 ? 2 * WAVES : 1];
     if (leader) mine = WalkCounts{};
+    if (threadIdx.x == 0) s_pair = 0;
     load_lds(L, sp);
     __syncthreads();
-    walk_block<NQ, WAVES>(sp, wd, iters, L, blockIdx.x, gridDim.x, mine);
+    walk_block<NQ, WAVES>(sp, wd, iters, L, blockIdx.x, gridDim.x, mine, &s_pair, s_back);
     flush_counts(wd, mine, leader);
 }
 
@@ -1441,6 +1535,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_walk_queue(const SpaceDev* __res
                                                            uint32_t* head) {
     __shared__ Lds<NQ, WAVES> L;
     __shared__ int32_t s_next;
+    __shared__ uint32_t s_pair;
+    __shared__ Back s_back[NQ == 4 ? 2 * WAVES : 1];
     // the loaded member's event counts so far, one slot per walk group, written by the group's leader
     // as events happen (in registers they would hold 22 more VGPRs through the step and spill)
     __shared__ __attribute__((aligned(8))) unsigned char s_cnt[WAVES * Geo<NQ>::WPW * sizeof(WalkCounts)];
@@ -1451,7 +1547,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_walk_queue(const SpaceDev* __res
     if (leader) mine = WalkCounts{};
     int32_t loaded = -1;
     for (;;) {
-        if (threadIdx.x == 0) s_next = (int32_t)atomicAdd(head, 1u);
+        if (threadIdx.x == 0) {
+            s_next = (int32_t)atomicAdd(head, 1u);
+            s_pair = 0;
+        }
         __syncthreads();
         // the same value in every thread of the block; read from the first lane so that the item and
         // the member's descriptors are scalar loads
@@ -1467,7 +1566,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_walk_queue(const SpaceDev* __res
             loaded = it.slot;
         }
         __syncthreads();
-        walk_block<NQ, WAVES>(sp, wds[it.slot], it.iters, L, it.unit, it.units, mine);
+        walk_block<NQ, WAVES>(sp, wds[it.slot], it.iters, L, it.unit, it.units, mine, &s_pair, s_back);
         __syncthreads();  // s_next and, for the next member, the LDS are rewritten after this
     }
     if (loaded >= 0) flush_counts(wds[loaded], mine, leader);
@@ -1728,12 +1827,6 @@ __device__ inline uint64_t prefix_keys3(uint64_t u, const uint32_t* p, int j, ui
     return u;
 }
 
-// the element map of the multiset hash on a digest c in [0, p]
-__device__ inline uint64_t digest_map(uint64_t c, uint32_t ka, uint32_t kb) {
-    const uint64_t d = c ^ (P61 & (0ull - ((c >> 60) & 1)));
-    return (uint64_t)((uint32_t)d + ka) * (uint64_t)((uint32_t)(d >> 32) + kb);
-}
-
 // v summed over the lane's 16-lane row
 __device__ inline uint64_t row_sum16(uint64_t v) {
     v += dpp64<0xB1>(v);
@@ -1827,32 +1920,21 @@ __global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_keys3(SpaceDev sp, int
 }
 
 // Two products' hash sums from one pass of 8 MFMAs: accumulator row 4g + i of lane l (g = l / 16) is
-// digit 4 (g & 1) + i of product g >> 1 in matrix row 16 nt + l % 16.  A swap of 16-lane rows between
-// the tiles nt and nt + 2 leaves every lane all eight digits of one row: of tile nt in even g, of tile
-// nt + 2 in odd g.  With |acc| <= 128 * 128 * 127 < 2^21 the halves lo + 2^8, hi + 2^8 stay below 2^30,
-// and x = A + 2^32 B (|A|, |B| < 2^47) is p + A + (B >> 29) + (B mod 2^29) 2^32 (mod p), in (0, 2^62);
-// its product by 2^s is ((x << s) mod 2^61) + (x >> (61 - s)) < 2^62, folded once into [0, p].
+// digit 4 (g & 1) + i of product g >> 1 in matrix row 16 nt + l % 16, |acc| <= 128 * 128 * 127.  The swap of
+// 16-lane rows between the tiles nt and nt + 2 leaves every lane all eight digits of one row.
 __device__ inline uint64_t pair_sum3(const v4i a0, const v4i a1, const v4i* bf, uint32_t s, uint32_t ka, uint32_t kb) {
-    v4i acc[N3_NT];
+    int32_t lo[N3_NT], hi[N3_NT];
 #pragma unroll
     for (int nt = 0; nt < N3_NT; ++nt) {
-        acc[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bf[2 * nt], v4i{0, 0, 0, 0}, 0, 0, 0);
-        acc[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bf[2 * nt + 1], acc[nt], 0, 0, 0);
+        v4i acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bf[2 * nt], v4i{0, 0, 0, 0}, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bf[2 * nt + 1], acc, 0, 0, 0);
+        lo[nt] = acc[0] + acc[1] * 256;
+        hi[nt] = acc[2] + acc[3] * 256;
     }
     uint64_t sum = 0;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)(acc[i][0] + acc[i][1] * 256),
-                                                         (uint32_t)(acc[2 + i][0] + acc[2 + i][1] * 256), false, false);
-        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(acc[i][2] + acc[i][3] * 256),
-                                                         (uint32_t)(acc[2 + i][2] + acc[2 + i][3] * 256), false, false);
-        const int64_t A = (int64_t)(int32_t)lo[0] + (int64_t)(int32_t)hi[0] * 65536;
-        const int64_t B = (int64_t)((int32_t)lo[1] + (1 << 28)) + (int64_t)(int32_t)hi[1] * 65536;
-        const uint64_t x =
-            P61 - (1ull << 60) + (uint64_t)(A + (B >> 29)) + ((uint64_t)((uint32_t)B & 0x1fffffffu) << 32);
-        const uint64_t t = ((x << s) & P61) + (x >> (61 - s));
-        sum += digest_map((t & P61) + (t >> 61), ka, kb);
-    }
+    for (int i = 0; i < 2; ++i)
+        sum += digest_map(digest_of(swap_rows16(lo[i], lo[2 + i]), swap_rows16(hi[i], hi[2 + i]), s), ka, kb);
     return sum;
 }
 
@@ -1896,7 +1978,8 @@ __global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_probe3(SpaceDev sp, co
 #pragma unroll
                 for (int i = 0; i < 4; ++i) nx[i] = f[(quad + 1) * 256 + 64 * i];
             }
-            const uint64_t s01 = pair_sum3(a[0], a[1], bf, s, ka, kb), s23 = pair_sum3(a[2], a[3], bf, s, ka, kb);
+            const uint64_t s01 = pair_sum3(a[0], a[1], bf, s, ka, kb),
+                           s23 = pair_sum3(a[2], a[3], bf, s, ka, kb);
             // 32-lane halves hold the two products of a pair; after the exchange row g of 16 lanes holds
             // product 0, 2, 1, 3 of the quad
             const uint64_t sum = row_sum16(half_add16(s01, s23));
