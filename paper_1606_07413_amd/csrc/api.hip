@@ -211,7 +211,7 @@ struct Space {
 
     static size_t phi_bytes(int n) { return (size_t)2 << (8 * n / 2); }
     static size_t key_bytes(int n) { return (size_t)8 << (2 * n); }
-    static size_t mem_bytes(int n) { return phi_bytes(n) + key_bytes(n) + 2 * 8 + 2 * 4; }
+    static size_t mem_bytes(int n) { return phi_bytes(n) + key_bytes(n) + 2 * 8 + 4 * tcw::MADE_WORDS; }
 
     void release() {
         if (mem && pooled && ctx)
@@ -311,7 +311,7 @@ int setup_space(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, Space& out
     out.delta = sp->delta;
     out.seed = sp->seed;
     out.U = t->U;
-    out.made = made ? made : reinterpret_cast<int32_t*>(out.mem + Space::mem_bytes(n) - 2 * 4);
+    out.made = made ? made : reinterpret_cast<int32_t*>(out.mem + Space::mem_bytes(n) - 4 * tcw::MADE_WORDS);
     if (n == 4 && (rc = rotated_keys(c, sp->seed, out.rk))) return rc;
     const tcw::SpaceJob j = out.job();
     const int h = sp->k / 2;
@@ -812,7 +812,8 @@ int tcw_trails(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, const uint6
     Space s;
     int rc = start_space(c, t, sp, s);
     if (rc) return rc;
-    HIP_TRY(c, tcw::launch_trails(t->n, s.dev, starts, count, cap, dp, len, c->stream));
+    HIP_TRY(c, tcw::launch_trails(t->n, s.dev, starts, count, cap, dp, len,
+                                   reinterpret_cast<unsigned int*>(s.made + 2), c->device, c->stream));
     return finish_space(c, s);
 }
 
@@ -2021,7 +2022,7 @@ struct BatchBuffers {
     int32_t* counts = nullptr;             // 5: items queued per qubit count
     int32_t* heads = nullptr;              // 5: queue positions (zeroed by a kernel at the start of a round)
     int32_t* restart = nullptr;            // count: slots restarted before the next round
-    int32_t* made = nullptr;               // count x 2: SpaceJob::out of each member's space
+    int32_t* made = nullptr;               // count x MADE_WORDS: SpaceJob::out of each member's space
     tcw::SpaceJob* jobs = nullptr;         // count
     std::vector<int32_t> pending;          // host: members whose restart waits for the next round
     std::vector<int32_t> unmade;           // host: members whose space the device has to make before it
@@ -2064,11 +2065,11 @@ int batch_make_spaces(tcw_ctx* c, std::vector<BatchTarget>& bt, BatchBuffers& bb
     HIP_TRY(c, hipMemcpyAsync(bb.jobs, jobs.data(), jobs.size() * sizeof(tcw::SpaceJob), hipMemcpyHostToDevice, c->stream));
     for (int n = 1; n <= 4; ++n)
         HIP_TRY(c, tcw::spaces_make(n, tcw::SpaceJob{}, bb.jobs + from[n], from[n + 1] - from[n], c->stream));
-    std::vector<int32_t> made(2 * bt.size());
+    std::vector<int32_t> made(tcw::MADE_WORDS * bt.size());
     HIP_TRY(c, hipMemcpyAsync(made.data(), bb.made, made.size() * 4, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     for (const int32_t i : bb.unmade)
-        if (int rc = accept_space(c, *bt[i].space, &made[2 * i])) return rc;
+        if (int rc = accept_space(c, *bt[i].space, &made[tcw::MADE_WORDS * i])) return rc;
     bb.unmade.clear();
     return TCW_OK;
 }
@@ -2181,7 +2182,7 @@ int batch_advance(tcw_ctx* c, BatchTarget& b, int slot, BatchBuffers& bb, double
             b.space->pooled = true;
         }
         tcw_space sp{b.k, b.chunk, b.p.seed, b.p.version, delta};
-        if ((rc = setup_space(c, b.t, &sp, *b.space, bb.made + 2 * slot))) return rc;
+        if ((rc = setup_space(c, b.t, &sp, *b.space, bb.made + tcw::MADE_WORDS * slot))) return rc;
         bb.unmade.push_back(slot);
         b.res->spaces++;
         b.res->versions++;
@@ -2295,9 +2296,9 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
     HIP_TRY(c, hipMalloc(&bb.counts, 5 * 4));
     HIP_TRY(c, hipMalloc(&bb.heads, 5 * 4));
     HIP_TRY(c, hipMalloc(&bb.restart, (size_t)count * 4));
-    HIP_TRY(c, hipMalloc(&bb.made, (size_t)count * 2 * 4));
+    HIP_TRY(c, hipMalloc(&bb.made, (size_t)count * 4 * tcw::MADE_WORDS));
     HIP_TRY(c, hipMalloc(&bb.jobs, (size_t)count * sizeof(tcw::SpaceJob)));
-    HIP_TRY(c, hipMemsetAsync(bb.made, 0, (size_t)count * 2 * 4, c->stream));
+    HIP_TRY(c, hipMemsetAsync(bb.made, 0, (size_t)count * 4 * tcw::MADE_WORDS, c->stream));
     HIP_TRY(c, hipMemsetAsync(bb.stats, 0, (size_t)count * tcw::ST_COUNT * 8, c->stream));
     HIP_TRY(c, hipMemsetAsync(bb.claw_count, 0, (size_t)count * 8, c->stream));
     HIP_TRY(c, hipMemsetAsync(bb.counts, 0, 5 * 4, c->stream));

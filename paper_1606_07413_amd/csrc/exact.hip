@@ -1072,7 +1072,7 @@ __global__ __launch_bounds__(1024) void k_space(SpaceJob one, const SpaceJob* ma
     const SpaceJob J = many ? many[blockIdx.x] : one;
     __shared__ unsigned long long ors[2];
     if (threadIdx.x < 2) ors[threadIdx.x] = 0;
-    if (threadIdx.x == 0) J.out[1] = 0;
+    if (threadIdx.x == 0) J.out[1] = J.out[2] = 0;
     __syncthreads();
     if (J.c) {
         T oa = 0, ob = 0;
@@ -1095,7 +1095,7 @@ __global__ void k_space_clear(SpaceJob one, const SpaceJob* many, int count) {
     for (int i = threadIdx.x; i < count; i += blockDim.x) {
         const SpaceJob J = many ? many[i] : one;
         J.ors[0] = J.ors[1] = 0;
-        J.out[1] = 0;
+        J.out[1] = J.out[2] = 0;
     }
 }
 __global__ __launch_bounds__(1024) void k_space_or4(SpaceJob one, const SpaceJob* many) {

@@ -68,8 +68,9 @@ struct WalkDev {
 };
 
 // One space to be made from a target on the device: S_c = U R(c)^T (c = 0: U itself) packed as int8 for
-// the walk step, the row-digest keys, and out = {exponent of S_c, flags}: 4 an exact value out of range,
-// 2 an entry of S_c outside int8.  S_c itself is not kept (the claw check starts from U).
+// the walk step, the row-digest keys, and out = {exponent of S_c, flags, 0}: flags 4 an exact value out of
+// range, 2 an entry of S_c outside int8; the zero is a queue position for what uses the space next.  S_c itself is not kept (the claw check starts from U).
+constexpr int MADE_WORDS = 3;
 struct SpaceJob {
     const void* a;       // U (ExactDev)
     const void* b;
@@ -78,7 +79,7 @@ struct SpaceJob {
     uint32_t* phi;
     uint64_t* keys;
     unsigned long long* ors;  // two words of scratch
-    int32_t* out;
+    int32_t* out;             // MADE_WORDS words
     uint32_t c;
     uint32_t pad;
 };
@@ -161,7 +162,7 @@ hipError_t rot_keys2_fill(const uint64_t* rkeys, uint64_t* rkeys2, hipStream_t s
 hipError_t launch_step(int n, const SpaceDev& sp, const uint64_t* in, uint64_t* out, uint64_t* hash, int64_t count,
                        hipStream_t s);
 hipError_t launch_trails(int n, const SpaceDev& sp, const uint64_t* starts, int64_t count, uint32_t cap,
-                         uint64_t* dp, uint32_t* len, hipStream_t s);
+                         uint64_t* dp, uint32_t* len, unsigned int* queue, int device, hipStream_t s);
 hipError_t launch_starts(const SpaceDev& sp, int64_t w0, uint32_t j, int64_t count, uint64_t* out, hipStream_t s);
 hipError_t launch_canon_hash(int n, const SpaceDev& sp, const uint32_t* phi_all, const int32_t* e, int64_t count,
                              uint64_t* out, hipStream_t s);

@@ -861,6 +861,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_step(SpaceDev sp, const uint64_t
     }
 }
 
+// A trail that comes back to a point it has passed has no distinguished point before it, so it never
+// reaches one: it is abandoned there (as at the cap) instead of going round up to 20 / theta times.  Brent's
+// cycle search (BIT 20, 1980): the point after 1, 2, 4, ... steps is kept and every later one compared with
+// it.  A few such trails among 16384 at theta = 2^-8 held a launch for 5,120 steps in a row.
 template <int NQ, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_trails(SpaceDev sp, const uint64_t* starts, int64_t count,
                                                        uint32_t cap, uint64_t* dp, uint32_t* len) {
@@ -876,8 +880,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_trails(SpaceDev sp, const uint64
     for (int64_t base = ((int64_t)blockIdx.x * WAVES + wave) * Gm::WPW; base < count; base += stride) {
         const int64_t i = base + gi;
         if (i < count) {
-            uint64_t pt = starts[i];
-            uint32_t d = 0, found = 0;
+            uint64_t pt = starts[i], seen = pt;
+            uint32_t d = 0, found = 0, mark = 1;
             for (uint32_t t = 1; t <= cap; ++t) {
                 uint64_t nx, hh;
                 walk_step<NQ, WAVES>(sp, L, limbs, pt, gl, gbase, nx, hh);
@@ -887,11 +891,86 @@ __global__ __launch_bounds__(WAVES * 64) void k_trails(SpaceDev sp, const uint64
                     found = 1;
                     break;
                 }
+                if (pt == seen) break;
+                if (t == mark) {
+                    seen = pt;
+                    mark *= 2;
+                }
             }
             if (gl == 0) {
                 dp[i] = found ? pt : 0;
                 len[i] = found ? d : 0;
             }
+        }
+    }
+}
+
+// n = 4: a wavefront runs two trails at a time and takes the next one from *queue (zero before the launch) when
+// one ends, so that two side-1 steps share a pass of the MFMAs as in the walk kernel and long trails leave no
+// wavefront idle.  With no more trails than wavefronts each runs alone.  16384 trails at n = 4, k = 7,
+// theta = 2^-8: 18 to 25 ms with one trail per wavefront to the cap, now 5.6 ms: about 3.3 ms at the walk
+// kernel's rate and the last, longest trails.
+struct TrailRun {
+    int64_t i;  // < 0: none
+    uint64_t pt, seen;
+    uint32_t n, mark;
+};
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void k_trails4(SpaceDev sp, const uint64_t* starts, int64_t count, uint32_t cap,
+                                                        uint64_t* dp, uint32_t* len, unsigned int* queue) {
+    __shared__ Lds<4, WAVES> L;
+    if (!space_ready(sp)) return;
+    load_lds(L, sp);
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = (int)uniform32(threadIdx.x >> 6);
+    uint32_t* limbs = L.limbs[wave];
+    const bool two = count > (int64_t)gridDim.x * WAVES;
+    auto take = [&](TrailRun& r) {
+        uint32_t i = 0;
+        if (lane == 0) i = atomicAdd(queue, 1u);
+        i = uniform32(i);
+        r.i = i < count ? (int64_t)i : -1;
+        r.pt = r.seen = r.i >= 0 ? uniform64(starts[r.i]) : 0;
+        r.n = 0;
+        r.mark = 1;
+    };
+    auto advance = [&](TrailRun& r, uint64_t nx) {
+        r.n++;
+        const bool dist = is_dist(sp, nx);
+        if (dist || nx == r.seen || r.n >= cap) {
+            if (lane == 0) {
+                dp[r.i] = dist ? nx : 0;
+                len[r.i] = dist ? r.n : 0;
+            }
+            take(r);
+            return;
+        }
+        if (r.n == r.mark) {
+            r.seen = nx;
+            r.mark *= 2;
+        }
+        r.pt = nx;
+    };
+    TrailRun a, b;
+    take(a);
+    b.i = -1;
+    b.pt = b.seen = 0;
+    b.n = b.mark = 0;
+    if (two) take(b);
+    while (a.i >= 0 || b.i >= 0) {
+        const bool side_a = (a.pt >> 32) & 1, side_b = (b.pt >> 32) & 1;
+        uint64_t na, ha, nb, hb;
+        if (a.i >= 0 && b.i >= 0 && side_a && side_b) {
+            walk_step_pair4<WAVES>(sp, L, limbs, a.pt, b.pt, lane, na, ha, nb, hb);
+            advance(a, na);
+            advance(b, nb);
+        } else {
+            const bool pick_b = a.i < 0 || (b.i >= 0 && side_a);
+            walk_step<4, WAVES>(sp, L, limbs, pick_b ? b.pt : a.pt, lane, 0, na, ha);
+            if (pick_b)
+                advance(b, na);
+            else
+                advance(a, na);
         }
     }
 }
@@ -2058,12 +2137,22 @@ hipError_t launch_step(int n, const SpaceDev& sp, const uint64_t* in, uint64_t* 
 }
 
 hipError_t launch_trails(int n, const SpaceDev& sp, const uint64_t* starts, int64_t count, uint32_t cap, uint64_t* dp,
-                         uint32_t* len, hipStream_t s) {
+                         uint32_t* len, unsigned int* queue, int device, hipStream_t s) {
     if (count <= 0) return hipSuccess;
     auto f = [&]<int NQ>() -> hipError_t {
         constexpr int W = WalkWaves<NQ>::value;
         const int64_t per_block = (int64_t)W * Geo<NQ>::WPW;
         int64_t blocks = (count + per_block - 1) / per_block;
+        if constexpr (NQ == 4) {
+            // few trails: a block for each, so that they do not share a CU
+            const int64_t cus = cu_count(device);
+            blocks = count < cus ? count : cus;
+            if (count < (1ll << 31)) {
+                hipLaunchKernelGGL((k_trails4<W>), dim3((unsigned)blocks), dim3(W * 64), 0, s, sp, starts, count, cap,
+                                   dp, len, queue);
+                return hipGetLastError();
+            }
+        }
         if (blocks > 4096) blocks = 4096;
         hipLaunchKernelGGL((k_trails<NQ, W>), dim3((unsigned)blocks), dim3(W * 64), 0, s, sp, starts, count, cap,
                            dp, len);

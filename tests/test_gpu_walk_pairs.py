@@ -61,3 +61,42 @@ def test_walks_without_distinguished_points(ctx, walks, iters):
             assert int(st["cur"][2 * q + i]) == cur[i] and int(st["len"][2 * q + i]) == done[i], (q, i)
             assert int(st["start"][2 * q + i]) == int(first["start"][2 * q + i])
     w.end()
+
+
+# small spaces, where many trails end in a cycle without a distinguished point: fewer trails than wavefronts,
+# more (two at a time), one; caps below, at and above a trail's length
+@pytest.mark.parametrize("n,k,delta,count,cap", [(4, 2, 3, 5000, 160), (4, 3, 5, 9000, 640), (4, 2, 4, 7, 3), (4, 2, 6, 1, 1280),
+                                                 (4, 2, 2, 4500, 1), (3, 2, 4, 300, 320), (3, 4, 7, 700, 100), (2, 4, 5, 200, 640),
+                                                 (1, 6, 4, 60, 7)])
+def test_trails_and_cycles(ctx, n, k, delta, count, cap):
+    import torch
+    print("trails", n, k, delta, count, cap, flush=True)
+    tw = seeded_inputs.target_words(n, max(k, 3), 77)
+    tgt = ctx.target_from_words(n, tw.paulis, tw.clifford)
+    chunk = tw.paulis[0] if k % 2 else 0
+    u = zmat.target_from_words(n, tw.paulis, tw.clifford)
+    spec = owalk.make_spec(u, n, k, chunk, 4, delta=delta)
+    # f on the whole space by the step call, which the parity tests hold to the oracle; a few points here too
+    pts = [x | (b << 32) for b in (0, 1) for x in range(spec.n_half)]
+    pin = torch.tensor(pts, dtype=torch.int64, device="cuda:0")
+    out = torch.empty_like(pin)
+    ctx.step(tgt, k, chunk, 4, delta, pin, out)
+    f = dict(zip(pts, out.cpu().tolist()))
+    for pt in pts[:: max(1, len(pts) // 4)]:
+        assert f[pt] == owalk.f(spec, pt)
+    starts = [pts[seeded_inputs.uniform_below(6, i, len(pts))] for i in range(count)]
+    dp = torch.empty(count, dtype=torch.int64, device="cuda:0")
+    ln = torch.empty(count, dtype=torch.int32, device="cuda:0")
+    ctx.trails(tgt, k, chunk, 4, delta, torch.tensor(starts, device="cuda:0"), cap, dp, ln)
+    dp, ln = dp.cpu().tolist(), ln.cpu().tolist()
+    want = {}
+    for s in set(starts):
+        pt, ans = s, (0, 0)
+        for t in range(1, cap + 1):
+            pt = f[pt]
+            if owalk.distinguished(spec, pt):
+                ans = (pt, t)
+                break
+        want[s] = ans
+    assert [(d, l) for d, l in zip(dp, ln)] == [want[s] for s in starts]
+    assert cap < 100 or delta < 3 or any(l == 0 for l in ln) or count == 1
