@@ -73,6 +73,10 @@ struct tcw_ctx {
     // device buffers of finished batch members, by exact size, for later batches (pool_alloc / pool_put)
     std::multimap<size_t, void*> pool;
     size_t pool_bytes = 0;
+    // streams and events of the batch rounds (batch_streams): [0] the round, [n] its branch of qubit count n.
+    // Creating one takes about 0.2 ms, more than a small depth's kernels.
+    hipStream_t gs[5] = {};
+    hipEvent_t fork = nullptr, join[5] = {};
 };
 
 struct tcw_target {
@@ -134,11 +138,34 @@ void pool_put(tcw_ctx* c, void* p, size_t bytes) {
     c->pool_bytes += bytes;
 }
 
+void drop_batch_streams(tcw_ctx* c) {
+    for (int n = 0; n <= 4; ++n) {
+        if (c->gs[n]) (void)hipStreamDestroy(c->gs[n]);
+        if (c->join[n]) (void)hipEventDestroy(c->join[n]);
+        c->gs[n] = nullptr;
+        c->join[n] = nullptr;
+    }
+    if (c->fork) (void)hipEventDestroy(c->fork);
+    c->fork = nullptr;
+}
+
 #define HIP_TRY(ctx, expr)                                   \
     do {                                                     \
         hipError_t _e = (expr);                              \
         if (_e != hipSuccess) return hip_fail(ctx, _e, #expr); \
     } while (0)
+
+// The streams and events of a round over the qubit counts in `has`, made on first use (default priority).
+int batch_streams(tcw_ctx* c, const bool* has) {
+    if (!c->gs[0]) HIP_TRY(c, hipStreamCreateWithFlags(&c->gs[0], hipStreamNonBlocking));
+    if (!c->fork) HIP_TRY(c, hipEventCreateWithFlags(&c->fork, hipEventDisableTiming));
+    for (int n = 1; n <= 4; ++n) {
+        if (!has[n]) continue;
+        if (!c->gs[n]) HIP_TRY(c, hipStreamCreateWithFlags(&c->gs[n], hipStreamNonBlocking));
+        if (!c->join[n]) HIP_TRY(c, hipEventCreateWithFlags(&c->join[n], hipEventDisableTiming));
+    }
+    return TCW_OK;
+}
 
 // Device buffers local to one call, freed when the call returns on any path (an early HIP_TRY
 // return included).
@@ -487,6 +514,7 @@ int tcw_create(tcw_ctx** out, int device, void* stream) {
 
 int tcw_destroy(tcw_ctx* c) {
     if (!c) return TCW_EINVAL;
+    drop_batch_streams(c);
     if (c->stopped) free_search_run(c->stopped);
     c->stopped = nullptr;
     if (c->flag) (void)hipFree(c->flag);
@@ -2324,29 +2352,29 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
     }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
 
-    // streams for the graph: one branch per qubit count (default priority)
-    hipStream_t gs[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-    hipEvent_t fork = nullptr, join[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+    // streams for the graph: one branch per qubit count
+    if ((rc = batch_streams(c, has_n))) {
+        for (auto& b : bt) free_walk_buffers(c, b);
+        return rc;
+    }
+    hipStream_t* gs = c->gs;
+    hipEvent_t &fork = c->fork, *join = c->join;
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
-    auto cleanup = [&]() {
+    auto cleanup = [&](bool failed) {
         // nothing may still use the members' buffers when they go back to the pool
-        if (gs[0]) (void)hipStreamSynchronize(gs[0]);
+        (void)hipStreamSynchronize(gs[0]);
         (void)hipStreamSynchronize(c->stream);
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
-        for (int n = 0; n <= 4; ++n) {
-            if (gs[n]) (void)hipStreamDestroy(gs[n]);
-            if (join[n]) (void)hipEventDestroy(join[n]);
-        }
-        if (fork) (void)hipEventDestroy(fork);
+        if (failed) drop_batch_streams(c);  // one of them may still be in a capture
         for (auto& b : bt) free_walk_buffers(c, b);
     };
 #define BATCH_TRY(expr)                      \
     do {                                     \
         hipError_t _e = (expr);              \
         if (_e != hipSuccess) {              \
-            cleanup();                       \
+            cleanup(true);                   \
             return hip_fail(c, _e, #expr);   \
         }                                    \
     } while (0)
@@ -2354,16 +2382,10 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
     do {                   \
         rc = (expr);       \
         if (rc) {          \
-            cleanup();     \
+            cleanup(true); \
             return rc;     \
         }                  \
     } while (0)
-    BATCH_TRY(hipStreamCreateWithFlags(&gs[0], hipStreamNonBlocking));
-    for (int n = 1; n <= 4; ++n) {
-        BATCH_TRY(hipStreamCreateWithFlags(&gs[n], hipStreamNonBlocking));
-        BATCH_TRY(hipEventCreateWithFlags(&join[n], hipEventDisableTiming));
-    }
-    BATCH_TRY(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
     int grid[5] = {0, 0, 0, 0, 0};
     for (int n = 1; n <= 4; ++n) grid[n] = has_n[n] ? tcw::walk_grid_blocks(n, c->device, true, 0) : 0;
     bool dirty = true, recapture = true;
@@ -2458,11 +2480,12 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
                     bb.items_cap[n] = cap;
                     recapture = true;
                 }
+                // the lists stay as they are until the round that reads them has been waited for
                 if (m > 0)
-                    BATCH_TRY(hipMemcpy(bb.items[n], h_items[n].data(), (size_t)m * sizeof(tcw::WorkItem),
-                                        hipMemcpyHostToDevice));
+                    BATCH_TRY(hipMemcpyAsync(bb.items[n], h_items[n].data(), (size_t)m * sizeof(tcw::WorkItem),
+                                             hipMemcpyHostToDevice, gs[0]));
             }
-            BATCH_TRY(hipMemcpy(bb.counts, h_counts, 5 * 4, hipMemcpyHostToDevice));
+            BATCH_TRY(hipMemcpyAsync(bb.counts, h_counts, 5 * 4, hipMemcpyHostToDevice, gs[0]));
             dirty = false;
         }
         if (recapture) {
@@ -2566,7 +2589,9 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
                     if (avail > b.seen) {
                         const int64_t m = avail - b.seen;
                         std::vector<uint64_t> pairs(2 * m);
-                        BATCH_TRY(hipMemcpy(pairs.data(), b.wd.claws + 2 * b.seen, 16 * m, hipMemcpyDeviceToHost));
+                        BATCH_TRY(hipMemcpyAsync(pairs.data(), b.wd.claws + 2 * b.seen, 16 * m, hipMemcpyDeviceToHost,
+                                                 gs[0]));
+                        BATCH_TRY(hipStreamSynchronize(gs[0]));
                         b.pu0.resize(m);
                         b.pu1.resize(m);
                         for (int64_t j = 0; j < m; ++j) {
@@ -2620,7 +2645,7 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
     }
 #undef BATCH_TRY
 #undef BATCH_RC
-    cleanup();
+    cleanup(false);
     for (auto& b : bt) {
         if (b.res->seconds == 0) b.res->seconds = now_s() - t0;
         set_minimal(b.res);
@@ -3091,29 +3116,43 @@ namespace {
 // matrix hash, value 255 - (least number of rotations), and the keys of the products with <= h_probe
 // rotations on the target's side; shared by the labelling and certificate calls.
 struct LevelTable {
+    tcw_ctx* ctx = nullptr;
+    std::vector<std::pair<void*, size_t>> bufs;  // from the context's pool and back to it
     uint64_t* table = nullptr;
     uint64_t* keys = nullptr;
     uint32_t* zero_phi = nullptr;
     void* frags = nullptr;  // the target side's keys (mitm_frags)
     int lg = 0;
     tcw::SpaceDev sp{};
+    template <typename T>
+    hipError_t take(T** p, size_t bytes) {
+        void* q = nullptr;
+        const hipError_t e = pool_alloc(ctx, &q, bytes);
+        if (e != hipSuccess) return e;
+        bufs.emplace_back(q, bytes);
+        *p = static_cast<T*>(q);
+        return hipSuccess;
+    }
+    explicit LevelTable(tcw_ctx* c) : ctx(c) {}
+    LevelTable(const LevelTable&) = delete;
+    LevelTable& operator=(const LevelTable&) = delete;
     ~LevelTable() {
-        for (void* q : {(void*)table, (void*)keys, (void*)zero_phi, frags})
-            if (q) (void)hipFree(q);
+        if (!bufs.empty()) (void)hipStreamSynchronize(ctx->stream);  // nothing pending on what goes back
+        for (auto& b : bufs) pool_put(ctx, b.first, b.second);
     }
 };
 
 int build_level_table(tcw_ctx* c, int n, int h_levels, int h_probe, uint64_t seed, LevelTable& lt) {
     const int R = 1 << (2 * n);
-    HIP_TRY(c, hipMalloc(&lt.zero_phi, (size_t)R * R / 2 * 4));
+    HIP_TRY(c, lt.take(&lt.zero_phi, (size_t)R * R / 2 * 4));
     HIP_TRY(c, hipMemsetAsync(lt.zero_phi, 0, (size_t)R * R / 2 * 4, c->stream));
-    HIP_TRY(c, hipMalloc(&lt.keys, (size_t)R * 8));
+    HIP_TRY(c, lt.take(&lt.keys, (size_t)R * 8));
     HIP_TRY(c, tcw::keys_fill(n, seed, lt.keys, c->stream));
     uint64_t entries = 0;
     for (int h = 0; h <= h_levels; ++h) entries += n_half_of(n, h);
     lt.lg = 10;
     while ((1ull << lt.lg) < 4 * entries && lt.lg < 30) ++lt.lg;
-    HIP_TRY(c, hipMalloc(&lt.table, ((size_t)1 << lt.lg) * 16));
+    HIP_TRY(c, lt.take(&lt.table, ((size_t)1 << lt.lg) * 16));
     HIP_TRY(c, tcw::launch_table_clear(lt.table, lt.lg, 0, c->stream));
     lt.sp.delta = 0;
     lt.sp.salt_h = tcw::sm64(tcw::sm64(seed, 2), 0x4C4142454Cull);
@@ -3125,7 +3164,7 @@ int build_level_table(tcw_ctx* c, int n, int h_levels, int h_probe, uint64_t see
         HIP_TRY(c, tcw::mitm_levels(n, lt.sp, h, lt.table, lt.lg, c->stream));
     }
     if (const size_t bytes = tcw::mitm_frag_bytes(n, h_probe)) {
-        HIP_TRY(c, hipMalloc(&lt.frags, bytes));
+        HIP_TRY(c, lt.take(&lt.frags, bytes));
         HIP_TRY(c, tcw::mitm_frags(n, lt.sp, h_probe, lt.frags, c->stream));
     }
     return TCW_OK;
@@ -3187,9 +3226,9 @@ extern "C" int tcw_label_batch(tcw_ctx* c, int n, int count, const uint16_t* wor
     uint16_t* dwords = nullptr;
     int32_t *doff = nullptr, *dk = nullptr, *rot = nullptr;
     uint32_t* phi = nullptr;
-    const int chunk = 4096;
+    const int chunk = std::min(count, 4096);
     auto cleanup = [&]() {
-        for (void* q : {(void*)dwords, (void*)doff, (void*)dk, (void*)rot, (void*)phi})
+        for (void* q : {(void*)dwords, (void*)doff, (void*)dk, (void*)rot})
             if (q) (void)hipFree(q);
     };
 #define LB_TRY(expr)                         \
@@ -3207,9 +3246,11 @@ extern "C" int tcw_label_batch(tcw_ctx* c, int n, int count, const uint16_t* wor
     LB_TRY(hipMemcpyAsync(doff, offsets, (count + 1) * 4, hipMemcpyHostToDevice, c->stream));
     LB_TRY(hipMemcpyAsync(dk, kof, count * 4, hipMemcpyHostToDevice, c->stream));
     LB_TRY(hipMalloc(&rot, chunk * 4));
-    LB_TRY(hipMalloc(&phi, (size_t)chunk * R * R / 2 * 4));
     const int h_id = mitm_split(n, h_max, count);
-    LevelTable lt;
+    LevelTable lt(c);
+    size_t room = 64;  // by powers of two, so that the pool holds few sizes
+    while ((int)room < chunk) room *= 2;
+    LB_TRY(lt.take(&phi, room * R * R / 2 * 4));
     if ((rc = build_level_table(c, n, h_id, 2 * h_max - h_id, seed, lt)) || (rc = clear_flag(c))) {
         cleanup();
         return rc;
@@ -3242,7 +3283,7 @@ extern "C" int tcw_min_tcount(tcw_ctx* c, const tcw_target* t, int h_max, uint64
         if (phi) (void)hipFree(phi);
         if (dev_i32) (void)hipFree(dev_i32);
     };
-    LevelTable lt;
+    LevelTable lt(c);
     int32_t e_u = 0;
     int flag = 0;
     hipError_t err = hipMalloc(&phi, (size_t)R * R / 2 * 4 + 16);
