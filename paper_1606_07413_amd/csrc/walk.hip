@@ -837,7 +837,7 @@ __device__ inline bool space_ready(SpaceDev& sp) {
 }
 
 template <int NQ, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_step(SpaceDev sp, const uint64_t* in, uint64_t* out,
+__global__ __launch_bounds__(WAVES * 64, 4) void k_step(SpaceDev sp, const uint64_t* in, uint64_t* out,
                                                      uint64_t* hash, int64_t count) {
     using Gm = Geo<NQ>;
     __shared__ Lds<NQ, WAVES> L;
@@ -866,7 +866,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_step(SpaceDev sp, const uint64_t
 // cycle search (BIT 20, 1980): the point after 1, 2, 4, ... steps is kept and every later one compared with
 // it.  A few such trails among 16384 at theta = 2^-8 held a launch for 5,120 steps in a row.
 template <int NQ, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_trails(SpaceDev sp, const uint64_t* starts, int64_t count,
+__global__ __launch_bounds__(WAVES * 64, 4) void k_trails(SpaceDev sp, const uint64_t* starts, int64_t count,
                                                        uint32_t cap, uint64_t* dp, uint32_t* len) {
     using Gm = Geo<NQ>;
     __shared__ Lds<NQ, WAVES> L;
@@ -916,7 +916,7 @@ struct TrailRun {
     uint32_t n, mark;
 };
 template <int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_trails4(SpaceDev sp, const uint64_t* starts, int64_t count, uint32_t cap,
+__global__ __launch_bounds__(WAVES * 64, 4) void k_trails4(SpaceDev sp, const uint64_t* starts, int64_t count, uint32_t cap,
                                                         uint64_t* dp, uint32_t* len, unsigned int* queue) {
     __shared__ Lds<4, WAVES> L;
     if (!space_ready(sp)) return;
@@ -977,7 +977,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_trails4(SpaceDev sp, const uint6
 
 // Canonical hash of explicit matrices: the side-1 product with u = K (no rotations).
 template <int NQ, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_canon(SpaceDev sp, const uint32_t* phi_all, const int32_t* e,
+__global__ __launch_bounds__(WAVES * 64, 4) void k_canon(SpaceDev sp, const uint32_t* phi_all, const int32_t* e,
                                                       int64_t count, uint64_t* out) {
     using Gm = Geo<NQ>;
     constexpr int NPHI = Gm::Q4 * Gm::R;
@@ -1586,7 +1586,7 @@ __device__ void walk_block(const SpaceDev& sp, const WalkDev& wd, int iters, Lds
 }
 
 template <int NQ, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_walk(SpaceDev sp, WalkDev wd, int iters) {
+__global__ __launch_bounds__(WAVES * 64, 4) void k_walk(SpaceDev sp, WalkDev wd, int iters) {
     __shared__ Lds<NQ, WAVES> L;
     // one count slot per walk group (raw storage: a __shared__ object cannot have initialisers)
     __shared__ __attribute__((aligned(8))) unsigned char s_cnt[WAVES * Geo<NQ>::WPW * sizeof(WalkCounts)];
@@ -1609,7 +1609,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_walk(SpaceDev sp, WalkDev wd, in
 // head[0] is the queue position (zeroed by a kernel before the launch); count[0] items are queued.
 // Every block leaves once the position passes the count, so the grid always drains.
 template <int NQ, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_walk_queue(const SpaceDev* __restrict__ sps, const WalkDev* __restrict__ wds,
+__global__ __launch_bounds__(WAVES * 64, 4) void k_walk_queue(const SpaceDev* __restrict__ sps, const WalkDev* __restrict__ wds,
                                                            const WorkItem* __restrict__ items, const int32_t* count,
                                                            uint32_t* head) {
     __shared__ Lds<NQ, WAVES> L;
@@ -1781,7 +1781,7 @@ __device__ inline bool keep_pair(uint32_t p0, uint32_t p1, bool anti) { return a
 
 // n <= 2: one walk group per product, as in the walk kernels.
 template <int NQ, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_mitm_levels(SpaceDev sp, int h, uint64_t* table, int log2_table) {
+__global__ __launch_bounds__(WAVES * 64, 4) void k_mitm_levels(SpaceDev sp, int h, uint64_t* table, int log2_table) {
     using Gm = Geo<NQ>;
     __shared__ Lds<NQ, WAVES> L;
     load_lds(L, sp);
@@ -1811,7 +1811,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_mitm_levels(SpaceDev sp, int h, 
 // table at level i; stops once j reaches the best total.  blockIdx.y shares a target's products between
 // the blocks of one column; best_out starts at -1 (none), which as unsigned is above every total.
 template <int NQ, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_mitm_probe(SpaceDev sp0, const uint32_t* phi_all,
+__global__ __launch_bounds__(WAVES * 64, 4) void k_mitm_probe(SpaceDev sp0, const uint32_t* phi_all,
                                                            const int32_t* rot_e_all, int count, int h_max,
                                                            const uint64_t* table, int log2_table, int32_t* best_out) {
     using Gm = Geo<NQ>;
@@ -1922,7 +1922,7 @@ __device__ inline uint64_t row_sum16(uint64_t v) {
 // product) with the pruned products left out: the 16 million products of levels 0..4 take 0.84 ms,
 // against 4.85 ms with a wavefront per product and one lane at the table.
 constexpr int MITM_WAVES = 4;
-__global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_levels3(SpaceDev sp, int h, uint32_t prefixes, uint64_t* table,
+__global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_levels3(SpaceDev sp, int h, uint32_t prefixes, uint64_t* table,
                                                                   int log2_table) {
     const int lane = threadIdx.x & 63;
     const uint32_t ka = (uint32_t)sp.salt_h, kb = (uint32_t)(sp.salt_h >> 32);
@@ -1968,7 +1968,7 @@ __global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_levels3(SpaceDev sp, i
 // 32 pairs a prefix (MITM_PREFIX_V4 vectors).  Lane l of a fragment holds row l % 16, columns
 // 16 (l / 16) .. + 15.
 constexpr int MITM_PREFIX_V4 = 32 * 2 * 64;
-__global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_keys3(SpaceDev sp, int j, uint32_t y0, uint32_t prefixes,
+__global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_keys3(SpaceDev sp, int j, uint32_t y0, uint32_t prefixes,
                                                                 v4i* frags) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint64_t anti, plus;
@@ -2021,23 +2021,29 @@ __device__ inline uint64_t pair_sum3(const v4i a0, const v4i a1, const v4i* bf, 
 // y0 + prefixes - 1 (frags from k_mitm_keys3).  A wavefront keeps its target's packed U as eight B
 // fragments in registers and shares the target's prefixes with the `slices` wavefronts of the same
 // target; two pairs of products fill the four 16-lane rows, as in k_mitm_levels3, and 64 lanes look up
-// at a time.  A target that an earlier level has answered is skipped, and one hit ends its level: every
-// coset of T-count <= h_id is tabled, so the first level with a hit is T - h_id (or 0) and its total T.
-// About 41 VALU instructions and four MFMAs a product; label batches read the fragments (3 MiB for
-// j <= 2) from L2.  16384 circuits against the table of T-count <= 4: 4.3 ms, one target's 142 thousand
-// products of <= 3 rotations 0.05 ms (its fragments 0.11 ms), against 34 ms and 63 ms with one block per
-// target that ran the walk step on each product.
-__global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_probe3(SpaceDev sp, const v4i* __restrict__ phi_all,
+// at a time.  A target that an earlier level has answered is skipped, and one hit ends its level (each
+// wavefront looks after every prefix): every coset of T-count <= h_id is tabled, so the first level with
+// a hit is T - h_id (or 0) and its total T.  The wavefronts are ordered by slice, then target, so that
+// a hit in one slice spares the target's later ones, and wavefronts that run together read the same
+// prefixes.
+// Bound by VALU issue: about 39 instructions and four MFMAs a product (64 % and 22 % of the time at four
+// wavefronts per SIMD, PMC); label batches read the fragments (3 MiB for j <= 2) from L2.  16384 circuits
+// against the table of T-count <= 4: 3.1 ms.  One target's 142 thousand products of <= 3 rotations:
+// 0.05 ms.  The accumulators stay in VGPRs (a budget of 128 by the second launch bound: with 512 the
+// compiler puts them in AGPRs and moves each out) and the fragments alternate between two register sets;
+// with AGPRs and a copied set a product took 52 instructions, with each target's two wavefronts side by
+// side the whole 4.35 ms.
+__global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_probe3(SpaceDev sp, const v4i* __restrict__ phi_all,
                                                                  const int32_t* __restrict__ rot_e_all, int count,
                                                                  int j, uint32_t y0, uint32_t prefixes, int slices,
                                                                  const v4i* __restrict__ frags, const uint64_t* table,
                                                                  int log2_table, int32_t* best_out) {
     const int lane = threadIdx.x & 63;
     const int64_t unit = uniform32(blockIdx.x * MITM_WAVES + (threadIdx.x >> 6));
-    const int t = (int)(unit / slices), slice = (int)(unit % slices);
-    if (t >= count) return;
+    const int t = (int)(unit % count), slice = (int)(unit / count);
+    if (slice >= slices) return;
     uint32_t* best = reinterpret_cast<uint32_t*>(&best_out[t]);
-    if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != ~0u) return;
+    if (uniform32(__hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != ~0u) return;
     const uint32_t ka = (uint32_t)sp.salt_h, kb = (uint32_t)(sp.salt_h >> 32);
     v4i bf[N3_NT * N3_KK];
 #pragma unroll
@@ -2050,19 +2056,29 @@ __global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_probe3(SpaceDev sp, co
         const v4i* f = frags + (size_t)y * MITM_PREFIX_V4 + lane;
         const int quads = (products + 3) / 4;
         uint64_t mine = 0;
-        v4i nx[4] = {f[0], f[64], f[128], f[192]};
-        for (int quad = 0; quad < quads; ++quad) {
-            const v4i a[4] = {nx[0], nx[1], nx[2], nx[3]};
-            if (quad + 1 < quads) {
+        // the next quad's fragments are on their way while one is worked on: two register sets in turn,
+        // so that none is copied to the other
+        const auto fetch = [&](int quad, v4i (&to)[4]) {
+            if (quad >= quads) return;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) nx[i] = f[(quad + 1) * 256 + 64 * i];
-            }
+            for (int i = 0; i < 4; ++i) to[i] = f[quad * 256 + 64 * i];
+        };
+        const auto work = [&](int quad, const v4i (&a)[4]) {
             const uint64_t s01 = pair_sum3(a[0], a[1], bf, s, ka, kb),
                            s23 = pair_sum3(a[2], a[3], bf, s, ka, kb);
             // 32-lane halves hold the two products of a pair; after the exchange row g of 16 lanes holds
             // product 0, 2, 1, 3 of the quad
             const uint64_t sum = row_sum16(half_add16(s01, s23));
             if ((lane & 15) == quad) mine = sum;
+        };
+        v4i even[4], odd[4];
+        fetch(0, even);
+        for (int quad = 0; quad < quads; quad += 2) {
+            fetch(quad + 1, odd);
+            work(quad, even);
+            if (quad + 1 >= quads) break;
+            fetch(quad + 2, even);
+            work(quad + 1, odd);
         }
         const int g = lane >> 4, in_quad = ((g & 1) << 1) | (g >> 1);
         int lvl = -1;
@@ -2072,6 +2088,7 @@ __global__ __launch_bounds__(MITM_WAVES * 64) void k_mitm_probe3(SpaceDev sp, co
         }
         if (lvl >= 0) atomicMin(best, (uint32_t)(j + lvl));
         if (__ballot(lvl >= 0) != 0) return;
+        if (uniform32(__hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != ~0u) return;
     }
 }
 
@@ -2314,10 +2331,12 @@ size_t mitm_frag_bytes(int n, int h_max) {
     return std::min<size_t>(all, MITM_CHUNK) * MITM_PREFIX_V4 * sizeof(v4i);
 }
 
-// The wavefronts of k_mitm_probe3 that share a target: enough for 8 wavefronts per SIMD of the chip, one
-// prefix each at least.
+// The wavefronts of k_mitm_probe3 that share a target: 32 rounds of the 4096 that the chip holds, one
+// prefix each at least.  A label batch's targets end anywhere between their first product and the last
+// (4096 at once, level 2: 16384 circuits take 3.89 ms with 8192 wavefronts, 3.49 with 16384, 3.22 with
+// 32768, 3.09 with 131072); a single target has its prefixes one to a wavefront either way.
 static int mitm_slices(int count, uint32_t prefixes) {
-    const int64_t want = (8192 + count - 1) / count;
+    const int64_t want = (131072 + count - 1) / count;
     return (int)std::max<int64_t>(1, std::min<int64_t>(want, prefixes));
 }
 
