@@ -1165,28 +1165,27 @@ __device__ inline uint64_t pack_value(uint64_t start, uint32_t len) {
     return (start & 0x1ffffffffull) | ((uint64_t)(len & 0x3fffffffu) << 33) | (1ull << 63);
 }
 
-// The walks of one block: walk slots first_block * WAVES * WPW + ... strided by nblocks blocks.
-// A walk group's event counts, added to the member's statistics by its leader lane (flush_counts).
+// A walk group's event counts in LDS, in the order of the statistics, written by its leader lane.
 struct WalkCounts {
     uint64_t steps = 0, dps = 0, ins = 0, ab = 0, rh = 0, same = 0, red = 0, claw = 0, full = 0, spin = 0,
              active = 0;
 };
+static_assert(sizeof(WalkCounts) == ST_COUNT * sizeof(uint64_t));
 
-__device__ inline void flush_counts(const WalkDev& wd, WalkCounts& c, bool leader) {
-    if (leader) {
-        atomicAdd(&wd.stats[ST_STEPS], (unsigned long long)c.steps);
-        atomicAdd(&wd.stats[ST_DPS], (unsigned long long)c.dps);
-        atomicAdd(&wd.stats[ST_INSERTS], (unsigned long long)c.ins);
-        atomicAdd(&wd.stats[ST_ABANDONED], (unsigned long long)c.ab);
-        atomicAdd(&wd.stats[ST_ROBIN], (unsigned long long)c.rh);
-        atomicAdd(&wd.stats[ST_SAME], (unsigned long long)c.same);
-        atomicAdd(&wd.stats[ST_REDUCTION], (unsigned long long)c.red);
-        atomicAdd(&wd.stats[ST_CLAWS], (unsigned long long)c.claw);
-        atomicAdd(&wd.stats[ST_FULL], (unsigned long long)c.full);
-        atomicAdd(&wd.stats[ST_SPIN], (unsigned long long)c.spin);
-        atomicAdd(&wd.stats[ST_ACTIVE], (unsigned long long)c.active);
-        c = WalkCounts{};
+// The counts of the block's `groups` walk groups, added to the walks' statistics and cleared; between two
+// barriers.  One addition a block and counter, none of a zero: additions to one address take about 9 ns
+// each whoever makes them, and eleven for every walk group were up to 0.5 ms at the end of every launch
+// (the three enumerations of an n = 3 search of depth 6: 413 us each, now 106; 2^18 walks x 16 steps at
+// n = 4: 3.52 ms, now 3.32).
+__device__ inline void flush_counts(const WalkDev& wd, uint64_t* counts, int groups) {
+    const int f = (int)threadIdx.x;
+    if (f >= ST_COUNT) return;
+    uint64_t sum = 0;
+    for (int g = 0; g < groups; ++g) {
+        sum += counts[g * ST_COUNT + f];
+        counts[g * ST_COUNT + f] = 0;
     }
+    if (sum) atomicAdd(&wd.stats[f], (unsigned long long)sum);
 }
 
 // Events of one evaluation, as bits: advance_walk returns them and the walk group's leader adds
@@ -1588,19 +1587,19 @@ __device__ void walk_block(const SpaceDev& sp, const WalkDev& wd, int iters, Lds
 template <int NQ, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 4) void k_walk(SpaceDev sp, WalkDev wd, int iters) {
     __shared__ Lds<NQ, WAVES> L;
-    // one count slot per walk group (raw storage: a __shared__ object cannot have initialisers)
-    __shared__ __attribute__((aligned(8))) unsigned char s_cnt[WAVES * Geo<NQ>::WPW * sizeof(WalkCounts)];
-    const int lane = threadIdx.x & 63;
-    const bool leader = lane % Geo<NQ>::G == 0;
-    WalkCounts& mine = reinterpret_cast<WalkCounts*>(s_cnt)[(threadIdx.x >> 6) * Geo<NQ>::WPW + lane / Geo<NQ>::G];
+    constexpr int GROUPS = WAVES * Geo<NQ>::WPW;
+    __shared__ uint64_t s_cnt[GROUPS * ST_COUNT];
+    const int group = (int)(threadIdx.x >> 6) * Geo<NQ>::WPW + (int)(threadIdx.x & 63) / Geo<NQ>::G;
+    WalkCounts& mine = reinterpret_cast<WalkCounts*>(s_cnt)[group];
     __shared__ uint32_t s_pair;
     __shared__ Back s_back[NQ == 4 ? 2 * WAVES : 1];
-    if (leader) mine = WalkCounts{};
+    for (int i = threadIdx.x; i < GROUPS * ST_COUNT; i += blockDim.x) s_cnt[i] = 0;
     if (threadIdx.x == 0) s_pair = 0;
     load_lds(L, sp);
     __syncthreads();
     walk_block<NQ, WAVES>(sp, wd, iters, L, blockIdx.x, gridDim.x, mine, &s_pair, s_back);
-    flush_counts(wd, mine, leader);
+    __syncthreads();
+    flush_counts(wd, s_cnt, GROUPS);
 }
 
 // Many members in one persistent launch per qubit count, fed from a device queue: each block takes
@@ -1618,12 +1617,12 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_walk_queue(const SpaceDev* __
     __shared__ Back s_back[NQ == 4 ? 2 * WAVES : 1];
     // the loaded member's event counts so far, one slot per walk group, written by the group's leader
     // as events happen (in registers they would hold 22 more VGPRs through the step and spill)
-    __shared__ __attribute__((aligned(8))) unsigned char s_cnt[WAVES * Geo<NQ>::WPW * sizeof(WalkCounts)];
+    constexpr int GROUPS = WAVES * Geo<NQ>::WPW;
+    __shared__ uint64_t s_cnt[GROUPS * ST_COUNT];
     const int32_t n_items = *count;
-    const int lane = threadIdx.x & 63;
-    const bool leader = lane % Geo<NQ>::G == 0;
-    WalkCounts& mine = reinterpret_cast<WalkCounts*>(s_cnt)[(threadIdx.x >> 6) * Geo<NQ>::WPW + lane / Geo<NQ>::G];
-    if (leader) mine = WalkCounts{};
+    const int group = (int)(threadIdx.x >> 6) * Geo<NQ>::WPW + (int)(threadIdx.x & 63) / Geo<NQ>::G;
+    WalkCounts& mine = reinterpret_cast<WalkCounts*>(s_cnt)[group];
+    for (int i = threadIdx.x; i < GROUPS * ST_COUNT; i += blockDim.x) s_cnt[i] = 0;  // read after the first barrier
     int32_t loaded = -1;
     for (;;) {
         if (threadIdx.x == 0) {
@@ -1640,7 +1639,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_walk_queue(const SpaceDev* __
         // the launch, which __restrict__ tells the compiler, so it may keep or reload them freely)
         const SpaceDev& sp = sps[it.slot];
         if (it.slot != loaded) {
-            if (loaded >= 0) flush_counts(wds[loaded], mine, leader);
+            if (loaded >= 0) flush_counts(wds[loaded], s_cnt, GROUPS);
             load_lds(L, sp);
             loaded = it.slot;
         }
@@ -1648,7 +1647,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_walk_queue(const SpaceDev* __
         walk_block<NQ, WAVES>(sp, wds[it.slot], it.iters, L, it.unit, it.units, mine, &s_pair, s_back);
         __syncthreads();  // s_next and, for the next member, the LDS are rewritten after this
     }
-    if (loaded >= 0) flush_counts(wds[loaded], mine, leader);
+    if (loaded >= 0) flush_counts(wds[loaded], s_cnt, GROUPS);  // the last item's closing barrier is past
 }
 
 __global__ void k_walk_init(SpaceDev sp, WalkDev wd) {
