@@ -2853,8 +2853,8 @@ int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels) {
         const void* A = l == 0 ? m->Xb : m->Hb[l - 1];
         const int K = m->sz[l], N = m->sz[l + 1];
         if (l < m->L - 1) {
-            HIP_TRY(c, tcw::mlp_gemm_nt(2, A, ld8(K), m->Wt[l], ld8(K), b, N, K, m->Z[l], N, m->P + m->b_off[l], nullptr,
-                                        0, m->Hb[l], ld8(N), train ? m->Ht[l] : nullptr, b8, m->part, m->part_floats,
+            HIP_TRY(c, tcw::mlp_gemm_nt(2, A, ld8(K), m->Wt[l], ld8(K), b, N, K, train ? m->Z[l] : nullptr, N,
+                                        m->P + m->b_off[l], nullptr, 0, m->Hb[l], ld8(N), train ? m->Ht[l] : nullptr, b8, m->part, m->part_floats,
                                         c->stream));
         } else {
             HIP_TRY(c, tcw::mlp_gemm_nt(1, A, ld8(K), m->Wt[l], ld8(K), b, N, K, m->logits, N, m->P + m->b_off[l],

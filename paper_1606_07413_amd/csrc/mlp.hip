@@ -17,6 +17,7 @@ namespace tcw {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 namespace {
@@ -46,20 +47,21 @@ __device__ inline bf16x8 load8(const __bf16* __restrict__ p, int ld, int r, int 
     return v;
 }
 
-// The epilogue of one output element v at (gm, gn); tv receives the BF16 value that also goes to the
-// transposed copy.
+// The epilogue of one output element v at (gm, gn), inside M x N; returns the BF16 value that also goes to
+// the transposed copy.  C may be null where only H is wanted (inference needs no Z).
 template <int EPI>
-__device__ inline void epilogue(float v, int gm, int gn, float* __restrict__ C, int ldc,
-                                const float* __restrict__ bias, const float* __restrict__ Zin, int ldz,
-                                __bf16* __restrict__ Hout, int ldh, __bf16& tv) {
+__device__ inline __bf16 epilogue(float v, int gm, int gn, float* __restrict__ C, int ldc,
+                                  const float* __restrict__ bias, const float* __restrict__ Zin, int ldz,
+                                  __bf16* __restrict__ Hout, int ldh) {
     const size_t o = (size_t)gm * ldc + gn;
+    __bf16 tv = (__bf16)0.0f;
     if (EPI == EPI_STORE) {
         C[o] = v;
     } else if (EPI == EPI_BIAS) {
         C[o] = v + bias[gn];
     } else if (EPI == EPI_BIAS_GELU) {
         v += bias[gn];
-        C[o] = v;
+        if (C != nullptr) C[o] = v;
         tv = (__bf16)gelu_f(v);
         Hout[(size_t)gm * ldh + gn] = tv;
     } else {
@@ -68,15 +70,46 @@ __device__ inline void epilogue(float v, int gm, int gn, float* __restrict__ C, 
         tv = (__bf16)v;
         Hout[(size_t)gm * ldh + gn] = tv;
     }
+    return tv;
+}
+
+// The same for the columns gn and gn + 1 (gn, ldc, ldz and ldh even): one store of each kind.
+template <int EPI>
+__device__ inline void epilogue2(float2& v, int gm, int gn, float* __restrict__ C, int ldc,
+                                 const float* __restrict__ bias, const float* __restrict__ Zin, int ldz,
+                                 __bf16* __restrict__ Hout, int ldh) {
+    float2* c = reinterpret_cast<float2*>(C + (size_t)gm * ldc + gn);
+    if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) {
+        v.x += bias[gn];
+        v.y += bias[gn + 1];
+    }
+    if (EPI == EPI_GELU_GRAD) {
+        const float2 z = *reinterpret_cast<const float2*>(Zin + (size_t)gm * ldz + gn);
+        v.x *= gelu_grad_f(z.x);
+        v.y *= gelu_grad_f(z.y);
+    }
+    if (EPI != EPI_BIAS_GELU || C != nullptr) *c = v;
+    if (EPI == EPI_BIAS_GELU || EPI == EPI_GELU_GRAD) {
+        bf16x2 h;
+        h[0] = (__bf16)(EPI == EPI_BIAS_GELU ? gelu_f(v.x) : v.x);
+        h[1] = (__bf16)(EPI == EPI_BIAS_GELU ? gelu_f(v.y) : v.y);
+        *reinterpret_cast<bf16x2*>(Hout + (size_t)gm * ldh + gn) = h;
+        v.x = (float)h[0];
+        v.y = (float)h[1];
+    }
 }
 
 // C[M x N] = A[M x K] B[N x K]^T.  (BM / WM) x (BN / WN) waves of 64 lanes, each computing a WM x WN
 // tile of 32 x 32 MFMA tiles (v_mfma_f32_32x32x16_bf16); K in steps of BK = 64 staged through
-// double-buffered LDS, the next step's 16-byte global loads held in registers while the current step
-// computes.
+// double-buffered LDS, the 16-byte global loads of the next PF = 2 steps held in registers (4 and 6 steps
+// measured the same: the loop is bound by LDS and barriers, not by the loads).
+// Eight wavefronts a block, with tiles that leave two each to every SIMD: one wavefront's GELU or LDS
+// reads fill the other's waits (4096 x 512 x 512: 9.8 us with GELU and 13.9 with the gradient and both
+// copies, with four wavefronts 12.7 and 18.8; 4096 x 512 x 4096 on 128 x 128 tiles 26.1 us, with four 29.0).
 // K split: blockIdx.z = z takes k in [z kchunk, (z + 1) kchunk).  With a workspace `part` every block
 // writes its FP32 partial tile to part[z] and k_splitk_epilogue adds the partials and applies the
-// epilogue; without one (only when gridDim.z = 1) the block applies the epilogue itself.
+// epilogue; without one (only when gridDim.z = 1) the block applies the epilogue itself, its tile passed
+// through LDS so that rows, and rows of the transposed copy, leave in whole segments.
 template <int BM, int BN_, int WM, int WN, int EPI>
 __global__ __launch_bounds__((BM / WM) * (BN_ / WN) * 64) void k_gemm_nt(
     const __bf16* __restrict__ A, int lda, const __bf16* __restrict__ B, int ldb, int M, int N, int K,
@@ -87,8 +120,11 @@ __global__ __launch_bounds__((BM / WM) * (BN_ / WN) * 64) void k_gemm_nt(
     constexpr int RSTEP = NT / 8;                      // rows covered by one vector per thread
     constexpr int AV = BM / RSTEP, BV = BN_ / RSTEP;  // 16-byte vectors per thread per step
     static_assert(BM % RSTEP == 0 && BN_ % RSTEP == 0, "tile rows must be a multiple of threads / 8");
-    __shared__ __attribute__((aligned(16))) __bf16 As[2][BM * LDK];
-    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][BN_ * LDK];
+    constexpr int AS = BM * LDK, BS = BN_ * LDK, LDT = BN_ + 2;
+    static_assert(BM * LDT * 4 <= 2 * (AS + BS) * 2, "the tile has to fit where the operands were");
+    __shared__ __attribute__((aligned(16))) __bf16 smem[2 * (AS + BS)];
+    __bf16* const As = smem;
+    __bf16* const Bs = smem + 2 * AS;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     // Workgroups go to the 8 XCDs in turn (linear id mod 8), each XCD with its own L2.  With the grid's
     // row panels a multiple of 8, ids are remapped so that every tile of one row panel (one slice of A)
@@ -104,28 +140,31 @@ __global__ __launch_bounds__((BM / WM) * (BN_ / WN) * 64) void k_gemm_nt(
     const int kb = blockIdx.z * kchunk, ke = min(K, kb + kchunk);
     const int kv = (t & 7) * 8, r0 = t >> 3;  // this thread's vectors: rows r0 + RSTEP i, k offset kv
     const bool inner_rows = m0 + BM <= M && n0 + BN_ <= N;  // uniform over the block
-    bf16x8 ra[AV], rb[BV];
-    auto gload = [&](int k0) {
+    constexpr int PF = 2;
+    bf16x8 ra[PF][AV], rb[PF][BV];
+    auto gload = [&](int st, int k0) {
         if (inner_rows && k0 + BK <= ke) {
             // the whole step lies inside both operands: plain 16-byte loads
 #pragma unroll
             for (int i = 0; i < AV; ++i)
-                ra[i] = *reinterpret_cast<const bf16x8*>(A + (size_t)(m0 + r0 + RSTEP * i) * lda + k0 + kv);
+                ra[st][i] = *reinterpret_cast<const bf16x8*>(A + (size_t)(m0 + r0 + RSTEP * i) * lda + k0 + kv);
 #pragma unroll
             for (int i = 0; i < BV; ++i)
-                rb[i] = *reinterpret_cast<const bf16x8*>(B + (size_t)(n0 + r0 + RSTEP * i) * ldb + k0 + kv);
+                rb[st][i] = *reinterpret_cast<const bf16x8*>(B + (size_t)(n0 + r0 + RSTEP * i) * ldb + k0 + kv);
         } else {
 #pragma unroll
-            for (int i = 0; i < AV; ++i) ra[i] = load8(A, lda, m0 + r0 + RSTEP * i, k0 + kv, M, ke);
+            for (int i = 0; i < AV; ++i) ra[st][i] = load8(A, lda, m0 + r0 + RSTEP * i, k0 + kv, M, ke);
 #pragma unroll
-            for (int i = 0; i < BV; ++i) rb[i] = load8(B, ldb, n0 + r0 + RSTEP * i, k0 + kv, N, ke);
+            for (int i = 0; i < BV; ++i) rb[st][i] = load8(B, ldb, n0 + r0 + RSTEP * i, k0 + kv, N, ke);
         }
     };
-    auto sstore = [&](int buf) {
+    auto sstore = [&](int st, int buf) {
 #pragma unroll
-        for (int i = 0; i < AV; ++i) *reinterpret_cast<bf16x8*>(&As[buf][(r0 + RSTEP * i) * LDK + kv]) = ra[i];
+        for (int i = 0; i < AV; ++i)
+            *reinterpret_cast<bf16x8*>(&As[buf * AS + (r0 + RSTEP * i) * LDK + kv]) = ra[st][i];
 #pragma unroll
-        for (int i = 0; i < BV; ++i) *reinterpret_cast<bf16x8*>(&Bs[buf][(r0 + RSTEP * i) * LDK + kv]) = rb[i];
+        for (int i = 0; i < BV; ++i)
+            *reinterpret_cast<bf16x8*>(&Bs[buf * BS + (r0 + RSTEP * i) * LDK + kv]) = rb[st][i];
     };
     f32x16 acc[FM][FN];
 #pragma unroll
@@ -137,67 +176,85 @@ __global__ __launch_bounds__((BM / WM) * (BN_ / WN) * 64) void k_gemm_nt(
     // operand fragments: lane l holds row l % 32 of its 32-row tile, k = 8 (l / 32) .. + 7 of each 16
     const int fr = lane & 31, fk = 8 * (lane >> 5);
     const int steps = ke > kb ? (ke - kb + BK - 1) / BK : 0;
-    if (steps > 0) {
-        gload(kb);
-        sstore(0);
-    }
-    __syncthreads();
-    for (int s = 0; s < steps; ++s) {
-        const int buf = s & 1;
-        const bool more = s + 1 < steps;
-        if (more) gload(kb + (s + 1) * BK);
+    static_assert(PF % 2 == 0, "a stage's LDS buffer is its parity");
 #pragma unroll
-        for (int ks = 0; ks < BK; ks += 16) {
-            bf16x8 a[FM], b[FN];
+    for (int st = 0; st < PF; ++st)
+        if (st < steps) gload(st, kb + st * BK);
+    for (int s0 = 0; s0 < steps; s0 += PF) {
 #pragma unroll
-            for (int i = 0; i < FM; ++i)
-                a[i] = *reinterpret_cast<const bf16x8*>(&As[buf][(wm + 32 * i + fr) * LDK + ks + fk]);
+        for (int st = 0; st < PF; ++st) {
+            if (s0 + st >= steps) break;
+            const int buf = st & 1;
+            // the buffer's last readers passed the barrier of the step before this one
+            sstore(st, buf);
+            __syncthreads();
+            if (s0 + st + PF < steps) gload(st, kb + (s0 + st + PF) * BK);
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
-                b[j] = *reinterpret_cast<const bf16x8*>(&Bs[buf][(wn + 32 * j + fr) * LDK + ks + fk]);
+            for (int ks = 0; ks < BK; ks += 16) {
+                bf16x8 a[FM], b[FN];
 #pragma unroll
-            for (int i = 0; i < FM; ++i)
+                for (int i = 0; i < FM; ++i)
+                    a[i] = *reinterpret_cast<const bf16x8*>(&As[buf * AS + (wm + 32 * i + fr) * LDK + ks + fk]);
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+                    b[j] = *reinterpret_cast<const bf16x8*>(&Bs[buf * BS + (wn + 32 * j + fr) * LDK + ks + fk]);
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
         }
-        if (more) sstore(buf ^ 1);
-        __syncthreads();
     }
     // D layout of a 32 x 32 tile: lane l holds column l % 32 and, in value r, row
     // 8 (r / 4) + 4 (l / 32) + r % 4
     if (part == nullptr) {
         // no workspace: the epilogue here (the host passes one whenever K is split)
+        float* tile = reinterpret_cast<float*>(smem);
+        __syncthreads();
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int gn = n0 + wn + 32 * j + fr;
-                if (gn >= N) continue;
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int gm4 = m0 + wm + 32 * i + 8 * q + 4 * (lane >> 5);
-                    __bf16 tv[4] = {(__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f};
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (gm4 + r < M)
-                            epilogue<EPI>(acc[i][j][4 * q + r], gm4 + r, gn, C, ldc, bias, Zin, ldz, Hout, ldh, tv[r]);
-                    if ((EPI == EPI_BIAS_GELU || EPI == EPI_GELU_GRAD) && Tout != nullptr) {
-                        // four consecutive rows of column gn: four consecutive entries of row gn of the transpose
-                        __bf16* tp = Tout + (size_t)gn * ldt + gm4;
-                        if (gm4 + 4 <= M) {
-                            bf16x4 w;
-                            w[0] = tv[0];
-                            w[1] = tv[1];
-                            w[2] = tv[2];
-                            w[3] = tv[3];
-                            *reinterpret_cast<bf16x4*>(tp) = w;
-                        } else {
-                            for (int r = 0; r < 4 && gm4 + r < M; ++r) tp[r] = tv[r];
-                        }
-                    }
-                }
+                for (int r = 0; r < 16; ++r)
+                    tile[(wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * LDT + wn + 32 * j + fr] = acc[i][j][r];
+        __syncthreads();
+        // rows, two columns a lane
+        const bool transposed = (EPI == EPI_BIAS_GELU || EPI == EPI_GELU_GRAD) && Tout != nullptr;
+        const bool even = ((ldc | ldz | ldh) & 1) == 0 && (((uintptr_t)C | (uintptr_t)Zin) & 7) == 0;
+        constexpr int LPR = BN_ / 2;
+        const int col = 2 * (t % LPR), gn = n0 + col;
+        for (int row = t / LPR; row < BM; row += NT / LPR) {
+            const int gm = m0 + row;
+            if (gm >= M) break;
+            float2& at = *reinterpret_cast<float2*>(&tile[row * LDT + col]);
+            float2 v = at;
+            if (even && gn + 1 < N) {
+                epilogue2<EPI>(v, gm, gn, C, ldc, bias, Zin, ldz, Hout, ldh);
+            } else {
+                if (gn < N) v.x = (float)epilogue<EPI>(v.x, gm, gn, C, ldc, bias, Zin, ldz, Hout, ldh);
+                if (gn + 1 < N) v.y = (float)epilogue<EPI>(v.y, gm, gn + 1, C, ldc, bias, Zin, ldz, Hout, ldh);
             }
+            if (transposed) at = v;
+        }
+        if (!transposed) return;
+        __syncthreads();
+        // rows of the transpose, four of its entries a lane (Tout's rows start 16-byte aligned)
+        constexpr int LPC = BM / 4;
+        const int row = 4 * (t % LPC);
+        for (int c = t / LPC; c < BN_; c += NT / LPC) {
+            if (n0 + c >= N) break;
+            __bf16* tp = Tout + (size_t)(n0 + c) * ldt + m0 + row;
+            bf16x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = (__bf16)tile[(row + e) * LDT + c];
+            if (m0 + row + 4 <= M) {
+                *reinterpret_cast<bf16x4*>(tp) = w;
+            } else {
+                for (int e = 0; e < 4 && m0 + row + e < M; ++e) tp[e] = w[e];
+            }
+        }
         return;
     }
     // split K: this block's partial tile
@@ -247,7 +304,7 @@ __global__ __launch_bounds__(256) void k_splitk_epilogue(const float* __restrict
                 v += a3;
             }
             for (; z < splits; ++z) v += p[(size_t)z * mn];
-            epilogue<EPI>(v, gm, gn, C, ldc, bias, Zin, ldz, Hout, ldh, tv);
+            tv = epilogue<EPI>(v, gm, gn, C, ldc, bias, Zin, ldz, Hout, ldh);
         }
         tile[rr][tx] = tv;
     }
@@ -443,7 +500,7 @@ int cu_count() {
     return cus;
 }
 
-// Tiles of 128 x 128 (four waves of 64 x 64) for the long products with many rows (M and K at least
+// Tiles of 128 x 128 (eight waves of 64 x 32) for the long products with many rows (M and K at least
 // 2048), where the larger tile's operand reuse pays; else 64 x 128.  With fewer rows or a short K the
 // 128 x 128 grid needs a deeper K split to fill the CUs, and its partials (written, then read back by
 // the split sum) cost more than the smaller tile loses: on MI355X the 4096 x 512 x 512 products and the
@@ -472,10 +529,7 @@ hipError_t gemm_nt_t(const __bf16* A, int lda, const __bf16* B, int ldb, int M, 
                      size_t part_floats, hipStream_t s) {
     if (M <= 0 || N <= 0) return hipSuccess;
     int splits = splits_of(M, N, K);
-    // an epilogue with a transposed BF16 copy always goes through the partial-sum kernel, which
-    // transposes through LDS (stored from the MFMA layout, each lane would write its own row of T)
-    const bool transposed = (EPI == EPI_BIAS_GELU || EPI == EPI_GELU_GRAD) && T != nullptr;
-    bool via_part = splits > 1 || transposed;
+    bool via_part = splits > 1;
     if (via_part && (part == nullptr || part_floats < (size_t)splits * M * N)) {
         splits = 1;  // no workspace: one workgroup per tile, epilogue in the GEMM
         via_part = false;
@@ -483,11 +537,11 @@ hipError_t gemm_nt_t(const __bf16* A, int lda, const __bf16* B, int ldb, int M, 
     const int kchunk = ((K + splits - 1) / splits + BK - 1) / BK * BK;
     if (big_tiles(M, N, K)) {
         dim3 grid((N + BN - 1) / BN, (M + 127) / 128, splits);
-        hipLaunchKernelGGL((k_gemm_nt<128, BN, 64, 64, EPI>), grid, dim3(256), 0, s, A, lda, B, ldb, M, N, K, C, ldc,
+        hipLaunchKernelGGL((k_gemm_nt<128, BN, 64, 32, EPI>), grid, dim3(512), 0, s, A, lda, B, ldb, M, N, K, C, ldc,
                            bias, Z, ldz, H, ldh, T, ldt, kchunk, via_part ? part : nullptr);
     } else {
         dim3 grid((N + BN - 1) / BN, (M + 63) / 64, splits);
-        hipLaunchKernelGGL((k_gemm_nt<64, BN, 32, 64, EPI>), grid, dim3(256), 0, s, A, lda, B, ldb, M, N, K, C, ldc,
+        hipLaunchKernelGGL((k_gemm_nt<64, BN, 32, 32, EPI>), grid, dim3(512), 0, s, A, lda, B, ldb, M, N, K, C, ldc,
                            bias, Z, ldz, H, ldh, T, ldt, kchunk, via_part ? part : nullptr);
     }
     if (via_part) {
@@ -503,7 +557,7 @@ hipError_t gemm_nt_t(const __bf16* A, int lda, const __bf16* B, int ldb, int M, 
 }  // namespace
 
 size_t mlp_gemm_part_floats(int M, int N, int K) {
-    // splits x M x N partials; M x N when unsplit (epilogues with a transposed copy)
+    // splits x M x N partials; M x N when unsplit, which serves the split products of smaller batches
     return (size_t)splits_of(M, N, K) * M * N;
 }
 
