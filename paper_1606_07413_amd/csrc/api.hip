@@ -2790,6 +2790,30 @@ namespace {
 // leading dimension of a bf16 buffer: a multiple of 8 elements, so every row starts 16-byte aligned
 int ld8(int cols) { return (cols + 7) / 8 * 8; }
 
+// the layers with the buffers that they have now
+tcw::MlpLayers mlp_layers(const tcw_mlp* m) {
+    tcw::MlpLayers net{};
+    net.count = m->L;
+    for (int l = 0; l < m->L; ++l) {
+        const int in = m->sz[l], out = m->sz[l + 1];
+        tcw::MlpLayer& y = net.l[l];
+        y.g = m->Gf.empty() ? nullptr : m->Gf[l];
+        y.db = m->G + m->b_off[l];
+        y.wb = m->Wb[l];
+        y.wt = m->Wt[l];
+        y.w = m->w_off[l];
+        y.in = in;
+        y.out = out;
+        y.ldb = ld8(out);
+        y.ldt = ld8(in);
+        y.tile0 = net.tiles;
+        y.strip0 = net.strips;
+        net.tiles += ((in + 1 + 31) / 32) * ((out + 31) / 32);
+        net.strips += (out + 63) / 64;
+    }
+    return net;
+}
+
 int mlp_ensure_batch(tcw_mlp* m, int b) {
     tcw_ctx* c = m->ctx;
     if (b <= m->cap_b) return TCW_OK;
@@ -2818,11 +2842,11 @@ int mlp_ensure_batch(tcw_mlp* m, int b) {
     HIP_TRY(c, hipMalloc(&m->probs, (size_t)b * m->classes * 4));
     // workspace of the split products (forward b x out, K = in; dX b x in, K = out; dW in x out, K = b) and
     // of the bias gradients' column sums
-    size_t part = 0;
+    size_t part = tcw::mlp_colsum_part_floats(b, mlp_layers(m));
     for (int l = 0; l < m->L; ++l) {
         const int in = m->sz[l], out = m->sz[l + 1];
         part = std::max({part, tcw::mlp_gemm_part_floats(b, out, in), tcw::mlp_gemm_part_floats(b, in, out),
-                         tcw::mlp_gemm_part_floats(in, out, b), tcw::mlp_colsum_part_floats(b, out)});
+                         tcw::mlp_gemm_part_floats(in, out, b)});
     }
     if (part > 0) {
         HIP_TRY(c, hipMalloc(&m->part, part * 4));
@@ -2840,32 +2864,39 @@ int mlp_sync_bf16(tcw_mlp* m) {
     return TCW_OK;
 }
 
-// forward over a batch; with labels (training) also the transposed activations, the loss sum and the
-// output-layer gradient
-int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels) {
+// forward over a batch to probs (batch x classes); with labels (training) also the transposed activations, the
+// loss sum and the output-layer gradient
+int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels, float* probs) {
     tcw_ctx* c = m->ctx;
     int rc = mlp_ensure_batch(m, b);
     if (rc) return rc;
     const bool train = labels != nullptr;
     const int b8 = ld8(b);
+    if (probs == nullptr) probs = m->probs;
     HIP_TRY(c, tcw::mlp_input_bf16(x, b, m->inp, m->Xb, ld8(m->inp), train ? m->Xt : nullptr, b8, c->stream));
+    if (train) HIP_TRY(c, hipMemsetAsync(m->loss, 0, 4, c->stream));
     for (int l = 0; l < m->L; ++l) {
         const void* A = l == 0 ? m->Xb : m->Hb[l - 1];
         const int K = m->sz[l], N = m->sz[l + 1];
+        const float* bias = m->P + m->b_off[l];
         if (l < m->L - 1) {
-            HIP_TRY(c, tcw::mlp_gemm_nt(2, A, ld8(K), m->Wt[l], ld8(K), b, N, K, train ? m->Z[l] : nullptr, N,
-                                        m->P + m->b_off[l], nullptr, 0, m->Hb[l], ld8(N), train ? m->Ht[l] : nullptr, b8, m->part, m->part_floats,
-                                        c->stream));
+            HIP_TRY(c, tcw::mlp_gemm_nt(2, A, ld8(K), m->Wt[l], ld8(K), b, N, K, train ? m->Z[l] : nullptr, N, bias,
+                                        nullptr, 0, m->Hb[l], ld8(N), train ? m->Ht[l] : nullptr, b8, m->part,
+                                        m->part_floats, c->stream));
+            continue;
+        }
+        float* g = train ? m->Gf[l] : nullptr;
+        void *gb = train ? m->Gb[l] : nullptr, *gt = train ? m->Gt[l] : nullptr;
+        float* loss = train ? m->loss : nullptr;
+        if (tcw::mlp_head_fits(N)) {
+            HIP_TRY(c, tcw::mlp_head(A, ld8(K), m->Wt[l], ld8(K), b, N, K, bias, labels, probs, g, gb, ld8(N), gt, b8,
+                                     loss, c->stream));
         } else {
-            HIP_TRY(c, tcw::mlp_gemm_nt(1, A, ld8(K), m->Wt[l], ld8(K), b, N, K, m->logits, N, m->P + m->b_off[l],
-                                        nullptr, 0, nullptr, 0, nullptr, 0, m->part, m->part_floats, c->stream));
+            HIP_TRY(c, tcw::mlp_gemm_nt(1, A, ld8(K), m->Wt[l], ld8(K), b, N, K, m->logits, N, bias, nullptr, 0, nullptr,
+                                        0, nullptr, 0, m->part, m->part_floats, c->stream));
+            HIP_TRY(c, tcw::mlp_softmax_ce(m->logits, labels, b, N, probs, g, gb, ld8(N), gt, b8, loss, c->stream));
         }
     }
-    if (train) HIP_TRY(c, hipMemsetAsync(m->loss, 0, 4, c->stream));
-    const int lo = m->L - 1;
-    HIP_TRY(c, tcw::mlp_softmax_ce(m->logits, labels, b, m->classes, m->probs, train ? m->Gf[lo] : nullptr,
-                                   train ? m->Gb[lo] : nullptr, ld8(m->classes), train ? m->Gt[lo] : nullptr, b8,
-                                   train ? m->loss : nullptr, c->stream));
     return TCW_OK;
 }
 
@@ -2878,7 +2909,6 @@ int mlp_backward(tcw_mlp* m, int b) {
         // dW_l = H_in^T G_l: rows of H_in^T and of G_l^T run over the batch
         HIP_TRY(c, tcw::mlp_gemm_nt(0, Hin_t, b8, m->Gt[l], b8, in, out, b, m->G + m->w_off[l], out, nullptr, nullptr,
                                     0, nullptr, 0, nullptr, 0, m->part, m->part_floats, c->stream));
-        HIP_TRY(c, tcw::mlp_colsum(m->Gf[l], b, out, m->G + m->b_off[l], m->part, m->part_floats, c->stream));
         if (l > 0) {
             // G_{l-1} = (G_l W_l^T) * gelu'(Z_{l-1}): B = W_l (in x out), rows over out
             HIP_TRY(c, tcw::mlp_gemm_nt(3, m->Gb[l], ld8(out), m->Wb[l], ld8(out), b, in, out, m->Gf[l - 1], in,
@@ -2886,6 +2916,7 @@ int mlp_backward(tcw_mlp* m, int b) {
                                         m->part_floats, c->stream));
         }
     }
+    HIP_TRY(c, tcw::mlp_colsum(mlp_layers(m), b, m->part, m->part_floats, c->stream));
     return TCW_OK;
 }
 
@@ -2989,10 +3020,8 @@ extern "C" int tcw_mlp_set_params(tcw_mlp* m, const float* host) {
 
 extern "C" int tcw_mlp_forward(tcw_mlp* m, const float* x, int batch, float* probs) {
     if (!m || !x || !probs || batch < 1) return TCW_EINVAL;
-    int rc = mlp_forward(m, x, batch, nullptr);
+    int rc = mlp_forward(m, x, batch, nullptr, probs);
     if (rc) return rc;
-    HIP_TRY(m->ctx, hipMemcpyAsync(probs, m->probs, (size_t)batch * m->classes * 4, hipMemcpyDeviceToDevice,
-                                   m->ctx->stream));
     HIP_TRY(m->ctx, hipStreamSynchronize(m->ctx->stream));
     return TCW_OK;
 }
@@ -3000,7 +3029,7 @@ extern "C" int tcw_mlp_forward(tcw_mlp* m, const float* x, int batch, float* pro
 extern "C" int tcw_mlp_gradients(tcw_mlp* m, const float* x, const int32_t* labels, int batch, float* grads_host,
                                  float* loss) {
     if (!m || !x || !labels || batch < 1) return TCW_EINVAL;
-    int rc = mlp_forward(m, x, batch, labels);
+    int rc = mlp_forward(m, x, batch, labels, nullptr);
     if (!rc) rc = mlp_backward(m, batch);
     if (rc) return rc;
     float ls = 0;
@@ -3013,13 +3042,11 @@ extern "C" int tcw_mlp_gradients(tcw_mlp* m, const float* x, const int32_t* labe
 
 extern "C" int tcw_mlp_train_step(tcw_mlp* m, const float* x, const int32_t* labels, int batch, float lr, float* loss) {
     if (!m || !x || !labels || batch < 1 || !(lr > 0)) return TCW_EINVAL;
-    int rc = mlp_forward(m, x, batch, labels);
+    int rc = mlp_forward(m, x, batch, labels, nullptr);
     if (!rc) rc = mlp_backward(m, batch);
     if (rc) return rc;
     m->step++;
-    HIP_TRY(m->ctx, tcw::mlp_adam(m->P, m->G, m->M, m->V, m->count, lr, 0.9f, 0.999f, 1e-8f, m->step, m->ctx->stream));
-    rc = mlp_sync_bf16(m);
-    if (rc) return rc;
+    HIP_TRY(m->ctx, tcw::mlp_adam(mlp_layers(m), m->P, m->G, m->M, m->V, lr, 0.9f, 0.999f, 1e-8f, m->step, m->ctx->stream));
     if (loss) {
         float ls = 0;
         HIP_TRY(m->ctx, hipMemcpyAsync(&ls, m->loss, 4, hipMemcpyDeviceToHost, m->ctx->stream));
@@ -3089,7 +3116,7 @@ extern "C" int tcw_mlp_depth_order(tcw_mlp* m, const tcw_target* t, int k_max, c
     if (R * R != m->inp) return fail(c, TCW_EINVAL, "network input size does not match the target");
     if (!m->xdev) HIP_TRY(c, hipMalloc(&m->xdev, (size_t)m->inp * 4));
     int rc = tcw_features(c, t, m->xdev);
-    if (!rc) rc = mlp_forward(m, m->xdev, 1, nullptr);
+    if (!rc) rc = mlp_forward(m, m->xdev, 1, nullptr, nullptr);
     if (rc) return rc;
     std::vector<float> p(m->classes);
     HIP_TRY(c, hipMemcpyAsync(p.data(), m->probs, m->classes * 4, hipMemcpyDeviceToHost, c->stream));

@@ -196,6 +196,20 @@ hipError_t pack_phi_i32(int n, const int32_t* a, const int32_t* b, int64_t count
                         int* flag_dev, hipStream_t s);
 
 // ---- depth-order network (mlp.hip) ----
+// The layers of a network for the kernels that take all of them: layer l's (in + 1) x out parameters (weights,
+// then bias) start at w, in 32 x 32 tiles tile0 .. of the launch; its columns are the strips strip0 .. of 64.
+constexpr int MLP_LAYERS_MAX = 17;
+struct MlpLayer {
+    const float* g;  // output gradient, batch x out fp32
+    float* db;       // bias gradient
+    void *wb, *wt;   // bf16 weights, in x out (ld ldb) and out x in (ld ldt)
+    int64_t w;
+    int in, out, ldb, ldt, tile0, strip0;
+};
+struct MlpLayers {
+    int count, tiles, strips;
+    MlpLayer l[MLP_LAYERS_MAX];
+};
 // C = A B^T: A (M x K) and B (N x K) bf16 with K-contiguous rows (leading dimensions multiples of 8),
 // FP32 accumulation.  epi 0: C = acc; 1: C = acc + bias; 2: C = Z = acc + bias, H = gelu(Z) (bf16, ld
 // ldh) and, if T != null, T = H^T (bf16, ld ldt); 3: C = acc * gelu'(Z) (Z fp32, ld ldz), H = C (bf16),
@@ -204,22 +218,27 @@ hipError_t pack_phi_i32(int n, const int32_t* a, const int32_t* b, int64_t count
 // summed in a fixed order; with a smaller workspace one workgroup takes each tile.  Products on one
 // stream may share the workspace.
 size_t mlp_gemm_part_floats(int M, int N, int K);
-// workspace floats of mlp_colsum over a rows x cols matrix
-size_t mlp_colsum_part_floats(int rows, int cols);
 hipError_t mlp_gemm_nt(int epi, const void* A, int lda, const void* B, int ldb, int M, int N, int K, float* C, int ldc,
                        const float* bias, const float* Z, int ldz, void* H, int ldh, void* T, int ldt, float* part,
                        size_t part_floats, hipStream_t s);
 // probabilities, loss sum and G = (p - onehot) / batch (fp32; bf16 with ld ldgb; transposed bf16 if gt)
 hipError_t mlp_softmax_ce(const float* logits, const int32_t* labels, int batch, int classes, float* probs, float* g,
                           void* gb, int ldgb, void* gt, int ldgt, float* loss_sum, hipStream_t s);
-// out[c] = sum over rows of g[r][c], in a fixed order; part: mlp_colsum_part_floats(rows, cols) floats
-hipError_t mlp_colsum(const float* g, int rows, int cols, float* out, float* part, size_t part_floats,
-                      hipStream_t s);
+// the output layer's product and mlp_softmax_ce in one kernel, for classes that mlp_head_fits: A (M x K), B
+// (N x K) and bias as in mlp_gemm_nt, N classes
+bool mlp_head_fits(int classes);
+hipError_t mlp_head(const void* A, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
+                    const int32_t* labels, float* probs, float* g, void* gb, int ldgb, void* gt, int ldgt,
+                    float* loss_sum, hipStream_t s);
+// every layer's db[c] = sum over rows of g[r][c], in a fixed order; part: mlp_colsum_part_floats floats
+size_t mlp_colsum_part_floats(int rows, const MlpLayers& net);
+hipError_t mlp_colsum(const MlpLayers& net, int rows, float* part, size_t part_floats, hipStream_t s);
 // x (rows x cols fp32) -> bf16 (ld ldy) and, if t != null, its transpose (ld ldt)
 hipError_t mlp_input_bf16(const float* x, int rows, int cols, void* y, int ldy, void* t, int ldt, hipStream_t s);
 // W (rows x cols fp32) -> bf16 W (ld ldb) and bf16 W^T (ld ldt)
 hipError_t mlp_weights_bf16(const float* w, int rows, int cols, void* wb, int ldb, void* wt, int ldt, hipStream_t s);
-hipError_t mlp_adam(float* p, const float* g, float* m, float* v, int64_t count, float lr, float b1, float b2,
+// one Adam step on every parameter, and the weights' bf16 copies
+hipError_t mlp_adam(const MlpLayers& net, float* p, const float* g, float* m, float* v, float lr, float b1, float b2,
                     float eps, int step, hipStream_t s);
 hipError_t mlp_init(float* w, int64_t count, int64_t index0, int fan_in, uint64_t seed, hipStream_t s);
 

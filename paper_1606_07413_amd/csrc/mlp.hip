@@ -12,6 +12,7 @@
 #include <stdint.h>
 
 #include "common.h"
+#include "internal.h"
 
 namespace tcw {
 
@@ -343,19 +344,114 @@ __global__ void k_softmax_ce(const float* logits, const int32_t* labels, int bat
     if (loss_sum && y >= 0 && y < classes) atomicAdd(loss_sum, -(z[y] - m - logf(s)));
 }
 
-// column sums: db[n] = sum_i G[i][n]
-// Column sums of g (rows x cols, row-major) in a fixed order.  k_colsum_part: a block covers 64
-// columns x a slab of COLSUM_SLAB = 64 rows; its four groups of 64 threads each load 16 consecutive
-// rows of one column at once (coalesced across the columns), sum them in row order, and the four
-// group sums are added in group order.  k_colsum_fin adds the slab sums the same way (four groups
-// of consecutive slabs, then the groups in order).
+// The output layer of at most 32 classes in one kernel: logits = A B^T + bias (A: M x K, B: N x K), then
+// k_softmax_ce's outputs.  A block takes 32 rows, its wavefront z the k of the product's split z in the
+// order of k_gemm_nt, the splits' partial logits meet in LDS and are added in order: the same logits as
+// from k_gemm_nt and k_splitk_epilogue, bit for bit.  With 11 classes the 64 x 128 tiles were nine tenths
+// padding; 4096 x 512: 7.5 us, as three kernels 18 (23 with the gradient's outputs).
+constexpr int HEAD_ROWS = 32, HEAD_MAX = 32, HEAD_LD = HEAD_MAX + 1, HEAD_SPLITS = 16;
+__global__ __launch_bounds__(HEAD_SPLITS * 64) void k_head(const __bf16* __restrict__ A, int lda,
+                                                           const __bf16* __restrict__ B, int ldb, int M, int N, int K,
+                                                           int kchunk, const float* __restrict__ bias,
+                                                           const int32_t* __restrict__ labels, float* __restrict__ probs,
+                                                           float* __restrict__ g, __bf16* __restrict__ gb, int ldgb,
+                                                           __bf16* __restrict__ gt, int ldgt, float* loss_sum) {
+    __shared__ float red[HEAD_SPLITS][HEAD_ROWS * HEAD_LD];
+    const int lane = threadIdx.x & 63, z = threadIdx.x >> 6, splits = blockDim.x >> 6;
+    const int m0 = blockIdx.x * HEAD_ROWS;
+    const int fr = lane & 31, fk = 8 * (lane >> 5);
+    const int kb = z * kchunk, ke = min(K, kb + kchunk);
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    // rows past the last one repeat it: their sums are not looked at
+    const __bf16* ap = A + (size_t)min(m0 + fr, M - 1) * lda + fk;
+    const __bf16* bp = B + (size_t)min(fr, N - 1) * ldb + fk;
+    int k = kb;
+    // eight steps' loads together: taken step by step, each waited for its own
+    for (; k + 128 <= ke; k += 128) {
+        bf16x8 a[8], b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            a[u] = *reinterpret_cast<const bf16x8*>(ap + k + 16 * u);
+            b[u] = *reinterpret_cast<const bf16x8*>(bp + k + 16 * u);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u], b[u], acc, 0, 0, 0);
+    }
+    for (; k + 16 <= ke; k += 16)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(ap + k),
+                                                      *reinterpret_cast<const bf16x8*>(bp + k), acc, 0, 0, 0);
+    if (k < ke)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load8(A, lda, m0 + fr, k + fk, M, ke),
+                                                      load8(B, ldb, fr, k + fk, N, ke), acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[z][(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * HEAD_LD + fr] = acc[r];
+    __syncthreads();
+    for (int i = threadIdx.x; i < HEAD_ROWS * HEAD_MAX; i += blockDim.x) {
+        const int o = (i >> 5) * HEAD_LD + (i & 31);
+        if ((i & 31) >= N) continue;
+        float v = 0.f;
+        for (int y = 0; y < splits; ++y) v += red[y][o];
+        red[0][o] = v + bias[i & 31];
+    }
+    __syncthreads();
+    const int i = m0 + (int)threadIdx.x;
+    if (threadIdx.x >= HEAD_ROWS) return;
+    float loss = 0.f;
+    if (i < M) {
+        float* l = &red[0][threadIdx.x * HEAD_LD];
+        float m = l[0];
+        for (int c = 1; c < N; ++c) m = fmaxf(m, l[c]);
+        const int y = labels ? labels[i] : -1;
+        const float zy = y >= 0 && y < N ? l[y] : 0.f;
+        float s = 0.f;
+        for (int c = 0; c < N; ++c) {
+            const float e = expf(l[c] - m);
+            l[c] = e;
+            s += e;
+        }
+        for (int c = 0; c < N; ++c) {
+            const float p = l[c] / s;
+            if (probs) probs[(size_t)i * N + c] = p;
+            if (g) {
+                const float gv = (p - (c == y ? 1.f : 0.f)) / (float)M;
+                g[(size_t)i * N + c] = gv;
+                gb[(size_t)i * ldgb + c] = (__bf16)gv;
+                if (gt) gt[(size_t)c * ldgt + i] = (__bf16)gv;
+            }
+        }
+        if (y >= 0 && y < N) loss = -(zy - m - logf(s));
+    }
+    if (loss_sum == nullptr) return;
+    // one addition a block (additions to one address take about 9 ns each)
+#pragma unroll
+    for (int d = HEAD_ROWS / 2; d >= 1; d >>= 1) loss += __shfl_down(loss, d, HEAD_ROWS);
+    if (threadIdx.x == 0) atomicAdd(loss_sum, loss);
+}
+
+// Column sums of every layer's G (rows x out, row-major) in a fixed order: the bias gradients, in two
+// launches for the whole network (two for each layer left 15 us between them at batch 4096).
+// k_colsum_part: a block covers 64 columns x a slab of COLSUM_SLAB = 64 rows; its four groups of 64
+// threads each load 16 consecutive rows of one column at once (coalesced across the columns), sum them
+// in row order, and the four group sums are added in group order.  k_colsum_fin adds the slab sums the
+// same way (four groups of consecutive slabs, then the groups in order).  A layer's columns are the strips
+// strip0 .. of 64 and the columns 64 strip0 .. of part.
 constexpr int COLSUM_SLAB = 64;
 
-__global__ __launch_bounds__(256) void k_colsum_part(const float* __restrict__ g, int rows, int cols,
-                                                     float* __restrict__ part) {
+__device__ inline const MlpLayer& layer_of_strip(const MlpLayers& net, int strip) {
+    int l = 0;
+    while (l + 1 < net.count && strip >= net.l[l + 1].strip0) ++l;
+    return net.l[l];
+}
+
+__global__ __launch_bounds__(256) void k_colsum_part(MlpLayers net, int rows, float* __restrict__ part) {
     __shared__ float red[4][64];
-    const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-    const int col = blockIdx.x * 64 + lane, r0 = blockIdx.y * COLSUM_SLAB + grp * 16;
+    const MlpLayer& y = layer_of_strip(net, (int)blockIdx.x);
+    const float* __restrict__ g = y.g;
+    const int cols = y.out, lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+    const int col = ((int)blockIdx.x - y.strip0) * 64 + lane, r0 = blockIdx.y * COLSUM_SLAB + grp * 16;
     float a[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) a[i] = (col < cols && r0 + i < rows) ? g[(size_t)(r0 + i) * cols + col] : 0.f;
@@ -364,31 +460,32 @@ __global__ __launch_bounds__(256) void k_colsum_part(const float* __restrict__ g
     for (int i = 0; i < 16; ++i) sum += a[i];
     red[grp][lane] = sum;
     __syncthreads();
-    if (grp == 0 && col < cols)
-        part[(size_t)blockIdx.y * cols + col] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+    if (grp == 0)
+        part[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 64 + lane] =
+            ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
-__global__ __launch_bounds__(256) void k_colsum_fin(const float* __restrict__ part, int slabs, int cols,
-                                                    float* __restrict__ out) {
+__global__ __launch_bounds__(256) void k_colsum_fin(MlpLayers net, const float* __restrict__ part, int slabs) {
     __shared__ float red[4][64];
+    const MlpLayer& y = layer_of_strip(net, (int)blockIdx.x);
     const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-    const int col = blockIdx.x * 64 + lane;
+    const int col = ((int)blockIdx.x - y.strip0) * 64 + lane;
     const int per = (slabs + 3) / 4, z0 = grp * per, z1 = min(slabs, z0 + per);
+    const size_t ld = (size_t)gridDim.x * 64;
+    const float* mine = part + (size_t)blockIdx.x * 64 + lane;
     float sum = 0.f;
-    if (col < cols) {
-        int z = z0;
-        for (; z + 8 <= z1; z += 8) {
-            float a[8];
+    int z = z0;
+    for (; z + 8 <= z1; z += 8) {
+        float a[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = part[(size_t)(z + i) * cols + col];
+        for (int i = 0; i < 8; ++i) a[i] = mine[(size_t)(z + i) * ld];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sum += a[i];
-        }
-        for (; z < z1; ++z) sum += part[(size_t)z * cols + col];
+        for (int i = 0; i < 8; ++i) sum += a[i];
     }
+    for (; z < z1; ++z) sum += mine[(size_t)z * ld];
     red[grp][lane] = sum;
     __syncthreads();
-    if (grp == 0 && col < cols) out[col] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+    if (grp == 0 && col < y.out) y.db[col] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
 // x (rows x cols fp32, ld cols) -> y (bf16, ld ldy) and, if t != null, its transpose (cols x rows, ld
@@ -463,16 +560,43 @@ __global__ __launch_bounds__(256) void k_weights_bf16(const float* __restrict__ 
     }
 }
 
-// Adam (Kingma & Ba 2015) on the FP32 master copy
-__global__ void k_adam(float* p, const float* g, float* m, float* v, int64_t count, float lr, float b1, float b2,
-                       float eps, float c1, float c2) {
-    for (int64_t i = threadIdx.x + (int64_t)blockIdx.x * blockDim.x; i < count; i += (int64_t)blockDim.x * gridDim.x) {
+// Adam (Kingma & Ba 2015) on the FP32 master copy and the new weights' BF16 copies in both orientations, all
+// layers in one launch: 32 x 32 tiles of each layer's (in + 1) x out parameters, the last row its bias.
+// Bound by memory (seven words a parameter); with the copies from a pass of their own for each layer the
+// 2.6 million parameters of the 4096 -> 512 x 3 -> 11 network took 16 + 17 us, now 22.
+__global__ __launch_bounds__(256) void k_adam(MlpLayers net, float* __restrict__ p, const float* __restrict__ g,
+                                              float* __restrict__ m, float* __restrict__ v, float lr, float b1,
+                                              float b2, float eps, float c1, float c2) {
+    __shared__ __bf16 tile[32][33];
+    int l = 0;
+    while (l + 1 < net.count && (int)blockIdx.x >= net.l[l + 1].tile0) ++l;
+    const MlpLayer& y = net.l[l];
+    const int across = (y.out + 31) / 32, at = (int)blockIdx.x - y.tile0;
+    const int c0 = at % across * 32, r0 = at / across * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    __bf16* wb = (__bf16*)y.wb;
+    __bf16* wt = (__bf16*)y.wt;
+#pragma unroll
+    for (int rr = ty; rr < 32; rr += 8) {
+        const int r = r0 + rr, c = c0 + tx;
+        if (r > y.in || c >= y.out) continue;
+        const int64_t i = y.w + (int64_t)r * y.out + c;
         const float gi = g[i];
         const float mi = b1 * m[i] + (1.f - b1) * gi;
         const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
         m[i] = mi;
         v[i] = vi;
-        p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+        const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+        p[i] = pi;
+        if (r == y.in) continue;
+        tile[rr][tx] = (__bf16)pi;
+        wb[(size_t)r * y.ldb + c] = (__bf16)pi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int cc = ty; cc < 32; cc += 8) {
+        const int c = c0 + cc, r = r0 + tx;
+        if (c < y.out && r < y.in) wt[(size_t)c * y.ldt + r] = tile[tx][cc];
     }
 }
 
@@ -561,9 +685,9 @@ size_t mlp_gemm_part_floats(int M, int N, int K) {
     return (size_t)splits_of(M, N, K) * M * N;
 }
 
-size_t mlp_colsum_part_floats(int rows, int cols) {
-    return (size_t)((rows + COLSUM_SLAB - 1) / COLSUM_SLAB) * cols;
-}
+static int colsum_slabs(int rows) { return (rows + COLSUM_SLAB - 1) / COLSUM_SLAB; }
+
+size_t mlp_colsum_part_floats(int rows, const MlpLayers& net) { return (size_t)colsum_slabs(rows) * net.strips * 64; }
 
 hipError_t mlp_gemm_nt(int epi, const void* A, int lda, const void* B, int ldb, int M, int N, int K, float* C, int ldc,
                        const float* bias, const float* Z, int ldz, void* H, int ldh, void* T, int ldt, float* part,
@@ -596,14 +720,27 @@ hipError_t mlp_softmax_ce(const float* logits, const int32_t* labels, int batch,
     return hipGetLastError();
 }
 
-hipError_t mlp_colsum(const float* g, int rows, int cols, float* out, float* part, size_t part_floats,
-                      hipStream_t s) {
-    if (rows <= 0 || cols <= 0) return hipSuccess;
-    const int slabs = (rows + COLSUM_SLAB - 1) / COLSUM_SLAB;
-    if (part == nullptr || part_floats < (size_t)slabs * cols) return hipErrorInvalidValue;
-    const unsigned strips = (unsigned)((cols + 63) / 64);
-    hipLaunchKernelGGL(k_colsum_part, dim3(strips, (unsigned)slabs), dim3(256), 0, s, g, rows, cols, part);
-    hipLaunchKernelGGL(k_colsum_fin, dim3(strips), dim3(256), 0, s, part, slabs, cols, out);
+hipError_t mlp_head(const void* A, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
+                    const int32_t* labels, float* probs, float* g, void* gb, int ldgb, void* gt, int ldgt,
+                    float* loss_sum, hipStream_t s) {
+    if (M <= 0) return hipSuccess;
+    if (N < 1 || N > HEAD_MAX) return hipErrorInvalidValue;
+    const int splits = splits_of(M, N, K);
+    const int kchunk = ((K + splits - 1) / splits + BK - 1) / BK * BK;
+    hipLaunchKernelGGL(k_head, dim3((M + HEAD_ROWS - 1) / HEAD_ROWS), dim3(64 * splits), 0, s, (const __bf16*)A, lda,
+                       (const __bf16*)B, ldb, M, N, K, kchunk, bias, labels, probs, g, (__bf16*)gb, ldgb, (__bf16*)gt,
+                       ldgt, loss_sum);
+    return hipGetLastError();
+}
+
+bool mlp_head_fits(int classes) { return classes <= HEAD_MAX; }
+
+hipError_t mlp_colsum(const MlpLayers& net, int rows, float* part, size_t part_floats, hipStream_t s) {
+    if (rows <= 0) return hipSuccess;
+    if (part == nullptr || part_floats < mlp_colsum_part_floats(rows, net)) return hipErrorInvalidValue;
+    const int slabs = colsum_slabs(rows);
+    hipLaunchKernelGGL(k_colsum_part, dim3(net.strips, (unsigned)slabs), dim3(256), 0, s, net, rows, part);
+    hipLaunchKernelGGL(k_colsum_fin, dim3(net.strips), dim3(256), 0, s, net, part, slabs);
     return hipGetLastError();
 }
 
@@ -620,12 +757,10 @@ hipError_t mlp_weights_bf16(const float* w, int rows, int cols, void* wb, int ld
     return hipGetLastError();
 }
 
-hipError_t mlp_adam(float* p, const float* g, float* m, float* v, int64_t count, float lr, float b1, float b2,
+hipError_t mlp_adam(const MlpLayers& net, float* p, const float* g, float* m, float* v, float lr, float b1, float b2,
                     float eps, int step, hipStream_t s) {
     const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    int64_t blocks = (count + 255) / 256;
-    if (blocks > 65535) blocks = 65535;
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)blocks), dim3(256), 0, s, p, g, m, v, count, lr, b1, b2, eps, c1, c2);
+    hipLaunchKernelGGL(k_adam, dim3(net.tiles), dim3(256), 0, s, net, p, g, m, v, lr, b1, b2, eps, c1, c2);
     return hipGetLastError();
 }
 
