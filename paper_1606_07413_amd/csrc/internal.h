@@ -221,6 +221,13 @@ size_t mlp_gemm_part_floats(int M, int N, int K);
 hipError_t mlp_gemm_nt(int epi, const void* A, int lda, const void* B, int ldb, int M, int N, int K, float* C, int ldc,
                        const float* bias, const float* Z, int ldz, void* H, int ldh, void* T, int ldt, float* part,
                        size_t part_floats, hipStream_t s);
+// epi 2 without C and T, from an FP32 A that is rounded to bf16 on the way (16-byte aligned, lda a multiple of 4)
+hipError_t mlp_gemm_nt_f32(const float* A, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
+                           void* H, int ldh, float* part, size_t part_floats, hipStream_t s);
+// the same for the few rows that mlp_rows_fits, without a workspace; A is bf16, or with f32 as above
+bool mlp_rows_fits(int M);
+hipError_t mlp_rows(const void* A, bool f32, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
+                    void* H, int ldh, hipStream_t s);
 // probabilities, loss sum and G = (p - onehot) / batch (fp32; bf16 with ld ldgb; transposed bf16 if gt)
 hipError_t mlp_softmax_ce(const float* logits, const int32_t* labels, int batch, int classes, float* probs, float* g,
                           void* gb, int ldgb, void* gt, int ldgt, float* loss_sum, hipStream_t s);

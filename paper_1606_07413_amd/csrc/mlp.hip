@@ -20,6 +20,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x8 __attribute__((ext_vector_type(8), aligned(16)));
 
 namespace {
 
@@ -37,12 +38,33 @@ __device__ inline float gelu_grad_f(float z) {
 
 constexpr int BN = 128, BK = 64, LDK = BK + 8;  // LDS rows of 64 k values padded to 144 bytes
 
-// 8 consecutive k of row r of a K-contiguous operand (leading dimension ld, a multiple of 8), zero
-// outside rows < rows and k < kend.
-__device__ inline bf16x8 load8(const __bf16* __restrict__ p, int ld, int r, int k, int rows, int kend) {
-    if (r < rows && k + 8 <= kend) return *reinterpret_cast<const bf16x8*>(p + (size_t)r * ld + k);
-    bf16x8 v;
-    const __bf16 zero = (__bf16)0.0f;
+// Eight consecutive k of an operand that is stored as BF16, or as FP32 and rounded on its way to LDS.
+template <typename T>
+struct Vec8;
+template <>
+struct Vec8<__bf16> {
+    typedef bf16x8 type;
+};
+template <>
+struct Vec8<float> {
+    typedef f32x8 type;
+};
+__device__ inline bf16x8 rounded(const bf16x8& v) { return v; }
+__device__ inline bf16x8 rounded(const f32x8& v) {
+    bf16x8 w;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = (__bf16)v[e];
+    return w;
+}
+
+// 8 consecutive k of row r of a K-contiguous operand (leading dimension ld: a multiple of 8 for BF16, of 4 for
+// FP32), zero outside rows < rows and k < kend.
+template <typename T>
+__device__ inline typename Vec8<T>::type load8(const T* __restrict__ p, int ld, int r, int k, int rows, int kend) {
+    typedef typename Vec8<T>::type V;
+    if (r < rows && k + 8 <= kend) return *reinterpret_cast<const V*>(p + (size_t)r * ld + k);
+    V v;
+    const T zero = (T)0.0f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = (r < rows && k + e < kend) ? p[(size_t)r * ld + k + e] : zero;
     return v;
@@ -111,9 +133,11 @@ __device__ inline void epilogue2(float2& v, int gm, int gn, float* __restrict__ 
 // writes its FP32 partial tile to part[z] and k_splitk_epilogue adds the partials and applies the
 // epilogue; without one (only when gridDim.z = 1) the block applies the epilogue itself, its tile passed
 // through LDS so that rows, and rows of the transposed copy, leave in whole segments.
-template <int BM, int BN_, int WM, int WN, int EPI>
+// TA = float: an FP32 A (the network's input in inference), rounded to BF16 between registers and LDS: 30.0 us for
+// 4096 x 512 x 4096, against 26.7 and the 16.4 of a pass that writes the BF16 input.
+template <typename TA, int BM, int BN_, int WM, int WN, int EPI>
 __global__ __launch_bounds__((BM / WM) * (BN_ / WN) * 64) void k_gemm_nt(
-    const __bf16* __restrict__ A, int lda, const __bf16* __restrict__ B, int ldb, int M, int N, int K,
+    const TA* __restrict__ A, int lda, const __bf16* __restrict__ B, int ldb, int M, int N, int K,
     float* __restrict__ C, int ldc, const float* __restrict__ bias, const float* __restrict__ Zin, int ldz,
     __bf16* __restrict__ Hout, int ldh, __bf16* __restrict__ Tout, int ldt, int kchunk, float* __restrict__ part) {
     constexpr int WAVES_N = BN_ / WN, NT = (BM / WM) * WAVES_N * 64;
@@ -142,13 +166,14 @@ __global__ __launch_bounds__((BM / WM) * (BN_ / WN) * 64) void k_gemm_nt(
     const int kv = (t & 7) * 8, r0 = t >> 3;  // this thread's vectors: rows r0 + RSTEP i, k offset kv
     const bool inner_rows = m0 + BM <= M && n0 + BN_ <= N;  // uniform over the block
     constexpr int PF = 2;
-    bf16x8 ra[PF][AV], rb[PF][BV];
+    typename Vec8<TA>::type ra[PF][AV];
+    bf16x8 rb[PF][BV];
     auto gload = [&](int st, int k0) {
         if (inner_rows && k0 + BK <= ke) {
             // the whole step lies inside both operands: plain 16-byte loads
 #pragma unroll
             for (int i = 0; i < AV; ++i)
-                ra[st][i] = *reinterpret_cast<const bf16x8*>(A + (size_t)(m0 + r0 + RSTEP * i) * lda + k0 + kv);
+                ra[st][i] = *reinterpret_cast<const typename Vec8<TA>::type*>(A + (size_t)(m0 + r0 + RSTEP * i) * lda + k0 + kv);
 #pragma unroll
             for (int i = 0; i < BV; ++i)
                 rb[st][i] = *reinterpret_cast<const bf16x8*>(B + (size_t)(n0 + r0 + RSTEP * i) * ldb + k0 + kv);
@@ -162,7 +187,7 @@ __global__ __launch_bounds__((BM / WM) * (BN_ / WN) * 64) void k_gemm_nt(
     auto sstore = [&](int st, int buf) {
 #pragma unroll
         for (int i = 0; i < AV; ++i)
-            *reinterpret_cast<bf16x8*>(&As[buf * AS + (r0 + RSTEP * i) * LDK + kv]) = ra[st][i];
+            *reinterpret_cast<bf16x8*>(&As[buf * AS + (r0 + RSTEP * i) * LDK + kv]) = rounded(ra[st][i]);
 #pragma unroll
         for (int i = 0; i < BV; ++i)
             *reinterpret_cast<bf16x8*>(&Bs[buf * BS + (r0 + RSTEP * i) * LDK + kv]) = rb[st][i];
@@ -317,6 +342,51 @@ __global__ __launch_bounds__(256) void k_splitk_epilogue(const float* __restrict
             if (gn < N && gm < M) Tout[(size_t)gn * ldt + gm] = tile[tx][cc];
         }
     }
+}
+
+// H = gelu(A W + b) for a few rows (M <= MR): a wavefront takes one column, its lanes eight k each, and
+// every row's sum ends in the wavefront.  Bound by the latency of reading W^T once (4 MiB for 4096 x 512);
+// the 64-row tiles of k_gemm_nt had four blocks to a row of tiles, K in splits and a second kernel to add
+// them.  One row, 4096 -> 512 -> 512 -> 512: 13.5 us for the three products, on tiles 26 and the input's
+// conversion.
+template <typename TA, int MR>
+__global__ __launch_bounds__(256) void k_rows(const TA* __restrict__ A, int lda, const __bf16* __restrict__ B, int ldb,
+                                              int M, int N, int K, const float* __restrict__ bias,
+                                              __bf16* __restrict__ Hout, int ldh) {
+    constexpr int U = MR == 1 ? 4 : 1;  // steps of 512 k whose loads are sent together
+    const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (n >= N) return;
+    float acc[MR];
+#pragma unroll
+    for (int m = 0; m < MR; ++m) acc[m] = 0.f;
+    for (int k0 = 0; k0 < K; k0 += 512 * U) {
+        bf16x8 b[U];
+        typename Vec8<TA>::type a[U][MR];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + 512 * u + 8 * lane;
+            b[u] = load8(B, ldb, n, k, N, K);
+#pragma unroll
+            for (int m = 0; m < MR; ++m) a[u][m] = load8(A, lda, m, k, M, K);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int m = 0; m < MR; ++m) {
+                const bf16x8 w = rounded(a[u][m]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[m] = fmaf((float)w[e], (float)b[u][e], acc[m]);
+            }
+    }
+    float mine = 0.f;
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+        float v = acc[m];
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+        if (lane == m) mine = v;
+    }
+    if (lane < M) Hout[(size_t)lane * ldh + n] = (__bf16)gelu_f(mine + bias[n]);
 }
 
 // softmax over `classes` logits per row, loss sum, G = (p - onehot) / batch as fp32 (g, ld classes),
@@ -647,8 +717,12 @@ int splits_of(int M, int N, int K) {
     return splits;
 }
 
-template <int EPI>
-hipError_t gemm_nt_t(const __bf16* A, int lda, const __bf16* B, int ldb, int M, int N, int K, float* C, int ldc,
+// Up to this many rows a product takes a wavefront per column instead of tiles: a whole pass of the 4096 ->
+// 512 x 3 -> 11 network over 8 rows takes 36 us so and 45 on tiles (over one row 30).
+constexpr int ROWS_MAX = 8;
+
+template <int EPI, typename TA>
+hipError_t gemm_nt_t(const TA* A, int lda, const __bf16* B, int ldb, int M, int N, int K, float* C, int ldc,
                      const float* bias, const float* Z, int ldz, __bf16* H, int ldh, __bf16* T, int ldt, float* part,
                      size_t part_floats, hipStream_t s) {
     if (M <= 0 || N <= 0) return hipSuccess;
@@ -661,11 +735,11 @@ hipError_t gemm_nt_t(const __bf16* A, int lda, const __bf16* B, int ldb, int M, 
     const int kchunk = ((K + splits - 1) / splits + BK - 1) / BK * BK;
     if (big_tiles(M, N, K)) {
         dim3 grid((N + BN - 1) / BN, (M + 127) / 128, splits);
-        hipLaunchKernelGGL((k_gemm_nt<128, BN, 64, 32, EPI>), grid, dim3(512), 0, s, A, lda, B, ldb, M, N, K, C, ldc,
+        hipLaunchKernelGGL((k_gemm_nt<TA, 128, BN, 64, 32, EPI>), grid, dim3(512), 0, s, A, lda, B, ldb, M, N, K, C, ldc,
                            bias, Z, ldz, H, ldh, T, ldt, kchunk, via_part ? part : nullptr);
     } else {
         dim3 grid((N + BN - 1) / BN, (M + 63) / 64, splits);
-        hipLaunchKernelGGL((k_gemm_nt<64, BN, 32, 32, EPI>), grid, dim3(512), 0, s, A, lda, B, ldb, M, N, K, C, ldc,
+        hipLaunchKernelGGL((k_gemm_nt<TA, 64, BN, 32, 32, EPI>), grid, dim3(512), 0, s, A, lda, B, ldb, M, N, K, C, ldc,
                            bias, Z, ldz, H, ldh, T, ldt, kchunk, via_part ? part : nullptr);
     }
     if (via_part) {
@@ -711,6 +785,34 @@ hipError_t mlp_gemm_nt(int epi, const void* A, int lda, const void* B, int ldb, 
                                             part_floats, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t mlp_gemm_nt_f32(const float* A, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
+                           void* H, int ldh, float* part, size_t part_floats, hipStream_t s) {
+    if ((lda & 3) != 0 || ((uintptr_t)A & 15) != 0) return hipErrorInvalidValue;
+    return gemm_nt_t<EPI_BIAS_GELU>(A, lda, (const __bf16*)B, ldb, M, N, K, nullptr, N, bias, nullptr, 0, (__bf16*)H,
+                                    ldh, nullptr, 0, part, part_floats, s);
+}
+
+bool mlp_rows_fits(int M) { return M <= ROWS_MAX; }
+
+hipError_t mlp_rows(const void* A, bool f32, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
+                    void* H, int ldh, hipStream_t s) {
+    if (M < 1 || M > ROWS_MAX || (f32 && ((lda & 3) != 0 || ((uintptr_t)A & 15) != 0))) return hipErrorInvalidValue;
+    const dim3 grid((N + 3) / 4);
+    const __bf16* b = (const __bf16*)B;
+    auto go = [&]<typename TA>(const TA* a) {
+        if (M == 1)
+            hipLaunchKernelGGL((k_rows<TA, 1>), grid, dim3(256), 0, s, a, lda, b, ldb, M, N, K, bias, (__bf16*)H, ldh);
+        else
+            hipLaunchKernelGGL((k_rows<TA, ROWS_MAX>), grid, dim3(256), 0, s, a, lda, b, ldb, M, N, K, bias, (__bf16*)H,
+                               ldh);
+    };
+    if (f32)
+        go((const float*)A);
+    else
+        go((const __bf16*)A);
+    return hipGetLastError();
 }
 
 hipError_t mlp_softmax_ce(const float* logits, const int32_t* labels, int batch, int classes, float* probs, float* g,

@@ -79,3 +79,23 @@ def test_adam_and_weight_copies(ctx, inp, hidden, depth, classes):
     net.forward(xd, a)
     fresh.forward(xd, b)
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("inp,hidden,batch,shift", [(36, 33, 1, 0), (36, 33, 8, 0), (38, 40, 3, 0), (516, 64, 2, 0),
+                                                    (2052, 65, 9, 0), (2056, 129, 2049, 0), (1028, 65, 200, 0),
+                                                    (64, 32, 4, 1), (64, 32, 70, 1)])
+def test_forward_routes(ctx, inp, hidden, batch, shift):
+    """Inference on few rows, on FP32 rows that the first product reads itself, and on rows that are not 16-byte
+    aligned (shift floats past an aligned address): probabilities within the running error bound."""
+    import torch
+    print("forward", inp, hidden, batch, shift, flush=True)
+    net, params, x, y, xd, _ = small_net(ctx, inp, hidden, 2, 11, batch)
+    flat = torch.empty(batch * inp + shift, dtype=torch.float32, device="cuda:0")
+    xs = flat[shift:].view(batch, inp)
+    xs.copy_(xd)
+    probs = torch.empty((batch, 11), dtype=torch.float32, device="cuda:0")
+    net.forward(xs, probs)
+    pr = {k: (omlp.bf16_round(v) if k.startswith("W") else v) for k, v in params.items()}
+    xb = omlp.bf16_round(x).astype(np.float64)
+    _, p_ref, p_bound = base.gradient_error_bounds(pr, xb, y, 2)
+    assert np.all(np.abs(probs.cpu().numpy().astype(np.float64) - p_ref) <= 2 * p_bound)
