@@ -3131,12 +3131,16 @@ extern "C" int tcw_mlp_depth_order(tcw_mlp* m, const tcw_target* t, int k_max, c
     const int R = 1 << (2 * t->n);
     if (R * R != m->inp) return fail(c, TCW_EINVAL, "network input size does not match the target");
     if (!m->xdev) HIP_TRY(c, hipMalloc(&m->xdev, (size_t)m->inp * 4));
-    int rc = tcw_features(c, t, m->xdev);
-    if (!rc) rc = mlp_forward(m, m->xdev, 1, nullptr, nullptr);
+    if (t->n > 3) return fail(c, TCW_EINVAL, "features are defined for n <= 3");
+    HIP_TRY(c, tcw::exact_features(t->U, m->xdev, c->stream));  // the network follows on the same stream
+    int rc = mlp_forward(m, m->xdev, 1, nullptr, nullptr);
     if (rc) return rc;
     std::vector<float> p(m->classes);
-    HIP_TRY(c, hipMemcpyAsync(p.data(), m->probs, m->classes * 4, hipMemcpyDeviceToHost, c->stream));
+    const size_t bytes = (size_t)m->classes * 4;
+    void* to = bytes <= PINNED_BYTES ? (void*)c->pinned : p.data();
+    HIP_TRY(c, hipMemcpyAsync(to, m->probs, bytes, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if (to != p.data()) std::memcpy(p.data(), to, bytes);
     if (probs_out)
         for (int i = 0; i < m->classes; ++i) probs_out[i] = p[i];
     // depths 0..k_max by descending key (ties: smaller depth first); the key is the predicted

@@ -572,12 +572,13 @@ __device__ void block_features(const T* a, const T* b, int e, int32_t* rows /* R
 }
 
 // ---- canonical features and packed targets from rows in registers (n <= 3) ----
-// A matrix is held by WPT wavefronts, NB row sets each (RowGeo: one row per lane group).
-template <int NQ>
+// A matrix is held by WPT wavefronts, NB row sets each (RowGeo: one row per lane group).  At n = 3 a batch's
+// targets take four each; a single target takes sixteen, one comparison of a row with four others each.
+template <int NQ, int W = NQ == 3 ? 4 : 1>
 struct FeatGeo {
     using Gm = RowGeo<NQ>;
     static constexpr int R = Gm::R;
-    static constexpr int WPT = NQ == 3 ? 4 : 1;
+    static constexpr int WPT = W;
     static constexpr int THREADS = WPT * 64;
     static constexpr int NB = NQ == 1 ? 1 : R / (Gm::RPW * WPT);
     static constexpr int WORDS = 2 * R / 8;          // 8-byte words of a row's sort key
@@ -594,9 +595,9 @@ struct FeatLds {
 // sequence (a_0, b_0, a_1, ...) as bytes v + 128, first entry in the highest byte, so rows compare as
 // unsigned 8-byte words; a row's place is the number of rows below it.  Lane i compares row i with
 // the rows j of its wavefront's share, a word at a time until every pair is decided.
-template <int NQ, typename T>
+template <int NQ, typename T, int W = FeatGeo<NQ>::WPT>
 __device__ void rows_features(T (*a)[1], T (*b)[1], int e, FeatLds<NQ>& L, float* out) {
-    using Fg = FeatGeo<NQ>;
+    using Fg = FeatGeo<NQ, W>;
     using Gm = RowGeo<NQ>;
     constexpr int R = Fg::R;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -656,10 +657,12 @@ __device__ void rows_features(T (*a)[1], T (*b)[1], int e, FeatLds<NQ>& L, float
 }
 
 // One target's features.  Entries beyond int8 take block_features' general sort (32-bit entries, one
-// row per thread): 72 us at n = 3 where the byte keys take 14 us.
+// row per thread): 72 us at n = 3 where the byte keys take 8 us (14 with four wavefronts).
+template <int NQ>
+using FeatOne = FeatGeo<NQ, NQ == 3 ? 16 : 1>;
 template <int NQ, typename T>
-__global__ __launch_bounds__(FeatGeo<NQ>::THREADS) void k_features(const T* a, const T* b, const int32_t* e, float* out) {
-    using Fg = FeatGeo<NQ>;
+__global__ __launch_bounds__(FeatOne<NQ>::THREADS) void k_features(const T* a, const T* b, const int32_t* e, float* out) {
+    using Fg = FeatOne<NQ>;
     using Gm = RowGeo<NQ>;
     constexpr int R = Fg::R;
     __shared__ FeatLds<NQ> L;
@@ -679,7 +682,7 @@ __global__ __launch_bounds__(FeatGeo<NQ>::THREADS) void k_features(const T* a, c
     if (__syncthreads_or(wide))
         block_features<NQ, T>(a, b, *e, rows, idx, out);
     else
-        rows_features<NQ, T>(ra, rb, *e, L, out);
+        rows_features<NQ, T, Fg::WPT>(ra, rb, *e, L, out);
 }
 
 // The signed permutation of columns that R(p)^2 is: an entry in column c of a row moves to column
@@ -1272,7 +1275,7 @@ namespace tcw {
 hipError_t exact_features(const ExactDev& m, float* out, hipStream_t s) {
     auto f = [&]<int NQ, typename T>() -> hipError_t {
         if constexpr (NQ <= 3) {
-            hipLaunchKernelGGL((k_features<NQ, T>), dim3(1), dim3(FeatGeo<NQ>::THREADS), 0, s, (const T*)m.a,
+            hipLaunchKernelGGL((k_features<NQ, T>), dim3(1), dim3(FeatOne<NQ>::THREADS), 0, s, (const T*)m.a,
                                (const T*)m.b, m.e, out);
             return hipGetLastError();
         } else {
