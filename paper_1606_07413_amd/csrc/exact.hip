@@ -722,9 +722,10 @@ constexpr int E_FREE = 56;
 // rows, reduced once at the end (and before every rotation beyond exponent E_FREE, where the entries'
 // range is checked).  Bound by instructions (about 2,200 per wavefront): 16384 circuits of 48 Clifford
 // factors and 1 to 10 rotations at n = 3 take 0.66 ms, against 33 ms with every factor as two rotations
-// through global memory, a reduction after each.
+// through global memory, a reduction after each.  The second launch bound keeps three wavefronts on a SIMD
+// (0.86 ms with the two that 169 registers leave; four spill, 0.70 ms).
 template <int NQ, typename T>
-__global__ __launch_bounds__(FeatGeo<NQ>::THREADS) void k_build_batch(const uint16_t* words, const int32_t* offsets,
+__global__ __launch_bounds__(FeatGeo<NQ>::THREADS, 3) void k_build_batch(const uint16_t* words, const int32_t* offsets,
                                                                       const int32_t* kof, int count, uint32_t* phi_out,
                                                                       int32_t* rot_e_out, float* feat_out, int* flag) {
     using Fg = FeatGeo<NQ>;
