@@ -3189,7 +3189,7 @@ struct LevelTable {
     }
 };
 
-int build_level_table(tcw_ctx* c, int n, int h_levels, int h_probe, uint64_t seed, LevelTable& lt) {
+int build_level_table(tcw_ctx* c, int n, int h_levels, int h_probe, int64_t targets, uint64_t seed, LevelTable& lt) {
     const int R = 1 << (2 * n);
     HIP_TRY(c, lt.take(&lt.zero_phi, (size_t)R * R / 2 * 4));
     HIP_TRY(c, hipMemsetAsync(lt.zero_phi, 0, (size_t)R * R / 2 * 4, c->stream));
@@ -3210,7 +3210,7 @@ int build_level_table(tcw_ctx* c, int n, int h_levels, int h_probe, uint64_t see
         lt.sp.n_half = (uint32_t)n_half_of(n, h);
         HIP_TRY(c, tcw::mitm_levels(n, lt.sp, h, lt.table, lt.lg, c->stream));
     }
-    if (const size_t bytes = tcw::mitm_frag_bytes(n, h_probe)) {
+    if (const size_t bytes = tcw::mitm_frag_bytes(n, h_probe, targets)) {
         HIP_TRY(c, lt.take(&lt.frags, bytes));
         HIP_TRY(c, tcw::mitm_frags(n, lt.sp, h_probe, lt.frags, c->stream));
     }
@@ -3298,7 +3298,7 @@ extern "C" int tcw_label_batch(tcw_ctx* c, int n, int count, const uint16_t* wor
     size_t room = 64;  // by powers of two, so that the pool holds few sizes
     while ((int)room < chunk) room *= 2;
     LB_TRY(lt.take(&phi, room * R * R / 2 * 4));
-    if ((rc = build_level_table(c, n, h_id, 2 * h_max - h_id, seed, lt)) || (rc = clear_flag(c))) {
+    if ((rc = build_level_table(c, n, h_id, 2 * h_max - h_id, count, seed, lt)) || (rc = clear_flag(c))) {
         cleanup();
         return rc;
     }
@@ -3357,7 +3357,7 @@ extern "C" int tcw_min_tcount(tcw_ctx* c, const tcw_target* t, int h_max, uint64
         return hip_fail(c, err, "rot_e upload");
     }
     const int h_id = mitm_split(n, h_max, 1);
-    if ((rc = build_level_table(c, n, h_id, 2 * h_max - h_id, seed, lt))) {
+    if ((rc = build_level_table(c, n, h_id, 2 * h_max - h_id, 1, seed, lt))) {
         cleanup();
         return rc;
     }

@@ -146,9 +146,10 @@ hipError_t build_batch(int n, const uint16_t* words, const int32_t* offsets, con
                        uint32_t* phi_out, int32_t* rot_e_out, float* feat_out, int* flag, hipStream_t s);
 // meet-in-the-middle level table and probes (walk.hip)
 hipError_t mitm_levels(int n, const SpaceDev& sp, int h, uint64_t* table, int log2_table, hipStream_t s);
-// the target side's workspace (mitm_frag_bytes(n, h_max) bytes, none at n <= 2), filled once for any number
-// of mitm_probe calls with the same sp and h_max (unless it holds only a part at a time)
-size_t mitm_frag_bytes(int n, int h_max);
+// the target side's workspace for `count` targets in all (mitm_frag_bytes bytes; none at n <= 2 and for few
+// targets, mitm_probe then takes null), filled once for any number of mitm_probe calls with the same sp and
+// h_max (unless it holds only a part at a time)
+size_t mitm_frag_bytes(int n, int h_max, int64_t count);
 hipError_t mitm_frags(int n, const SpaceDev& sp, int h_max, void* frags, hipStream_t s);
 hipError_t mitm_probe(int n, const SpaceDev& sp, const uint32_t* phi_all, const int32_t* rot_e_all, int count,
                       int h_max, void* frags, const uint64_t* table, int log2_table, int32_t* best_out, hipStream_t s);

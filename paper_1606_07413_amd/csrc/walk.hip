@@ -1855,14 +1855,25 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_mitm_probe(SpaceDev sp0, cons
 // A wavefront takes one prefix (p_1, ..., p_{j-1}) and every p_0 that the pruning keeps (at most 62 of 63).
 
 // Row r = lane of the n = 3 butterflies: bit p of anti = P_p and P_r anticommute, bit p of plus = the
-// butterfly of R (side 0) adds the partner.
+// butterfly of R (side 0) adds the partner; ROT3_TAB with the Paulis of a row side by side.
+struct Rot3Masks {
+    uint64_t anti[64], plus[64];
+};
+constexpr Rot3Masks make_rot3_masks() {
+    Rot3Masks t{};
+    constexpr Rot3Tab tab = make_rot3_tab();
+    for (int r = 0; r < 64; ++r)
+        for (int p = 1; p < 64; ++p) {
+            t.anti[r] |= (uint64_t)(tab.v[p * 64 + r] & 1) << p;
+            t.plus[r] |= (uint64_t)((tab.v[p * 64 + r] >> 1) & 1) << p;
+        }
+    return t;
+}
+__device__ constexpr Rot3Masks ROT3_MASKS = make_rot3_masks();
+
 __device__ inline void rot3_masks(int lane, uint64_t& anti, uint64_t& plus) {
-    anti = plus = 0;
-    for (uint32_t p = 1; p < 64; ++p) {
-        const uint32_t b = ROT3_TAB.v[p * 64 + lane];
-        anti |= (uint64_t)(b & 1) << p;
-        plus |= (uint64_t)((b >> 1) & 1) << p;
-    }
+    anti = ROT3_MASKS.anti[lane];
+    plus = ROT3_MASKS.plus[lane];
 }
 
 // one rotation of rotate1 at n = 3, p uniform
@@ -1897,6 +1908,13 @@ __device__ inline uint64_t prefix3(uint32_t y, int j, uint32_t* p) {
     return m;
 }
 
+// the next p_0 of a prefix's products, 0 after the last
+__device__ inline uint32_t next_product(uint64_t& todo) {
+    const uint32_t p0 = todo ? (uint32_t)__builtin_ctzll(todo) : 0u;
+    todo &= todo - 1;
+    return p0;
+}
+
 // The keys through the prefix's rotations (side 0: R, side 1: R^T), p_{j-1} first.
 __device__ inline uint64_t prefix_keys3(uint64_t u, const uint32_t* p, int j, uint64_t anti, uint64_t plus, int lane) {
 #pragma unroll
@@ -1918,7 +1936,7 @@ __device__ inline uint64_t row_sum16(uint64_t v) {
 // cross-half exchanges leave one product per 16-lane row), each kept by one lane; then every lane
 // finishes and stores its own product, so that the table's atomics, each a round trip to memory, run 64
 // at a time.  Bound by the butterfly, the element map and the sums (about 45 VALU instructions a
-// product) with the pruned products left out: the 16 million products of levels 0..4 take 0.84 ms,
+// product) with the pruned products left out: the 16 million products of levels 0..4 take 0.81 ms,
 // against 4.85 ms with a wavefront per product and one lane at the table.
 constexpr int MITM_WAVES = 4;
 __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_levels3(SpaceDev sp, int h, uint32_t prefixes, uint64_t* table,
@@ -1943,8 +1961,7 @@ __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_levels3(SpaceDev sp
             uint64_t acc[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const uint32_t p0 = todo ? (uint32_t)__builtin_ctzll(todo) : 0u;
-                todo &= todo - 1;
+                const uint32_t p0 = next_product(todo);
                 const uint64_t v = p0 ? rot3(u, p0, anti, plus, lane) : u;
                 acc[i] = digest_map(m61_fold(v), ka, kb);
             }
@@ -1961,15 +1978,44 @@ __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_levels3(SpaceDev sp
     }
 }
 
-// The target-side keys u = R(p_0)^T ... R(p_{j-1})^T K as MFMA A-operand fragments, the same for every
-// target: prefix y's products in the order of their p_0, two per 16-row operand (rows 0..7 the signed
-// base-256 digits of the first, rows 8..15 of the second), K = [u | 2^31 u] in two steps: 2 KiB a pair,
-// 32 pairs a prefix (MITM_PREFIX_V4 vectors).  Lane l of a fragment holds row l % 16, columns
-// 16 (l / 16) .. + 15.
+// The target-side keys u = R(p_0)^T ... R(p_{j-1})^T K as MFMA A-operand fragments: a prefix's products in the
+// order of their p_0, two per 16-row operand (rows 0..7 the signed base-256 digits of the first, rows 8..15
+// of the second), K = [u | 2^31 u] in two steps.  Lane l of a fragment holds row l % 16, columns
+// 16 (l / 16) .. + 15.  The digits meet in PairRows, one for each wavefront.
+constexpr int PAIR_PITCH = 64 + 16;  // bytes of a row of 64 digits: 16-byte aligned, spread over the banks
+struct PairRows {
+    v4i rows[2 * 16 * PAIR_PITCH / 16];
+};
+// the products p of the prefix's keys u (p = 0: u itself)
+__device__ inline void pair_frags3(PairRows& L, uint64_t u, const uint32_t (&p)[2], uint64_t anti, uint64_t plus, int lane,
+                                   v4i& a0, v4i& a1) {
+    uint8_t* at = reinterpret_cast<uint8_t*>(L.rows) + lane;
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const uint64_t v = p[w] ? rot3(u, p[w], anti, plus, lane) : u;
+#pragma unroll
+        for (int set = 0; set < 2; ++set) {
+            const uint64_t x = set ? (v >> 30) + ((v & 0x3fffffffull) << 31) : v;
+            const uint64_t b = (x + 0x8080808080808080ull) ^ 0x8080808080808080ull;
+#pragma unroll
+            for (int m = 0; m < N4_DIG; ++m) at[(set * 16 + w * 8 + m) * PAIR_PITCH] = (uint8_t)(b >> (8 * m));
+        }
+    }
+    wave_sync();
+    const v4i* from = L.rows + (lane & 15) * (PAIR_PITCH / 16) + (lane >> 4);
+    a0 = from[0];
+    a1 = from[16 * (PAIR_PITCH / 16)];
+    wave_sync();
+}
+
+// Many targets share the fragments (2 KiB a pair, 32 pairs a prefix: MITM_PREFIX_V4 vectors), made once.  Bound
+// by the stores: 142 thousand products (at most three rotations) 79 us, 112 with a byte stored at a time and the
+// masks collected from the table of bytes.
 constexpr int MITM_PREFIX_V4 = 32 * 2 * 64;
 __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_keys3(SpaceDev sp, int j, uint32_t y0, uint32_t prefixes,
                                                                 v4i* frags) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ PairRows L[MITM_WAVES];
+    const int lane = threadIdx.x & 63, wave = (int)uniform32(threadIdx.x >> 6);
     uint64_t anti, plus;
     rot3_masks(lane, anti, plus);
     plus = ~plus;  // R^T: the butterfly adds where R subtracts
@@ -1978,21 +2024,15 @@ __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_keys3(SpaceDev sp, 
         uint64_t todo = prefix3(uniform32(y0 + i), j, p);
         if (todo == 0) continue;
         const uint64_t u = prefix_keys3(sp.keys[lane], p, j, anti, plus, lane);
-        uint8_t* out = reinterpret_cast<uint8_t*>(frags + (size_t)i * MITM_PREFIX_V4);
-        const int slots = ((int)__popcll(todo) + 3) / 4 * 4;  // whole quads; what no product fills repeats the prefix
-        for (int s = 0; s < slots; ++s) {
-            const uint32_t p0 = todo ? (uint32_t)__builtin_ctzll(todo) : 0u;
-            todo &= todo - 1;
-            if ((s & (MITM_WAVES - 1)) != wave) continue;
-            const uint64_t v = p0 ? rot3(u, p0, anti, plus, lane) : u;
-            uint8_t* at = out + (size_t)(s >> 1) * 2048 + ((lane >> 4) * 16 + (s & 1) * 8) * 16 + (lane & 15);
-#pragma unroll
-            for (int set = 0; set < 2; ++set) {
-                const uint64_t w = set ? (v >> 30) + ((v & 0x3fffffffull) << 31) : v;
-                const uint64_t b = w + 0x8080808080808080ull;
-#pragma unroll
-                for (int m = 0; m < N4_DIG; ++m) at[set * 1024 + m * 16] = (uint8_t)((b >> (8 * m)) ^ 0x80);
-            }
+        v4i* out = frags + (size_t)i * MITM_PREFIX_V4 + lane;
+        const int pairs = ((int)__popcll(todo) + 3) / 4 * 2;  // whole quads; what no product fills repeats the prefix
+        for (int q = 0; q < pairs; ++q) {
+            const uint32_t two[2] = {next_product(todo), next_product(todo)};
+            if ((q & (MITM_WAVES - 1)) != wave) continue;
+            v4i a0, a1;
+            pair_frags3(L[wave], u, two, anti, plus, lane, a0, a1);
+            out[q * 128] = a0;
+            out[q * 128 + 64] = a1;
         }
     }
 }
@@ -2028,10 +2068,12 @@ __device__ inline uint64_t pair_sum3(const v4i a0, const v4i a1, const v4i* bf, 
 // Bound by VALU issue: about 39 instructions and four MFMAs a product (64 % and 22 % of the time at four
 // wavefronts per SIMD, PMC); label batches read the fragments (3 MiB for j <= 2) from L2.  16384 circuits
 // against the table of T-count <= 4: 3.1 ms.  One target's 142 thousand products of <= 3 rotations:
-// 0.05 ms.  The accumulators stay in VGPRs (a budget of 128 by the second launch bound: with 512 the
+// 0.05 ms (its own fragments made on the way).  The accumulators stay in VGPRs (a budget of 128 by the second launch bound: with 512 the
 // compiler puts them in AGPRs and moves each out) and the fragments alternate between two register sets;
 // with AGPRs and a copied set a product took 52 instructions, with each target's two wavefronts side by
 // side the whole 4.35 ms.
+// MAKE: no fragments were made (frags unused), the wavefront makes its own, about 30 instructions a product.
+template <bool MAKE>
 __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_probe3(SpaceDev sp, const v4i* __restrict__ phi_all,
                                                                  const int32_t* __restrict__ rot_e_all, int count,
                                                                  int j, uint32_t y0, uint32_t prefixes, int slices,
@@ -2048,20 +2090,20 @@ __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_probe3(SpaceDev sp,
 #pragma unroll
     for (int i = 0; i < N3_NT * N3_KK; ++i) bf[i] = phi_all[((size_t)t * N3_NT * N3_KK + i) * 64 + lane];
     const uint32_t s = uniform32((uint32_t)rot_e_all[t]);
+    __shared__ PairRows L[MAKE ? MITM_WAVES : 1];
+    uint64_t anti = 0, plus = 0, key0 = 0;
+    if constexpr (MAKE) {
+        rot3_masks(lane, anti, plus);
+        plus = ~plus;  // R^T
+        key0 = sp.keys[lane];
+    }
     for (uint32_t y = (uint32_t)slice; y < prefixes; y += (uint32_t)slices) {
         uint32_t p[Geo<3>::HMAX] = {};
-        const int products = (int)__popcll(prefix3(y0 + y, j, p));
+        uint64_t todo = prefix3(uniform32(y0 + y), j, p);
+        const int products = (int)__popcll(todo);
         if (products == 0) continue;
-        const v4i* f = frags + (size_t)y * MITM_PREFIX_V4 + lane;
         const int quads = (products + 3) / 4;
         uint64_t mine = 0;
-        // the next quad's fragments are on their way while one is worked on: two register sets in turn,
-        // so that none is copied to the other
-        const auto fetch = [&](int quad, v4i (&to)[4]) {
-            if (quad >= quads) return;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) to[i] = f[quad * 256 + 64 * i];
-        };
         const auto work = [&](int quad, const v4i (&a)[4]) {
             const uint64_t s01 = pair_sum3(a[0], a[1], bf, s, ka, kb),
                            s23 = pair_sum3(a[2], a[3], bf, s, ka, kb);
@@ -2070,14 +2112,36 @@ __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_probe3(SpaceDev sp,
             const uint64_t sum = row_sum16(half_add16(s01, s23));
             if ((lane & 15) == quad) mine = sum;
         };
-        v4i even[4], odd[4];
-        fetch(0, even);
-        for (int quad = 0; quad < quads; quad += 2) {
-            fetch(quad + 1, odd);
-            work(quad, even);
-            if (quad + 1 >= quads) break;
-            fetch(quad + 2, even);
-            work(quad + 1, odd);
+        if constexpr (MAKE) {
+            const uint64_t u = prefix_keys3(key0, p, j, anti, plus, lane);
+            PairRows& rows = L[threadIdx.x >> 6];
+            for (int quad = 0; quad < quads; ++quad) {
+                v4i a[4];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const uint32_t two[2] = {next_product(todo), next_product(todo)};
+                    pair_frags3(rows, u, two, anti, plus, lane, a[2 * i], a[2 * i + 1]);
+                }
+                work(quad, a);
+            }
+        } else {
+            // the next quad's fragments are on their way while one is worked on: two register sets in turn,
+            // so that none is copied to the other
+            const v4i* f = frags + (size_t)y * MITM_PREFIX_V4 + lane;
+            const auto fetch = [&](int quad, v4i (&to)[4]) {
+                if (quad >= quads) return;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) to[i] = f[quad * 256 + 64 * i];
+            };
+            v4i even[4], odd[4];
+            fetch(0, even);
+            for (int quad = 0; quad < quads; quad += 2) {
+                fetch(quad + 1, odd);
+                work(quad, even);
+                if (quad + 1 >= quads) break;
+                fetch(quad + 2, even);
+                work(quad + 1, odd);
+            }
         }
         const int g = lane >> 4, in_quad = ((g & 1) << 1) | (g >> 1);
         int lvl = -1;
@@ -2323,8 +2387,12 @@ static uint32_t mitm_prefixes(int j) {
     return v;
 }
 
-size_t mitm_frag_bytes(int n, int h_max) {
-    if (n != 3) return 0;
+// Up to MITM_MAKE targets make their fragments themselves: the products of at most three rotations take 48 us
+// for one target so, in one launch a level, and 45 with stored fragments, which take 79 to make and, by chunks,
+// ten more launches.  A target more costs three quarters more instructions a product so.
+constexpr int MITM_MAKE = 4;
+size_t mitm_frag_bytes(int n, int h_max, int64_t count) {
+    if (n != 3 || count <= MITM_MAKE) return 0;
     size_t all = 0;
     for (int j = 0; j <= h_max; ++j) all += mitm_prefixes(j);
     return std::min<size_t>(all, MITM_CHUNK) * MITM_PREFIX_V4 * sizeof(v4i);
@@ -2349,8 +2417,14 @@ static hipError_t mitm_probe3(const SpaceDev& sp, const uint32_t* phi_all, const
                               int32_t* best_out, hipStream_t s) {
     const int slices = mitm_slices(count, prefixes);
     const int64_t blocks = ((int64_t)count * slices + MITM_WAVES - 1) / MITM_WAVES;
-    hipLaunchKernelGGL(k_mitm_probe3, dim3((unsigned)blocks), dim3(MITM_WAVES * 64), 0, s, sp, (const v4i*)phi_all,
-                       rot_e_all, count, j, y0, prefixes, slices, (const v4i*)frags, table, log2_table, best_out);
+    if (frags != nullptr)
+        hipLaunchKernelGGL(k_mitm_probe3<false>, dim3((unsigned)blocks), dim3(MITM_WAVES * 64), 0, s, sp,
+                           (const v4i*)phi_all, rot_e_all, count, j, y0, prefixes, slices, (const v4i*)frags, table,
+                           log2_table, best_out);
+    else
+        hipLaunchKernelGGL(k_mitm_probe3<true>, dim3((unsigned)blocks), dim3(MITM_WAVES * 64), 0, s, sp,
+                           (const v4i*)phi_all, rot_e_all, count, j, y0, prefixes, slices, (const v4i*)nullptr, table,
+                           log2_table, best_out);
     return hipGetLastError();
 }
 
@@ -2377,9 +2451,9 @@ hipError_t mitm_probe(int n, const SpaceDev& sp, const uint32_t* phi_all, const 
         for (int j = 0; j <= h_max; ++j) all += mitm_prefixes(j);
         for (int j = 0; j <= h_max; ++j) {
             const uint32_t m = mitm_prefixes(j);
-            if (all <= MITM_CHUNK) {
-                e = mitm_probe3(sp, phi_all, rot_e_all, count, j, 0, m, (v4i*)frags + (size_t)at * MITM_PREFIX_V4,
-                                table, log2_table, best_out, s);
+            if (frags == nullptr || all <= MITM_CHUNK) {
+                const v4i* f = frags != nullptr ? (const v4i*)frags + (size_t)at * MITM_PREFIX_V4 : nullptr;
+                e = mitm_probe3(sp, phi_all, rot_e_all, count, j, 0, m, f, table, log2_table, best_out, s);
                 if (e != hipSuccess) return e;
                 at += m;
                 continue;

@@ -84,6 +84,21 @@ def test_labels_match_search(ctx, n, h_max, count):
         assert ctx.min_tcount(tgt, h_max, 17) == labels[i], i
 
 
+@pytest.mark.parametrize("count", [4, 5])
+def test_labels_by_own_and_stored_keys(ctx, count):
+    """Up to four targets make the keys of their side themselves, more share stored ones, here in parts
+    (three rotations on the targets' side): labels up to 6, and the certificate of each."""
+    import torch
+    print("labels", count, flush=True)
+    tws = [seeded_inputs.target_words(3, 3 + i, 7700 + i) for i in range(count)]
+    feats = torch.empty((count, 16 ** 3), dtype=torch.float32, device="cuda:0")
+    labels = torch.empty(count, dtype=torch.int32, device="cuda:0")
+    ctx.label_batch(3, [(t.paulis, t.clifford) for t in tws], 3, 5, feats, labels)
+    for i, got in enumerate(labels.cpu().tolist()):
+        assert got <= 3 + i and (got >= 0 or 3 + i > 6), i
+        assert ctx.min_tcount(ctx.target_from_words(3, tws[i].paulis, tws[i].clifford), 3, 9) == got, i
+
+
 def test_certificate_above_six(ctx):
     """h_max = 4: the target's products come in parts; the Toffoli's T-count is 7."""
     v = seeded_inputs.permutation_unitary(seeded_inputs.NAMED_GATES["toffoli"])
