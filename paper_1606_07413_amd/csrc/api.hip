@@ -2787,6 +2787,9 @@ struct tcw_mlp {
 
 namespace {
 
+// training steps whose loss sums are on the device before they are read
+constexpr int LOSS_SLOTS = 256;
+
 // leading dimension of a bf16 buffer: a multiple of 8 elements, so every row starts 16-byte aligned
 int ld8(int cols) { return (cols + 7) / 8 * 8; }
 
@@ -2865,8 +2868,8 @@ int mlp_sync_bf16(tcw_mlp* m) {
 }
 
 // forward over a batch to probs (batch x classes); with labels (training) also the transposed activations, the
-// loss sum and the output-layer gradient
-int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels, float* probs) {
+// loss sum (to m->loss[slot]) and the output-layer gradient
+int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels, float* probs, int slot = 0) {
     tcw_ctx* c = m->ctx;
     int rc = mlp_ensure_batch(m, b);
     if (rc) return rc;
@@ -2879,7 +2882,7 @@ int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels, float*
     const bool few = !train && tcw::mlp_rows_fits(b);
     if (!direct)
         HIP_TRY(c, tcw::mlp_input_bf16(x, b, m->inp, m->Xb, ld8(m->inp), train ? m->Xt : nullptr, b8, c->stream));
-    if (train) HIP_TRY(c, hipMemsetAsync(m->loss, 0, 4, c->stream));
+    if (train) HIP_TRY(c, hipMemsetAsync(m->loss + slot, 0, 4, c->stream));
     for (int l = 0; l < m->L; ++l) {
         const void* A = l == 0 ? m->Xb : m->Hb[l - 1];
         const int K = m->sz[l], N = m->sz[l + 1];
@@ -2903,7 +2906,7 @@ int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels, float*
         }
         float* g = train ? m->Gf[l] : nullptr;
         void *gb = train ? m->Gb[l] : nullptr, *gt = train ? m->Gt[l] : nullptr;
-        float* loss = train ? m->loss : nullptr;
+        float* loss = train ? m->loss + slot : nullptr;
         if (tcw::mlp_head_fits(N)) {
             HIP_TRY(c, tcw::mlp_head(A, ld8(K), m->Wt[l], ld8(K), b, N, K, bias, labels, probs, g, gb, ld8(N), gt, b8,
                                      loss, c->stream));
@@ -2969,7 +2972,7 @@ extern "C" int tcw_mlp_create(tcw_ctx* c, int inp, int hidden, int depth, int cl
     if (e == hipSuccess) e = hipMalloc(&m->G, off * 4);
     if (e == hipSuccess) e = hipMalloc(&m->M, off * 4);
     if (e == hipSuccess) e = hipMalloc(&m->V, off * 4);
-    if (e == hipSuccess) e = hipMalloc(&m->loss, 4);
+    if (e == hipSuccess) e = hipMalloc(&m->loss, LOSS_SLOTS * 4);
     if (e != hipSuccess) return bail(e);
     m->Wb.assign(m->L, nullptr);
     m->Wt.assign(m->L, nullptr);
@@ -3056,13 +3059,23 @@ extern "C" int tcw_mlp_gradients(tcw_mlp* m, const float* x, const int32_t* labe
     return TCW_OK;
 }
 
-extern "C" int tcw_mlp_train_step(tcw_mlp* m, const float* x, const int32_t* labels, int batch, float lr, float* loss) {
-    if (!m || !x || !labels || batch < 1 || !(lr > 0)) return TCW_EINVAL;
-    int rc = mlp_forward(m, x, batch, labels, nullptr);
+namespace {
+
+// one step, its loss sum to m->loss[slot]
+int mlp_train_step(tcw_mlp* m, const float* x, const int32_t* labels, int batch, float lr, int slot) {
+    int rc = mlp_forward(m, x, batch, labels, nullptr, slot);
     if (!rc) rc = mlp_backward(m, batch);
     if (rc) return rc;
     m->step++;
     HIP_TRY(m->ctx, tcw::mlp_adam(mlp_layers(m), m->P, m->G, m->M, m->V, lr, 0.9f, 0.999f, 1e-8f, m->step, m->ctx->stream));
+    return TCW_OK;
+}
+
+}  // namespace
+
+extern "C" int tcw_mlp_train_step(tcw_mlp* m, const float* x, const int32_t* labels, int batch, float lr, float* loss) {
+    if (!m || !x || !labels || batch < 1 || !(lr > 0)) return TCW_EINVAL;
+    if (int rc = mlp_train_step(m, x, labels, batch, lr, 0)) return rc;
     if (loss) {
         float ls = 0;
         HIP_TRY(m->ctx, hipMemcpyAsync(&ls, m->loss, 4, hipMemcpyDeviceToHost, m->ctx->stream));
@@ -3373,18 +3386,32 @@ extern "C" int tcw_min_tcount(tcw_ctx* c, const tcw_target* t, int h_max, uint64
 extern "C" int tcw_mlp_train(tcw_mlp* m, const float* x, const int32_t* labels, int64_t count, int batch, int epochs,
                              float lr, float* last_epoch_loss) {
     if (!m || !x || !labels || count < 1 || batch < 1 || epochs < 1 || !(lr > 0)) return TCW_EINVAL;
+    tcw_ctx* c = m->ctx;
     double tot = 0;
     int64_t nb = 0;
+    // the steps follow each other on the stream; their losses are read LOSS_SLOTS at a time
+    std::vector<float> sums(LOSS_SLOTS);
     for (int ep = 0; ep < epochs; ++ep) {
         tot = 0;
         nb = 0;
-        for (int64_t first = 0; first < count; first += batch) {
-            const int b = (int)std::min<int64_t>(batch, count - first);
-            float ls = 0;
-            int rc = tcw_mlp_train_step(m, x + first * m->inp, labels + first, b, lr, &ls);
-            if (rc) return rc;
-            tot += ls * b;
-            nb += b;
+        for (int64_t first = 0; first < count;) {
+            const int64_t from = first;
+            int steps = 0;
+            for (; first < count && steps < LOSS_SLOTS; first += batch) {
+                const int b = (int)std::min<int64_t>(batch, count - first);
+                if (int rc = mlp_train_step(m, x + first * m->inp, labels + first, b, lr, steps++)) {
+                    (void)hipStreamSynchronize(c->stream);  // earlier steps still read x and the labels
+                    return rc;
+                }
+            }
+            HIP_TRY(c, hipMemcpyAsync(sums.data(), m->loss, steps * 4, hipMemcpyDeviceToHost, c->stream));
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+            for (int i = 0; i < steps; ++i) {
+                const int b = (int)std::min<int64_t>(batch, count - from - (int64_t)i * batch);
+                const float ls = sums[i] / (float)b;
+                tot += ls * b;
+                nb += b;
+            }
         }
     }
     if (last_epoch_loss) *last_epoch_loss = (float)(tot / (double)nb);
