@@ -2175,14 +2175,13 @@ int cu_count(int device) {
 
 }  // namespace
 
-int walk_grid_blocks(int n, int device, bool queue, int64_t walks) {
+int walk_grid_blocks(int n, int device) {
     // one persistent block per CU for n = 4 (the int8 S_c fills most of the 160 KiB LDS); at n = 3 the
-    // walk kernel's 71 VGPRs leave room for six 4-wave blocks per CU, which pays with many walks
-    // (2^20 walks: 13.8 ms per 3.4e7 steps against 14.4 ms with five) but not with a search's usual
-    // 2^16 (the Toffoli search at theta = 1/2: 0.140 s with five, 0.151 s with six); the queue
-    // kernel's 88 VGPRs leave room for five
+    // kernels' 66 and 69 VGPRs leave room for seven 4-wave blocks, of which six measured best: 2^16 walks
+    // 2.35 steps a ns against 2.22 with five and 2.24 with seven, 2^20 walks 2.60 against 2.47 and 2.54; an
+    // enumerated search's launches 102 and 119 us against 107 and 124 with five
     const int cus = cu_count(device);
-    if (n == 3) return cus * (!queue && walks >= (1 << 19) ? 6 : 5);
+    if (n == 3) return cus * 6;
     return n == 4 ? cus : cus * 4;
 }
 
