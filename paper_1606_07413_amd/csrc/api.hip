@@ -2755,6 +2755,8 @@ struct tcw_mlp {
     float *logits = nullptr, *probs = nullptr, *loss = nullptr, *xdev = nullptr;
     float* part = nullptr;  // partial products of the GEMMs whose K is split over workgroups
     size_t part_floats = 0;
+    std::vector<float*> Wp;  // a training step's partial weight gradients, null for a layer whose K is not split
+    std::vector<size_t> Wp_floats;
 
     void free_batch() {
         for (void* q : {Xb, Xt, (void*)logits, (void*)probs, (void*)part})
@@ -2767,7 +2769,7 @@ struct tcw_mlp {
                 if (q) (void)hipFree(q);
             v->clear();
         }
-        for (auto* v : {&Z, &Gf}) {
+        for (auto* v : {&Z, &Gf, &Wp}) {
             for (float* q : *v)
                 if (q) (void)hipFree(q);
             v->clear();
@@ -2807,6 +2809,7 @@ tcw::MlpLayers mlp_layers(const tcw_mlp* m) {
         y.w = m->w_off[l];
         y.in = in;
         y.out = out;
+        y.splits = 1;
         y.ldb = ld8(out);
         y.ldt = ld8(in);
         y.tile0 = net.tiles;
@@ -2855,6 +2858,8 @@ int mlp_ensure_batch(tcw_mlp* m, int b) {
         HIP_TRY(c, hipMalloc(&m->part, part * 4));
         m->part_floats = part;
     }
+    m->Wp.assign(m->L, nullptr);
+    m->Wp_floats.assign(m->L, 0);
     m->cap_b = b;
     return TCW_OK;
 }
@@ -2919,15 +2924,39 @@ int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels, float*
     return TCW_OK;
 }
 
-int mlp_backward(tcw_mlp* m, int b) {
+// room for layer l's partial weight gradients, kept with the batch's buffers; without it they are summed as
+// for m->G
+bool mlp_ensure_parts(tcw_mlp* m, int l, size_t floats) {
+    if (m->Wp_floats[l] >= floats) return true;
+    if (m->Wp[l]) (void)hipFree(m->Wp[l]);
+    m->Wp[l] = nullptr;
+    m->Wp_floats[l] = 0;
+    if (hipMalloc(&m->Wp[l], floats * 4) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    m->Wp_floats[l] = floats;
+    return true;
+}
+
+// gradients of a batch after mlp_forward: to m->G, or with a net the split weight gradients as partial
+// products for mlp_adam
+int mlp_backward(tcw_mlp* m, int b, tcw::MlpLayers* net) {
     tcw_ctx* c = m->ctx;
     const int b8 = ld8(b);
     for (int l = m->L - 1; l >= 0; --l) {
         const void* Hin_t = l == 0 ? m->Xt : m->Ht[l - 1];
         const int in = m->sz[l], out = m->sz[l + 1];
         // dW_l = H_in^T G_l: rows of H_in^T and of G_l^T run over the batch
-        HIP_TRY(c, tcw::mlp_gemm_nt(0, Hin_t, b8, m->Gt[l], b8, in, out, b, m->G + m->w_off[l], out, nullptr, nullptr,
-                                    0, nullptr, 0, nullptr, 0, m->part, m->part_floats, c->stream));
+        const int splits = net != nullptr ? tcw::mlp_gemm_splits(in, out, b) : 1;
+        if (splits > 1 && mlp_ensure_parts(m, l, (size_t)splits * in * out)) {
+            HIP_TRY(c, tcw::mlp_gemm_parts(Hin_t, b8, m->Gt[l], b8, in, out, b, m->Wp[l], m->Wp_floats[l], c->stream));
+            net->l[l].part = m->Wp[l];
+            net->l[l].splits = splits;
+        } else {
+            HIP_TRY(c, tcw::mlp_gemm_nt(0, Hin_t, b8, m->Gt[l], b8, in, out, b, m->G + m->w_off[l], out, nullptr,
+                                        nullptr, 0, nullptr, 0, nullptr, 0, m->part, m->part_floats, c->stream));
+        }
         if (l > 0) {
             // G_{l-1} = (G_l W_l^T) * gelu'(Z_{l-1}): B = W_l (in x out), rows over out
             HIP_TRY(c, tcw::mlp_gemm_nt(3, m->Gb[l], ld8(out), m->Wb[l], ld8(out), b, in, out, m->Gf[l - 1], in,
@@ -3049,7 +3078,7 @@ extern "C" int tcw_mlp_gradients(tcw_mlp* m, const float* x, const int32_t* labe
                                  float* loss) {
     if (!m || !x || !labels || batch < 1) return TCW_EINVAL;
     int rc = mlp_forward(m, x, batch, labels, nullptr);
-    if (!rc) rc = mlp_backward(m, batch);
+    if (!rc) rc = mlp_backward(m, batch, nullptr);
     if (rc) return rc;
     float ls = 0;
     HIP_TRY(m->ctx, hipMemcpyAsync(&ls, m->loss, 4, hipMemcpyDeviceToHost, m->ctx->stream));
@@ -3064,10 +3093,11 @@ namespace {
 // one step, its loss sum to m->loss[slot]
 int mlp_train_step(tcw_mlp* m, const float* x, const int32_t* labels, int batch, float lr, int slot) {
     int rc = mlp_forward(m, x, batch, labels, nullptr, slot);
-    if (!rc) rc = mlp_backward(m, batch);
     if (rc) return rc;
+    tcw::MlpLayers net = mlp_layers(m);
+    if ((rc = mlp_backward(m, batch, &net))) return rc;
     m->step++;
-    HIP_TRY(m->ctx, tcw::mlp_adam(mlp_layers(m), m->P, m->G, m->M, m->V, lr, 0.9f, 0.999f, 1e-8f, m->step, m->ctx->stream));
+    HIP_TRY(m->ctx, tcw::mlp_adam(net, m->P, m->G, m->M, m->V, lr, 0.9f, 0.999f, 1e-8f, m->step, m->ctx->stream));
     return TCW_OK;
 }
 

@@ -204,8 +204,9 @@ struct MlpLayer {
     const float* g;  // output gradient, batch x out fp32
     float* db;       // bias gradient
     void *wb, *wt;   // bf16 weights, in x out (ld ldb) and out x in (ld ldt)
+    const float* part;  // splits > 1: the weight gradient's partial products (mlp_gemm_parts)
     int64_t w;
-    int in, out, ldb, ldt, tile0, strip0;
+    int in, out, ldb, ldt, tile0, strip0, splits;
 };
 struct MlpLayers {
     int count, tiles, strips;
@@ -225,7 +226,11 @@ hipError_t mlp_gemm_nt(int epi, const void* A, int lda, const void* B, int ldb, 
 // epi 2 without C and T, from an FP32 A that is rounded to bf16 on the way (16-byte aligned, lda a multiple of 4)
 hipError_t mlp_gemm_nt_f32(const float* A, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
                            void* H, int ldh, float* part, size_t part_floats, hipStream_t s);
-// the same for the few rows that mlp_rows_fits, without a workspace; A is bf16, or with f32 as above
+// epi 0 with the partial products left in part, mlp_gemm_splits (> 1) of them one after the other
+int mlp_gemm_splits(int M, int N, int K);
+hipError_t mlp_gemm_parts(const void* A, int lda, const void* B, int ldb, int M, int N, int K, float* part,
+                          size_t part_floats, hipStream_t s);
+// epi 2 as mlp_gemm_nt_f32 for the few rows that mlp_rows_fits, without a workspace; A is bf16, or with f32 as above
 bool mlp_rows_fits(int M);
 hipError_t mlp_rows(const void* A, bool f32, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
                     void* H, int ldh, hipStream_t s);

@@ -632,8 +632,10 @@ __global__ __launch_bounds__(256) void k_weights_bf16(const float* __restrict__ 
 
 // Adam (Kingma & Ba 2015) on the FP32 master copy and the new weights' BF16 copies in both orientations, all
 // layers in one launch: 32 x 32 tiles of each layer's (in + 1) x out parameters, the last row its bias.
-// Bound by memory (seven words a parameter); with the copies from a pass of their own for each layer the
-// 2.6 million parameters of the 4096 -> 512 x 3 -> 11 network took 16 + 17 us, now 22.
+// A weight gradient whose K was split comes as its partial products, summed here in the order of
+// k_splitk_epilogue, so that it is not written and read again.  Bound by memory (seven words a parameter
+// and a word a split).  The 2.6 million parameters of the 4096 -> 512 x 3 -> 11 network at batch 4096 (4, 8, 8
+// and 16 splits): 34 us, with the sums and the copies in passes of their own for each layer 24 + 16 + 17.
 __global__ __launch_bounds__(256) void k_adam(MlpLayers net, float* __restrict__ p, const float* __restrict__ g,
                                               float* __restrict__ m, float* __restrict__ v, float lr, float b1,
                                               float b2, float eps, float c1, float c2) {
@@ -650,8 +652,23 @@ __global__ __launch_bounds__(256) void k_adam(MlpLayers net, float* __restrict__
     for (int rr = ty; rr < 32; rr += 8) {
         const int r = r0 + rr, c = c0 + tx;
         if (r > y.in || c >= y.out) continue;
-        const int64_t i = y.w + (int64_t)r * y.out + c;
-        const float gi = g[i];
+        const int64_t o = (int64_t)r * y.out + c, i = y.w + o;
+        float gi = 0.f;
+        if (y.splits > 1 && r < y.in) {
+            const float* part = y.part + o;
+            const int64_t wn = (int64_t)y.in * y.out;
+            int z = 0;
+            for (; z + 4 <= y.splits; z += 4) {
+                const float a0 = part[z * wn], a1 = part[(z + 1) * wn], a2 = part[(z + 2) * wn], a3 = part[(z + 3) * wn];
+                gi += a0;
+                gi += a1;
+                gi += a2;
+                gi += a3;
+            }
+            for (; z < y.splits; ++z) gi += part[z * wn];
+        } else {
+            gi = g[i];
+        }
         const float mi = b1 * m[i] + (1.f - b1) * gi;
         const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
         m[i] = mi;
@@ -724,7 +741,7 @@ constexpr int ROWS_MAX = 8;
 template <int EPI, typename TA>
 hipError_t gemm_nt_t(const TA* A, int lda, const __bf16* B, int ldb, int M, int N, int K, float* C, int ldc,
                      const float* bias, const float* Z, int ldz, __bf16* H, int ldh, __bf16* T, int ldt, float* part,
-                     size_t part_floats, hipStream_t s) {
+                     size_t part_floats, hipStream_t s, bool sum = true) {
     if (M <= 0 || N <= 0) return hipSuccess;
     int splits = splits_of(M, N, K);
     bool via_part = splits > 1;
@@ -742,7 +759,7 @@ hipError_t gemm_nt_t(const TA* A, int lda, const __bf16* B, int ldb, int M, int 
         hipLaunchKernelGGL((k_gemm_nt<TA, 64, BN, 32, 32, EPI>), grid, dim3(512), 0, s, A, lda, B, ldb, M, N, K, C, ldc,
                            bias, Z, ldz, H, ldh, T, ldt, kchunk, via_part ? part : nullptr);
     }
-    if (via_part) {
+    if (via_part && sum) {
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         dim3 grid((N + 31) / 32, (M + 31) / 32);
@@ -792,6 +809,16 @@ hipError_t mlp_gemm_nt_f32(const float* A, int lda, const void* B, int ldb, int 
     if ((lda & 3) != 0 || ((uintptr_t)A & 15) != 0) return hipErrorInvalidValue;
     return gemm_nt_t<EPI_BIAS_GELU>(A, lda, (const __bf16*)B, ldb, M, N, K, nullptr, N, bias, nullptr, 0, (__bf16*)H,
                                     ldh, nullptr, 0, part, part_floats, s);
+}
+
+int mlp_gemm_splits(int M, int N, int K) { return splits_of(M, N, K); }
+
+hipError_t mlp_gemm_parts(const void* A, int lda, const void* B, int ldb, int M, int N, int K, float* part,
+                          size_t part_floats, hipStream_t s) {
+    const int splits = splits_of(M, N, K);
+    if (splits < 2 || part == nullptr || part_floats < (size_t)splits * M * N) return hipErrorInvalidValue;
+    return gemm_nt_t<EPI_STORE>((const __bf16*)A, lda, (const __bf16*)B, ldb, M, N, K, nullptr, N, nullptr, nullptr, 0,
+                                nullptr, 0, nullptr, 0, part, part_floats, s, false);
 }
 
 bool mlp_rows_fits(int M) { return M <= ROWS_MAX; }

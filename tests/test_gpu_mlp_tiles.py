@@ -58,14 +58,17 @@ def test_output_layer(ctx, inp, depth, classes, batch):
             assert np.all(np.abs(got - ref[name]) <= 2 * bounds[name]), name
 
 
-@pytest.mark.parametrize("inp,hidden,depth,classes", [(33, 31, 2, 5), (64, 32, 1, 32), (7, 1, 0, 2)])
-def test_adam_and_weight_copies(ctx, inp, hidden, depth, classes):
+# the larger batches split the weight gradients' K: 2, 8 and 16 partial products
+@pytest.mark.parametrize("inp,hidden,depth,classes,batch", [(33, 31, 2, 5, 21), (64, 32, 1, 32, 21), (7, 1, 0, 2, 21),
+                                                            (33, 31, 1, 5, 519), (64, 40, 2, 11, 2056),
+                                                            (40, 33, 1, 7, 8192)])
+def test_adam_and_weight_copies(ctx, inp, hidden, depth, classes, batch):
     """The first Adam step from the gradients themselves (eight roundings of at most 2^-24 relative, and the
     subtraction's), and a forward pass on its BF16 weights: that of a new network with those parameters."""
     import torch
     from paper_1606_07413_amd import tcw
-    print("adam", inp, hidden, depth, classes, flush=True)
-    net, params, _, _, xd, yd = small_net(ctx, inp, hidden, depth, classes, 21)
+    print("adam", inp, hidden, depth, classes, batch, flush=True)
+    net, params, _, _, xd, yd = small_net(ctx, inp, hidden, depth, classes, batch)
     p0 = net.params().astype(np.float64)
     g = net.gradients(xd, yd)[0].astype(np.float64)
     lr = 1e-3
@@ -75,7 +78,7 @@ def test_adam_and_weight_copies(ctx, inp, hidden, depth, classes):
     tol = 2.0 ** -24 * np.abs(p0) + 16 * 2.0 ** -24 * np.abs(step)
     assert np.all(np.abs(p1 - (p0 - step)) <= tol)
     fresh = tcw.Network(ctx, inp, hidden, depth, classes, init=p1)
-    a, b = (torch.empty((21, classes), dtype=torch.float32, device="cuda:0") for _ in range(2))
+    a, b = (torch.empty((batch, classes), dtype=torch.float32, device="cuda:0") for _ in range(2))
     net.forward(xd, a)
     fresh.forward(xd, b)
     assert torch.equal(a, b)
