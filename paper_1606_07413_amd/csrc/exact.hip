@@ -363,8 +363,9 @@ __device__ inline void fetch_cols(const T* v, int src, T* part) {
 }
 
 // One rotation R(p) (R(p)^T if transposed) applied to NB rows held by the lane's group, unreduced: the
-// exponent grows by one.  p is the same in every lane of the wavefront (1..4^n - 1).
-template <int NQ, int NB, typename T>
+// exponent grows by one.  p is the same in every lane of the wavefront (1..4^n - 1).  SMALL: the values stay
+// below 2^23 in magnitude, so a 24-bit multiply-add takes the partner with its sign, or not at all.
+template <int NQ, int NB, typename T, bool SMALL = false>
 __device__ inline void rotate_rows(T (*a)[RowGeo<NQ>::CPL], T (*b)[RowGeo<NQ>::CPL], uint32_t p, bool transposed, int gl,
                                    int gbase) {
     constexpr int CPL = RowGeo<NQ>::CPL;
@@ -392,6 +393,13 @@ __device__ inline void rotate_rows(T (*a)[RowGeo<NQ>::CPL], T (*b)[RowGeo<NQ>::C
         }
 #pragma unroll
         for (int j = 0; j < CPL; ++j) {
+            if constexpr (SMALL) {
+                const int32_t s = anti[j] ? (plus[j] ? 1 : -1) : 0;
+                const int32_t ra = anti[j] ? a[i][j] : 2 * b[i][j], rb = anti[j] ? b[i][j] : a[i][j];
+                a[i][j] = __mul24(pa[j], s) + ra;
+                b[i][j] = __mul24(pb[j], s) + rb;
+                continue;
+            }
             const T sa = plus[j] ? pa[j] : -pa[j], sb = plus[j] ? pb[j] : -pb[j];
             const T na = anti[j] ? a[i][j] + sa : 2 * b[i][j];
             b[i][j] = anti[j] ? b[i][j] + sb : a[i][j];
@@ -409,8 +417,9 @@ __device__ inline void rotate_rows(T (*a)[RowGeo<NQ>::CPL], T (*b)[RowGeo<NQ>::C
 // e_S <= log2(3 R 127^2), e_U <= e_S + 1 and every value, bounded by 2^(E/2), stays below 2^17 at n >= 3
 // and 2^30 at n <= 2.  A row must hold one unit entry
 // and the columns must differ; the first row that does not ends the pair.  Bound by the butterflies
-// (2 h R^2 of them).  256 pairs at n = 4, k = 7, half of them claws: 0.14 ms the whole call; the
-// dense product W V^T it replaces (R^3 64-bit products a pair, 16 blocks) took 244 ms.
+// (2 h R^2 of them).  256 pairs at n = 4, k = 7, half of them claws: 81 us the whole call, 51 of them here
+// (56 before the 24-bit multiply-adds); the dense product W V^T it replaces (R^3 64-bit products a pair,
+// 16 blocks) took 244 ms.
 constexpr int CLAW_WAVES = 16;
 template <int NQ, typename T>
 __global__ __launch_bounds__(CLAW_WAVES * 64) void k_claw(const T* __restrict__ sa, const T* __restrict__ sb,
@@ -470,7 +479,7 @@ __global__ __launch_bounds__(CLAW_WAVES * 64) void k_claw(const T* __restrict__ 
                     b[i][j] = row < R ? sb[at] : 0;
                 }
             for (int t = 0; t < steps; ++t)
-                rotate_rows<NQ, NB, T>(a, b, (uint32_t)__builtin_amdgcn_readfirstlane(seq[t]), true, gl, gbase);
+                rotate_rows<NQ, NB, T, NQ >= 3>(a, b, (uint32_t)__builtin_amdgcn_readfirstlane(seq[t]), true, gl, gbase);
             bool row_ok = true;
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
