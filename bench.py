@@ -150,7 +150,7 @@ def walk_roofline(n, h, steps_per_launch, avg_ms, walks, iters):
     traffic = measured_traffic(walks, iters)
     out = {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK_OPS / 1e12, "unit": "Tops/s",
            "frac": achieved / VALU_PEAK_OPS, "traffic": traffic, "traffic_unit": "HBM bytes per launch",
-           "kernel": "k_walk<4,12>", "kernel_ms": avg_ms, "kernel_source_sha256": kernel_source_digest(),
+           "kernel": "k_walk<4,16>", "kernel_ms": avg_ms, "kernel_source_sha256": kernel_source_digest(),
            "ops_per_step": ops, "ops_unit": "32-bit VALU lane-operations of the phi-linear step",
            "literal_method": {"ops_per_step": LITERAL_OPS_PER_STEP_N4,
                               "frac": LITERAL_OPS_PER_STEP_N4 * steps_per_launch / secs / VALU_PEAK_OPS,
