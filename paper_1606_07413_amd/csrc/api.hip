@@ -3232,14 +3232,41 @@ struct LevelTable {
     }
 };
 
+// n = 3: the products of h rotations that the level kernel keeps, for h = 0 .. 5: of two commuting
+// neighbours those with the smaller Pauli first, no two equal ones.
+struct KeptProducts {
+    uint64_t v[6];
+};
+constexpr KeptProducts kept_products3() {
+    KeptProducts k{{1, 0, 0, 0, 0, 0}};
+    uint64_t from[64] = {};  // kept products that start with this Pauli
+    for (int p = 1; p < 64; ++p) from[p] = 1;
+    for (int h = 1; h < 6; ++h) {
+        uint64_t next[64] = {};
+        for (int p = 1; p < 64; ++p) {
+            k.v[h] += from[p];
+            for (int q = 1; q < 64; ++q) {
+                const int both = ((p & 7) & (q >> 3)) ^ ((p >> 3) & (q & 7));  // parity: P_p, P_q anticommute
+                if (((both ^ both >> 1 ^ both >> 2) & 1) || p < q) next[p] += from[q];
+            }
+        }
+        for (int p = 1; p < 64; ++p) from[p] = next[p];
+    }
+    return k;
+}
+constexpr KeptProducts KEPT3 = kept_products3();
+static_assert(KEPT3.v[1] == 63 && KEPT3.v[2] == 2961 && KEPT3.v[4] == 6093325);
+
 int build_level_table(tcw_ctx* c, int n, int h_levels, int h_probe, int64_t targets, uint64_t seed, LevelTable& lt) {
     const int R = 1 << (2 * n);
     HIP_TRY(c, lt.take(&lt.zero_phi, (size_t)R * R / 2 * 4));
     HIP_TRY(c, hipMemsetAsync(lt.zero_phi, 0, (size_t)R * R / 2 * 4, c->stream));
     HIP_TRY(c, lt.take(&lt.keys, (size_t)R * 8));
     HIP_TRY(c, tcw::keys_fill(n, seed, lt.keys, c->stream));
+    // four slots to a product: half the table, and half the clearing, of one for all products at T-count <= 4
+    // (16,384 labels: 4.98 -> 4.81 ms)
     uint64_t entries = 0;
-    for (int h = 0; h <= h_levels; ++h) entries += n_half_of(n, h);
+    for (int h = 0; h <= h_levels; ++h) entries += n == 3 && h < 6 ? KEPT3.v[h] : n_half_of(n, h);
     lt.lg = 10;
     while ((1ull << lt.lg) < 4 * entries && lt.lg < 30) ++lt.lg;
     HIP_TRY(c, lt.take(&lt.table, ((size_t)1 << lt.lg) * 16));
