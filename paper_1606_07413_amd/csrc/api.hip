@@ -3278,7 +3278,7 @@ int build_level_table(tcw_ctx* c, int n, int h_levels, int h_probe, int64_t targ
     for (int h = 0; h <= h_levels; ++h) {
         lt.sp.h = h;
         lt.sp.n_half = (uint32_t)n_half_of(n, h);
-        HIP_TRY(c, tcw::mitm_levels(n, lt.sp, h, lt.table, lt.lg, c->stream));
+        HIP_TRY(c, tcw::mitm_levels(n, lt.sp, h, targets, lt.table, lt.lg, c->stream));
     }
     if (const size_t bytes = tcw::mitm_frag_bytes(n, h_probe, targets)) {
         HIP_TRY(c, lt.take(&lt.frags, bytes));

@@ -144,8 +144,9 @@ hipError_t exact_features(const ExactDev& m, float* out_dev, hipStream_t s);
 // many targets from words: phi (n <= 3 int8 layout), rot_e, features; flag |= 2 / 4 / 8 on range errors
 hipError_t build_batch(int n, const uint16_t* words, const int32_t* offsets, const int32_t* kof, int count,
                        uint32_t* phi_out, int32_t* rot_e_out, float* feat_out, int* flag, hipStream_t s);
-// meet-in-the-middle level table and probes (walk.hip)
-hipError_t mitm_levels(int n, const SpaceDev& sp, int h, uint64_t* table, int log2_table, hipStream_t s);
+// meet-in-the-middle level table and probes (walk.hip); count: the targets in all, the same for the levels and
+// the workspace
+hipError_t mitm_levels(int n, const SpaceDev& sp, int h, int64_t count, uint64_t* table, int log2_table, hipStream_t s);
 // the target side's workspace for `count` targets in all (mitm_frag_bytes bytes; none at n <= 2 and for few
 // targets, mitm_probe then takes null), filled once for any number of mitm_probe calls with the same sp and
 // h_max (unless it holds only a part at a time)

@@ -1141,9 +1141,9 @@ __global__ void k_keys(int r, uint64_t seed, uint64_t* keys) {
 // ---- the walk kernel: trails, distinguished-point table, backtracking (Sec. 3) ----
 
 // Claim a slot for `dp` (linear probing).  Returns 1 = new (claimed), 2 = key present, 3 = full.
-__device__ inline int table_claim(const WalkDev& wd, uint64_t dp, uint64_t& slot) {
+__device__ inline int table_claim_at(const WalkDev& wd, uint64_t dp, uint64_t s, uint64_t& slot) {
     const uint64_t mask = (1ull << wd.log2_table) - 1;
-    uint64_t s = mix64(dp ^ 0x5bd1e9955bd1e995ull) & mask;
+    s &= mask;
     for (int probe = 0; probe < 64; ++probe) {
         uint64_t expected = EMPTY_KEY;
         const bool won = __hip_atomic_compare_exchange_strong(&wd.table[2 * s], &expected, dp, __ATOMIC_RELAXED,
@@ -1159,6 +1159,10 @@ __device__ inline int table_claim(const WalkDev& wd, uint64_t dp, uint64_t& slot
         s = (s + 1) & mask;
     }
     return 3;
+}
+
+__device__ inline int table_claim(const WalkDev& wd, uint64_t dp, uint64_t& slot) {
+    return table_claim_at(wd, dp, mix64(dp ^ 0x5bd1e9955bd1e995ull), slot);
 }
 
 __device__ inline uint64_t pack_value(uint64_t start, uint32_t len) {
@@ -1923,6 +1927,58 @@ __device__ inline uint64_t prefix_keys3(uint64_t u, const uint32_t* p, int j, ui
     return u;
 }
 
+// The level table's first look: the same row digests in the field of p31 = 2^31 - 1 elements (sqrt2 -> 2^16,
+// a square root of 2 there; 1/sqrt2 -> 2^15), half the words of the hash's field.  Products whose first
+// hash finds no entry with its tag are done; one that does is looked up by its full hash, so what counts as
+// a match is decided by the full hash alone (equal cosets have equal first hashes, whatever their rows' order and
+// signs).
+constexpr uint32_t P31 = 0x7fffffffu;
+
+// x mod p31 for x < 2^32 - 1, in [0, p31]
+__device__ inline uint32_t fold31(uint32_t x) { return (x & P31) + (x >> 31); }
+
+// a key of the hash's field as one of this field
+__device__ inline uint32_t key31(uint64_t k) {
+    return fold31(fold31((uint32_t)k & P31) + fold31((uint32_t)(k >> 31)));
+}
+
+// rot3 here: u and the partner in [0, p31], and so the result
+__device__ inline uint32_t rot31(uint32_t u, uint32_t p, uint64_t anti, uint64_t plus, int lane) {
+    const uint32_t part = shfl32(u, lane ^ (int)p);
+    const uint32_t sum = u + (((plus >> p) & 1) ? part : P31 - part);
+    const uint32_t rot = fold31(((sum & 0xffffu) << 15) + (sum >> 16));  // below 2^31 + 2^16 before the fold
+    return ((anti >> p) & 1) ? rot : u;
+}
+__device__ inline uint32_t prefix_keys31(uint32_t u, const uint32_t* p, int j, uint64_t anti, uint64_t plus, int lane) {
+#pragma unroll
+    for (int t = Geo<3>::HMAX - 1; t >= 1; --t)
+        if (t < j) u = rot31(u, p[t], anti, plus, lane);
+    return u;
+}
+
+// an element of the first hash: of a digest c in [0, p31] and its negative the smaller (0 for p31)
+__device__ inline uint64_t digest_map31(uint32_t c, uint32_t ka, uint32_t kb) {
+    const uint32_t m = min(c, P31 - c);
+    return (uint64_t)(m + ka) * (uint64_t)(m ^ kb);
+}
+
+// A table entry's value: the tag of its first hash over 255 - (least h that reaches it).
+__device__ inline uint64_t level_value(uint64_t h31, int h) { return (h31 & ~255ull) | (uint64_t)(255 - h); }
+
+// The level of the entry with this first hash, or -1; with a key also that full hash is asked for.
+__device__ inline int level_lookup31(const uint64_t* table, int log2_table, uint64_t h31, bool full, uint64_t key) {
+    const uint64_t mask = (1ull << log2_table) - 1;
+    uint64_t s = (h31 >> 8) & mask;
+    for (int probe = 0; probe < 64; ++probe) {
+        const uint64_t k = __hip_atomic_load(&table[2 * s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t v = __hip_atomic_load(&table[2 * s + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (k == EMPTY_KEY) return -1;
+        if (full ? k == key : ((v ^ h31) & ~255ull) == 0) return 255 - (int)(v & 255);
+        s = (s + 1) & mask;
+    }
+    return -1;
+}
+
 // v summed over the lane's 16-lane row
 __device__ inline uint64_t row_sum16(uint64_t v) {
     v += dpp64<0xB1>(v);
@@ -1936,9 +1992,11 @@ __device__ inline uint64_t row_sum16(uint64_t v) {
 // cross-half exchanges leave one product per 16-lane row), each kept by one lane; then every lane
 // finishes and stores its own product, so that the table's atomics, each a round trip to memory, run 64
 // at a time.  Bound by the butterfly, the element map and the sums (about 45 VALU instructions a
-// product) with the pruned products left out: the 16 million products of levels 0..4 take 0.81 ms,
+// product) with the pruned products left out: the 16 million products of levels 0..4 take 0.78 ms (0.97 with FIRST, the
+// first hash beside the full one),
 // against 4.85 ms with a wavefront per product and one lane at the table.
 constexpr int MITM_WAVES = 4;
+template <bool FIRST>
 __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_levels3(SpaceDev sp, int h, uint32_t prefixes, uint64_t* table,
                                                                   int log2_table) {
     const int lane = threadIdx.x & 63;
@@ -1946,6 +2004,7 @@ __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_levels3(SpaceDev sp
     uint64_t anti, plus;
     rot3_masks(lane, anti, plus);
     const uint64_t key0 = sp.keys[lane];
+    const uint32_t key0_31 = key31(key0);
     WalkDev wd{};
     wd.table = table;
     wd.log2_table = log2_table;
@@ -1956,24 +2015,32 @@ __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_levels3(SpaceDev sp
         const int products = (int)__popcll(todo);
         if (products == 0) continue;
         const uint64_t u = prefix_keys3(key0, p, h, anti, plus, lane);
-        uint64_t mine = 0;
+        uint32_t u31 = 0;
+        if constexpr (FIRST) u31 = prefix_keys31(key0_31, p, h, anti, plus, lane);
+        uint64_t mine = 0, mine31 = 0;
         for (int quad = 0; todo != 0; ++quad) {
-            uint64_t acc[4];
+            uint64_t acc[4], acc31[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const uint32_t p0 = next_product(todo);
                 const uint64_t v = p0 ? rot3(u, p0, anti, plus, lane) : u;
                 acc[i] = digest_map(m61_fold(v), ka, kb);
+                if constexpr (FIRST) acc31[i] = digest_map31(p0 ? rot31(u31, p0, anti, plus, lane) : u31, ka, kb);
             }
             // rows 0..3 of 16 lanes: products 0, 1, 2, 3
             const uint64_t sum = row_sum16(half_add16(half_add32(acc[0], acc[2]), half_add32(acc[1], acc[3])));
             if ((lane & 15) == quad) mine = sum;
+            if constexpr (FIRST) {
+                const uint64_t sum31 =
+                    row_sum16(half_add16(half_add32(acc31[0], acc31[2]), half_add32(acc31[1], acc31[3])));
+                if ((lane & 15) == quad) mine31 = sum31;
+            }
         }
         if (4 * (lane & 15) + (lane >> 4) < products) {
-            const uint64_t H = mix64(mine);
+            const uint64_t H = mix64(mine), key = H == EMPTY_KEY ? (H ^ 1) : H, h31 = mix64(mine31);
             uint64_t slot = 0;
-            if (table_claim(wd, H == EMPTY_KEY ? (H ^ 1) : H, slot) != 3)
-                atomicMax(&table[2 * slot + 1], (uint64_t)(255 - h));
+            if ((FIRST ? table_claim_at(wd, key, h31 >> 8, slot) : table_claim(wd, key, slot)) != 3)
+                atomicMax(&table[2 * slot + 1], FIRST ? level_value(h31, h) : (uint64_t)(255 - h));
         }
     }
 }
@@ -2008,10 +2075,34 @@ __device__ inline void pair_frags3(PairRows& L, uint64_t u, const uint32_t (&p)[
     wave_sync();
 }
 
-// Many targets share the fragments (2 KiB a pair, 32 pairs a prefix: MITM_PREFIX_V4 vectors), made once.  Bound
-// by the stores: 142 thousand products (at most three rotations) 79 us, 112 with a byte stored at a time and the
-// masks collected from the table of bytes.
-constexpr int MITM_PREFIX_V4 = 32 * 2 * 64;
+// The first hash's fragments: four products to an operand, the signed base-256 digits of their keys in
+// (-2^30, 2^30) as rows 4w .. 4w + 3, K = [u | 2^16 u].
+__device__ inline void quad_frags31(PairRows& L, uint32_t u, const uint32_t (&p)[4], uint64_t anti, uint64_t plus,
+                                    int lane, v4i& a0, v4i& a1) {
+    uint8_t* at = reinterpret_cast<uint8_t*>(L.rows) + lane;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const uint32_t v = p[w] ? rot31(u, p[w], anti, plus, lane) : u;
+#pragma unroll
+        for (int set = 0; set < 2; ++set) {
+            // 2^16 v = a 2^31 + b 2^16 with v = a 2^15 + b
+            const uint32_t x = set ? fold31(((v & 0x7fffu) << 16) + (v >> 15)) : v;
+            const uint32_t c = x > (P31 >> 1) ? x - P31 : x;
+            const uint32_t b = (c + 0x80808080u) ^ 0x80808080u;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) at[(set * 16 + w * 4 + m) * PAIR_PITCH] = (uint8_t)(b >> (8 * m));
+        }
+    }
+    wave_sync();
+    const v4i* from = L.rows + (lane & 15) * (PAIR_PITCH / 16) + (lane >> 4);
+    a0 = from[0];
+    a1 = from[16 * (PAIR_PITCH / 16)];
+    wave_sync();
+}
+
+// Many targets share these fragments (2 KiB a quad, 16 quads a prefix: MITM_PREFIX_V4 vectors), made once.  Bound
+// by the stores.
+constexpr int MITM_PREFIX_V4 = 16 * 2 * 64;
 __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_keys3(SpaceDev sp, int j, uint32_t y0, uint32_t prefixes,
                                                                 v4i* frags) {
     __shared__ PairRows L[MITM_WAVES];
@@ -2023,18 +2114,38 @@ __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_keys3(SpaceDev sp, 
         uint32_t p[Geo<3>::HMAX] = {};
         uint64_t todo = prefix3(uniform32(y0 + i), j, p);
         if (todo == 0) continue;
-        const uint64_t u = prefix_keys3(sp.keys[lane], p, j, anti, plus, lane);
+        const uint32_t u = prefix_keys31(key31(sp.keys[lane]), p, j, anti, plus, lane);
         v4i* out = frags + (size_t)i * MITM_PREFIX_V4 + lane;
-        const int pairs = ((int)__popcll(todo) + 3) / 4 * 2;  // whole quads; what no product fills repeats the prefix
-        for (int q = 0; q < pairs; ++q) {
-            const uint32_t two[2] = {next_product(todo), next_product(todo)};
+        const int quads = ((int)__popcll(todo) + 3) / 4;  // what no product fills repeats the prefix
+        for (int q = 0; q < quads; ++q) {
+            const uint32_t four[4] = {next_product(todo), next_product(todo), next_product(todo), next_product(todo)};
             if ((q & (MITM_WAVES - 1)) != wave) continue;
             v4i a0, a1;
-            pair_frags3(L[wave], u, two, anti, plus, lane, a0, a1);
+            quad_frags31(L[wave], u, four, anti, plus, lane, a0, a1);
             out[q * 128] = a0;
             out[q * 128 + 64] = a1;
         }
     }
+}
+
+// Four products' first hash sums from one pass of 8 MFMAs: accumulator row 4g + i of lane l (g = l / 16) is digit
+// i of product g in matrix row 16 nt + l % 16, |acc| <= 128 * 128 * 127 < 2^21.  s31: the target's exponent as
+// a power of two, (2^15)^e = 2^s31.
+__device__ inline uint64_t quad_sum31(const v4i a0, const v4i a1, const v4i* bf, uint32_t two_s31, uint32_t ka, uint32_t kb) {
+    constexpr int64_t BIAS = (int64_t)P31 << 17;  // a multiple of p31 above every |digest|
+    uint64_t sum = 0;
+#pragma unroll
+    for (int nt = 0; nt < N3_NT; ++nt) {
+        v4i acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bf[2 * nt], v4i{0, 0, 0, 0}, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bf[2 * nt + 1], acc, 0, 0, 0);
+        const int32_t x = acc[0] + acc[1] * 256, y = acc[2] + acc[3] * 256;  // below 2^30 in magnitude
+        const uint64_t v = (uint64_t)((int64_t)y * 65536 + ((int64_t)x + BIAS));  // below 2^49
+        const uint32_t r = ((uint32_t)v & P31) + (uint32_t)(v >> 31);  // below 2^31 + 2^18
+        const uint64_t w = (uint64_t)r * two_s31;                       // below 2^61 + 2^48
+        const uint32_t c = fold31(((uint32_t)w & P31) + (uint32_t)(w >> 31));  // below 2^31 + 2^30 + 2^17 before
+        sum += digest_map31(c, ka, kb);
+    }
+    return sum;
 }
 
 // Two products' hash sums from one pass of 8 MFMAs: accumulator row 4g + i of lane l (g = l / 16) is
@@ -2059,20 +2170,18 @@ __device__ inline uint64_t pair_sum3(const v4i a0, const v4i a1, const v4i* bf, 
 // Probes of `count` targets against the level table, products of j rotations of prefixes y0 ..
 // y0 + prefixes - 1 (frags from k_mitm_keys3).  A wavefront keeps its target's packed U as eight B
 // fragments in registers and shares the target's prefixes with the `slices` wavefronts of the same
-// target; two pairs of products fill the four 16-lane rows, as in k_mitm_levels3, and 64 lanes look up
+// target; four products fill the four 16-lane rows, as in k_mitm_levels3, and 64 lanes look up
 // at a time.  A target that an earlier level has answered is skipped, and one hit ends its level (each
 // wavefront looks after every prefix): every coset of T-count <= h_id is tabled, so the first level with
 // a hit is T - h_id (or 0) and its total T.  The wavefronts are ordered by slice, then target, so that
 // a hit in one slice spares the target's later ones, and wavefronts that run together read the same
 // prefixes.
-// Bound by VALU issue: about 39 instructions and four MFMAs a product (64 % and 22 % of the time at four
-// wavefronts per SIMD, PMC); label batches read the fragments (3 MiB for j <= 2) from L2.  16384 circuits
-// against the table of T-count <= 4: 3.1 ms.  One target's 142 thousand products of <= 3 rotations:
-// 0.05 ms (its own fragments made on the way).  The accumulators stay in VGPRs (a budget of 128 by the second launch bound: with 512 the
-// compiler puts them in AGPRs and moves each out) and the fragments alternate between two register sets;
-// with AGPRs and a copied set a product took 52 instructions, with each target's two wavefronts side by
-// side the whole 4.35 ms.
-// MAKE: no fragments were made (frags unused), the wavefront makes its own, about 30 instructions a product.
+// MAKE (few targets): by the full hash, the wavefront's own fragments.  Else by the first hash from stored
+// fragments, and the full hash of what it finds: half the instructions and MFMAs a product (39 and four by
+// the full hash alone, VALU-bound at 0.64 busy).  16384 circuits against the table of T-count <= 4: 2.1 ms, 3.1
+// by the full hash alone (4.35 with its accumulators in AGPRs, a copied fragment set and each target's two
+// wavefronts side by side: the second launch bound's 128 registers keep the accumulators in VGPRs).  One
+// target's 142 thousand products of <= 3 rotations: 0.05 ms.
 template <bool MAKE>
 __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_probe3(SpaceDev sp, const v4i* __restrict__ phi_all,
                                                                  const int32_t* __restrict__ rot_e_all, int count,
@@ -2090,67 +2199,95 @@ __global__ __launch_bounds__(MITM_WAVES * 64, 4) void k_mitm_probe3(SpaceDev sp,
 #pragma unroll
     for (int i = 0; i < N3_NT * N3_KK; ++i) bf[i] = phi_all[((size_t)t * N3_NT * N3_KK + i) * 64 + lane];
     const uint32_t s = uniform32((uint32_t)rot_e_all[t]);
-    __shared__ PairRows L[MAKE ? MITM_WAVES : 1];
-    uint64_t anti = 0, plus = 0, key0 = 0;
-    if constexpr (MAKE) {
-        rot3_masks(lane, anti, plus);
-        plus = ~plus;  // R^T
-        key0 = sp.keys[lane];
-    }
+    // the exponent e from 30 e mod 61 (59 is 30's inverse there; e < 61 for int8 entries)
+    const uint32_t two_s31 = 1u << (15u * (s * 59u % 61u) % 31u);
+    __shared__ PairRows L[MITM_WAVES];
+    PairRows& rows = L[threadIdx.x >> 6];
+    uint64_t anti, plus;
+    rot3_masks(lane, anti, plus);
+    plus = ~plus;  // R^T
+    const uint64_t key0 = sp.keys[lane];
     for (uint32_t y = (uint32_t)slice; y < prefixes; y += (uint32_t)slices) {
         uint32_t p[Geo<3>::HMAX] = {};
-        uint64_t todo = prefix3(uniform32(y0 + y), j, p);
-        const int products = (int)__popcll(todo);
+        const uint64_t all = prefix3(uniform32(y0 + y), j, p);
+        const int products = (int)__popcll(all);
         if (products == 0) continue;
         const int quads = (products + 3) / 4;
         uint64_t mine = 0;
-        const auto work = [&](int quad, const v4i (&a)[4]) {
-            const uint64_t s01 = pair_sum3(a[0], a[1], bf, s, ka, kb),
-                           s23 = pair_sum3(a[2], a[3], bf, s, ka, kb);
-            // 32-lane halves hold the two products of a pair; after the exchange row g of 16 lanes holds
-            // product 0, 2, 1, 3 of the quad
-            const uint64_t sum = row_sum16(half_add16(s01, s23));
-            if ((lane & 15) == quad) mine = sum;
-        };
         if constexpr (MAKE) {
+            uint64_t todo = all;
             const uint64_t u = prefix_keys3(key0, p, j, anti, plus, lane);
-            PairRows& rows = L[threadIdx.x >> 6];
             for (int quad = 0; quad < quads; ++quad) {
-                v4i a[4];
+                uint64_t pair[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const uint32_t two[2] = {next_product(todo), next_product(todo)};
-                    pair_frags3(rows, u, two, anti, plus, lane, a[2 * i], a[2 * i + 1]);
+                    v4i a0, a1;
+                    pair_frags3(rows, u, two, anti, plus, lane, a0, a1);
+                    pair[i] = pair_sum3(a0, a1, bf, s, ka, kb);
                 }
-                work(quad, a);
+                // 32-lane halves hold the two products of a pair; after the exchange row g of 16 lanes holds
+                // product 0, 2, 1, 3 of the quad
+                const uint64_t sum = row_sum16(half_add16(pair[0], pair[1]));
+                if ((lane & 15) == quad) mine = sum;
             }
-        } else {
-            // the next quad's fragments are on their way while one is worked on: two register sets in turn,
-            // so that none is copied to the other
-            const v4i* f = frags + (size_t)y * MITM_PREFIX_V4 + lane;
-            const auto fetch = [&](int quad, v4i (&to)[4]) {
-                if (quad >= quads) return;
+            const int g = lane >> 4, in_quad = ((g & 1) << 1) | (g >> 1);
+            int lvl = -1;
+            if (4 * (lane & 15) + in_quad < products) {
+                const uint64_t H = mix64(mine);
+                lvl = level_lookup(table, log2_table, H == EMPTY_KEY ? (H ^ 1) : H);
+            }
+            if (lvl >= 0) atomicMin(best, (uint32_t)(j + lvl));
+            if (__ballot(lvl >= 0) != 0) return;
+            if (uniform32(__hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != ~0u) return;
+            continue;
+        }
+        const auto work = [&](int quad, const v4i (&a)[2]) {
+            const uint64_t sum = row_sum16(quad_sum31(a[0], a[1], bf, two_s31, ka, kb));
+            if ((lane & 15) == quad) mine = sum;  // of product 4 quad + lane / 16
+        };
+        // the next quad's fragments are on their way while one is worked on: two register sets in turn, so
+        // that none is copied to the other
+        const v4i* f = frags + (size_t)y * MITM_PREFIX_V4 + lane;
+        const auto fetch = [&](int quad, v4i (&to)[2]) {
+            if (quad >= quads) return;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) to[i] = f[quad * 256 + 64 * i];
-            };
-            v4i even[4], odd[4];
-            fetch(0, even);
-            for (int quad = 0; quad < quads; quad += 2) {
-                fetch(quad + 1, odd);
-                work(quad, even);
-                if (quad + 1 >= quads) break;
-                fetch(quad + 2, even);
-                work(quad + 1, odd);
+            for (int i = 0; i < 2; ++i) to[i] = f[quad * 128 + 64 * i];
+        };
+        v4i even[2], odd[2];
+        fetch(0, even);
+        for (int quad = 0; quad < quads; quad += 2) {
+            fetch(quad + 1, odd);
+            work(quad, even);
+            if (quad + 1 >= quads) break;
+            fetch(quad + 2, even);
+            work(quad + 1, odd);
+        }
+        const int mine_at = 4 * (lane & 15) + (lane >> 4);
+        const uint64_t h31 = mix64(mine);
+        uint64_t found = __ballot(mine_at < products && level_lookup31(table, log2_table, h31, false, 0) >= 0);
+        bool hit = false;
+        while (found != 0) {
+            // the whole wavefront takes the full hash of one such product
+            const int l = (int)__builtin_ctzll(found);
+            found &= found - 1;
+            uint64_t rest = all;
+            for (int i = 4 * (l & 15) + (l >> 4); i > 0; --i) rest &= rest - 1;
+            const uint32_t p0 = next_product(rest), two[2] = {p0, p0};
+            const uint64_t u = prefix_keys3(key0, p, j, anti, plus, lane);
+            v4i a0, a1;
+            pair_frags3(rows, u, two, anti, plus, lane, a0, a1);
+            const uint64_t half = pair_sum3(a0, a1, bf, s, ka, kb);
+            const uint64_t H = mix64(row_sum16(half_add16(half, half)));  // the same in every lane
+            if (lane == l) {
+                const int lvl = level_lookup31(table, log2_table, h31, true, H == EMPTY_KEY ? (H ^ 1) : H);
+                if (lvl >= 0) {
+                    atomicMin(best, (uint32_t)(j + lvl));
+                    hit = true;
+                }
             }
         }
-        const int g = lane >> 4, in_quad = ((g & 1) << 1) | (g >> 1);
-        int lvl = -1;
-        if (4 * (lane & 15) + in_quad < products) {
-            const uint64_t H = mix64(mine);
-            lvl = level_lookup(table, log2_table, H == EMPTY_KEY ? (H ^ 1) : H);
-        }
-        if (lvl >= 0) atomicMin(best, (uint32_t)(j + lvl));
-        if (__ballot(lvl >= 0) != 0) return;
+        if (__ballot(hit) != 0) return;
         if (uniform32(__hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != ~0u) return;
     }
 }
@@ -2354,15 +2491,24 @@ hipError_t launch_enum_pairs(const WalkDev& wd, hipStream_t s) {
 
 namespace tcw {
 
-hipError_t mitm_levels(int n, const SpaceDev& sp, int h, uint64_t* table, int log2_table, hipStream_t s) {
+// Up to MITM_MAKE targets are probed by the full hash alone and make their fragments themselves: the products of
+// at most three rotations take 48 us for one target so, in one launch a level, and stored fragments of the
+// full hash 79 to make and 45 to use.  More targets share stored fragments of the first hash, which the table
+// then needs too: 0.97 ms instead of 0.78 for T-count <= 4, and 2.1 instead of 3.1 to probe 16384 circuits.
+constexpr int MITM_MAKE = 4;
+hipError_t mitm_levels(int n, const SpaceDev& sp, int h, int64_t count, uint64_t* table, int log2_table, hipStream_t s) {
     auto f = [&]<int NQ>() -> hipError_t {
         constexpr int W = WalkWaves<NQ>::value;
         if constexpr (NQ == 3) {
             const uint32_t prefixes = h == 0 ? 1 : sp.n_half / Geo<3>::XI;
             uint32_t blocks = (prefixes + MITM_WAVES - 1) / MITM_WAVES;
             if (blocks > 4096) blocks = 4096;
-            hipLaunchKernelGGL(k_mitm_levels3, dim3(blocks), dim3(MITM_WAVES * 64), 0, s, sp, h, prefixes, table,
-                               log2_table);
+            if (count > MITM_MAKE)
+                hipLaunchKernelGGL(k_mitm_levels3<true>, dim3(blocks), dim3(MITM_WAVES * 64), 0, s, sp, h, prefixes, table,
+                                   log2_table);
+            else
+                hipLaunchKernelGGL(k_mitm_levels3<false>, dim3(blocks), dim3(MITM_WAVES * 64), 0, s, sp, h, prefixes, table,
+                                   log2_table);
             return hipGetLastError();
         } else if constexpr (NQ <= 2) {
             int64_t blocks = ((int64_t)sp.n_half + W * Geo<NQ>::WPW - 1) / (W * Geo<NQ>::WPW);
@@ -2386,10 +2532,6 @@ static uint32_t mitm_prefixes(int j) {
     return v;
 }
 
-// Up to MITM_MAKE targets make their fragments themselves: the products of at most three rotations take 48 us
-// for one target so, in one launch a level, and 45 with stored fragments, which take 79 to make and, by chunks,
-// ten more launches.  A target more costs three quarters more instructions a product so.
-constexpr int MITM_MAKE = 4;
 size_t mitm_frag_bytes(int n, int h_max, int64_t count) {
     if (n != 3 || count <= MITM_MAKE) return 0;
     size_t all = 0;
