@@ -1832,9 +1832,9 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_mitm_probe(SpaceDev sp0, cons
         load_lds(L, sp);
         if (threadIdx.x == 0) best = ~0u;
         __syncthreads();
-        uint32_t nh = 1;
+        uint32_t nh = 1, so_far = ~0u;
         for (int j = 0; j <= h_max; ++j) {
-            if ((uint32_t)j >= best) break;
+            if ((uint32_t)j >= so_far) break;
             sp.h = j;
             sp.n_half = nh;
             for (int64_t base = ((int64_t)blockIdx.y * WAVES + wave) * Gm::WPW; base < (int64_t)nh;
@@ -1849,6 +1849,10 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_mitm_probe(SpaceDev sp0, cons
                 }
             }
             nh *= Gm::XI;
+            // read between two barriers: a level's wavefronts have all stopped changing it and the next level's
+            // have not begun, so the block leaves the loop together
+            __syncthreads();
+            so_far = best;
             __syncthreads();
         }
         if (threadIdx.x == 0 && best != ~0u) atomicMin(reinterpret_cast<uint32_t*>(&best_out[t]), best);
