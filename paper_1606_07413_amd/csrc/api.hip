@@ -103,29 +103,47 @@ int hip_fail(tcw_ctx* c, hipError_t e, const char* where) {
 // A search at n = 4 opens hundreds of chunk spaces as batch members, and allocating and freeing
 // their buffers costs more than the kernels that fill them.  A finished batch returns its members'
 // buffers here (after its streams are synchronised, so no work on them is pending) and later members
-// take buffers of exactly the size they need; beyond POOL_MAX bytes they are freed.  tcw_destroy
-// frees the rest.
+// take buffers of exactly the size they need; beyond POOL_MAX bytes they are freed, and all of them when an
+// allocation of the context finds no memory.  tcw_destroy frees the rest.
 constexpr size_t POOL_MAX = (size_t)40 << 30;
+
+// Runs an allocation; where memory has run out while the pool holds idle buffers (nothing is pending on
+// them), those are freed and it is run once more.  A failed call's error is cleared so that later launch
+// checks do not see it.  Every device allocation of a context but its first goes through here.
+template <typename F>
+hipError_t freeing_pool(tcw_ctx* c, F&& alloc) {
+    hipError_t e = alloc();
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    if (c->pool.empty()) return e;
+    for (auto& kv : c->pool) (void)hipFree(kv.second);
+    c->pool.clear();
+    c->pool_bytes = 0;
+    e = alloc();
+    if (e == hipErrorOutOfMemory) (void)hipGetLastError();
+    return e;
+}
+
+template <typename T>
+hipError_t dev_alloc(tcw_ctx* c, T** p, size_t bytes) {
+    return freeing_pool(c, [&] { return hipMalloc(reinterpret_cast<void**>(p), bytes); });
+}
+
+hipError_t target_alloc(tcw_ctx* c, tcw::ExactDev& U, int n) {
+    return freeing_pool(c, [&] {
+        const hipError_t e = tcw::exact_alloc(U, n);
+        if (e != hipSuccess) tcw::exact_free(U);
+        return e;
+    });
+}
 
 hipError_t pool_alloc(tcw_ctx* c, void** p, size_t bytes) {
     auto it = c->pool.find(bytes);
-    if (it != c->pool.end()) {
-        *p = it->second;
-        c->pool.erase(it);
-        c->pool_bytes -= bytes;
-        return hipSuccess;
-    }
-    hipError_t e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory && !c->pool.empty()) {
-        // pooled buffers of other sizes hold the memory: free them (nothing is pending on them) and
-        // try once more; the failed call's error is cleared so that later launch checks do not see it
-        (void)hipGetLastError();
-        for (auto& kv : c->pool) (void)hipFree(kv.second);
-        c->pool.clear();
-        c->pool_bytes = 0;
-        e = hipMalloc(p, bytes);
-    }
-    return e;
+    if (it == c->pool.end()) return dev_alloc(c, p, bytes);
+    *p = it->second;
+    c->pool.erase(it);
+    c->pool_bytes -= bytes;
+    return hipSuccess;
 }
 
 void pool_put(tcw_ctx* c, void* p, size_t bytes) {
@@ -171,7 +189,7 @@ int batch_streams(tcw_ctx* c, const bool* has) {
 // return included).
 class DevScope {
    public:
-    DevScope() = default;
+    explicit DevScope(tcw_ctx* c) : ctx_(c) {}
     DevScope(const DevScope&) = delete;
     DevScope& operator=(const DevScope&) = delete;
     ~DevScope() {
@@ -180,7 +198,7 @@ class DevScope {
     template <typename T>
     hipError_t alloc(T** p, size_t bytes) {
         void* q = nullptr;
-        const hipError_t e = hipMalloc(&q, bytes);
+        const hipError_t e = dev_alloc(ctx_, &q, bytes);
         if (e != hipSuccess) return e;
         bufs_.push_back(q);
         *p = static_cast<T*>(q);
@@ -188,6 +206,7 @@ class DevScope {
     }
 
    private:
+    tcw_ctx* ctx_;
     std::vector<void*> bufs_;
 };
 
@@ -299,11 +318,11 @@ int rotated_keys(tcw_ctx* c, uint64_t seed, std::shared_ptr<tcw::RotKeys>& out) 
             c->rot_keys.erase(victim);
         }
         auto rk = std::make_shared<tcw::RotKeys>();
-        HIP_TRY(c, hipMalloc(&rk->keys, 256 * sizeof(uint64_t)));
+        HIP_TRY(c, dev_alloc(c, &rk->keys, 256 * sizeof(uint64_t)));
         HIP_TRY(c, tcw::keys_fill(4, seed, rk->keys, c->stream));
-        HIP_TRY(c, hipMalloc(&rk->t1, (size_t)2 * 256 * 256 * sizeof(uint64_t)));
+        HIP_TRY(c, dev_alloc(c, &rk->t1, (size_t)2 * 256 * 256 * sizeof(uint64_t)));
         HIP_TRY(c, tcw::rot_keys_fill(rk->keys, rk->t1, c->stream));
-        if (hipMalloc(&rk->t2, (size_t)2 * 256 * 256 * 256 * sizeof(uint64_t)) == hipSuccess) {
+        if (dev_alloc(c, &rk->t2, (size_t)2 * 256 * 256 * 256 * sizeof(uint64_t)) == hipSuccess) {
             HIP_TRY(c, tcw::rot_keys2_fill(rk->t1, rk->t2, c->stream));
         } else {
             rk->t2 = nullptr;  // without the 256 MiB table the step applies one more rotation
@@ -330,7 +349,7 @@ int setup_space(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, Space& out
         if (out.pooled)
             HIP_TRY(c, pool_alloc(c, reinterpret_cast<void**>(&out.mem), Space::mem_bytes(n)));
         else
-            HIP_TRY(c, hipMalloc(&out.mem, Space::mem_bytes(n)));
+            HIP_TRY(c, dev_alloc(c, &out.mem, Space::mem_bytes(n)));
     }
     out.ctx = c;
     out.k = sp->k;
@@ -557,7 +576,7 @@ int tcw_target_from_words(tcw_ctx* c, int n, const uint16_t* paulis, int k, cons
     if (!t) return TCW_ENOMEM;
     t->ctx = c;
     t->n = n;
-    hipError_t e = tcw::exact_alloc(t->U, n);
+    hipError_t e = target_alloc(c, t->U, n);
     int flag = 0;
     int rc = TCW_OK;
     if (tcw::exact_words_fit(m, k)) {
@@ -570,13 +589,16 @@ int tcw_target_from_words(tcw_ctx* c, int n, const uint16_t* paulis, int k, cons
         seq.reserve(2 * (size_t)m + k);
         for (int j = 0; j < m; ++j) seq.insert(seq.end(), 2, clifford[j]);
         seq.insert(seq.end(), rot.begin(), rot.end());
-        DevScope scope;
+        DevScope scope(c);
         uint16_t* seq_dev = nullptr;
         if (e == hipSuccess) e = scope.alloc(&seq_dev, seq.size() * sizeof(uint16_t));
         if (e == hipSuccess)
             e = hipMemcpyAsync(seq_dev, seq.data(), seq.size() * sizeof(uint16_t), hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->flag, 0, sizeof(int), c->stream);
-        if (e == hipSuccess) e = tcw::exact_build(t->U, seq_dev, nullptr, (int)seq.size(), c->flag, c->stream);
+        if (e == hipSuccess)
+            e = freeing_pool(c, [&] {  // its two work matrices
+                return tcw::exact_build(t->U, seq_dev, nullptr, (int)seq.size(), c->flag, c->stream);
+            });
         if (e == hipSuccess) rc = read_flag(c, &flag);
     }
     if (e != hipSuccess) rc = hip_fail(c, e, "target build");
@@ -601,9 +623,9 @@ int tcw_target_from_channel(tcw_ctx* c, int n, const int32_t* a, const int32_t* 
     t->ctx = c;
     t->n = n;
     int32_t *da = nullptr, *db = nullptr;
-    hipError_t e = tcw::exact_alloc(t->U, n);
-    if (e == hipSuccess) e = hipMalloc(&da, rr * 4);
-    if (e == hipSuccess) e = hipMalloc(&db, rr * 4);
+    hipError_t e = target_alloc(c, t->U, n);
+    if (e == hipSuccess) e = dev_alloc(c, &da, rr * 4);
+    if (e == hipSuccess) e = dev_alloc(c, &db, rr * 4);
     if (e == hipSuccess) e = hipMemcpyAsync(da, a, rr * 4, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(db, b, rr * 4, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->flag, 0, sizeof(int), c->stream);
@@ -643,10 +665,10 @@ int tcw_target_from_unitary(tcw_ctx* c, int n, const int64_t* v, int32_t e, tcw_
     t->n = n;
     int64_t* dv = nullptr;
     int32_t *da = nullptr, *db = nullptr;
-    hipError_t err = tcw::exact_alloc(t->U, n);
-    if (err == hipSuccess) err = hipMalloc(&dv, d * d * 4 * sizeof(int64_t));
-    if (err == hipSuccess) err = hipMalloc(&da, rr * 4);
-    if (err == hipSuccess) err = hipMalloc(&db, rr * 4);
+    hipError_t err = target_alloc(c, t->U, n);
+    if (err == hipSuccess) err = dev_alloc(c, &dv, d * d * 4 * sizeof(int64_t));
+    if (err == hipSuccess) err = dev_alloc(c, &da, rr * 4);
+    if (err == hipSuccess) err = dev_alloc(c, &db, rr * 4);
     if (err == hipSuccess) err = hipMemcpyAsync(dv, v, d * d * 4 * sizeof(int64_t), hipMemcpyHostToDevice, c->stream);
     if (err == hipSuccess) err = hipMemsetAsync(c->flag, 0, sizeof(int), c->stream);
     if (err == hipSuccess) err = tcw::exact_from_unitary(t->U, dv, e, da, db, c->flag, c->stream);
@@ -702,7 +724,7 @@ int tcw_target_random(tcw_ctx* c, int n, int k, uint64_t seed, tcw_target** out,
         std::vector<int32_t> perm(R);
         std::vector<int8_t> sign(R);
         {
-            DevScope scope;
+            DevScope scope(c);
             hipError_t e = scope.alloc(&dok, 4);
             if (e == hipSuccess) e = scope.alloc(&dperm, R * 4);
             if (e == hipSuccess) e = scope.alloc(&dsign, R);
@@ -747,7 +769,7 @@ int tcw_target_channel(tcw_ctx* c, const tcw_target* t, int32_t* a, int32_t* b, 
         return TCW_OK;
     }
     int32_t *da = nullptr, *db = nullptr;
-    DevScope scope;
+    DevScope scope(c);
     HIP_TRY(c, scope.alloc(&da, rr * 4));
     HIP_TRY(c, scope.alloc(&db, rr * 4));
     int rc = clear_flag(c);
@@ -870,7 +892,7 @@ int tcw_canon_hash(tcw_ctx* c, int n, const tcw_space* sp, const int32_t* a, con
     if (count > (int64_t)1 << 31) return fail(c, TCW_EINVAL, "count above 2^31");  // keeps the byte count exact
     uint32_t* phi = nullptr;
     uint64_t* keys = nullptr;
-    DevScope scope;
+    DevScope scope(c);
     HIP_TRY(c, scope.alloc(&phi, (size_t)count * R * R / 2 * sizeof(uint32_t)));
     HIP_TRY(c, scope.alloc(&keys, (size_t)R * sizeof(uint64_t)));
     int rc = clear_flag(c);
@@ -929,10 +951,10 @@ int tcw_walk_begin(tcw_ctx* c, const tcw_target* t, const tcw_space* sp, int64_t
     wd.enumerate = enumerate ? 1 : 0;
     wd.n_points = 2ull * w->space.dev.n_half;
     wd.claw_cap = 4096;
-    hipError_t e = hipMalloc(&wd.states, (size_t)walks * sizeof(tcw::WalkState));
-    if (e == hipSuccess) e = hipMalloc(&wd.table, ((size_t)1 << log2_table) * 16);
-    if (e == hipSuccess) e = hipMalloc(&wd.stats, (tcw::ST_COUNT + 1) * sizeof(unsigned long long));
-    if (e == hipSuccess) e = hipMalloc(&wd.claws, (size_t)wd.claw_cap * 16);
+    hipError_t e = dev_alloc(c, &wd.states, (size_t)walks * sizeof(tcw::WalkState));
+    if (e == hipSuccess) e = dev_alloc(c, &wd.table, ((size_t)1 << log2_table) * 16);
+    if (e == hipSuccess) e = dev_alloc(c, &wd.stats, (tcw::ST_COUNT + 1) * sizeof(unsigned long long));
+    if (e == hipSuccess) e = dev_alloc(c, &wd.claws, (size_t)wd.claw_cap * 16);
     wd.claw_count = wd.stats ? wd.stats + tcw::ST_COUNT : nullptr;
     if (e != hipSuccess) {
         delete w;
@@ -1148,13 +1170,13 @@ struct ClawWs {
         cap = 0;
         r = 0;
     }
-    hipError_t reserve(int64_t m, int rows) {
+    hipError_t reserve(tcw_ctx* c, int64_t m, int rows) {
         if (m <= cap && rows <= r) return hipSuccess;
         release();
         hipError_t e;
-        if ((e = hipMalloc(&d0, m * 8)) != hipSuccess || (e = hipMalloc(&d1, m * 8)) != hipSuccess ||
-            (e = hipMalloc(&ok, m * 4)) != hipSuccess || (e = hipMalloc(&perm, m * rows * 4)) != hipSuccess ||
-            (e = hipMalloc(&sign, m * rows)) != hipSuccess) {
+        if ((e = dev_alloc(c, &d0, m * 8)) != hipSuccess || (e = dev_alloc(c, &d1, m * 8)) != hipSuccess ||
+            (e = dev_alloc(c, &ok, m * 4)) != hipSuccess || (e = dev_alloc(c, &perm, m * rows * 4)) != hipSuccess ||
+            (e = dev_alloc(c, &sign, m * rows)) != hipSuccess) {
             release();
             return e;
         }
@@ -1173,7 +1195,7 @@ int check_pairs_ws(tcw_ctx* c, const Space& sp, const uint64_t* u0, const uint64
     if (m <= 0) return TCW_OK;
     const int n = sp.n;
     const int R = 1 << (2 * n);
-    HIP_TRY(c, ws.reserve(m, R));
+    HIP_TRY(c, ws.reserve(c, m, R));
     HIP_TRY(c, hipMemcpyAsync(ws.d0, u0, m * 8, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipMemcpyAsync(ws.d1, u1, m * 8, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, tcw::exact_claw_check(sp.U, (uint32_t)sp.chunk, sp.k, sp.made, ws.d0, ws.d1, m, ws.ok, ws.perm, ws.sign,
@@ -1280,7 +1302,7 @@ int search_k0(tcw_ctx* c, const tcw_target* t, tcw_result* res, int* found) {
     *found = 0;
     int32_t *dok = nullptr, *dperm = nullptr;
     int8_t* dsign = nullptr;
-    DevScope scope;
+    DevScope scope(c);
     HIP_TRY(c, scope.alloc(&dok, 4));
     HIP_TRY(c, scope.alloc(&dperm, R * 4));
     HIP_TRY(c, scope.alloc(&dsign, R));
@@ -2316,16 +2338,16 @@ void set_minimal(tcw_result* r) {
 int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, double t0, double* agg, StopCtl* stop) {
     const int count = (int)bt.size();
     BatchBuffers bb;
-    HIP_TRY(c, hipMalloc(&bb.stats, (size_t)count * tcw::ST_COUNT * 8));
-    HIP_TRY(c, hipMalloc(&bb.claw_count, (size_t)count * 8));
-    HIP_TRY(c, hipMalloc(&bb.claws, (size_t)count * BATCH_CLAW_CAP * 16));
-    HIP_TRY(c, hipMalloc(&bb.sps, (size_t)count * sizeof(tcw::SpaceDev)));
-    HIP_TRY(c, hipMalloc(&bb.wds, (size_t)count * sizeof(tcw::WalkDev)));
-    HIP_TRY(c, hipMalloc(&bb.counts, 5 * 4));
-    HIP_TRY(c, hipMalloc(&bb.heads, 5 * 4));
-    HIP_TRY(c, hipMalloc(&bb.restart, (size_t)count * 4));
-    HIP_TRY(c, hipMalloc(&bb.made, (size_t)count * 4 * tcw::MADE_WORDS));
-    HIP_TRY(c, hipMalloc(&bb.jobs, (size_t)count * sizeof(tcw::SpaceJob)));
+    HIP_TRY(c, dev_alloc(c, &bb.stats, (size_t)count * tcw::ST_COUNT * 8));
+    HIP_TRY(c, dev_alloc(c, &bb.claw_count, (size_t)count * 8));
+    HIP_TRY(c, dev_alloc(c, &bb.claws, (size_t)count * BATCH_CLAW_CAP * 16));
+    HIP_TRY(c, dev_alloc(c, &bb.sps, (size_t)count * sizeof(tcw::SpaceDev)));
+    HIP_TRY(c, dev_alloc(c, &bb.wds, (size_t)count * sizeof(tcw::WalkDev)));
+    HIP_TRY(c, dev_alloc(c, &bb.counts, 5 * 4));
+    HIP_TRY(c, dev_alloc(c, &bb.heads, 5 * 4));
+    HIP_TRY(c, dev_alloc(c, &bb.restart, (size_t)count * 4));
+    HIP_TRY(c, dev_alloc(c, &bb.made, (size_t)count * 4 * tcw::MADE_WORDS));
+    HIP_TRY(c, dev_alloc(c, &bb.jobs, (size_t)count * sizeof(tcw::SpaceJob)));
     HIP_TRY(c, hipMemsetAsync(bb.made, 0, (size_t)count * 4 * tcw::MADE_WORDS, c->stream));
     HIP_TRY(c, hipMemsetAsync(bb.stats, 0, (size_t)count * tcw::ST_COUNT * 8, c->stream));
     HIP_TRY(c, hipMemsetAsync(bb.claw_count, 0, (size_t)count * 8, c->stream));
@@ -2338,7 +2360,7 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
         has_n[b.t->n] = true;
     }
     ClawWs cws;
-    HIP_TRY(c, cws.reserve(BATCH_CLAW_CAP, 1 << (2 * nmax)));
+    HIP_TRY(c, cws.reserve(c, BATCH_CLAW_CAP, 1 << (2 * nmax)));
     int rc = TCW_OK;
     for (int i = 0; i < count && !rc; ++i) {
         rc = batch_advance(c, bt[i], i, bb, t0, false);
@@ -2476,7 +2498,7 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
                     if (bb.items[n]) (void)hipFree(bb.items[n]);
                     bb.items[n] = nullptr;
                     bb.items_cap[n] = 0;
-                    BATCH_TRY(hipMalloc(&bb.items[n], (size_t)cap * sizeof(tcw::WorkItem)));
+                    BATCH_TRY(dev_alloc(c, &bb.items[n], (size_t)cap * sizeof(tcw::WorkItem)));
                     bb.items_cap[n] = cap;
                     recapture = true;
                 }
@@ -2825,8 +2847,8 @@ int mlp_ensure_batch(tcw_mlp* m, int b) {
     if (b <= m->cap_b) return TCW_OK;
     m->free_batch();
     const size_t b8 = (size_t)ld8(b);
-    HIP_TRY(c, hipMalloc(&m->Xb, (size_t)b * ld8(m->inp) * 2));
-    HIP_TRY(c, hipMalloc(&m->Xt, (size_t)m->inp * b8 * 2));
+    HIP_TRY(c, dev_alloc(c, &m->Xb, (size_t)b * ld8(m->inp) * 2));
+    HIP_TRY(c, dev_alloc(c, &m->Xt, (size_t)m->inp * b8 * 2));
     m->Z.assign(m->depth, nullptr);
     m->Hb.assign(m->depth, nullptr);
     m->Ht.assign(m->depth, nullptr);
@@ -2834,18 +2856,18 @@ int mlp_ensure_batch(tcw_mlp* m, int b) {
     m->Gb.assign(m->L, nullptr);
     m->Gt.assign(m->L, nullptr);
     for (int l = 0; l < m->depth; ++l) {
-        HIP_TRY(c, hipMalloc(&m->Z[l], (size_t)b * m->hidden * 4));
-        HIP_TRY(c, hipMalloc(&m->Hb[l], (size_t)b * ld8(m->hidden) * 2));
-        HIP_TRY(c, hipMalloc(&m->Ht[l], (size_t)m->hidden * b8 * 2));
+        HIP_TRY(c, dev_alloc(c, &m->Z[l], (size_t)b * m->hidden * 4));
+        HIP_TRY(c, dev_alloc(c, &m->Hb[l], (size_t)b * ld8(m->hidden) * 2));
+        HIP_TRY(c, dev_alloc(c, &m->Ht[l], (size_t)m->hidden * b8 * 2));
     }
     for (int l = 0; l < m->L; ++l) {
         const int out = m->sz[l + 1];
-        HIP_TRY(c, hipMalloc(&m->Gf[l], (size_t)b * out * 4));
-        HIP_TRY(c, hipMalloc(&m->Gb[l], (size_t)b * ld8(out) * 2));
-        HIP_TRY(c, hipMalloc(&m->Gt[l], (size_t)out * b8 * 2));
+        HIP_TRY(c, dev_alloc(c, &m->Gf[l], (size_t)b * out * 4));
+        HIP_TRY(c, dev_alloc(c, &m->Gb[l], (size_t)b * ld8(out) * 2));
+        HIP_TRY(c, dev_alloc(c, &m->Gt[l], (size_t)out * b8 * 2));
     }
-    HIP_TRY(c, hipMalloc(&m->logits, (size_t)b * m->classes * 4));
-    HIP_TRY(c, hipMalloc(&m->probs, (size_t)b * m->classes * 4));
+    HIP_TRY(c, dev_alloc(c, &m->logits, (size_t)b * m->classes * 4));
+    HIP_TRY(c, dev_alloc(c, &m->probs, (size_t)b * m->classes * 4));
     // workspace of the split products (forward b x out, K = in; dX b x in, K = out; dW in x out, K = b) and
     // of the bias gradients' column sums
     size_t part = tcw::mlp_colsum_part_floats(b, mlp_layers(m));
@@ -2855,7 +2877,7 @@ int mlp_ensure_batch(tcw_mlp* m, int b) {
                          tcw::mlp_gemm_part_floats(in, out, b)});
     }
     if (part > 0) {
-        HIP_TRY(c, hipMalloc(&m->part, part * 4));
+        HIP_TRY(c, dev_alloc(c, &m->part, part * 4));
         m->part_floats = part;
     }
     m->Wp.assign(m->L, nullptr);
@@ -2931,7 +2953,7 @@ bool mlp_ensure_parts(tcw_mlp* m, int l, size_t floats) {
     if (m->Wp[l]) (void)hipFree(m->Wp[l]);
     m->Wp[l] = nullptr;
     m->Wp_floats[l] = 0;
-    if (hipMalloc(&m->Wp[l], floats * 4) != hipSuccess) {
+    if (dev_alloc(m->ctx, &m->Wp[l], floats * 4) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
@@ -2997,17 +3019,17 @@ extern "C" int tcw_mlp_create(tcw_ctx* c, int inp, int hidden, int depth, int cl
         delete m;
         return hip_fail(c, e, "network allocation");
     };
-    hipError_t e = hipMalloc(&m->P, off * 4);
-    if (e == hipSuccess) e = hipMalloc(&m->G, off * 4);
-    if (e == hipSuccess) e = hipMalloc(&m->M, off * 4);
-    if (e == hipSuccess) e = hipMalloc(&m->V, off * 4);
-    if (e == hipSuccess) e = hipMalloc(&m->loss, LOSS_SLOTS * 4);
+    hipError_t e = dev_alloc(c, &m->P, off * 4);
+    if (e == hipSuccess) e = dev_alloc(c, &m->G, off * 4);
+    if (e == hipSuccess) e = dev_alloc(c, &m->M, off * 4);
+    if (e == hipSuccess) e = dev_alloc(c, &m->V, off * 4);
+    if (e == hipSuccess) e = dev_alloc(c, &m->loss, LOSS_SLOTS * 4);
     if (e != hipSuccess) return bail(e);
     m->Wb.assign(m->L, nullptr);
     m->Wt.assign(m->L, nullptr);
     for (int l = 0; l < m->L && e == hipSuccess; ++l) {
-        e = hipMalloc(&m->Wb[l], (size_t)m->sz[l] * ld8(m->sz[l + 1]) * 2);
-        if (e == hipSuccess) e = hipMalloc(&m->Wt[l], (size_t)m->sz[l + 1] * ld8(m->sz[l]) * 2);
+        e = dev_alloc(c, &m->Wb[l], (size_t)m->sz[l] * ld8(m->sz[l + 1]) * 2);
+        if (e == hipSuccess) e = dev_alloc(c, &m->Wt[l], (size_t)m->sz[l + 1] * ld8(m->sz[l]) * 2);
     }
     if (e == hipSuccess) e = hipMemsetAsync(m->M, 0, off * 4, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(m->V, 0, off * 4, c->stream);
@@ -3173,7 +3195,7 @@ extern "C" int tcw_mlp_depth_order(tcw_mlp* m, const tcw_target* t, int k_max, c
         if (int rc = check_params(c, sp, t->n, true)) return rc;
     const int R = 1 << (2 * t->n);
     if (R * R != m->inp) return fail(c, TCW_EINVAL, "network input size does not match the target");
-    if (!m->xdev) HIP_TRY(c, hipMalloc(&m->xdev, (size_t)m->inp * 4));
+    if (!m->xdev) HIP_TRY(c, dev_alloc(c, &m->xdev, (size_t)m->inp * 4));
     if (t->n > 3) return fail(c, TCW_EINVAL, "features are defined for n <= 3");
     HIP_TRY(c, tcw::exact_features(t->U, m->xdev, c->stream));  // the network follows on the same stream
     int rc = mlp_forward(m, m->xdev, 1, nullptr, nullptr);
@@ -3356,13 +3378,13 @@ extern "C" int tcw_label_batch(tcw_ctx* c, int n, int count, const uint16_t* wor
             return hip_fail(c, _e, #expr);   \
         }                                    \
     } while (0)
-    LB_TRY(hipMalloc(&dwords, nw * 2 + 2));
-    LB_TRY(hipMalloc(&doff, (count + 1) * 4));
-    LB_TRY(hipMalloc(&dk, count * 4));
+    LB_TRY(dev_alloc(c, &dwords, nw * 2 + 2));
+    LB_TRY(dev_alloc(c, &doff, (count + 1) * 4));
+    LB_TRY(dev_alloc(c, &dk, count * 4));
     LB_TRY(hipMemcpyAsync(dwords, words, nw * 2, hipMemcpyHostToDevice, c->stream));
     LB_TRY(hipMemcpyAsync(doff, offsets, (count + 1) * 4, hipMemcpyHostToDevice, c->stream));
     LB_TRY(hipMemcpyAsync(dk, kof, count * 4, hipMemcpyHostToDevice, c->stream));
-    LB_TRY(hipMalloc(&rot, chunk * 4));
+    LB_TRY(dev_alloc(c, &rot, chunk * 4));
     const int h_id = mitm_split(n, h_max, count);
     LevelTable lt(c);
     size_t room = 64;  // by powers of two, so that the pool holds few sizes
@@ -3403,8 +3425,8 @@ extern "C" int tcw_min_tcount(tcw_ctx* c, const tcw_target* t, int h_max, uint64
     LevelTable lt(c);
     int32_t e_u = 0;
     int flag = 0;
-    hipError_t err = hipMalloc(&phi, (size_t)R * R / 2 * 4 + 16);
-    if (err == hipSuccess) err = hipMalloc(&dev_i32, 2 * sizeof(int32_t));
+    hipError_t err = dev_alloc(c, &phi, (size_t)R * R / 2 * 4 + 16);
+    if (err == hipSuccess) err = dev_alloc(c, &dev_i32, 2 * sizeof(int32_t));
     if (err == hipSuccess) err = hipMemsetAsync(c->flag, 0, sizeof(int), c->stream);
     if (err == hipSuccess) err = tcw::exact_pack_phi(t->U, phi, c->flag, c->stream);
     if (err == hipSuccess) err = hipMemcpyAsync(&e_u, t->U.e, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);

@@ -35,3 +35,68 @@ def test_labels_of_cliffords(ctx, n, count):
         assert labels.cpu().tolist() == want, h_max
     tgt = ctx.target_from_words(n, *words[-1])
     assert ctx.min_tcount(tgt, 0) == (0 if (count - 1) % 3 else -1)
+
+
+@pytest.fixture
+def full_memory():
+    """Fills the GPU's memory to about the given number of bytes, in blocks, until the test ends."""
+    import torch
+    held = []
+
+    def fill(leave):
+        torch.cuda.synchronize()
+        while True:
+            room = torch.cuda.mem_get_info()[0] - leave
+            if room < 1 << 26:
+                return
+            held.append(torch.empty(min(room, 16 << 30), dtype=torch.uint8, device="cuda:0"))
+    yield fill
+    held.clear()
+    torch.cuda.empty_cache()
+
+
+def test_allocations_take_the_pool_back(full_memory):
+    """With the rest of the memory in use, a context's other allocations get what its idle pool holds (1 GiB of
+    a label call's table): a walk session's table, a network; what does not fit at all is refused, and the
+    refusal does not reach later calls."""
+    import torch
+    from paper_1606_07413_amd import tcw
+    own = tcw.Context(0)
+    tw = seeded_inputs.target_words(2, 4, 7)
+    tgt = own.target_from_words(2, tw.paulis, tw.clifford)
+    count = 16384
+    words = [seeded_inputs.target_words(2, 1 + i % 8, 20 + i % 64) for i in range(count)]
+    words = [(t.paulis, t.clifford) for t in words]
+    feats = torch.empty((count, 256), dtype=torch.float32, device="cuda:0")
+    labels = torch.empty(count, dtype=torch.int32, device="cuda:0")
+
+    def fill_pool():
+        own.label_batch(2, words, 4, 3, feats, labels)
+
+    def walk(log2_table):
+        w = own.walk(tgt, 4, 0, 3, 4, 64, log2_table, 1 << 10)
+        w.run(4)
+        assert w.stats().steps == 256
+        w.end()
+
+    before = torch.cuda.mem_get_info()[0]
+    fill_pool()
+    assert before - torch.cuda.mem_get_info()[0] >= 1 << 30
+    full_memory(3 << 28)
+    print("walk table beside an idle pool", flush=True)
+    walk(26)
+    assert torch.cuda.mem_get_info()[0] >= 1 << 30
+    fill_pool()
+    print("network beside an idle pool", flush=True)
+    net = tcw.Network(own, 4096, 8192, 1, 11, seed=1)      # 4 x 128 MiB of FP32, 2 x 64 of BF16
+    x = torch.zeros((2, 4096), dtype=torch.float32, device="cuda:0")
+    probs = torch.empty((2, 11), dtype=torch.float32, device="cuda:0")
+    net.forward(x, probs)
+    assert torch.allclose(probs.sum(1), torch.ones(2, device="cuda:0"))
+    net.free()
+    print("more than there is", flush=True)
+    with pytest.raises(tcw.TcwError) as err:
+        walk(30)
+    assert tcw.ERRORS[err.value.code] == "ENOMEM"
+    walk(12)
+    own.target_from_words(2, tw.paulis, tw.clifford)
