@@ -56,7 +56,8 @@ typedef struct tcw_walk tcw_walk;
  * (257 MiB each), kept for later searches with the same seed and released by tcw_destroy.  It also
  * keeps the device buffers of finished batch members and concurrently searched chunks (S_c, keys,
  * walk states, tables; at most 40 GiB) for later members of the same sizes, those of labelling and
- * certificate calls with them, also until tcw_destroy.
+ * certificate calls up to 1 GiB each with them, also until tcw_destroy or until an allocation of the context
+ * finds no memory.
  * tcw_last_error's string is owned by the context and valid until the next call on it. */
 int tcw_create(tcw_ctx** out, int device, void* hip_stream);
 int tcw_destroy(tcw_ctx* ctx);
