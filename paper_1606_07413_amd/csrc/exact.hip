@@ -1144,10 +1144,16 @@ __global__ void k_fill_i32(int* dst, int v, int count) {
 hipError_t spaces_make(int n, const SpaceJob& one, const SpaceJob* many, int count, hipStream_t s) {
     if (count <= 0) return hipSuccess;
     if (n == 4) {
-        hipLaunchKernelGGL(k_space_clear, dim3(1), dim3(many ? 256 : 64), 0, s, one, many, count);
-        if (many || one.c)
-            hipLaunchKernelGGL(k_space_or4, dim3(SPACE_BLOCKS, count), dim3(1024), 0, s, one, many);
-        hipLaunchKernelGGL(k_space_pack4, dim3(SPACE_BLOCKS, count), dim3(1024), 0, s, one, many);
+        // a grid's second dimension ends at 65,536 blocks: a batch of more members takes several launches
+        constexpr int MOST = 32768;
+        for (int at = 0; at < count; at += MOST) {
+            const int jobs = count - at < MOST ? count - at : MOST;
+            const SpaceJob* from = many ? many + at : nullptr;
+            hipLaunchKernelGGL(k_space_clear, dim3(1), dim3(many ? 256 : 64), 0, s, one, from, jobs);
+            if (many || one.c)
+                hipLaunchKernelGGL(k_space_or4, dim3(SPACE_BLOCKS, jobs), dim3(1024), 0, s, one, from);
+            hipLaunchKernelGGL(k_space_pack4, dim3(SPACE_BLOCKS, jobs), dim3(1024), 0, s, one, from);
+        }
         return hipGetLastError();
     }
     auto f = [&]<int NQ, typename T>() -> hipError_t {

@@ -119,3 +119,22 @@ def test_large_tables_are_not_kept():
     got = labels.cpu().tolist()
     assert all(0 <= g <= i % 9 for i, g in enumerate(got))
     assert before - after < 1 << 28
+
+
+def test_batch_of_many_members(ctx):
+    """More 4-qubit members than a grid's second dimension has blocks: their spaces are made together."""
+    from paper_1606_07413_amd import tcw
+    tw = seeded_inputs.target_words(4, 1, 5)
+    tgt = ctx.target_from_words(4, tw.paulis, tw.clifford)
+    p = ctx.default_params(4)
+    p.k_max = p.depth_order_len = p.depth_order[0] = 1
+    p.depth_order_kind = 2                       # depth 1 at its one chunk, first found
+    p.chunk_first = p.chunk_last = tw.paulis[0]
+    count = 65537
+    print("batch of", count, flush=True)
+    res, _ = ctx.search_batch([tgt] * count, [p] * count)
+    assert all(r.status == 1 and r.t == 1 and r.paulis[0] == tw.paulis[0] for r in res)
+    one = tcw.decomposition_of(ctx.search(tgt, p))
+    for r in (res[0], res[-1]):
+        dec = tcw.decomposition_of(r)
+        assert (dec.paulis_desc, dec.perm, dec.sign) == (one.paulis_desc, one.perm, one.sign)
