@@ -2585,8 +2585,15 @@ int batch_run(tcw_ctx* c, std::vector<BatchTarget>& bt, bool stop_on_first, doub
                 if (stats[(size_t)i * tcw::ST_COUNT + tcw::ST_STEPS] >= b.budget) whole.push_back(i);
             }
             if (!whole.empty()) {
+                // those with tables of one size in one launch
+                std::stable_sort(whole.begin(), whole.end(),
+                                 [&](int32_t x, int32_t y) { return bt[x].wd.log2_table < bt[y].wd.log2_table; });
                 BATCH_TRY(hipMemcpyAsync(bb.restart, whole.data(), whole.size() * 4, hipMemcpyHostToDevice, gs[0]));
-                BATCH_TRY(tcw::launch_member_pairs(bb.wds, bb.restart, (int)whole.size(), gs[0]));
+                for (size_t at = 0, end; at < whole.size(); at = end) {
+                    const int lg = bt[whole[at]].wd.log2_table;
+                    for (end = at + 1; end < whole.size() && bt[whole[end]].wd.log2_table == lg; ++end) {}
+                    BATCH_TRY(tcw::launch_member_pairs(bb.wds, bb.restart + at, (int)(end - at), lg, gs[0]));
+                }
                 BATCH_TRY(hipMemcpyAsync(stats.data(), bb.stats, stats.size() * 8, hipMemcpyDeviceToHost, gs[0]));
             }
             BATCH_TRY(hipMemcpyAsync(ccount.data(), bb.claw_count, count * 8, hipMemcpyDeviceToHost, gs[0]));

@@ -191,8 +191,9 @@ hipError_t launch_member_restart(const SpaceDev* sps, const WalkDev* wds, const 
                                  hipStream_t s);
 // enumeration mode, after the last point: one claw candidate per key reached from both sides
 hipError_t launch_enum_pairs(const WalkDev& wd, hipStream_t s);
-// the same for batch members slots[0..count) (descriptors and slots on the device) in one launch
-hipError_t launch_member_pairs(const WalkDev* wds, const int32_t* slots, int count, hipStream_t s);
+// the same for batch members slots[0..count) with tables of one size (descriptors and slots on the device) in one
+// launch
+hipError_t launch_member_pairs(const WalkDev* wds, const int32_t* slots, int count, int log2_table, hipStream_t s);
 int walk_grid_blocks(int n, int device);
 hipError_t pack_phi_i32(int n, const int32_t* a, const int32_t* b, int64_t count, uint32_t* phi_out,
                         int* flag_dev, hipStream_t s);

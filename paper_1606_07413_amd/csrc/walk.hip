@@ -1751,10 +1751,10 @@ __device__ inline void enum_pairs(const WalkDev& wd, uint64_t first, uint64_t st
 __global__ void k_enum_pairs(WalkDev wd) {
     enum_pairs(wd, threadIdx.x + (uint64_t)blockIdx.x * blockDim.x, (uint64_t)blockDim.x * gridDim.x);
 }
-// the same for batch member slots[blockIdx.x / RESTART_PER], RESTART_PER blocks each
-__global__ __launch_bounds__(256) void k_member_pairs(const WalkDev* wds, const int32_t* slots) {
-    const WalkDev wd = wds[slots[blockIdx.x / RESTART_PER]];
-    enum_pairs(wd, (uint64_t)(blockIdx.x % RESTART_PER) * blockDim.x + threadIdx.x, (uint64_t)RESTART_PER * blockDim.x);
+// the same for batch member slots[blockIdx.x / per], per blocks each
+__global__ __launch_bounds__(256) void k_member_pairs(const WalkDev* wds, const int32_t* slots, int per) {
+    const WalkDev wd = wds[slots[blockIdx.x / (unsigned)per]];
+    enum_pairs(wd, (uint64_t)(blockIdx.x % (unsigned)per) * blockDim.x + threadIdx.x, (uint64_t)per * blockDim.x);
 }
 
 // ---- meet-in-the-middle labels for the depth-order network ----
@@ -2477,9 +2477,15 @@ hipError_t launch_table_clear(uint64_t* table, int log2_table, uint64_t value, h
     return hipGetLastError();
 }
 
-hipError_t launch_member_pairs(const WalkDev* wds, const int32_t* slots, int count, hipStream_t s) {
+// The scan is a chain of reads for each thread, so it wants a thread a slot, up to what fills the chip: the
+// members of a launch share 4,096 blocks (as many as k_enum_pairs starts for one table), with at least 32 a
+// member.  One member, 2^27 slots: 0.37 ms, with 32 blocks whatever the table's size 9.4; a depth's 63 chunks at
+// n = 3 get 65 blocks each, its 255 at n = 4 32.
+hipError_t launch_member_pairs(const WalkDev* wds, const int32_t* slots, int count, int log2_table, hipStream_t s) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_member_pairs, dim3((unsigned)(count * RESTART_PER)), dim3(256), 0, s, wds, slots);
+    const int64_t most = std::max<int64_t>(1, (int64_t)1 << std::max(0, log2_table - 8));
+    const int per = (int)std::min<int64_t>(most, std::max(32, 4096 / count));
+    hipLaunchKernelGGL(k_member_pairs, dim3((unsigned)count * per), dim3(256), 0, s, wds, slots, per);
     return hipGetLastError();
 }
 

@@ -138,3 +138,53 @@ def test_batch_of_many_members(ctx):
     for r in (res[0], res[-1]):
         dec = tcw.decomposition_of(r)
         assert (dec.paulis_desc, dec.perm, dec.sign) == (one.paulis_desc, one.perm, one.sign)
+
+
+def enumerated(ctx, n, k, seed):
+    """A target of k rotations and parameters that search depth k alone, exhaustively (the first hit ends it)."""
+    tw = seeded_inputs.target_words(n, k, seed)
+    p = ctx.default_params(n)
+    p.k_max = p.depth_order[0] = k
+    p.depth_order_kind, p.depth_order_len, p.enum_max, p.walks = 2, 1, 1 << 26, 1 << 18
+    return ctx.target_from_words(n, tw.paulis, tw.clifford), p
+
+
+def best_of(reps, fn):
+    import time
+    import torch
+    out = []
+    for _ in range(reps):
+        t0 = time.perf_counter()
+        fn()
+        torch.cuda.synchronize()
+        out.append(time.perf_counter() - t0)
+    return min(out)
+
+
+def test_enumerated_members_of_several_sizes(ctx):
+    """Members with tables from 2^5 to 2^27 slots, some alike: as many candidates as a session's exhaustive walk
+    of the same space has, and the single search's answer; and the one large table is read out by as many blocks as in a single search (the whole
+    searches take about the same time, where 32 blocks took twice as long)."""
+    specs = [(2, 12, 1), (1, 2, 2), (2, 4, 3), (3, 4, 4), (2, 4, 5), (1, 6, 6), (4, 2, 7)]
+    members = [enumerated(ctx, *s) for s in specs]
+    for _, p in members:
+        p.iters_per_launch = 64
+    res, _ = ctx.search_batch([t for t, _ in members], [p for _, p in members])
+    for s, (t, p), r in zip(specs, members, res):
+        n, k, _ = s
+        points = 2 * (4 ** n - 1) ** (k // 2)
+        w = ctx.walk(t, k, 0, p.seed, 0, min(points, p.walks), max(4, (4 * points - 1).bit_length()), 2, enumerate=True,
+                     version=p.version)
+        while w.stats().steps < points:
+            w.run(64)
+        claws = w.claws()[1]
+        w.end()
+        one = ctx.search(t, p)
+        print("enumerated", s, r.status, r.t, r.stats.claws, claws, flush=True)
+        assert (r.status, r.t, r.stats.steps) == (one.status, one.t, one.stats.steps) == (1, k, points)
+        assert r.stats.claws == claws >= 1
+    t, p = members[0]
+    batch = best_of(4, lambda: ctx.search_batch([t], [p]))
+    single = best_of(4, lambda: ctx.search(t, p))
+    print("batch %.2f ms, single %.2f ms" % (batch * 1e3, single * 1e3), flush=True)
+    assert batch < 1.5 * single
