@@ -2910,10 +2910,9 @@ int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels, float*
     const bool train = labels != nullptr;
     const int b8 = ld8(b);
     if (probs == nullptr) probs = m->probs;
-    // inference's first product reads x itself where its rows are 16-byte aligned; training needs the
+    // inference's first product may read x itself where its rows are 16-byte aligned; training needs the
     // transposed copy for the weight gradient in any case, and the output layer reads BF16
     const bool direct = !train && m->depth > 0 && m->inp % 4 == 0 && ((uintptr_t)x & 15) == 0;
-    const bool few = !train && tcw::mlp_rows_fits(b);
     if (!direct)
         HIP_TRY(c, tcw::mlp_input_bf16(x, b, m->inp, m->Xb, ld8(m->inp), train ? m->Xt : nullptr, b8, c->stream));
     if (train) HIP_TRY(c, hipMemsetAsync(m->loss + slot, 0, 4, c->stream));
@@ -2923,7 +2922,7 @@ int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels, float*
         const float* bias = m->P + m->b_off[l];
         if (l < m->L - 1) {
             const bool f32 = direct && l == 0;
-            if (few) {
+            if (!train && tcw::mlp_rows_fits(b, N, K, f32)) {
                 HIP_TRY(c, tcw::mlp_rows(f32 ? x : A, f32, f32 ? m->inp : ld8(K), m->Wt[l], ld8(K), b, N, K, bias,
                                          m->Hb[l], ld8(N), c->stream));
                 continue;

@@ -734,8 +734,7 @@ int splits_of(int M, int N, int K) {
     return splits;
 }
 
-// Up to this many rows a product takes a wavefront per column instead of tiles: a whole pass of the 4096 ->
-// 512 x 3 -> 11 network over 8 rows takes 36 us so and 45 on tiles (over one row 30).
+// The most rows for which a product may take a wavefront per column instead of tiles (mlp_rows_fits).
 constexpr int ROWS_MAX = 8;
 
 template <int EPI, typename TA>
@@ -821,7 +820,19 @@ hipError_t mlp_gemm_parts(const void* A, int lda, const void* B, int ldb, int M,
                                 nullptr, 0, nullptr, 0, part, part_floats, s, false);
 }
 
-bool mlp_rows_fits(int M) { return M <= ROWS_MAX; }
+// A wavefront per column or tiles, for a few rows.  k_rows saves the second kernel that tiles need once their K is
+// split (from 512 on), but every column reads all rows again and waits for a load every 512 k (2,048 k for one row,
+// whose loads are sent four steps together).  So one row takes it unless K is short or the columns are many for
+// their K; more rows only for a K in between, which ends earlier where A is FP32 and twice as long.  A product and
+// the rest of a pass, wavefront per column against tiles in us: 1 x 512 x 4096 22.2, 26.6; 1 x 96 x 64 23.9, 21.9;
+// 1 x 8192 x 256 34.7, 32.5; 8 x 2048 x 1024 (FP32) 25.9, 27.7; 2 x 512 x 4096 (FP32) 33.6, 27.0; 8 x 8192 x 1024
+// (FP32) 42.8, 37.5.  A hidden layer alone: 8 x 512 x 512 3.7, 11.1; 2 x 2048 x 2048 9.8, 11.1; 2 x 2560 x 2560 12.6,
+// 11.1; 8 x 256 x 256 5.5, 4.9.
+bool mlp_rows_fits(int M, int N, int K, bool f32) {
+    if (M > ROWS_MAX) return false;
+    if (M == 1) return K >= 192 && N <= (int64_t)16 * K;
+    return N <= 2048 && (f32 ? K >= 256 && K <= 1536 : K >= 384 && K <= 2048);
+}
 
 hipError_t mlp_rows(const void* A, bool f32, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
                     void* H, int ldh, hipStream_t s) {

@@ -188,3 +188,52 @@ def test_enumerated_members_of_several_sizes(ctx):
     single = best_of(4, lambda: ctx.search(t, p))
     print("batch %.2f ms, single %.2f ms" % (batch * 1e3, single * 1e3), flush=True)
     assert batch < 1.5 * single
+
+
+# (inputs, hidden width, layers, classes, batch) on both sides of each line: one row by K and by N for its K; a few
+# rows by K (FP32, then in the hidden layers BF16) and N
+ROUTES = [(188, 96, 1, 11, 1), (192, 3072, 1, 11, 1), (192, 3073, 1, 11, 1), (40, 191, 2, 11, 1), (40, 192, 2, 11, 1),
+          (252, 130, 1, 11, 2), (256, 130, 1, 11, 3), (1536, 2048, 1, 11, 8), (1536, 2049, 1, 11, 2), (1540, 64, 1, 11, 8),
+          (40, 383, 2, 11, 5), (40, 384, 2, 11, 8), (40, 2048, 2, 11, 2), (40, 2052, 2, 11, 8)]
+
+
+@pytest.mark.parametrize("inp,hidden,depth,classes,batch", ROUTES)
+def test_network_routes(ctx, inp, hidden, depth, classes, batch):
+    """Probabilities within the running error bound of the GPU's arithmetic (as in the gradient tests)."""
+    import torch
+    from oracle import mlp as omlp
+    from paper_1606_07413_amd import tcw
+    import test_gpu_mlp as base
+    print("network", inp, hidden, depth, classes, batch, flush=True)
+    params = seeded_inputs.mlp_init(inp, hidden, depth, classes, 7)
+    x = (np.random.default_rng(batch).normal(size=(batch, inp)) * 0.5).astype(np.float32)
+    net = tcw.Network(ctx, inp, hidden, depth, classes, init=tcw.flatten_params(params, depth))
+    probs = torch.empty((batch, classes), dtype=torch.float32, device="cuda:0")
+    net.forward(torch.tensor(x, device="cuda:0"), probs)
+    pr = {k: (omlp.bf16_round(v) if k.startswith("W") else v) for k, v in params.items()}
+    y = np.zeros(batch, dtype=np.int32)
+    _, p_ref, p_bound = base.gradient_error_bounds(pr, omlp.bf16_round(x).astype(np.float64), y, depth)
+    assert np.all(np.abs(probs.cpu().numpy().astype(np.float64) - p_ref) <= 2 * p_bound)
+
+
+def forward_time(ctx, inp, hidden, depth, classes, batch, shift=0):
+    import torch
+    from paper_1606_07413_amd import tcw
+    net = tcw.Network(ctx, inp, hidden, depth, classes, seed=1)
+    x = torch.zeros(batch * inp + shift, dtype=torch.float32, device="cuda:0")[shift:].view(batch, inp)
+    probs = torch.empty((batch, classes), dtype=torch.float32, device="cuda:0")
+
+    def some():
+        for _ in range(8):
+            net.forward(x, probs)
+    some()
+    t = best_of(8, some) / 8 * 1e6
+    net.free()
+    print("forward", inp, hidden, depth, classes, batch, shift, "%.1f us" % t, flush=True)
+    return t
+
+
+# a pass takes no longer than one that does more: two rows and nine (78 and 41 us with a rule that looked at the rows alone)
+@pytest.mark.parametrize("less,more,most", [((16384, 2048, 1, 11, 2), (16384, 2048, 1, 11, 9), 1.3)])
+def test_less_work_takes_no_longer(ctx, less, more, most):
+    assert forward_time(ctx, *less) < most * forward_time(ctx, *more)
