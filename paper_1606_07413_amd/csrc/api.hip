@@ -2912,7 +2912,8 @@ int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels, float*
     if (probs == nullptr) probs = m->probs;
     // inference's first product may read x itself where its rows are 16-byte aligned; training needs the
     // transposed copy for the weight gradient in any case, and the output layer reads BF16
-    const bool direct = !train && m->depth > 0 && m->inp % 4 == 0 && ((uintptr_t)x & 15) == 0;
+    const bool direct = !train && m->depth > 0 && m->inp % 4 == 0 && ((uintptr_t)x & 15) == 0 &&
+                        (tcw::mlp_rows_fits(b, m->hidden, m->inp, true) || tcw::mlp_f32_fits(b, m->hidden, m->inp));
     if (!direct)
         HIP_TRY(c, tcw::mlp_input_bf16(x, b, m->inp, m->Xb, ld8(m->inp), train ? m->Xt : nullptr, b8, c->stream));
     if (train) HIP_TRY(c, hipMemsetAsync(m->loss + slot, 0, 4, c->stream));

@@ -232,6 +232,8 @@ hipError_t mlp_gemm_nt_f32(const float* A, int lda, const void* B, int ldb, int 
 int mlp_gemm_splits(int M, int N, int K);
 hipError_t mlp_gemm_parts(const void* A, int lda, const void* B, int ldb, int M, int N, int K, float* part,
                           size_t part_floats, hipStream_t s);
+// whether that is the faster way to a product of an FP32 A
+bool mlp_f32_fits(int M, int N, int K);
 // epi 2 as mlp_gemm_nt_f32 for the few rows that mlp_rows_fits, without a workspace; A is bf16, or with f32 as above
 bool mlp_rows_fits(int M, int N, int K, bool f32);
 hipError_t mlp_rows(const void* A, bool f32, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,

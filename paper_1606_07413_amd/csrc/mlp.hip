@@ -834,6 +834,16 @@ bool mlp_rows_fits(int M, int N, int K, bool f32) {
     return N <= 2048 && (f32 ? K >= 256 && K <= 1536 : K >= 384 && K <= 2048);
 }
 
+// Whether the first product of inference reads its FP32 input itself.  That saves the conversion pass, but each
+// panel of 128 columns then reads four bytes where it would read two: worth it up to 16 panels, or 8 where a
+// tile's rows of A no longer stay in an XCD's L2 (128 x 8192 x 4 bytes), and for any N while the pass is mostly its
+// launch.  FP32 against converted in us: 4096 x 512 x 4096 56.5, 68.4; 4096 x 2048 x 4096 120, 125; 4096 x 4096 x 4096
+// 232, 223; 4096 x 1024 x 16384 0.92 of it, 4096 x 4096 x 16384 834, 751; 64 x 4096 x 4096 43.6, 46.2; 256 x 8192 x 4096
+// 81.0, 79.6.
+bool mlp_f32_fits(int M, int N, int K) {
+    return N <= 1024 || (N <= 2048 && K <= 8192) || (int64_t)M * K <= (1 << 21);
+}
+
 hipError_t mlp_rows(const void* A, bool f32, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
                     void* H, int ldh, hipStream_t s) {
     if (M < 1 || M > ROWS_MAX || (f32 && ((lda & 3) != 0 || ((uintptr_t)A & 15) != 0))) return hipErrorInvalidValue;
