@@ -2941,7 +2941,7 @@ int mlp_forward(tcw_mlp* m, const float* x, int b, const int32_t* labels, float*
         float* g = train ? m->Gf[l] : nullptr;
         void *gb = train ? m->Gb[l] : nullptr, *gt = train ? m->Gt[l] : nullptr;
         float* loss = train ? m->loss + slot : nullptr;
-        if (tcw::mlp_head_fits(N)) {
+        if (tcw::mlp_head_fits(b, N, K)) {
             HIP_TRY(c, tcw::mlp_head(A, ld8(K), m->Wt[l], ld8(K), b, N, K, bias, labels, probs, g, gb, ld8(N), gt, b8,
                                      loss, c->stream));
         } else {

@@ -241,9 +241,9 @@ hipError_t mlp_rows(const void* A, bool f32, int lda, const void* B, int ldb, in
 // probabilities, loss sum and G = (p - onehot) / batch (fp32; bf16 with ld ldgb; transposed bf16 if gt)
 hipError_t mlp_softmax_ce(const float* logits, const int32_t* labels, int batch, int classes, float* probs, float* g,
                           void* gb, int ldgb, void* gt, int ldgt, float* loss_sum, hipStream_t s);
-// the output layer's product and mlp_softmax_ce in one kernel, for classes that mlp_head_fits: A (M x K), B
+// the output layer's product and mlp_softmax_ce in one kernel, for sizes that mlp_head_fits: A (M x K), B
 // (N x K) and bias as in mlp_gemm_nt, N classes
-bool mlp_head_fits(int classes);
+bool mlp_head_fits(int M, int N, int K);
 hipError_t mlp_head(const void* A, int lda, const void* B, int ldb, int M, int N, int K, const float* bias,
                     const int32_t* labels, float* probs, float* g, void* gb, int ldgb, void* gt, int ldgt,
                     float* loss_sum, hipStream_t s);

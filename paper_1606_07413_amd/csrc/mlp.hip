@@ -883,7 +883,16 @@ hipError_t mlp_head(const void* A, int lda, const void* B, int ldb, int M, int N
     return hipGetLastError();
 }
 
-bool mlp_head_fits(int classes) { return classes <= HEAD_MAX; }
+// A block of k_head reads its (up to 32) rows and B alone, on one CU, which three kernels on split tiles overtake
+// where K is long, the blocks are few and what a block reads is much.  In us, k_head against the three: 4096 x 11 x
+// 4096 44.1, 60.9; 32 x 11 x 4096 30.1, 33.2; 8 x 11 x 8192 32.4, 34.0; 32 x 11 x 8192 40.2, 38.0; 1 x 11 x 16384 40.0,
+// 42.9; 8 x 11 x 16384 45.1, 43.5; 32 x 11 x 16384 61.2, 47.6; 4096 x 11 x 16384 137, 186; 32 x 32 x 65536 245, 109; at
+// K = 6144 0.85 to 1.02 of them, from 512 rows on at K = 8192 0.91 to 1.04.
+bool mlp_head_fits(int M, int N, int K) {
+    if (N > HEAD_MAX) return false;
+    if (K <= 6144 || M >= 2048 || (M >= 512 && K <= 8192)) return true;
+    return (int64_t)K * (N + (M < HEAD_ROWS ? M : HEAD_ROWS)) <= 1 << 18;
+}
 
 hipError_t mlp_colsum(const MlpLayers& net, int rows, float* part, size_t part_floats, hipStream_t s) {
     if (rows <= 0) return hipSuccess;

@@ -191,11 +191,14 @@ def test_enumerated_members_of_several_sizes(ctx):
 
 
 # (inputs, hidden width, layers, classes, batch) on both sides of each line: one row by K and by N for its K; a few
-# rows by K (FP32, then in the hidden layers BF16) and N; the FP32 first product by N, by K and by its whole size
+# rows by K (FP32, then in the hidden layers BF16) and N; the FP32 first product by N, by K and by its whole size;
+# the output layer by K and rows
 ROUTES = [(188, 96, 1, 11, 1), (192, 3072, 1, 11, 1), (192, 3073, 1, 11, 1), (40, 191, 2, 11, 1), (40, 192, 2, 11, 1),
           (252, 130, 1, 11, 2), (256, 130, 1, 11, 3), (1536, 2048, 1, 11, 8), (1536, 2049, 1, 11, 2), (1540, 64, 1, 11, 8),
           (40, 383, 2, 11, 5), (40, 384, 2, 11, 8), (40, 2048, 2, 11, 2), (40, 2052, 2, 11, 8),
-          (4096, 2048, 1, 11, 513), (4096, 2049, 1, 11, 513), (4096, 2049, 1, 11, 512), (8196, 1025, 1, 11, 257)]
+          (4096, 2048, 1, 11, 513), (4096, 2049, 1, 11, 513), (4096, 2049, 1, 11, 512), (8196, 1025, 1, 11, 257),
+          (6144, 1, 0, 11, 33), (6148, 1, 0, 11, 33), (8192, 1, 0, 11, 21), (8192, 1, 0, 11, 22), (8192, 1, 0, 5, 511),
+          (8192, 1, 0, 5, 512), (8196, 1, 0, 5, 2047), (8196, 1, 0, 5, 2048)]
 
 
 @pytest.mark.parametrize("inp,hidden,depth,classes,batch", ROUTES)
@@ -234,10 +237,11 @@ def forward_time(ctx, inp, hidden, depth, classes, batch, shift=0):
     return t
 
 
-# a pass takes no longer than one that does more: two rows and nine, an aligned input and
-# one that has to be converted first (78 and 41 us, 834 and 751, with rules that looked at the rows or
-# the alignment alone)
+# a pass takes no longer than one that does more: two rows and nine, 32 classes and 33, an aligned input and
+# one that has to be converted first (78 and 41 us, 245 and 109, 834 and 751, with rules that looked at the rows or at
+# the classes alone)
 @pytest.mark.parametrize("less,more,most", [((16384, 2048, 1, 11, 2), (16384, 2048, 1, 11, 9), 1.3),
+                                            ((65536, 1, 0, 32, 32), (65536, 1, 0, 33, 32), 1.3),
                                             ((16384, 4096, 1, 11, 4096), (16384, 4096, 1, 11, 4096, 1), 1.05)])
 def test_less_work_takes_no_longer(ctx, less, more, most):
     assert forward_time(ctx, *less) < most * forward_time(ctx, *more)
