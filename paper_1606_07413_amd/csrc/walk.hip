@@ -1494,8 +1494,11 @@ __device__ void walk_block_single(const SpaceDev& sp, const WalkDev& wd, int ite
 // alone; when both next points are on side 1 the two steps share one MFMA product (walk_step_pair4).  So
 // the pair's steps add up to 2 iters while each walk's share varies with its sides: a launch's total is
 // walks x iters.
-// The block's pairs are q = block * WAVES + i for i < WAVES, then every nblocks * WAVES further; its
-// wavefronts take them in turn from *next (LDS, zero at the start).  With a fixed share each, the
+// The block's pairs are runs of WAVES neighbours, q = block * WAVES + i for i < WAVES, then every nblocks * WAVES
+// further while every block has a whole run; those left go to the blocks one at a time, so that a few walks spread
+// over the CUs instead of filling the first ones' wavefronts (20,000 walks x 64 steps at k = 7: 1.10 -> 0.97 ms;
+// all pairs one at a time cost 2^20 walks 0.7 percent).
+// Its wavefronts take them in turn from *next (LDS, zero at the start).  With a fixed share each, the
 // wavefronts that the SIMDs prefer finished early and few were left at the end: a wavefront lived 0.78 of
 // the launch on average, now 0.98 (2^18 walks x 16 steps: 3.96 -> 3.62 ms).
 template <int WAVES>
@@ -1509,11 +1512,13 @@ __device__ void walk_block_pairs(const SpaceDev& sp, const WalkDev& wd, int iter
     Back &ba = back[2 * wave], &bb = back[2 * wave + 1];  // every lane writes the same values
     uint32_t steps = 0, active = 0, dps = 0, ins = 0;  // frequent events in registers, as in walk_block_single
     const int64_t pairs = (wd.walks + 1) / 2;
+    // of the block's, those in runs (at most 2^31 walks, no more blocks than runs: 32 bits hold both)
+    const uint32_t whole = (uint32_t)pairs / ((uint32_t)nblocks * WAVES) * WAVES;
     for (;;) {
         uint32_t i = 0;
         if (leader) i = atomicAdd(next, 1u);
         i = uniform32(i);
-        const int64_t q = (int64_t)(i / WAVES) * nblocks * WAVES + block * WAVES + i % WAVES;
+        const int64_t q = i < whole ? ((int64_t)(i / WAVES) * nblocks + block) * WAVES + i % WAVES : i * nblocks + block;
         if (q >= pairs) break;
         const int64_t w0 = 2 * q, w1 = 2 * q + 1;
         const bool has_b = w1 < wd.walks;
@@ -2426,7 +2431,9 @@ hipError_t launch_walk(int n, const SpaceDev& sp, const WalkDev& wd, int iters, 
     auto f = [&]<int NQ>() -> hipError_t {
         constexpr int W = WalkWaves<NQ>::value;
         const int64_t per_block = (int64_t)W * Geo<NQ>::WPW;
-        int64_t blocks = (wd.walks + per_block - 1) / per_block;
+        // n = 4: a CU for each pair of walks while there are enough, so that they do not share one (64 walks x 64
+        // steps, k = 5, theta = 2^-4: 209 us; with a block for every 16 walks, of which two had pairs, 340)
+        int64_t blocks = NQ == 4 ? (wd.walks + 1) / 2 : (wd.walks + per_block - 1) / per_block;
         if (blocks > grid_blocks) blocks = grid_blocks;
         hipLaunchKernelGGL((k_walk<NQ, W>), dim3((unsigned)blocks), dim3(W * 64), 0, s, sp, wd, iters);
         return hipGetLastError();

@@ -245,3 +245,45 @@ def forward_time(ctx, inp, hidden, depth, classes, batch, shift=0):
                                             ((16384, 4096, 1, 11, 4096), (16384, 4096, 1, 11, 4096, 1), 1.05)])
 def test_less_work_takes_no_longer(ctx, less, more, most):
     assert forward_time(ctx, *less) < most * forward_time(ctx, *more)
+
+
+# pairs of walks: fewer than blocks, one to a block, a whole run of 16 to a block, one pair less and more, an odd walk
+@pytest.mark.parametrize("walks", [2, 511, 514, 8190, 8192, 8193, 16384 + 6])
+def test_walks_over_blocks(ctx, walks):
+    """n = 4, theta so small that no trail ends: every pair of walks makes its 2 x iters steps, once, and the walks of
+    a session do what they do in a session of another size."""
+    n, k, iters = 4, 7, 3
+    tw = seeded_inputs.target_words(n, k, 31)
+    tgt = ctx.target_from_words(n, tw.paulis, tw.clifford)
+    print("walks", walks, flush=True)
+
+    def session(count):
+        w = ctx.walk(tgt, k, tw.paulis[0], 9, 32, count, 12, 1 << 20)
+        w.run(iters)
+        st, steps = w.read_states(0, count), w.stats().steps
+        w.end()
+        assert steps == count * iters
+        pairs = st["len"][: count // 2 * 2].astype(np.int64).reshape(-1, 2).sum(1)
+        assert np.all(pairs == 2 * iters) and (count % 2 == 0 or st["len"][-1] == iters)
+        return st
+    st, more = session(walks), session(walks // 2 * 2 + 34)
+    assert np.array_equal(st[: walks // 2 * 2], more[: walks // 2 * 2])
+
+
+def test_few_walks_spread_over_the_chip(ctx):
+    """A launch of 64 walks takes less than two and a bit of one walk's: the pairs run beside each other, not on a
+    few CUs (2.85 times while 16 pairs shared a block's wavefronts)."""
+    n, k = 4, 7
+    tw = seeded_inputs.target_words(n, k, 5)
+    tgt = ctx.target_from_words(n, tw.paulis, tw.clifford)
+    ms = {}
+    for walks in (1, 64):
+        w = ctx.walk(tgt, k, tw.paulis[0], 3, 12, walks, 16, 20 << 12)
+        took = []
+        for _ in range(8):
+            w.run(64)
+            took.append(w.last_ms())
+        w.end()
+        ms[walks] = min(took)
+    print("one walk %.3f ms, 64 walks %.3f ms" % (ms[1], ms[64]), flush=True)
+    assert ms[64] < 2.2 * ms[1]
