@@ -1258,13 +1258,18 @@ __device__ inline void store_state(const WalkDev& wd, int64_t w, const Trail& tr
     wd.states[w] = st;
 }
 
-// The point a walk evaluates f on next: its current point while walking, else the backtracking
-// point that ALIGN / LOCK advances.
+// The point a walk evaluates f on next: its current point while walking, else the backtracking point
+// that ALIGN / LOCK advances.  Masks, since a choice of field would go through memory; a wavefront's own walk branches
+// on its mode first, but where lanes of several walks share the wavefront a branch is two of them in a row.
 template <bool WHOLE>
 __device__ inline uint64_t step_arg(const Trail& tr, const Back& bk) {
-    if ((tr.mode & 0xff) == MODE_WALK) return tr.cur;
-    const uint64_t second = 0ull - (uint64_t)((tr.mode >> 8) & 1);  // masks: a choice of field would go through memory
-    return same64<WHOLE>((bk.pb & second) | (bk.pa & ~second));
+    const bool walking = (tr.mode & 0xff) == MODE_WALK;
+    if (WHOLE && walking) return tr.cur;
+    const uint64_t second = 0ull - (uint64_t)((tr.mode >> 8) & 1);
+    const uint64_t back = same64<WHOLE>((bk.pb & second) | (bk.pa & ~second));
+    if constexpr (WHOLE) return back;
+    const uint64_t walk = 0ull - (uint64_t)walking;
+    return (tr.cur & walk) | (back & ~walk);
 }
 
 // Walk w's state after one evaluation f(arg) = (nxt, H): distinguished points into the table,
@@ -1370,9 +1375,15 @@ __device__ inline uint32_t advance_walk(const SpaceDev& sp, const WalkDev& wd, T
             st.cur = nxt;
         }
     } else if (mode == MODE_ALIGN) {
-        const uint64_t second = 0ull - (uint64_t)which;
-        bk.pa = (bk.pa & second) | (nxt & ~second);
-        bk.pb = (nxt & second) | (bk.pb & ~second);
+        if constexpr (WHOLE) {
+            const uint64_t second = 0ull - (uint64_t)which;
+            bk.pa = (bk.pa & second) | (nxt & ~second);
+            bk.pb = (nxt & second) | (bk.pb & ~second);
+        } else {
+            // the state is in registers; with the masks above n = 1 and 2 took 4 to 9 percent more a step (64 walks x 640
+            // steps at n = 1, k = 8: 917 us, 995 with them and a branch in step_arg)
+            if (which) bk.pb = nxt; else bk.pa = nxt;
+        }
         const uint32_t rem = (uint32_t)same64<WHOLE>(bk.rem) - 1;
         bk.rem = rem;
         if (rem == 0) {
