@@ -3414,6 +3414,7 @@ extern "C" int tcw_label_batch(tcw_ctx* c, int n, int count, const uint16_t* wor
         const int cnt = std::min(chunk, count - first);
         LB_TRY(tcw::build_batch(n, dwords, doff + first, dk + first, cnt, phi, rot,
                                 features_dev + (size_t)first * R * R, c->flag, c->stream));
+        LB_TRY(tcw::fill_i32(labels_dev + first, -1, cnt, c->stream));
         LB_TRY(tcw::mitm_probe(n, lt.sp, phi, rot, cnt, 2 * h_max - h_id, lt.frags, lt.table, lt.lg,
                                labels_dev + first, c->stream));
     }
@@ -3439,27 +3440,27 @@ extern "C" int tcw_min_tcount(tcw_ctx* c, const tcw_target* t, int h_max, uint64
         if (dev_i32) (void)hipFree(dev_i32);
     };
     LevelTable lt(c);
-    int32_t e_u = 0;
-    int flag = 0;
+    // what goes between the host and the device passes through pinned memory (a copy of four pageable bytes is
+    // waited for on the way): [0] the exponent, [1] the flags, then [2] rot_e, [3] the answer's -1
+    int32_t* host = c->pinned;
     hipError_t err = dev_alloc(c, &phi, (size_t)R * R / 2 * 4 + 16);
     if (err == hipSuccess) err = dev_alloc(c, &dev_i32, 2 * sizeof(int32_t));
     if (err == hipSuccess) err = hipMemsetAsync(c->flag, 0, sizeof(int), c->stream);
     if (err == hipSuccess) err = tcw::exact_pack_phi(t->U, phi, c->flag, c->stream);
-    if (err == hipSuccess) err = hipMemcpyAsync(&e_u, t->U.e, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
+    if (err == hipSuccess) err = hipMemcpyAsync(host, t->U.e, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
+    if (err == hipSuccess) err = hipMemcpyAsync(host + 1, c->flag, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
+    if (err == hipSuccess) err = hipStreamSynchronize(c->stream);
     if (err != hipSuccess) {
         cleanup();
         return hip_fail(c, err, "target packing");
     }
-    if ((rc = read_flag(c, &flag))) {
-        cleanup();
-        return rc;
-    }
-    if (flag) {
+    if (host[1]) {
         cleanup();
         return fail(c, TCW_EOVERFLOW, "target entry outside the int8 range (exponent too large)");
     }
-    const int32_t rot_e = (int32_t)((30ll * e_u) % 61);
-    err = hipMemcpyAsync(dev_i32, &rot_e, sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
+    host[2] = (int32_t)((30ll * host[0]) % 61);
+    host[3] = -1;
+    err = hipMemcpyAsync(dev_i32, host + 2, 2 * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
     if (err != hipSuccess) {
         cleanup();
         return hip_fail(c, err, "rot_e upload");
@@ -3471,10 +3472,11 @@ extern "C" int tcw_min_tcount(tcw_ctx* c, const tcw_target* t, int h_max, uint64
     }
     err = tcw::mitm_probe(n, lt.sp, phi, dev_i32, 1, 2 * h_max - h_id, lt.frags, lt.table, lt.lg, dev_i32 + 1,
                           c->stream);
-    if (err == hipSuccess) err = hipMemcpyAsync(t_out, dev_i32 + 1, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
+    if (err == hipSuccess) err = hipMemcpyAsync(host, dev_i32 + 1, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
     if (err == hipSuccess) err = hipStreamSynchronize(c->stream);
     cleanup();
     if (err != hipSuccess) return hip_fail(c, err, "meet-in-the-middle probe");
+    *t_out = host[0];
     return TCW_OK;
 }
 

@@ -152,6 +152,7 @@ hipError_t mitm_levels(int n, const SpaceDev& sp, int h, int64_t count, uint64_t
 // h_max (unless it holds only a part at a time)
 size_t mitm_frag_bytes(int n, int h_max, int64_t count);
 hipError_t mitm_frags(int n, const SpaceDev& sp, int h_max, void* frags, hipStream_t s);
+// best_out: -1 for every target on entry
 hipError_t mitm_probe(int n, const SpaceDev& sp, const uint32_t* phi_all, const int32_t* rot_e_all, int count,
                       int h_max, void* frags, const uint64_t* table, int log2_table, int32_t* best_out, hipStream_t s);
 

@@ -2613,8 +2613,7 @@ hipError_t mitm_frags(int n, const SpaceDev& sp, int h_max, void* frags, hipStre
 
 hipError_t mitm_probe(int n, const SpaceDev& sp, const uint32_t* phi_all, const int32_t* rot_e_all, int count,
                       int h_max, void* frags, const uint64_t* table, int log2_table, int32_t* best_out, hipStream_t s) {
-    hipError_t e = fill_i32(best_out, -1, count, s);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
     if (n == 3) {
         uint32_t at = 0, all = 0;
         for (int j = 0; j <= h_max; ++j) all += mitm_prefixes(j);
