@@ -92,8 +92,9 @@ def valu_ops_per_step(n: int, h: int) -> float:
           4 rows: 52
     which at h = 3 is 64 x (52 + 8 + 56 + 144) = 16,640 lane-operations (mean of the sides: side 0
     64 x 124, side 1 64 x 396).
-    The compiled kernel issues more (address arithmetic, the trail and table logic); the counters
-    give that figure separately."""
+    A fixed yardstick that rates of different kernels can be compared by: the side-1 recombination in it is that of
+    an earlier kernel.  The present one needs kernel_ops_per_step, so a share of the peak by this count is
+    not a share of issue slots; the counters give that (issued lanes and the VALU's busy cycles)."""
     if n != 4:
         raise ValueError("the lane-operation count is stated for n = 4")
     rows = 4
@@ -101,6 +102,29 @@ def valu_ops_per_step(n: int, h: int) -> float:
     side0 = 4 * rows
     both = 5 * rows + 5 * rows + 16
     side1 = 84 + 32 + 8 * 15 + 52
+    return 64.0 * (rotations + 0.5 * side0 + both + 0.5 * side1)
+
+
+def kernel_ops_per_step(n: int, h: int) -> float:
+    """32-bit VALU lane-operations that the present n = 4 kernel's step is made of, counted per lane as in
+    valu_ops_per_step (64-bit add 2, 64-bit shift 1, 32 x 32 + 64-bit multiply-add 1), mean over the two sides:
+
+      per computed rotation, per row: 13, as there
+      side 0: the digest folded twice (mask, shift, add): 8 per row
+      both sides: sign fold (bit 60 spread, two xors, a mask): 4 per row; element map and accumulation (two key
+          adds, one multiply-add): 3 per row; the wave sum: 16 per lane
+      side 1, two walks to a pass: digits of u and 2^31 u (the second set 7 per value, the bias 2 per value and
+          set, 32 byte permutes, 16 xors): 92; raw tile sums (2 per tile, 16 tiles, for both walks): 16; per row
+          two swaps of 16-lane rows, and the digest from its four halves (bias and widening 2, multiply-add,
+          add, masks and shift 3, carries 3, multiply-add, the exponent's rotation 5, fold 3): 21
+    which at h = 3 is 64 x (52 + 16 + 44 + 96) = 13,312."""
+    if n != 4:
+        raise ValueError("the lane-operation count is stated for n = 4")
+    rows = 4
+    rotations = 13 * rows * max(h - 2, 0)
+    side0 = 8 * rows
+    both = (4 + 3) * rows + 16
+    side1 = 92 + 16 + (2 + 19) * rows
     return 64.0 * (rotations + 0.5 * side0 + both + 0.5 * side1)
 
 
@@ -142,8 +166,9 @@ def measured_counters(walks: int, iters: int):
 
 
 def walk_roofline(n, h, steps_per_launch, avg_ms, walks, iters):
-    """The walk kernel against the VALU peak (its bound), with the literal method's count, the
-    compiled kernel's issued VALU work and busy share (counters), the int8 MFMA rate and HBM bytes."""
+    """The walk kernel against the VALU peak (its bound): the compiled kernel's issued VALU work and busy share
+    (counters), the peak's share by the fixed count of the step and by the present kernel's, the literal
+    method's count, the int8 MFMA rate and HBM bytes."""
     secs = avg_ms * 1e-3
     ops = valu_ops_per_step(n, h)
     achieved = ops * steps_per_launch / secs
@@ -151,7 +176,10 @@ def walk_roofline(n, h, steps_per_launch, avg_ms, walks, iters):
     out = {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK_OPS / 1e12, "unit": "Tops/s",
            "frac": achieved / VALU_PEAK_OPS, "traffic": traffic, "traffic_unit": "HBM bytes per launch",
            "kernel": "k_walk<4,16>", "kernel_ms": avg_ms, "kernel_source_sha256": kernel_source_digest(),
-           "ops_per_step": ops, "ops_unit": "32-bit VALU lane-operations of the phi-linear step",
+           "ops_per_step": ops, "ops_unit": "32-bit VALU lane-operations of the phi-linear step, a fixed yardstick",
+           "kernel_count": {"ops_per_step": kernel_ops_per_step(n, h),
+                            "frac": kernel_ops_per_step(n, h) * steps_per_launch / secs / VALU_PEAK_OPS,
+                            "note": "what the present kernel's step is made of; the shares of issue slots are in counters"},
            "literal_method": {"ops_per_step": LITERAL_OPS_PER_STEP_N4,
                               "frac": LITERAL_OPS_PER_STEP_N4 * steps_per_launch / secs / VALU_PEAK_OPS,
                               "note": "above 1: the kernel does not form the channel representation; it "

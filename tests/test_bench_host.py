@@ -89,3 +89,15 @@ def test_counter_summary_reading(tmp_path, monkeypatch):
         f.write("\n// changed\n")
     assert bench.measured_counters(1 << 20, 8) is None
     assert bench.walk_roofline(4, 3, steps, 10.0, 1 << 20, 8)["counters"] is None
+
+
+def test_present_kernel_count():
+    """What the present kernel's step is made of: below the fixed yardstick, and below what the compiled kernel was
+    measured to issue (15,041 lane-operations a step)."""
+    assert bench.kernel_ops_per_step(4, 3) == 64 * 208 == 13312
+    assert bench.kernel_ops_per_step(4, 4) - bench.kernel_ops_per_step(4, 3) == 64 * 13 * 4
+    assert bench.kernel_ops_per_step(4, 3) < 15041 < bench.valu_ops_per_step(4, 3)
+    roof = bench.walk_roofline(4, 3, (1 << 20) * 8, 10.0, 1 << 20, 8)
+    assert roof["kernel_count"]["frac"] == pytest.approx(roof["frac"] * 13312 / 16640)
+    with pytest.raises(ValueError):
+        bench.kernel_ops_per_step(3, 3)
