@@ -1876,7 +1876,8 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_mitm_probe(SpaceDev sp0, cons
 }
 
 // ---- n = 3: both halves by families of products that share all but their last-applied rotation ----
-// A wavefront takes one prefix (p_1, ..., p_{j-1}) and every p_0 that the pruning keeps (at most 62 of 63).
+// A wavefront takes one prefix (p_1, ..., p_{j-1}) and every p_0 that the pruning keeps: all 63 at j = 1, at most 62
+// beyond.
 
 // Row r = lane of the n = 3 butterflies: bit p of anti = P_p and P_r anticommute, bit p of plus = the
 // butterfly of R (side 0) adds the partner; ROT3_TAB with the Paulis of a row side by side.

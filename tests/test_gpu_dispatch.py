@@ -287,3 +287,16 @@ def test_few_walks_spread_over_the_chip(ctx):
         ms[walks] = min(took)
     print("one walk %.3f ms, 64 walks %.3f ms" % (ms[1], ms[64]), flush=True)
     assert ms[64] < 2.2 * ms[1]
+
+
+@pytest.mark.parametrize("n,h_max", [(1, 1), (2, 2), (3, 1), (3, 3)])
+def test_labels_within_their_range(ctx, n, h_max):
+    """A label is -1 or at most 2 h_max, and a circuit of no more rotations than that is never -1."""
+    import torch
+    tws = [seeded_inputs.target_words(n, i % 11, 4000 + i) for i in range(66)]
+    feats = torch.empty((66, 16 ** n), dtype=torch.float32, device="cuda:0")
+    labels = torch.empty(66, dtype=torch.int32, device="cuda:0")
+    ctx.label_batch(n, [(t.paulis, t.clifford) for t in tws], h_max, 3, feats, labels)
+    for t, got in zip(tws, labels.cpu().tolist()):
+        assert got == -1 or 0 <= got <= min(t.k, 2 * h_max)
+        assert got >= 0 or t.k > 2 * h_max
