@@ -1506,13 +1506,15 @@ __device__ void walk_block_single(const SpaceDev& sp, const WalkDev& wd, int ite
 // the pair's steps add up to 2 iters while each walk's share varies with its sides: a launch's total is
 // walks x iters.
 // The block's pairs are runs of WAVES neighbours, q = block * WAVES + i for i < WAVES, then every nblocks * WAVES
-// further while every block has a whole run; those left go to the blocks one at a time, so that a few walks spread
-// over the CUs instead of filling the first ones' wavefronts (20,000 walks x 64 steps at k = 7: 1.10 -> 0.97 ms;
-// all pairs one at a time cost 2^20 walks 0.7 percent).
+// further.  SPREAD (one launch's blocks, side by side): runs while every block has a whole one; those left go to the
+// blocks one at a time, so that a few walks spread over the CUs instead of filling the first ones' wavefronts (20,000
+// walks x 64 steps at k = 7: 1.10 -> 0.96 ms; all pairs one at a time cost 2^20 walks 0.7 percent).  A queue's items
+// follow each other on a CU, where a part of a run at the end of each would leave wavefronts idle every time (a
+// batch of mixed n: 1.34e9 steps/s, 1.38e9 in runs).
 // Its wavefronts take them in turn from *next (LDS, zero at the start).  With a fixed share each, the
 // wavefronts that the SIMDs prefer finished early and few were left at the end: a wavefront lived 0.78 of
 // the launch on average, now 0.98 (2^18 walks x 16 steps: 3.96 -> 3.62 ms).
-template <int WAVES>
+template <int WAVES, bool SPREAD>
 __device__ void walk_block_pairs(const SpaceDev& sp, const WalkDev& wd, int iters, Lds<4, WAVES>& L, int64_t block,
                                  int64_t nblocks, WalkCounts& cnt, uint32_t* next, Back* back) {
     // the wavefront's index made explicitly uniform, and with it the walks' numbers and states: they stay
@@ -1523,8 +1525,8 @@ __device__ void walk_block_pairs(const SpaceDev& sp, const WalkDev& wd, int iter
     Back &ba = back[2 * wave], &bb = back[2 * wave + 1];  // every lane writes the same values
     uint32_t steps = 0, active = 0, dps = 0, ins = 0;  // frequent events in registers, as in walk_block_single
     const int64_t pairs = (wd.walks + 1) / 2;
-    // of the block's, those in runs (at most 2^31 walks, no more blocks than runs: 32 bits hold both)
-    const uint32_t whole = (uint32_t)pairs / ((uint32_t)nblocks * WAVES) * WAVES;
+    // of the block's, those in runs (at most 2^31 walks, and no more blocks than CUs: 32 bits hold both)
+    const uint32_t whole = SPREAD ? (uint32_t)pairs / ((uint32_t)nblocks * WAVES) * WAVES : ~0u;
     for (;;) {
         uint32_t i = 0;
         if (leader) i = atomicAdd(next, 1u);
@@ -1595,11 +1597,11 @@ __device__ void walk_block_pairs(const SpaceDev& sp, const WalkDev& wd, int iter
 }
 
 // The walks of one slice: paired on side 1 at n = 4, one walk group at a time otherwise.
-template <int NQ, int WAVES>
+template <int NQ, int WAVES, bool SPREAD>
 __device__ void walk_block(const SpaceDev& sp, const WalkDev& wd, int iters, Lds<NQ, WAVES>& L, int64_t block,
                            int64_t nblocks, WalkCounts& cnt, uint32_t* next, Back* back) {
     if constexpr (NQ == 4)
-        walk_block_pairs<WAVES>(sp, wd, iters, L, block, nblocks, cnt, next, back);
+        walk_block_pairs<WAVES, SPREAD>(sp, wd, iters, L, block, nblocks, cnt, next, back);
     else
         walk_block_single<NQ, WAVES>(sp, wd, iters, L, block, nblocks, cnt);
 }
@@ -1617,7 +1619,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_walk(SpaceDev sp, WalkDev wd,
     if (threadIdx.x == 0) s_pair = 0;
     load_lds(L, sp);
     __syncthreads();
-    walk_block<NQ, WAVES>(sp, wd, iters, L, blockIdx.x, gridDim.x, mine, &s_pair, s_back);
+    walk_block<NQ, WAVES, true>(sp, wd, iters, L, blockIdx.x, gridDim.x, mine, &s_pair, s_back);
     __syncthreads();
     flush_counts(wd, s_cnt, GROUPS);
 }
@@ -1664,7 +1666,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_walk_queue(const SpaceDev* __
             loaded = it.slot;
         }
         __syncthreads();
-        walk_block<NQ, WAVES>(sp, wds[it.slot], it.iters, L, it.unit, it.units, mine, &s_pair, s_back);
+        walk_block<NQ, WAVES, false>(sp, wds[it.slot], it.iters, L, it.unit, it.units, mine, &s_pair, s_back);
         __syncthreads();  // s_next and, for the next member, the LDS are rewritten after this
     }
     if (loaded >= 0) flush_counts(wds[loaded], s_cnt, GROUPS);  // the last item's closing barrier is past
